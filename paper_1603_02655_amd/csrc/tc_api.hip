@@ -130,26 +130,12 @@ int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long
 }
 
 int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags, const bucket_params& bp,
-               hipStream_t stream, device_graph* out, tc_graph_info* info) {
-    const int32_t *s_dev = src, *d_dev = dst;
-    int32_t* tmp = nullptr;
-    hipError_t e = hipSuccess;
-    if (!(flags & TC_BUILD_DEVICE_PTRS) && m > 0) {
-        e = hipMalloc((void**)&tmp, sizeof(int32_t) * 2 * (size_t)m);
-        if (e == hipSuccess) e = hipMemcpyAsync(tmp, src, sizeof(int32_t) * m, hipMemcpyHostToDevice, stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(tmp + m, dst, sizeof(int32_t) * m, hipMemcpyHostToDevice, stream);
-        s_dev = tmp;
-        d_dev = tmp + m;
-    }
-    build_status st;
-    if (e == hipSuccess) st = build_graph_device(n, m, s_dev, d_dev, bp, stream, out);
-    if (tmp) {
-        (void)hipStreamSynchronize(stream);
-        (void)hipFree(tmp);
-    }
+               hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out, tc_graph_info* info) {
+    const build_status st =
+        build_graph_device(n, m, src, dst, !(flags & TC_BUILD_DEVICE_PTRS), bp, stream, sp, out);
+    space_trim(sp, keep, stream);
     int rc = TC_OK;
-    if (e != hipSuccess) rc = status_from_hip(e);
-    else if (st.bad_ids) rc = TC_ERR_ARG;
+    if (st.bad_ids) rc = TC_ERR_ARG;
     else if (st.too_large) rc = TC_ERR_RANGE;
     else if (!st.ok) rc = status_from_hip(st.hip);
     else if ((flags & TC_BUILD_STRICT) && (st.self_loops > 0 || st.duplicates > 0)) rc = TC_ERR_ARG;
@@ -322,6 +308,7 @@ int tc_context_destroy(tc_context ctx) {
     for (int i = 0; i < 2; ++i)
         if (ctx->fork[i]) (void)hipEventDestroy(ctx->fork[i]);
     if (ctx->side) (void)hipStreamDestroy(ctx->side);
+    space_free(&ctx->space);
     if (ctx->acc) (void)hipFree(ctx->acc);
     if (ctx->tables) (void)hipFree(ctx->tables);
     if (ctx->counters) (void)hipFree(ctx->counters);
@@ -342,7 +329,8 @@ int tc_build_graph(tc_context ctx, int32_t n, int64_t m, const int32_t* src, con
     tc_graph_s* g = new (std::nothrow) tc_graph_s();
     if (!g) return TC_ERR_NOMEM;
     std::lock_guard<std::mutex> lk(ctx->mu);
-    int rc = build_into(n, m, src, dst, flags, params_of(ctx->tuning), ctx->stream, &g->g, &g->info);
+    int rc = build_into(n, m, src, dst, flags, params_of(ctx->tuning), ctx->stream, &ctx->space, space_keep(ctx),
+                        &g->g, &g->info);
     if (rc != TC_OK) {
         delete g;
         return rc;
@@ -561,7 +549,9 @@ int tc_graph_rebucket(tc_context ctx, tc_graph g) {
         g->g.bp.hub_tile == bp.hub_tile)
         return TC_OK;
     batch_forget_graph_locked(ctx, g);
-    return status_from_hip(bucket_dyads(&g->g, bp, ctx->stream));
+    const hipError_t e = bucket_dyads(&g->g, bp, ctx->stream, &ctx->space);
+    space_trim(&ctx->space, space_keep(ctx), ctx->stream);
+    return status_from_hip(e);
 }
 
 int tc_set_timing(tc_context ctx, int enable) {

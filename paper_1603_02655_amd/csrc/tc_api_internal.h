@@ -1,5 +1,6 @@
 // Host-side state behind the C ABI handles.
 #pragma once
+#include <algorithm>
 #include <atomic>
 #include <condition_variable>
 #include <deque>
@@ -42,6 +43,7 @@ struct tc_context_s {
     hipEvent_t ev[2 * tc::kBuckets + 2] = {};
     hipStream_t side = nullptr;         // runs the totals pass beside the bucket kernels
     hipEvent_t fork[2] = {};            // side stream start / end
+    tc::build_space space;              // scratch of the builds on `stream`
     bool timing = false;
     tc_kernel_stats kstats{};
     tc_tuning tuning{};
@@ -69,9 +71,13 @@ int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_sli
 // them and g has them, else through the dyad records.
 int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long raw[16], int table = 0);
 // Builds a device graph from host (or, with TC_BUILD_DEVICE_PTRS, device) arcs
-// on `stream`; returns a TC_* status and fills the build part of *info.
+// on `stream`, with the scratch of *sp (trimmed to `keep` bytes at the end);
+// returns a TC_* status and fills the build part of *info.
 int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags, const bucket_params& bp,
-               hipStream_t stream, device_graph* out, tc_graph_info* info);
+               hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out, tc_graph_info* info);
+// Build scratch a context or a serving slot keeps between builds: at most
+// kSpaceKeep, and at most an eighth of the context's memory budget.
+inline uint64_t space_keep(const tc_context_s* ctx) { return std::min<uint64_t>(kSpaceKeep, ctx->budget / 8); }
 bucket_params params_of(const tc_tuning& t);
 // A copy of ctx->tuning taken under tuning_mu (for threads that do not hold mu).
 tc_tuning tuning_snapshot(tc_context_s* ctx);

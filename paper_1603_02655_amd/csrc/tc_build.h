@@ -74,11 +74,26 @@ struct build_status {
     uint64_t sum_d2 = 0;
 };
 
-build_status build_graph_device(int32_t n, int64_t m, const int32_t* src_dev, const int32_t* dst_dev,
-                                const bucket_params& bp, hipStream_t s, device_graph* g);
-hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s);
+// Device scratch and a page of pinned host memory that builds reuse: grown to
+// the largest build, kept between builds up to kSpaceKeep bytes (space_trim)
+// and freed with its owner.  One build at a time uses a build_space.
+constexpr uint32_t kSpaceHostWords = 64;
+constexpr uint32_t kSpaceHostStats = 32;          // words the build's statistics are published to
+constexpr uint64_t kSpaceKeep = 1ull << 30;
+struct build_space {
+    void* base = nullptr;
+    uint64_t cap = 0;
+    uint64_t* host = nullptr;
+};
+hipError_t space_reserve(build_space* sp, uint64_t bytes, hipStream_t s);
+void space_trim(build_space* sp, uint64_t keep, hipStream_t s);
+void space_free(build_space* sp);
+
+// Arcs on the device, or with host_arcs in host memory.
+build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, bool host_arcs,
+                                const bucket_params& bp, hipStream_t s, build_space* sp, device_graph* g);
+hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s, build_space* sp);
 void free_device_graph(device_graph* g);
 uint64_t device_graph_bytes(const device_graph& g);
-hipError_t fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 
 }  // namespace tc

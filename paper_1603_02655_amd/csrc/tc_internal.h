@@ -140,8 +140,4 @@ struct census_args {
     const uint8_t* table;     // 64 bin indices (device memory), one per code
     uint32_t hub_chunk;       // hub kernel: records per task and per group of tasks
 };
-
-// device scan / sort helpers (tc_build.hip)
-hipError_t scan_exclusive_u64(const uint64_t* in, uint64_t* out, uint64_t count, uint64_t* total_dev,
-                              hipStream_t s);
 }  // namespace tc

@@ -55,6 +55,7 @@ struct slot_buf {
     work_item* h_items = nullptr;
     uint32_t* h_num = nullptr;
     unsigned long long* h_accs = nullptr;
+    build_space space;                    // scratch of the builds of the slot's rounds
 };
 
 void slot_free(slot_buf& s) {
@@ -176,7 +177,7 @@ private:
             bucket_params bp = params_of(tun);
             bp.tri = 0;   // cold graphs live for one round: no forward lists (not in their footprint)
             j->status = build_into(j->n, (int64_t)j->src.size(), j->src.data(), j->dst.data(), j->flags, bp, s.stream,
-                                   &j->built, nullptr);
+                                   &s.space, space_keep(ctx_), &j->built, nullptr);
             std::vector<int32_t>().swap(j->src);
             std::vector<int32_t>().swap(j->dst);
         }
@@ -416,6 +417,7 @@ void serve_shutdown(tc_context_s* ctx) {
     st->S.reset();                        // frees the jobs left unpolled
     for (slot_buf& s : st->ex.slots) {
         slot_free(s);
+        space_free(&s.space);
         if (s.stream) (void)hipStreamDestroy(s.stream);
     }
     st->ex.release(true);
