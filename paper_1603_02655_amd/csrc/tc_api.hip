@@ -130,9 +130,10 @@ int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long
 }
 
 int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags, const bucket_params& bp,
-               hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out, tc_graph_info* info) {
+               graph_pool* pool, hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out,
+               tc_graph_info* info) {
     const build_status st =
-        build_graph_device(n, m, src, dst, !(flags & TC_BUILD_DEVICE_PTRS), bp, stream, sp, out);
+        build_graph_device(n, m, src, dst, !(flags & TC_BUILD_DEVICE_PTRS), bp, pool, stream, sp, out);
     space_trim(sp, keep, stream);
     int rc = TC_OK;
     if (st.bad_ids) rc = TC_ERR_ARG;
@@ -272,6 +273,7 @@ int tc_context_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, t
         size_t free_b = 0, total_b = 0;
         e = hipMemGetInfo(&free_b, &total_b);
         ctx->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)free_b);
+        ctx->pool.keep = pool_keep(ctx);
         hipDeviceProp_t prop;
         if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
         if (e == hipSuccess) {
@@ -329,8 +331,8 @@ int tc_build_graph(tc_context ctx, int32_t n, int64_t m, const int32_t* src, con
     tc_graph_s* g = new (std::nothrow) tc_graph_s();
     if (!g) return TC_ERR_NOMEM;
     std::lock_guard<std::mutex> lk(ctx->mu);
-    int rc = build_into(n, m, src, dst, flags, params_of(ctx->tuning), ctx->stream, &ctx->space, space_keep(ctx),
-                        &g->g, &g->info);
+    int rc = build_into(n, m, src, dst, flags, params_of(ctx->tuning), &ctx->pool, ctx->stream, &ctx->space,
+                        space_keep(ctx), &g->g, &g->info);
     if (rc != TC_OK) {
         delete g;
         return rc;
@@ -357,6 +359,7 @@ int tc_graph_release(tc_context ctx, tc_graph g) {
     if (g->pending.load() > 0) return TC_ERR_BUSY;
     batch_forget_graph_locked(ctx, g);
     (void)hipStreamSynchronize(ctx->stream);
+    serve_wait_abandoned(ctx);
     ctx->graphs.erase(g);
     free_device_graph(&g->g);
     delete g;
@@ -549,6 +552,8 @@ int tc_graph_rebucket(tc_context ctx, tc_graph g) {
         g->g.bp.hub_tile == bp.hub_tile)
         return TC_OK;
     batch_forget_graph_locked(ctx, g);
+    (void)hipStreamSynchronize(ctx->stream);
+    serve_wait_abandoned(ctx);
     const hipError_t e = bucket_dyads(&g->g, bp, ctx->stream, &ctx->space);
     space_trim(&ctx->space, space_keep(ctx), ctx->stream);
     return status_from_hip(e);

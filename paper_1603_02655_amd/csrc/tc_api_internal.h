@@ -43,6 +43,7 @@ struct tc_context_s {
     hipEvent_t ev[2 * tc::kBuckets + 2] = {};
     hipStream_t side = nullptr;         // runs the totals pass beside the bucket kernels
     hipEvent_t fork[2] = {};            // side stream start / end
+    tc::graph_pool pool;                // memory of the context's graphs
     tc::build_space space;              // scratch of the builds on `stream`
     bool timing = false;
     tc_kernel_stats kstats{};
@@ -74,10 +75,14 @@ int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long
 // on `stream`, with the scratch of *sp (trimmed to `keep` bytes at the end);
 // returns a TC_* status and fills the build part of *info.
 int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags, const bucket_params& bp,
-               hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out, tc_graph_info* info);
+               graph_pool* pool, hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out,
+               tc_graph_info* info);
 // Build scratch a context or a serving slot keeps between builds: at most
 // kSpaceKeep, and at most an eighth of the context's memory budget.
 inline uint64_t space_keep(const tc_context_s* ctx) { return std::min<uint64_t>(kSpaceKeep, ctx->budget / 8); }
+// Freed graph memory the context's pool keeps: at most 4 GiB and an eighth of
+// the budget (R-MAT 2^20 holds 1.4 GB).
+inline uint64_t pool_keep(const tc_context_s* ctx) { return std::min<uint64_t>(4ull << 30, ctx->budget / 8); }
 bucket_params params_of(const tc_tuning& t);
 // A copy of ctx->tuning taken under tuning_mu (for threads that do not hold mu).
 tc_tuning tuning_snapshot(tc_context_s* ctx);
@@ -114,6 +119,8 @@ void batch_forget_graph_locked(tc_context_s* ctx, tc_graph g);
 
 // serving loop (tc_serve.cpp)
 void serve_stop(tc_context_s* ctx);
+// Waits for rounds the watchdog gave up on (they may still read graphs).
+void serve_wait_abandoned(tc_context_s* ctx);
 void serve_shutdown(tc_context_s* ctx);
 
 }  // namespace tc

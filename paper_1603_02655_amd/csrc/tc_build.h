@@ -1,5 +1,9 @@
 // Device graph storage and the build entry points (definitions in tc_build.hip).
 #pragma once
+#include <deque>
+#include <mutex>
+#include <unordered_map>
+
 #include "tc_internal.h"
 
 namespace tc {
@@ -43,7 +47,34 @@ struct forward_lists {
     rec_set edges;
 };
 
+// Device memory of a context's graphs.  Freed blocks are kept, up to `keep`
+// bytes in all, and given to later allocations of about their size; beyond
+// that the oldest are returned to the driver, which takes 2-40 ms per graph of
+// R-MAT 2^20's size and waits for the whole device.  A block is put back only
+// once nothing on the device uses it any more (a graph is freed after the
+// streams that ran on it were waited for), so it can serve any stream next.
+// Safe from several threads.
+class graph_pool {
+public:
+    ~graph_pool();
+    hipError_t alloc(void** out, uint64_t bytes);
+    void put(void* p);
+    uint64_t keep = 0;
+
+private:
+    struct block {
+        void* p;
+        uint64_t bytes;
+    };
+    void shrink(uint64_t to);      // mu_ held
+    std::mutex mu_;
+    std::deque<block> free_;       // oldest first
+    std::unordered_map<void*, uint64_t> live_;
+    uint64_t held_ = 0;            // bytes in free_
+};
+
 struct device_graph {
+    graph_pool* mem = nullptr;
     int32_t n = 0;
     uint64_t U = 0;            // neighbour entries (2 x canonical dyads)
     uint64_t p = 0;            // canonical dyads
@@ -80,10 +111,17 @@ struct build_status {
 constexpr uint32_t kSpaceHostWords = 64;
 constexpr uint32_t kSpaceHostStats = 32;          // words the build's statistics are published to
 constexpr uint64_t kSpaceKeep = 1ull << 30;
+// Host arcs are copied to the device through pinned chunks, two per copying
+// thread: the runtime's own path for pageable memory pins the caller's pages
+// on each call (132 MB from arrays that change from call to call: 2-3 GB/s).
+constexpr int kStageThreads = 4;
+constexpr uint64_t kStageChunk = 1ull << 20;
 struct build_space {
     void* base = nullptr;
     uint64_t cap = 0;
     uint64_t* host = nullptr;
+    char* stage = nullptr;                        // pinned chunks host arcs go through
+    hipEvent_t stage_ev[2 * kStageThreads] = {};  // end of each chunk's last copy
 };
 hipError_t space_reserve(build_space* sp, uint64_t bytes, hipStream_t s);
 void space_trim(build_space* sp, uint64_t keep, hipStream_t s);
@@ -91,7 +129,8 @@ void space_free(build_space* sp);
 
 // Arcs on the device, or with host_arcs in host memory.
 build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, bool host_arcs,
-                                const bucket_params& bp, hipStream_t s, build_space* sp, device_graph* g);
+                                const bucket_params& bp, graph_pool* pool, hipStream_t s, build_space* sp,
+                                device_graph* g);
 hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s, build_space* sp);
 void free_device_graph(device_graph* g);
 uint64_t device_graph_bytes(const device_graph& g);

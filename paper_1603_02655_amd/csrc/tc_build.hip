@@ -11,7 +11,8 @@
 #include "tc_build.h"
 
 #include <algorithm>
-#include <vector>
+#include <cstring>
+#include <thread>
 
 namespace tc {
 
@@ -856,6 +857,81 @@ hipError_t fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
     return hipGetLastError();
 }
 
+graph_pool::~graph_pool() {
+    shrink(0);
+    for (auto& b : live_) (void)hipFree(b.first);
+}
+
+void graph_pool::shrink(uint64_t to) {
+    while (held_ > to && !free_.empty()) {
+        held_ -= free_.front().bytes;
+        (void)hipFree(free_.front().p);
+        free_.pop_front();
+    }
+}
+
+hipError_t graph_pool::alloc(void** out, uint64_t bytes) {
+    *out = nullptr;
+    // sizes in steps of an eighth of their power of two, so that graphs of
+    // about one size reuse each other's blocks
+    uint64_t step = 4096;
+    while (16 * step < bytes) step *= 2;
+    bytes = (std::max<uint64_t>(bytes, 1) + step - 1) / step * step;
+    std::lock_guard<std::mutex> lk(mu_);
+    try {
+        size_t best = free_.size();
+        for (size_t i = 0; i < free_.size(); ++i)
+            if (free_[i].bytes >= bytes && free_[i].bytes <= bytes + bytes / 4 &&
+                (best == free_.size() || free_[i].bytes < free_[best].bytes))
+                best = i;
+        if (best < free_.size()) {
+            const block b = free_[best];
+            live_.emplace(b.p, b.bytes);
+            free_.erase(free_.begin() + (std::ptrdiff_t)best);
+            held_ -= b.bytes;
+            *out = b.p;
+            return hipSuccess;
+        }
+        void* p = nullptr;
+        hipError_t e = hipMalloc(&p, bytes);
+        if (e != hipSuccess && held_ > 0) {   // full: what is kept goes back first
+            (void)hipGetLastError();
+            shrink(0);
+            e = hipMalloc(&p, bytes);
+        }
+        if (e != hipSuccess) return e;
+        try {
+            live_.emplace(p, bytes);
+        } catch (...) {
+            (void)hipFree(p);
+            return hipErrorOutOfMemory;
+        }
+        *out = p;
+        return hipSuccess;
+    } catch (...) {
+        return hipErrorOutOfMemory;
+    }
+}
+
+void graph_pool::put(void* p) {
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(mu_);
+    const auto it = live_.find(p);
+    if (it == live_.end()) return;
+    const uint64_t bytes = it->second;
+    live_.erase(it);
+    if (bytes <= keep) {
+        try {
+            free_.push_back(block{p, bytes});
+            held_ += bytes;
+            shrink(keep);
+            return;
+        } catch (...) {
+        }
+    }
+    (void)hipFree(p);
+}
+
 hipError_t space_reserve(build_space* sp, uint64_t bytes, hipStream_t s) {
     hipError_t e = hipSuccess;
     if (!sp->host) e = hipHostMalloc((void**)&sp->host, sizeof(uint64_t) * kSpaceHostWords);
@@ -878,7 +954,70 @@ void space_trim(build_space* sp, uint64_t keep, hipStream_t s) {
     sp->cap = 0;
 }
 
+namespace {
+
+hipError_t stage_reserve(build_space* sp) {
+    hipError_t e = hipSuccess;
+    if (!sp->stage) e = hipHostMalloc((void**)&sp->stage, 2 * kStageThreads * kStageChunk);
+    for (int k = 0; k < 2 * kStageThreads && e == hipSuccess; ++k)
+        if (!sp->stage_ev[k]) e = hipEventCreateWithFlags(&sp->stage_ev[k], hipEventDisableTiming);
+    return e;
+}
+
+// Copies bytes [begin, end) of `from` to `to` on stream s through the two
+// chunks of thread t.
+hipError_t stage_range(build_space* sp, int device, int t, const char* from, char* to, uint64_t begin, uint64_t end,
+                       hipStream_t s) {
+    hipError_t e = hipSetDevice(device);
+    for (uint64_t b = begin, k = 0; b < end && e == hipSuccess; b += kStageChunk, ++k) {
+        const uint64_t len = std::min(kStageChunk, end - b);
+        const int c = 2 * t + (int)(k & 1);
+        char* chunk = sp->stage + (uint64_t)c * kStageChunk;
+        e = hipEventSynchronize(sp->stage_ev[c]);   // (an event never recorded has ended)
+        if (e != hipSuccess) break;
+        std::memcpy(chunk, from + b, len);
+        e = hipMemcpyAsync(to + b, chunk, len, hipMemcpyHostToDevice, s);
+        if (e == hipSuccess) e = hipEventRecord(sp->stage_ev[c], s);
+    }
+    return e;
+}
+
+// Host bytes to device memory on stream s; the source is not read after the
+// return.  Arrays of 16 MiB or more are copied by kStageThreads threads, since
+// one thread's copy into the chunks is slower than the bus.
+hipError_t stage_copy(build_space* sp, const void* from, void* to, uint64_t bytes, hipStream_t s) {
+    hipError_t e = stage_reserve(sp);
+    int device = 0;
+    if (e == hipSuccess) e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    const char* f = (const char*)from;
+    char* d = (char*)to;
+    if (bytes < (16ull << 20)) return stage_range(sp, device, 0, f, d, 0, bytes, s);
+    const uint64_t part = ((bytes + kStageThreads - 1) / kStageThreads + 255) & ~255ull;
+    hipError_t got[kStageThreads];
+    std::thread th[kStageThreads];
+    for (int t = 1; t < kStageThreads; ++t) {
+        const uint64_t b = std::min(bytes, part * t), n = std::min(bytes, part * (t + 1));
+        try {
+            th[t] = std::thread([=, &got] { got[t] = stage_range(sp, device, t, f, d, b, n, s); });
+        } catch (...) {
+            got[t] = stage_range(sp, device, t, f, d, b, n, s);
+        }
+    }
+    got[0] = stage_range(sp, device, 0, f, d, 0, std::min(bytes, part), s);
+    for (int t = 1; t < kStageThreads; ++t)
+        if (th[t].joinable()) th[t].join();
+    for (int t = 0; t < kStageThreads; ++t)
+        if (got[t] != hipSuccess) e = got[t];
+    return e;
+}
+
+}  // namespace
+
 void space_free(build_space* sp) {
+    if (sp->stage) (void)hipHostFree(sp->stage);
+    for (hipEvent_t ev : sp->stage_ev)
+        if (ev) (void)hipEventDestroy(ev);
     if (sp->base) (void)hipFree(sp->base);
     if (sp->host) (void)hipHostFree(sp->host);
     *sp = build_space{};
@@ -957,7 +1096,8 @@ hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* 
 #define TAKE(p, T, count) do { p = ar.take<T>(count); if (!p) { err = hipErrorOutOfMemory; goto done; } } while (0)
 
 build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, bool host_arcs,
-                                const bucket_params& bp, hipStream_t s, build_space* sp, device_graph* g) {
+                                const bucket_params& bp, graph_pool* pool, hipStream_t s, build_space* sp,
+                                device_graph* g) {
     build_status st{};
     hipError_t err = hipSuccess;
     // ids below 2^bits; the sentinel key is a loop of id 2^bits - 1
@@ -965,6 +1105,7 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     const uint64_t keys_n = 2ull * (uint64_t)m;
     *g = device_graph{};
     g->n = n;
+    g->mem = pool;
     const uint64_t small = 1024 + sizeof(uint32_t) * (uint64_t)n + 1024;
     const uint64_t need = small + std::max(sort_space_bytes((uint64_t)m, bits), bucket_space_bytes(keys_n, (uint64_t)n));
     if ((err = space_reserve(sp, need, s)) != hipSuccess) {
@@ -988,8 +1129,8 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
         TAKE(types, uint64_t, tiles);
         if (host_arcs) {   // the second key buffer holds the arcs until the first sort pass
             int32_t* a = (int32_t*)tmp;
-            TRY(hipMemcpyAsync(a, src, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, s));
-            TRY(hipMemcpyAsync(a + m, dst, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, s));
+            TRY(stage_copy(sp, src, a, sizeof(int32_t) * (uint64_t)m, s));
+            TRY(stage_copy(sp, dst, a + m, sizeof(int32_t) * (uint64_t)m, s));
             src = a;
             dst = a + m;
         }
@@ -1011,11 +1152,11 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     g->U = U;
     st.arcs_kept = (int64_t)(total_types & 0xffffffffull);
     st.duplicates = m - st.self_loops - st.arcs_kept;
-    TRY(hipMalloc((void**)&g->row_ptr, sizeof(int64_t) * ((size_t)n + 1)));
-    TRY(hipMalloc((void**)&g->nbr, sizeof(uint32_t) * (U + kRowPad)));
-    TRY(hipMalloc((void**)&g->owner, sizeof(uint32_t) * (U ? U : 1)));
-    TRY(hipMalloc((void**)&g->tpre, sizeof(uint64_t) * (U + 1)));
-    TRY(hipMalloc((void**)&g->rinfo, sizeof(uint4) * ((size_t)n + 1)));
+    TRY(g->mem->alloc((void**)&g->row_ptr, sizeof(int64_t) * ((size_t)n + 1)));
+    TRY(g->mem->alloc((void**)&g->nbr, sizeof(uint32_t) * (U + kRowPad)));
+    TRY(g->mem->alloc((void**)&g->owner, sizeof(uint32_t) * (U ? U : 1)));
+    TRY(g->mem->alloc((void**)&g->tpre, sizeof(uint64_t) * (U + 1)));
+    TRY(g->mem->alloc((void**)&g->rinfo, sizeof(uint4) * ((size_t)n + 1)));
     if (U > 0) {
         hipLaunchKernelGGL(k_runs_emit, dim3((uint32_t)tiles), dim3(kT), 0, s, keys, keys_n, bits, ents, types, U,
                            total_types, n, g->nbr, g->owner, g->tpre, g->row_ptr);
@@ -1048,7 +1189,7 @@ namespace {
 // sum over the tasks of the anchor-row length.
 hipError_t cut_hub_tasks(const uint32_t* first, const uint32_t* past, int32_t n, const uint32_t* len,
                          uint64_t hub_begin, const dyad_rec* recs, const bucket_params& bp, uint32_t chunk,
-                         build_space* sp, arena& ar, hipStream_t s, hub_task** tasks_out, uint32_t* ntasks_out,
+                         graph_pool* mem, build_space* sp, arena& ar, hipStream_t s, hub_task** tasks_out, uint32_t* ntasks_out,
                          uint32_t* ngroups_out, uint64_t* staged_out) {
     hipError_t err = hipSuccess;
     const size_t mark = ar.mark();
@@ -1069,7 +1210,7 @@ hipError_t cut_hub_tasks(const uint32_t* first, const uint32_t* past, int32_t n,
     TRY(hipStreamSynchronize(s));
     ntasks = (sp->host[0] >> 32) + (sp->host[0] & 0xffffffffull);
     *staged_out = sp->host[1];
-    TRY(hipMalloc((void**)&tasks, sizeof(hub_task) * (ntasks ? ntasks : 1)));
+    TRY(mem->alloc((void**)&tasks, sizeof(hub_task) * (ntasks ? ntasks : 1)));
     hipLaunchKernelGGL(k_hub_emit, dim3(grid1((uint64_t)n)), dim3(kT), 0, s, first, past, n, len,
                        (const uint64_t*)task_off, bp.hub_tile, chunk, hub_begin, tasks);
     windows = (ntasks + kHubGroupTasks - 1) / kHubGroupTasks;
@@ -1087,7 +1228,7 @@ hipError_t cut_hub_tasks(const uint32_t* first, const uint32_t* past, int32_t n,
     *ntasks_out = (uint32_t)ntasks;
     *ngroups_out = (uint32_t)sp->host[0];
 done:
-    if (tasks) (void)hipFree(tasks);
+    mem->put(tasks);
     ar.rewind(mark);
     return err;
 }
@@ -1096,8 +1237,8 @@ done:
 // entries and n rows of length len) into `out`: records, hub tasks and the
 // per-bucket sums.
 hipError_t bucket_records(const uint32_t* nbr, const uint32_t* owner, const int64_t* row_ptr, const uint32_t* len,
-                          uint64_t U, int32_t n, int tri, const bucket_params& bp, build_space* sp, arena& ar,
-                          hipStream_t s, rec_set* out, uint64_t* mutual) {
+                          uint64_t U, int32_t n, int tri, const bucket_params& bp, graph_pool* mem,
+                          build_space* sp, arena& ar, hipStream_t s, rec_set* out, uint64_t* mutual) {
     hipError_t err = hipSuccess;
     const size_t mark = ar.mark();
     uint64_t *counts = nullptr, *part = nullptr;
@@ -1105,9 +1246,9 @@ hipError_t bucket_records(const uint32_t* nbr, const uint32_t* owner, const int6
     uint32_t *first = nullptr, *past = nullptr, *anchors = nullptr;
     uint64_t total = 0, hubs = 0;
     const uint32_t nb = blocks_for(U ? U : 1);
-    if (out->recs) (void)hipFree(out->recs);
-    if (out->tasks) (void)hipFree(out->tasks);
-    if (out->fine_tasks) (void)hipFree(out->fine_tasks);
+    mem->put(out->recs);
+    mem->put(out->tasks);
+    mem->put(out->fine_tasks);
     *out = rec_set{};
     TAKE(counts, uint64_t, (uint64_t)kBuckets * nb + 1);
     TAKE(part, uint64_t, (uint64_t)kPartWords * nb);
@@ -1132,7 +1273,7 @@ hipError_t bucket_records(const uint32_t* nbr, const uint32_t* owner, const int6
     if (mutual) *mutual = sp->host[2 * kBuckets + 2];
     total = out->off[kBuckets];
     hubs = out->off[kBucketHub + 1] - out->off[kBucketHub];
-    TRY(hipMalloc((void**)&out->recs, sizeof(dyad_rec) * (total ? total : 1)));
+    TRY(mem->alloc((void**)&out->recs, sizeof(dyad_rec) * (total ? total : 1)));
     if (hubs > 0) {
         if (tri) {
             TRY(scan_exclusive<uint32_t>(hubcnt, first, (uint64_t)n, nullptr, ar, s));
@@ -1158,10 +1299,10 @@ hipError_t bucket_records(const uint32_t* nbr, const uint32_t* owner, const int6
             hipLaunchKernelGGL(k_hub_runs, dim3(grid1(hubs)), dim3(kT), 0, s, (const uint32_t*)anchors, (uint32_t)hubs,
                                first, past);
         const bool fine = tri && hubs >= kHubSplitRecords;
-        TRY(cut_hub_tasks(first, past, n, len, out->off[kBucketHub], out->recs, bp, kHubChunk, sp, ar, s, &out->tasks,
-                          &out->n_tasks, &out->n_groups, &out->staged));
+        TRY(cut_hub_tasks(first, past, n, len, out->off[kBucketHub], out->recs, bp, kHubChunk, mem, sp, ar, s,
+                          &out->tasks, &out->n_tasks, &out->n_groups, &out->staged));
         if (fine)
-            TRY(cut_hub_tasks(first, past, n, len, out->off[kBucketHub], out->recs, bp, kHubChunk / 2, sp, ar, s,
+            TRY(cut_hub_tasks(first, past, n, len, out->off[kBucketHub], out->recs, bp, kHubChunk / 2, mem, sp, ar, s,
                               &out->fine_tasks, &out->fine_n_tasks, &out->fine_n_groups, &out->fine_staged));
     }
 done:
@@ -1169,13 +1310,13 @@ done:
     return err;
 }
 
-void free_forward(forward_lists* t) {
-    if (t->fwd) (void)hipFree(t->fwd);
-    if (t->fwd_owner) (void)hipFree(t->fwd_owner);
-    if (t->fwd_ptr) (void)hipFree(t->fwd_ptr);
-    if (t->edges.recs) (void)hipFree(t->edges.recs);
-    if (t->edges.tasks) (void)hipFree(t->edges.tasks);
-    if (t->edges.fine_tasks) (void)hipFree(t->edges.fine_tasks);
+void free_forward(graph_pool* mem, forward_lists* t) {
+    mem->put(t->fwd);
+    mem->put(t->fwd_owner);
+    mem->put(t->fwd_ptr);
+    mem->put(t->edges.recs);
+    mem->put(t->edges.tasks);
+    mem->put(t->edges.fine_tasks);
     *t = forward_lists{};
 }
 
@@ -1188,9 +1329,9 @@ hipError_t build_forward(device_graph* g, arena& ar, hipStream_t s) {
     const int32_t n = g->n;
     forward_lists& t = g->tri;
     t.entries = U / 2;   // every joined pair is in one forward list
-    TRY(hipMalloc((void**)&t.fwd_ptr, sizeof(int64_t) * ((size_t)n + 1)));
-    TRY(hipMalloc((void**)&t.fwd, sizeof(uint32_t) * (t.entries + kRowPad)));
-    TRY(hipMalloc((void**)&t.fwd_owner, sizeof(uint32_t) * (t.entries ? t.entries : 1)));
+    TRY(g->mem->alloc((void**)&t.fwd_ptr, sizeof(int64_t) * ((size_t)n + 1)));
+    TRY(g->mem->alloc((void**)&t.fwd, sizeof(uint32_t) * (t.entries + kRowPad)));
+    TRY(g->mem->alloc((void**)&t.fwd_owner, sizeof(uint32_t) * (t.entries ? t.entries : 1)));
     TAKE(pos, uint64_t, U + 1);
     if (U > 0)
         hipLaunchKernelGGL(k_fwd_flag, dim3(grid1(U)), dim3(kT), 0, s, g->nbr, g->owner, g->row_ptr, U, pos);
@@ -1217,7 +1358,7 @@ hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* 
     g->n_hub_groups = 0;
     uint64_t mutual = 0;
     hipError_t err =
-        bucket_records(g->nbr, g->owner, g->row_ptr, deg, g->U, g->n, 0, bp, sp, ar, s, &d, &mutual);
+        bucket_records(g->nbr, g->owner, g->row_ptr, deg, g->U, g->n, 0, bp, g->mem, sp, ar, s, &d, &mutual);
     g->dyads = d.recs;
     g->hub_tasks = d.tasks;
     if (err != hipSuccess) return err;
@@ -1232,13 +1373,13 @@ hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* 
     g->hub_staged = d.staged;
     g->bp = bp;
     if (!bp.tri) {
-        free_forward(&g->tri);
+        free_forward(g->mem, &g->tri);
         return hipSuccess;
     }
     if (!g->tri.fwd_ptr) {
         err = build_forward(g, ar, s);
         if (err != hipSuccess) {
-            free_forward(&g->tri);
+            free_forward(g->mem, &g->tri);
             return err;
         }
     }
@@ -1250,8 +1391,9 @@ hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* 
         err = hipGetLastError();
     }
     if (err == hipSuccess)
-        err = bucket_records(t.fwd, t.fwd_owner, t.fwd_ptr, flen, t.entries, g->n, 1, bp, sp, ar, s, &t.edges, nullptr);
-    if (err != hipSuccess) free_forward(&g->tri);
+        err = bucket_records(t.fwd, t.fwd_owner, t.fwd_ptr, flen, t.entries, g->n, 1, bp, g->mem, sp, ar, s, &t.edges,
+                             nullptr);
+    if (err != hipSuccess) free_forward(g->mem, &g->tri);
     return err;
 }
 
@@ -1276,15 +1418,17 @@ hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s,
 }
 
 void free_device_graph(device_graph* g) {
-    free_forward(&g->tri);
-    if (g->row_ptr) (void)hipFree(g->row_ptr);
-    if (g->nbr) (void)hipFree(g->nbr);
-    if (g->owner) (void)hipFree(g->owner);
-    if (g->tpre) (void)hipFree(g->tpre);
-    if (g->rinfo) (void)hipFree(g->rinfo);
-    if (g->dyads) (void)hipFree(g->dyads);
-    if (g->hub_tasks) (void)hipFree(g->hub_tasks);
-    int32_t n = g->n;
+    graph_pool* mem = g->mem;
+    const int32_t n = g->n;
+    if (!mem) return;   // nothing was allocated
+    free_forward(mem, &g->tri);
+    mem->put(g->row_ptr);
+    mem->put(g->nbr);
+    mem->put(g->owner);
+    mem->put(g->tpre);
+    mem->put(g->rinfo);
+    mem->put(g->dyads);
+    mem->put(g->hub_tasks);
     *g = device_graph{};
     g->n = n;
 }

@@ -44,7 +44,7 @@ struct serve_job : sched::job {
 
 struct slot_buf {
     hipStream_t stream = nullptr;
-    bool dead = false;                    // abandoned by the watchdog: never reused
+    std::atomic<bool> dead{false};        // abandoned by the watchdog: never reused
     uint32_t cap_graphs = 0, cap_items = 0;
     graph_desc* d_desc = nullptr;
     work_item* d_items = nullptr;
@@ -176,8 +176,8 @@ private:
             if (!j->cold) continue;
             bucket_params bp = params_of(tun);
             bp.tri = 0;   // cold graphs live for one round: no forward lists (not in their footprint)
-            j->status = build_into(j->n, (int64_t)j->src.size(), j->src.data(), j->dst.data(), j->flags, bp, s.stream,
-                                   &s.space, space_keep(ctx_), &j->built, nullptr);
+            j->status = build_into(j->n, (int64_t)j->src.size(), j->src.data(), j->dst.data(), j->flags, bp, &ctx_->pool,
+                                   s.stream, &s.space, space_keep(ctx_), &j->built, nullptr);
             std::vector<int32_t>().swap(j->src);
             std::vector<int32_t>().swap(j->dst);
         }
@@ -296,6 +296,7 @@ public:
             if (held_.empty() || (!idle && held_bytes_ < ctx_->budget / 4)) return;
             out.swap(held_);
         }
+        wait_abandoned();
         uint64_t freed = 0;
         for (device_graph& g : out) {
             freed += device_graph_bytes(g);
@@ -310,7 +311,14 @@ public:
         return held_bytes_;
     }
 
-    void abandon(int si) override { slots[si].dead = true; }
+    void abandon(int si) override { slots[si].dead.store(true); }
+
+    // Ends the rounds the watchdog gave up on: before graphs' memory goes back
+    // to the pool, since such a round may still read them.
+    void wait_abandoned() {
+        for (slot_buf& s : slots)
+            if (s.dead.load()) (void)hipStreamSynchronize(s.stream);
+    }
 
     void drain() override {
         {
@@ -322,7 +330,7 @@ public:
             });
         }
         for (slot_buf& s : slots)
-            if (!s.dead) (void)hipStreamSynchronize(s.stream);
+            if (!s.dead.load()) (void)hipStreamSynchronize(s.stream);
     }
 
 private:
@@ -401,6 +409,10 @@ serve_state* ensure_serving(tc_context_s* ctx, int* rc) {
 
 }  // namespace
 
+void serve_wait_abandoned(tc_context_s* ctx) {
+    if (ctx->serve) ctx->serve->ex.wait_abandoned();
+}
+
 // Stops the scheduler; queued tickets end with TC_ERR_SHUTDOWN (still pollable).
 void serve_stop(tc_context_s* ctx) {
     if (ctx->serve) ctx->serve->S->stop();
@@ -415,12 +427,15 @@ void serve_shutdown(tc_context_s* ctx) {
     for (slot_buf& s : st->ex.slots)
         if (s.stream) (void)hipStreamSynchronize(s.stream);
     st->S.reset();                        // frees the jobs left unpolled
+    st->ex.release(true);                 // (on the slots' streams)
     for (slot_buf& s : st->ex.slots) {
         slot_free(s);
         space_free(&s.space);
-        if (s.stream) (void)hipStreamDestroy(s.stream);
+        if (s.stream) {
+            (void)hipStreamSynchronize(s.stream);
+            (void)hipStreamDestroy(s.stream);
+        }
     }
-    st->ex.release(true);
     delete st;
     ctx->serve = nullptr;
 }
