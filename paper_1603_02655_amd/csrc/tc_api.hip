@@ -32,6 +32,9 @@ census_slices full_slices(const device_graph& g, bool tri) {
         sl.begin[b] = tri ? g.tri.edges.off[b] : g.bucket_off[b];
         sl.end[b] = tri ? g.tri.edges.off[b + 1] : g.bucket_off[b + 1];
     }
+    sl.row_end = (uint32_t)g.n;
+    sl.asym = g.p - g.mutual;
+    sl.mutual = g.mutual;
     return sl;
 }
 
@@ -97,13 +100,14 @@ int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_sli
     hipEvent_t* ev = ctx->timing ? ctx->ev : nullptr;
     census_config cfg = config_of(ctx->tuning);
     cfg.side_blocks = (uint32_t)ctx->cu_count;
-    hipError_t e = census_launch(g, sl, tri, ctx->tables + 64 * table, ctx->acc, ctx->counters, cfg, ctx->stream,
-                                 ev, ctx->side, ctx->fork);
+    hipError_t e = ctx->acc_clear ? hipSuccess : census_clear(ctx->acc, ctx->counters, ctx->stream);
+    ctx->acc_clear = false;
     if (e == hipSuccess)
-        e = hipMemcpyAsync(ctx->host_raw, ctx->acc, sizeof(unsigned long long) * kNumClasses,
-                           hipMemcpyDeviceToHost, ctx->stream);
+        e = census_launch(g, sl, tri, ctx->tables + 64 * table, table != 0, ctx->acc, ctx->counters, ctx->host_raw, cfg,
+                          ctx->stream, ev, ctx->side, ctx->fork);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return status_from_hip(e);
+    ctx->acc_clear = true;
     std::memcpy(raw, ctx->host_raw, sizeof(unsigned long long) * kNumClasses);
     if (ev) {
         for (int b = 0; b < kBuckets; ++b) {
@@ -115,7 +119,7 @@ int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_sli
             }
         }
         float ms = 0.f;
-        if (tri && g.p > 0 && hipEventElapsedTime(&ms, ev[2 * kBuckets], ev[2 * kBuckets + 1]) == hipSuccess) {
+        if (!sl.per_dyad && g.p > 0 && hipEventElapsedTime(&ms, ev[2 * kBuckets], ev[2 * kBuckets + 1]) == hipSuccess) {
             ctx->kstats.totals_ms += ms;
             ctx->kstats.totals_launches += 1;
         }
@@ -158,7 +162,7 @@ int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uin
 
 // ---------------------------------------------------------------------------
 // Scratch of tc_census_each_noalloc: kNoAllocCounterBytes of work counters,
-// then one block of 16 accumulators per graph.  Each GPU holds its own copy of
+// then the accumulators' copies (the rest is room for more).  Each GPU holds its own copy of
 // this array; host code never passes its name to a kernel (on the host it is a
 // stand-in, not a device address) but the address hipGetSymbolAddress returns
 // for the current device, looked up once per device by scratch_for_device.
@@ -248,7 +252,7 @@ int tc_context_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, t
         ctx->own_stream = true;
     }
     if (e == hipSuccess) e = census_upload_table();
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->acc, sizeof(unsigned long long) * kNumClasses);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->acc, sizeof(unsigned long long) * kNumClasses * kAccCopies);
     if (e == hipSuccess) e = hipMalloc((void**)&ctx->counters, sizeof(unsigned int) * 64);
     if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->host_raw, sizeof(unsigned long long) * kNumClasses);
     if (e == hipSuccess)
@@ -436,6 +440,7 @@ int tc_census_range(tc_context ctx, tc_graph g, int32_t u_begin, int32_t u_end, 
         }
         sl.begin[kBucketHub] = g->g.bucket_off[kBucketHub];
         sl.end[kBucketHub] = g->g.bucket_off[kBucketHub + 1];
+        sl.per_dyad = true;
         sl.u_lo = (uint32_t)u_begin;
         sl.u_hi = (uint32_t)u_end;
         int rc = run_census_locked(ctx, g->g, sl, raw);
@@ -466,8 +471,11 @@ int tc_census_shard(tc_context ctx, tc_graph g, int32_t shard, int32_t nshards, 
                             : dg.tri.edges.fine_tasks ? dg.tri.edges.fine_n_groups : dg.tri.edges.n_groups;
         sl.hub_g0 = (uint32_t)(ng * k / G);
         sl.hub_g1 = (uint32_t)(ng * (k + 1) / G);
-        sl.totals_begin = dg.U * k / G;
-        sl.totals_end = dg.U * (k + 1) / G;
+        const uint64_t n = (uint64_t)dg.n, asym = sl.asym, mutual = sl.mutual;
+        sl.row_begin = (uint32_t)(n * k / G);
+        sl.row_end = (uint32_t)(n * (k + 1) / G);
+        sl.asym = asym * (k + 1) / G - asym * k / G;
+        sl.mutual = mutual * (k + 1) / G - mutual * k / G;
         int rc = run_census_locked(ctx, dg, sl, raw, 0, tri);
         if (rc != TC_OK) return rc;
     }
@@ -505,18 +513,15 @@ int tc_census_each_noalloc(tc_context ctx, const tc_graph* graphs, int32_t count
         reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ctx->scratch) + kNoAllocCounterBytes);
     census_config cfg = config_of(ctx->tuning);
     cfg.side_blocks = (uint32_t)ctx->cu_count;
-    // every graph's launch sequence zeroes its own accumulator block and the
-    // counters before its kernels; the stream orders the graphs
-    hipError_t e = hipSuccess;
+    // every graph's launch sequence leaves the accumulators and the counters
+    // zero for the next; the stream orders the graphs
+    hipError_t e = census_clear(accs, ctr, ctx->stream);
     for (int32_t i = 0; i < count && e == hipSuccess; ++i) {
         const device_graph& g = graphs[i]->g;
         const bool tri = ctx->tuning.tri && g.tri.fwd_ptr;
-        e = census_launch(g, full_slices(g, tri), tri, ctx->tables, accs + (size_t)kNumClasses * i, ctr, cfg,
-                          ctx->stream, nullptr, ctx->side, ctx->fork);
+        e = census_launch(g, full_slices(g, tri), tri, ctx->tables, false, accs, ctr,
+                          ctx->host_many + (size_t)kNumClasses * i, cfg, ctx->stream, nullptr, ctx->side, ctx->fork);
     }
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ctx->host_many, accs, sizeof(unsigned long long) * kNumClasses * (size_t)count,
-                           hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return status_from_hip(e);
     for (int32_t i = 0; i < count; ++i)

@@ -35,9 +35,10 @@ struct tc_context_s {
     std::mutex mu;                      // serialises work on `stream` and the buffers below
     std::mutex tuning_mu;               // held (inside mu) while `tuning` is written; lets the
                                         // serving thread copy it without waiting for mu
-    unsigned long long* acc = nullptr;  // 16 accumulators (device)
+    unsigned long long* acc = nullptr;  // kAccCopies x 16 accumulators (device)
     unsigned int* counters = nullptr;   // work counters (device)
-    unsigned long long* host_raw = nullptr;  // pinned copy of acc
+    bool acc_clear = false;             // acc and counters are zero (the last census ended normally)
+    unsigned long long* host_raw = nullptr;  // pinned: the 16 sums of a census
     uint8_t* tables = nullptr;          // 4 x 64 bin indices (device): the 16-class table,
                                         // then the labelled census's pass tables for f_uv = 1, 2, 3
     hipEvent_t ev[2 * tc::kBuckets + 2] = {};

@@ -79,20 +79,23 @@ graph_desc describe(const device_graph& g) {
     d.tri_groups = g.tri.edges.n_groups;
     d.hub_chunk = g.hub_chunk;
     d.tri_chunk = g.tri.edges.chunk;
+    d.asym = g.p - g.mutual;
+    d.mutual = g.mutual;
     return d;
 }
 
-// Work items of one graph: hub tasks into `hub`; into `out` the totals chunks
-// (when `tri`), then group-mode records (largest), wave-mode chunks and
+// Work items of one graph: hub tasks into `hub`; into `out` the chunks of
+// rows, then group-mode records (largest), wave-mode chunks and
 // lane-mode chunks, over the forward-list edge records when `tri`.
 void append_items(const device_graph& g, uint32_t gi, bool tri, std::vector<work_item>& hub,
                   std::vector<work_item>& out) {
     const uint64_t* off = g.bucket_off;
     uint32_t ngroups = g.n_hub_groups, flag = 0;
+    if (g.p > 0)
+        for (uint64_t x = 0; x < (uint64_t)g.n; x += kBatchRowsPerItem)
+            out.push_back(work_item{gi, kItemRows, (uint32_t)x,
+                                    (uint32_t)std::min<uint64_t>(x + kBatchRowsPerItem, (uint64_t)g.n)});
     if (tri) {
-        for (uint64_t e = 0; e < g.U; e += kBatchTotalsPerItem)
-            out.push_back(work_item{gi, kItemTotals, (uint32_t)e,
-                                    (uint32_t)std::min<uint64_t>(e + kBatchTotalsPerItem, g.U)});
         off = g.tri.edges.off;
         ngroups = g.tri.edges.n_groups;
         flag = kItemTri;

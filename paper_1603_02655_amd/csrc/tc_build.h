@@ -37,8 +37,8 @@ struct rec_set {
 // A triangle {x, y, z} in degree order is found exactly once, as the shared
 // vertex z of the forward lists of x and y.  The edge records (recs of `edges`)
 // use the dyad_rec layout with forward-list bounds: bu..ev bound N+(u), N+(v)
-// for u < v by id, vf = (v << 2) | f_uv, iv = iu = 0; edges whose two forward
-// lists cannot share a vertex (one is empty) are left out.
+// for u < v by id, vf = (v << 2) | f_uv; edges whose two forward lists cannot
+// share a vertex (one is empty) are left out.
 struct forward_lists {
     uint32_t* fwd = nullptr;
     uint32_t* fwd_owner = nullptr;

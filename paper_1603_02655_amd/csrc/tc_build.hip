@@ -579,15 +579,6 @@ __global__ __launch_bounds__(kT) void k_bucket_sums(const uint64_t* __restrict__
     if (threadIdx.x == 0) host[kBuckets + 1 + q] = s;
 }
 
-__device__ inline uint32_t find_in_row(const uint32_t* nbr, uint32_t lo, uint32_t hi, uint32_t x) {
-    // first position in [lo, hi) whose vertex is >= x
-    while (lo < hi) {
-        uint32_t mid = lo + ((hi - lo) >> 1);
-        if ((nbr[mid] >> 2) < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // Writes the records.  Lane / wave / group records keep the entry order of the
 // view (u-major for dyads) through a stable per-bucket ranking.  Hub records
 // of the dyad view come from their anchor's row and so are anchor-major in
@@ -633,22 +624,8 @@ __global__ __launch_bounds__(kT) void k_dyad_scatter(const uint32_t* __restrict_
             rec.bv = (uint32_t)row_ptr[v];
             rec.ev = rec.bv + len[v];
             rec.u = u;
-            if (tri) {
-                const uint32_t fo = nbr[e] & 3u;
-                const uint32_t fuv = o == u ? fo : ((fo & 1u) << 1) | (fo >> 1);
-                rec.iv = 0;
-                rec.iu = 0;
-                rec.vf = (v << 2) | fuv;
-            } else {
-                if (o == u) {
-                    rec.iv = (uint32_t)e;
-                    rec.iu = find_in_row(nbr, rec.bv, rec.ev, u);
-                } else {
-                    rec.iu = (uint32_t)e;
-                    rec.iv = find_in_row(nbr, rec.bu, rec.eu, v);
-                }
-                rec.vf = nbr[rec.iv];   // (v << 2) | f_uv
-            }
+            const uint32_t fo = nbr[e] & 3u;
+            rec.vf = (v << 2) | (o == u ? fo : ((fo & 1u) << 1) | (fo >> 1));
             if (tri && b == kBucketHub)
                 out[hub_begin + rec_off[anchor] + atomicAdd(&cursor[anchor], 1u)] = rec;
             else {

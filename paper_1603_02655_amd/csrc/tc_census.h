@@ -22,14 +22,17 @@ bool tile_supported(uint32_t hub_tile, uint32_t wave_tile, uint32_t group_tile, 
 
 // Per-bucket record slices [begin, end) into g.dyads or the edge records
 // (merge buckets); the hub bucket runs its task groups [hub_g0, hub_g1),
-// restricted to dyads with u in [u_lo, u_hi); the totals pass of the
-// forward-list path covers the neighbour entries [totals_begin, totals_end).
+// restricted to dyads with u in [u_lo, u_hi).  The terms that need no
+// intersection are added dyad by dyad (per_dyad, dyad records only), or cover
+// the rows [row_begin, row_end) and the bases of `asym` and `mutual` pairs.
 struct census_slices {
     uint64_t begin[kBuckets];
     uint64_t end[kBuckets];
     uint32_t u_lo = 0, u_hi = 0xffffffffu;
     uint32_t hub_g0 = 0, hub_g1 = 0xffffffffu;
-    uint64_t totals_begin = 0, totals_end = ~0ull;
+    bool per_dyad = false;
+    uint32_t row_begin = 0, row_end = 0;
+    uint64_t asym = 0, mutual = 0;
 };
 
 // ---- batched launch over many graphs ----
@@ -49,16 +52,17 @@ struct graph_desc {
     uint32_t hub_ntasks, hub_groups;   // tasks and task groups over the dyad records
     uint32_t tri_tasks, tri_groups;    // tasks and task groups over the edge records
     uint32_t hub_chunk, tri_chunk;     // records per hub task and per group, each view
+    uint64_t asym, mutual;             // joined pairs, one way and both ways
 };
 // Item kinds: the mode (lane / wave / group / hub), with kItemTri when the item
-// indexes the forward-list edge records; kItemTotals covers neighbour entries
-// [begin, end) of the totals pass.
-enum : uint32_t { kItemLane = 0, kItemWave = 1, kItemGroup = 2, kItemHub = 3, kItemTri = 4, kItemTotals = 8 };
+// indexes the forward-list edge records; kItemRows covers the rows [begin, end)
+// of the terms that need no intersection.
+enum : uint32_t { kItemLane = 0, kItemWave = 1, kItemGroup = 2, kItemHub = 3, kItemTri = 4, kItemRows = 8 };
 struct work_item {
     uint32_t graph, kind, begin, end;   // records [begin, end) of graph `graph`'s record array;
                                         // hub items: task groups [begin, end) of the graph
 };
-constexpr uint32_t kBatchTotalsPerItem = 4096;   // neighbour entries per totals item
+constexpr uint32_t kBatchRowsPerItem = 4096;   // rows per rows item
 constexpr uint32_t kBatchLanePerItem = 256;   // one dyad per thread of a 256-thread workgroup
 constexpr uint32_t kBatchWavePerItem = 16;    // four wavefronts, four dyads each
 
@@ -77,17 +81,25 @@ hipError_t batch_launch(const graph_desc* descs, const work_item* items, const u
 
 // Copies the 16-class table into the constant table the batch kernel reads.
 hipError_t census_upload_table();
-// Zeroes acc (16 x u64) and counters (kBuckets x u32), then runs the bucket
-// kernels over the given slices with `table` (64 bytes of device memory: the
-// bin of every code, kNumClasses for codes that are not counted).  With `tri`
-// the slices index the forward-list edge records (g.tri.edges) and a totals
-// pass over every dyad record runs too: first on s, or, when `side` is given
+// One census on stream s: the bucket kernels over the given slices with
+// `table` (64 bytes of device memory: the bin of every code, kNumClasses for
+// codes that are not counted), the terms that need no intersection, and a last
+// kernel that writes the 16 sums to `out` (pinned host memory) and leaves acc
+// (kAccCopies x 16 u64) and counters (kBuckets x 8 u32) zero, as they have to
+// be before.  With `tri` the slices index the forward-list edge records
+// (g.tri.edges).  `labelled`: the table is one of the labelled census's, whose
+// terms come from a pass over the neighbour entries.  When `side` is given
 // (with two events in `fork`) and the hub bucket streams more entries than the
-// graph has, on `side` with side_blocks workgroups, followed there by the lane
-// bucket, beside the other bucket kernels; s waits for it at the end.  ev, when not null, holds
-// 2*kBuckets + 2 events: around each bucket's launch, then around the totals.
-hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tri, const uint8_t* table,
-                         unsigned long long* acc, unsigned int* counters, const census_config& cfg, hipStream_t s,
-                         hipEvent_t* ev, hipStream_t side = nullptr, hipEvent_t* fork = nullptr);
+// graph has, these terms run on `side`, followed there by the lane bucket,
+// beside the other bucket kernels; s waits for it at the end.  ev, when not
+// null, holds 2*kBuckets + 2 events: around each bucket's launch, then around
+// the terms.
+hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tri, const uint8_t* table, bool labelled,
+                         unsigned long long* acc, unsigned int* counters, unsigned long long* out,
+                         const census_config& cfg, hipStream_t s, hipEvent_t* ev, hipStream_t side = nullptr,
+                         hipEvent_t* fork = nullptr);
+// Zeroes acc and counters (before the first census that uses them, or after a
+// failed launch).
+hipError_t census_clear(unsigned long long* acc, unsigned int* counters, hipStream_t s);
 
 }  // namespace tc

@@ -8,6 +8,8 @@
 //                         32 bits and (f >> 1) in the high 32 bits; a range
 //                         [a, b) of a row holds lo(tpre[b]-tpre[a]) arcs leaving
 //                         the owner and hi(...) arcs entering it
+//   rinfo[n]      uint4   row bounds and tpre at the row's end: the row's counts
+//                         of each direction type are a difference of two records
 //   dyads[p]      dyad_rec one task per canonical dyad (u < v joined either way),
 //                         partitioned into degree buckets; u-major inside the
 //                         merge buckets, anchor-major inside the hub bucket
@@ -29,12 +31,16 @@ constexpr int kMaxN = 4801280;         // largest n with C(n,3) < 2^64
 struct __attribute__((aligned(16))) dyad_rec {
     uint32_t bu, eu;   // row of u: [bu, eu)
     uint32_t bv, ev;   // row of v: [bv, ev)
-    uint32_t iv;       // position of v inside row u
-    uint32_t iu;       // position of u inside row v
     uint32_t u;        // vertex u
     uint32_t vf;       // (v << 2) | f_uv, f_uv = IsEdge(u,v) + 2 IsEdge(v,u)
+    uint32_t pad[2];   // (24-byte records, read 8 bytes at a time: 2 % slower on R-MAT 2^20)
 };
-static_assert(sizeof(dyad_rec) == 32, "dyad record is two 16-byte loads");
+static_assert(sizeof(dyad_rec) == 32, "dyad record is a 16-byte and an 8-byte load");
+
+// Accumulators of one census: kAccCopies blocks of 16 (one per workgroup
+// modulo the copies, so that the workgroups' final atomics spread over as many
+// addresses), added up by the last kernel of the census.
+constexpr int kAccCopies = 32;
 
 // A run of hub-bucket records [begin, end) whose dyads all contain `anchor`.
 // Consecutive tasks form groups that a workgroup runs with one LDS tile;
@@ -135,9 +141,10 @@ struct census_args {
     const uint32_t* nbr;
     const uint64_t* tpre;
     uint64_t n;               // vertices of the graph
-    unsigned long long* acc;  // 16 accumulators of the graph
+    unsigned long long* acc;  // kAccCopies blocks of 16 accumulators
     uint32_t u_lo, u_hi;      // hub kernel: only dyads with u in [u_lo, u_hi)
     const uint8_t* table;     // 64 bin indices (device memory), one per code
     uint32_t hub_chunk;       // hub kernel: records per task and per group of tasks
+    bool per_dyad;            // dyad records: add each dyad's own terms (a census of part of the dyads)
 };
 }  // namespace tc

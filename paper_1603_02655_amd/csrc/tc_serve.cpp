@@ -104,7 +104,7 @@ uint64_t job_footprint(const serve_job& j) {
         uint64_t items = (tri ? g.tri.edges.n_groups : g.n_hub_groups) + (off[3] - off[2]) +
                          (off[2] - off[1] + kBatchWavePerItem - 1) / kBatchWavePerItem +
                          (off[1] - off[0] + kBatchLanePerItem - 1) / kBatchLanePerItem;
-        if (tri) items += (g.U + kBatchTotalsPerItem - 1) / kBatchTotalsPerItem;
+        items += ((uint64_t)g.n + kBatchRowsPerItem - 1) / kBatchRowsPerItem;
         return ws + sizeof(work_item) * items;
     }
     uint64_t m = j.src.size();
