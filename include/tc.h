@@ -72,20 +72,18 @@ typedef struct {
     uint64_t hub_staged;          /* sum over hub tasks of the anchor degree (entries staged in LDS) */
     /* forward lists (built when the tuning has tri = 1; zero otherwise) */
     uint64_t fwd_entries;                      /* = canonical dyads */
-    uint64_t tri_bucket_edges[TC_NUM_BUCKETS]; /* edge records per bucket (edges with an empty forward list omitted) */
+    uint64_t tri_bucket_edges[TC_NUM_BUCKETS]; /* edge records per bucket (edges that close no triangle
+                                                  with a vertex after both omitted) */
     uint64_t tri_bucket_cost[TC_NUM_BUCKETS];  /* sum of |N+(x)|+|N+(y)| per bucket */
     uint64_t tri_tasks;           /* hub tasks over the forward lists */
-    uint64_t tri_stream;          /* sum over hub edges of the non-anchor forward-list length */
-    uint64_t tri_staged;          /* sum over those tasks of the anchor forward-list length */
+    uint64_t tri_stream;          /* sum over hub edges (x, y) of the entries of N+(x) before y */
+    uint64_t tri_staged;          /* sum over those tasks of the shared vertex's forward-list length */
     /* groups of consecutive hub tasks that one workgroup stages into a single LDS tile */
     uint64_t hub_groups;          /* over the hub dyads */
-    uint64_t tri_groups;          /* over the hub edges of the forward lists */
+    uint64_t tri_groups;          /* over the hub edges of the forward lists: each task is one */
     uint64_t hub_chunk;           /* records per hub task and per group, hub dyads (512) */
-    uint64_t tri_chunk;           /* the same over the hub edges of the forward lists as tc_census runs
-                                     them: 256 for hub buckets of 2^20 edges or more, else 512; such a
-                                     bucket also holds a set of 512-record tasks over the same edges,
-                                     which batched and served launches run.  tri_tasks, tri_staged and
-                                     tri_groups describe the set tc_census runs */
+    uint64_t tri_chunk;           /* records per hub task of the forward lists: 256 for hub buckets of 2^20
+                                     edges or more, 64 from 2^13 edges on, else 512 */
 } tc_graph_info;
 
 /* Degree-bucket thresholds and launch sizes.  A dyad one of whose endpoints
@@ -100,11 +98,12 @@ typedef struct {
  * tri = 1 (graphs built or rebucketed while it is set) also builds forward
  * lists: N+(x), the neighbours that follow x in degree order ((|N|, id)
  * ascending).  tc_census, tc_census_each and tc_census64 then add the
- * intersection-free per-dyad terms in one pass over the dyads and find every
+ * intersection-free per-dyad terms in one pass over the rows and find every
  * shared vertex of every dyad through the triangles of the graph, each
  * triangle once, as a shared vertex of the forward lists of its two first
  * vertices; the same thresholds bucket those edge records by
- * |N+(x)| + |N+(y)| (and t_hub by the longer forward list).  The counts are
+ * |N+(x)| + |N+(y)| (and t_hub by the longer forward list; hub_tile has no
+ * effect on them).  The counts are
  * identical either way.  The batched and the served modes take the same path
  * per graph (forward-list items for graphs that have forward lists while tri
  * is set, dyad-record items otherwise; requests that carry their arcs are built
@@ -196,8 +195,9 @@ int tc_census(tc_context ctx, tc_graph g, uint64_t counts[16]);
  * counts it, w the third vertex); the term n - |S| - 2 of a dyad goes to the
  * code of the (u, v) pair alone; counts[0] is C(n, 3) minus the rest.  The
  * histogram depends on the vertex ids (it is not an isomorphism invariant);
- * folding it through the 64 -> 16 table gives tc_census.  Runs the census
- * kernels three times (one pass per (u, v) dyad type).  Errors as tc_census. */
+ * folding it through the 64 -> 16 table gives tc_census.  One pass of
+ * the census kernels through the forward lists, three (one per (u, v) dyad
+ * type) over the dyad records.  Errors as tc_census. */
 int tc_census64(tc_context ctx, tc_graph g, uint64_t counts[64]);
 
 /* Partial census over the canonical dyads (u, v) with u in [u_begin, u_end):
@@ -232,10 +232,9 @@ int tc_census_each(tc_context ctx, const tc_graph* graphs, int32_t count, uint64
 /* For callers that cannot allocate device memory while they run (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same counts as tc_census_each, without any allocation.  The kernels'
- * scratch (work counters and one block of 16 accumulators per graph) lives in
- * a fixed device array of the library, 33,024 bytes per GPU, held until the
- * process ends; the read-back goes through pinned host memory the context
- * allocated when it was created.  The launches of all graphs are queued back
+ * scratch (work counters and accumulators) lives in a fixed device array of the
+ * library, 33,024 bytes per GPU, held until the process ends; the counts go to
+ * pinned host memory the context allocated when it was created.  The launches of all graphs are queued back
  * to back and the counts read once at the end.
  *   graphs: count resident graphs of ctx (the same graph may repeat);
  *   counts (host): receives count*16 values, graph i at counts[16*i].

@@ -79,36 +79,35 @@ void fill_info(const tc_graph_s* g, tc_graph_info* info) {
     info->hub_stream = g->g.hub_stream;
     info->hub_staged = g->g.hub_staged;
     const forward_lists& t = g->g.tri;
-    info->fwd_entries = t.fwd_ptr ? t.entries : 0;
+    info->fwd_entries = t.fptr ? t.entries : 0;
     for (int b = 0; b < kBuckets; ++b) {
         info->tri_bucket_edges[b] = t.edges.off[b + 1] - t.edges.off[b];
         info->tri_bucket_cost[b] = t.edges.cost[b];
     }
-    // the forward lists' hub tasks a census runs: the half-size set when there is one
-    const bool fine = t.edges.fine_tasks != nullptr;
-    info->tri_tasks = fine ? t.edges.fine_n_tasks : t.edges.n_tasks;
+    info->tri_tasks = t.edges.n_tasks;
     info->tri_stream = t.edges.stream;
-    info->tri_staged = fine ? t.edges.fine_staged : t.edges.staged;
+    info->tri_staged = t.edges.staged;
     info->hub_groups = g->g.n_hub_groups;
-    info->tri_groups = fine ? t.edges.fine_n_groups : t.edges.n_groups;
+    info->tri_groups = t.edges.n_groups;
     info->hub_chunk = g->g.hub_chunk;
-    info->tri_chunk = !t.fwd_ptr ? 0 : fine ? kHubChunk / 2 : t.edges.chunk;
+    info->tri_chunk = t.fptr ? t.edges.chunk : 0;
 }
 
 int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_slices& sl,
-                      unsigned long long raw[16], int table, bool tri) {
+                      unsigned long long* raw, int table, bool tri) {
     hipEvent_t* ev = ctx->timing ? ctx->ev : nullptr;
     census_config cfg = config_of(ctx->tuning);
     cfg.side_blocks = (uint32_t)ctx->cu_count;
-    hipError_t e = ctx->acc_clear ? hipSuccess : census_clear(ctx->acc, ctx->counters, ctx->stream);
+    hipError_t e = ctx->acc_clear ? hipSuccess : census_clear(ctx->acc, kAccWords, ctx->counters, ctx->stream);
+    const census_kind kind = table == 0 ? kClasses : table == kAllCodes ? kLabelled : kLabelledPass;
     ctx->acc_clear = false;
     if (e == hipSuccess)
-        e = census_launch(g, sl, tri, ctx->tables + 64 * table, table != 0, ctx->acc, ctx->counters, ctx->host_raw, cfg,
+        e = census_launch(g, sl, tri, ctx->tables + 64 * table, kind, ctx->acc, ctx->counters, ctx->host_raw, cfg,
                           ctx->stream, ev, ctx->side, ctx->fork);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return status_from_hip(e);
     ctx->acc_clear = true;
-    std::memcpy(raw, ctx->host_raw, sizeof(unsigned long long) * kNumClasses);
+    std::memcpy(raw, ctx->host_raw, sizeof(unsigned long long) * (kind == kLabelled ? 64 : kNumClasses));
     if (ev) {
         for (int b = 0; b < kBuckets; ++b) {
             if (sl.end[b] <= sl.begin[b]) continue;
@@ -128,8 +127,8 @@ int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_sli
     return TC_OK;
 }
 
-int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long raw[16], int table) {
-    const bool tri = ctx->tuning.tri && g.tri.fwd_ptr;
+int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long* raw, int table) {
+    const bool tri = ctx->tuning.tri && g.tri.fptr;
     return run_census_locked(ctx, g, full_slices(g, tri), raw, table, tri);
 }
 
@@ -166,10 +165,10 @@ int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uin
 // this array; host code never passes its name to a kernel (on the host it is a
 // stand-in, not a device address) but the address hipGetSymbolAddress returns
 // for the current device, looked up once per device by scratch_for_device.
-constexpr size_t kNoAllocCounterBytes = 256;   // 64 work counters (the kernels use kBuckets x 8)
-constexpr size_t kNoAllocBytes =
-    kNoAllocCounterBytes + sizeof(unsigned long long) * kNumClasses * (size_t)TC_NOALLOC_MAX_GRAPHS;
-static_assert(kNoAllocBytes == 33024, "size stated in tc.h");
+constexpr size_t kNoAllocCounterBytes = sizeof(unsigned int) * kBuckets * kCounterWords;   // work counters
+constexpr size_t kNoAllocBytes = 33024;   // stated in tc.h
+static_assert(kNoAllocCounterBytes + sizeof(unsigned long long) * kNumClasses * kAccCopies <= kNoAllocBytes,
+              "counters and accumulators fit");
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
@@ -252,19 +251,21 @@ int tc_context_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, t
         ctx->own_stream = true;
     }
     if (e == hipSuccess) e = census_upload_table();
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->acc, sizeof(unsigned long long) * kNumClasses * kAccCopies);
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->counters, sizeof(unsigned int) * 64);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->host_raw, sizeof(unsigned long long) * kNumClasses);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->acc, sizeof(unsigned long long) * kAccWords);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->counters, sizeof(unsigned int) * kBuckets * kCounterWords);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->host_raw, sizeof(unsigned long long) * 64);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&ctx->host_many,
                           sizeof(unsigned long long) * kNumClasses * (size_t)TC_NOALLOC_MAX_GRAPHS);
     if (e == hipSuccess) e = scratch_for_device(device, &ctx->scratch);
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->tables, 4 * 64);
+    if (e == hipSuccess) e = hipMalloc((void**)&ctx->tables, 5 * 64);
     if (e == hipSuccess) {
         // table 0: the 64 -> 16 class map; table f (1..3): code -> code >> 2 for
-        // the codes whose (u, v) part is f, every other code to the discard bin
-        uint8_t host[4 * 64];
+        // the codes whose (u, v) part is f, every other code to the discard bin;
+        // table kAllCodes: every code to itself
+        uint8_t host[5 * 64];
         for (int c = 0; c < 64; ++c) {
+            host[64 * kAllCodes + c] = (uint8_t)c;
             host[c] = kTable.t[c];
             for (int f = 1; f < 4; ++f) host[64 * f + c] = (c & 3) == f ? (uint8_t)(c >> 2) : (uint8_t)kNumClasses;
         }
@@ -390,7 +391,15 @@ int tc_census64(tc_context ctx, tc_graph g, uint64_t counts[64]) {
     uint64_t out[64] = {0};
     typedef unsigned __int128 u128;
     u128 sum = 0;
-    for (int f = 1; f < 4; ++f) {
+    if (ctx->tuning.tri && g->g.tri.fptr) {
+        unsigned long long raw[64];
+        int rc = run_full_locked(ctx, g->g, raw, kAllCodes);
+        if (rc != TC_OK) return rc;
+        for (int c = 1; c < 64; ++c) {
+            out[c] = raw[c];
+            sum += raw[c];
+        }
+    } else for (int f = 1; f < 4; ++f) {
         unsigned long long raw[16];
         int rc = run_full_locked(ctx, g->g, raw, f);
         if (rc != TC_OK) return rc;
@@ -459,7 +468,7 @@ int tc_census_shard(tc_context ctx, tc_graph g, int32_t shard, int32_t nshards, 
     const device_graph& dg = g->g;
     unsigned long long raw[16] = {0};
     if (dg.p > 0) {
-        const bool tri = ctx->tuning.tri && dg.tri.fwd_ptr;
+        const bool tri = ctx->tuning.tri && dg.tri.fptr;
         census_slices sl = full_slices(dg, tri);
         const uint64_t k = (uint64_t)shard, G = (uint64_t)nshards;
         for (int b = 0; b < kBucketHub; ++b) {
@@ -467,8 +476,7 @@ int tc_census_shard(tc_context ctx, tc_graph g, int32_t shard, int32_t nshards, 
             sl.begin[b] = lo + len * k / G;
             sl.end[b] = lo + len * (k + 1) / G;
         }
-        const uint64_t ng = !tri ? dg.n_hub_groups
-                            : dg.tri.edges.fine_tasks ? dg.tri.edges.fine_n_groups : dg.tri.edges.n_groups;
+        const uint64_t ng = tri ? dg.tri.edges.n_tasks : dg.n_hub_groups;
         sl.hub_g0 = (uint32_t)(ng * k / G);
         sl.hub_g1 = (uint32_t)(ng * (k + 1) / G);
         const uint64_t n = (uint64_t)dg.n, asym = sl.asym, mutual = sl.mutual;
@@ -515,11 +523,11 @@ int tc_census_each_noalloc(tc_context ctx, const tc_graph* graphs, int32_t count
     cfg.side_blocks = (uint32_t)ctx->cu_count;
     // every graph's launch sequence leaves the accumulators and the counters
     // zero for the next; the stream orders the graphs
-    hipError_t e = census_clear(accs, ctr, ctx->stream);
+    hipError_t e = census_clear(accs, kNumClasses * kAccCopies, ctr, ctx->stream);
     for (int32_t i = 0; i < count && e == hipSuccess; ++i) {
         const device_graph& g = graphs[i]->g;
-        const bool tri = ctx->tuning.tri && g.tri.fwd_ptr;
-        e = census_launch(g, full_slices(g, tri), tri, ctx->tables, false, accs, ctr,
+        const bool tri = ctx->tuning.tri && g.tri.fptr;
+        e = census_launch(g, full_slices(g, tri), tri, ctx->tables, kClasses, accs, ctr,
                           ctx->host_many + (size_t)kNumClasses * i, cfg, ctx->stream, nullptr, ctx->side, ctx->fork);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);

@@ -35,12 +35,12 @@ struct tc_context_s {
     std::mutex mu;                      // serialises work on `stream` and the buffers below
     std::mutex tuning_mu;               // held (inside mu) while `tuning` is written; lets the
                                         // serving thread copy it without waiting for mu
-    unsigned long long* acc = nullptr;  // kAccCopies x 16 accumulators (device)
+    unsigned long long* acc = nullptr;  // kAccWords accumulators (device)
     unsigned int* counters = nullptr;   // work counters (device)
     bool acc_clear = false;             // acc and counters are zero (the last census ended normally)
-    unsigned long long* host_raw = nullptr;  // pinned: the 16 sums of a census
-    uint8_t* tables = nullptr;          // 4 x 64 bin indices (device): the 16-class table,
-                                        // then the labelled census's pass tables for f_uv = 1, 2, 3
+    unsigned long long* host_raw = nullptr;  // pinned: the sums of a census (16, or 64 codes)
+    uint8_t* tables = nullptr;          // 5 x 64 bin indices (device): the 16-class table, the labelled
+                                        // census's pass tables for f_uv = 1, 2, 3, and every code itself
     hipEvent_t ev[2 * tc::kBuckets + 2] = {};
     hipStream_t side = nullptr;         // runs the totals pass beside the bucket kernels
     hipEvent_t fork[2] = {};            // side stream start / end
@@ -65,13 +65,15 @@ census_slices full_slices(const device_graph& g, bool tri = false);
 census_config config_of(const tc_tuning& t);
 void fill_info(const tc_graph_s* g, tc_graph_info* info);
 // Runs the bucket kernels over `sl` with table `table` (0: 16 classes; 1..3:
-// labelled census pass for f_uv = table) and copies the 16 raw sums to host.
-// With `tri` the slices index the forward-list edge records.
-int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_slices& sl, unsigned long long raw[16],
+// labelled census pass for f_uv = table, 16 sums; kAllCodes: 64 code sums,
+// forward lists only) and copies the raw sums to host.  With `tri` the slices
+// index the forward-list edge records.
+constexpr int kAllCodes = 4;
+int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_slices& sl, unsigned long long* raw,
                       int table = 0, bool tri = false);
 // The whole census of g: through the forward lists when the tuning asks for
 // them and g has them, else through the dyad records.
-int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long raw[16], int table = 0);
+int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long* raw, int table = 0);
 // Builds a device graph from host (or, with TC_BUILD_DEVICE_PTRS, device) arcs
 // on `stream`, with the scratch of *sp (trimmed to `keep` bytes at the end);
 // returns a TC_* status and fills the build part of *info.
@@ -113,8 +115,19 @@ inline tc_tuning default_tuning(int cu_count) {
 
 // batched mode (tc_batch.hip)
 graph_desc describe(const device_graph& g);
-void append_items(const device_graph& g, uint32_t gi, bool tri, std::vector<work_item>& hub,
-                  std::vector<work_item>& out);
+struct item_lists {
+    std::vector<work_item> tri, hub, rest;
+    // All items in launch order (in `tri`), and the ends of the three lists.
+    std::vector<work_item>& join(uint32_t nums[3]) {
+        nums[0] = (uint32_t)tri.size();
+        nums[1] = nums[0] + (uint32_t)hub.size();
+        nums[2] = nums[1] + (uint32_t)rest.size();
+        tri.insert(tri.end(), hub.begin(), hub.end());
+        tri.insert(tri.end(), rest.begin(), rest.end());
+        return tri;
+    }
+};
+void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it);
 void batch_release_all(tc_context_s* ctx);
 void batch_forget_graph_locked(tc_context_s* ctx, tc_graph g);
 

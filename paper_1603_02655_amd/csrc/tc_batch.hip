@@ -23,9 +23,8 @@ struct batch_plan {
     unsigned long long* h_accs = nullptr;   // pinned
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    uint32_t grid = 0, hub_grid = 0;
+    uint32_t grid = 0, hub_grid = 0, tri_grid = 0;
     uint32_t hub_tile = 0, batch_tile = 0;  // LDS tiles the captured kernels use
-    uint32_t hub_chunk = 0;                 // largest records per hub task of the graphs (hub kernel instance)
     bool valid = false;                     // buffers describe `graphs`
     bool tri = false;                       // ... through their forward lists
 
@@ -75,32 +74,33 @@ graph_desc describe(const device_graph& g) {
     d.edge_tasks = g.tri.edges.tasks;
     d.hub_ntasks = g.n_hub_tasks;
     d.hub_groups = g.n_hub_groups;
-    d.tri_tasks = g.tri.edges.n_tasks;
-    d.tri_groups = g.tri.edges.n_groups;
-    d.hub_chunk = g.hub_chunk;
     d.tri_chunk = g.tri.edges.chunk;
     d.asym = g.p - g.mutual;
     d.mutual = g.mutual;
     return d;
 }
 
-// Work items of one graph: hub tasks into `hub`; into `out` the chunks of
-// rows, then group-mode records (largest), wave-mode chunks and
+// Work items of one graph: into it.tri runs of hub tasks of the forward lists,
+// or into it.hub the hub task groups of the dyad records; into it.rest the
+// chunks of rows, then group-mode records (largest), wave-mode chunks and
 // lane-mode chunks, over the forward-list edge records when `tri`.
-void append_items(const device_graph& g, uint32_t gi, bool tri, std::vector<work_item>& hub,
-                  std::vector<work_item>& out) {
+void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it) {
+    std::vector<work_item>& out = it.rest;
     const uint64_t* off = g.bucket_off;
-    uint32_t ngroups = g.n_hub_groups, flag = 0;
+    uint32_t flag = 0;
     if (g.p > 0)
         for (uint64_t x = 0; x < (uint64_t)g.n; x += kBatchRowsPerItem)
             out.push_back(work_item{gi, kItemRows, (uint32_t)x,
                                     (uint32_t)std::min<uint64_t>(x + kBatchRowsPerItem, (uint64_t)g.n)});
     if (tri) {
         off = g.tri.edges.off;
-        ngroups = g.tri.edges.n_groups;
         flag = kItemTri;
+        const uint32_t nt = g.tri.edges.n_tasks;
+        for (uint32_t t = 0; t < nt; t += kBatchTasksPerItem)
+            it.tri.push_back(work_item{gi, kItemHub | kItemTri, t, std::min(t + kBatchTasksPerItem, nt)});
+    } else {
+        for (uint32_t t = 0; t < g.n_hub_groups; ++t) it.hub.push_back(work_item{gi, kItemHub, t, t + 1});
     }
-    for (uint32_t t = 0; t < ngroups; ++t) hub.push_back(work_item{gi, kItemHub | flag, t, t + 1});
     for (uint64_t d = off[2]; d < off[3]; ++d)
         out.push_back(work_item{gi, kItemGroup | flag, (uint32_t)d, (uint32_t)d + 1});
     for (uint64_t d = off[1]; d < off[2]; d += kBatchWavePerItem)
@@ -114,9 +114,9 @@ void append_items(const device_graph& g, uint32_t gi, bool tri, std::vector<work
 namespace {
 
 hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipStream_t s, uint32_t grid,
-                           uint32_t hub_grid, uint32_t hub_tile, uint32_t batch_tile, uint32_t hub_chunk) {
+                           uint32_t hub_grid, uint32_t tri_grid, uint32_t hub_tile, uint32_t batch_tile) {
     if (p->exec && graphs <= p->cap_graphs && items <= p->cap_items && grid == p->grid && hub_grid == p->hub_grid &&
-        hub_tile == p->hub_tile && batch_tile == p->batch_tile && hub_chunk == p->hub_chunk)
+        tri_grid == p->tri_grid && hub_tile == p->hub_tile && batch_tile == p->batch_tile)
         return hipSuccess;
     (void)hipStreamSynchronize(s);
     p->release();
@@ -126,12 +126,12 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
     p->hub_grid = hub_grid;
     p->hub_tile = hub_tile;
     p->batch_tile = batch_tile;
-    p->hub_chunk = hub_chunk;
+    p->tri_grid = tri_grid;
     hipError_t e = hipMalloc((void**)&p->d_desc, sizeof(graph_desc) * p->cap_graphs);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_items, sizeof(work_item) * p->cap_items);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_num, 2 * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc((void**)&p->d_num, 3 * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_ctr, sizeof(unsigned int) * 64);
+    if (e == hipSuccess) e = hipMalloc((void**)&p->d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&p->h_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs);
     if (e != hipSuccess) {
@@ -141,8 +141,8 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
     // capture: zero accumulators and counters, persistent kernel, read-back
     e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
-    hipError_t el = batch_launch(p->d_desc, p->d_items, p->d_num, p->d_accs, (uint64_t)kNumClasses * p->cap_graphs,
-                                 p->d_ctr, p->grid, p->hub_grid, p->hub_tile, p->batch_tile, p->hub_chunk, s);
+    const batch_buffers bb{p->d_desc, p->d_items, p->d_num, p->d_accs, p->d_ctr, p->tri_grid, p->hub_grid, p->grid};
+    hipError_t el = batch_launch(bb, (uint64_t)kNumClasses * p->cap_graphs, p->hub_tile, p->batch_tile, s);
     hipError_t ec = hipMemcpyAsync(p->h_accs, p->d_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs,
                                    hipMemcpyDeviceToHost, s);
     e = hipStreamEndCapture(s, &p->graph);
@@ -173,21 +173,22 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
     hipError_t e = hipSuccess;
     const bool tri = ctx->tuning.tri != 0;
     if (!(p->valid && p->graphs == want && p->grid == ctx->tuning.batch_blocks &&
-          p->hub_grid == ctx->tuning.hub_blocks && p->hub_tile == ctx->tuning.hub_tile &&
+          std::max(p->hub_grid, p->tri_grid) == ctx->tuning.hub_blocks && p->hub_tile == ctx->tuning.hub_tile &&
           p->batch_tile == ctx->tuning.batch_tile && p->tri == tri)) {
-        std::vector<work_item> items, rest;
+        item_lists lists;
         std::vector<graph_desc> descs(count);
-        uint32_t hub_chunk = 0;
         for (int32_t i = 0; i < count; ++i) {
             const device_graph& g = graphs[i]->g;
             descs[i] = describe(g);
-            append_items(g, (uint32_t)i, tri && g.tri.fwd_ptr, items, rest);
-            hub_chunk = std::max(hub_chunk, tri && g.tri.fwd_ptr ? g.tri.edges.chunk : g.hub_chunk);
+            append_items(g, (uint32_t)i, tri && g.tri.fptr, lists);
         }
-        const uint32_t nums[2] = {(uint32_t)items.size(), (uint32_t)(items.size() + rest.size())};
-        items.insert(items.end(), rest.begin(), rest.end());     // hub items first
-        e = ensure_capacity(p, (uint32_t)count, (uint32_t)items.size(), ctx->stream, ctx->tuning.batch_blocks,
-                            ctx->tuning.hub_blocks, ctx->tuning.hub_tile, ctx->tuning.batch_tile, hub_chunk);
+        // a hub kernel runs when it has items (one of them also when neither has)
+        const uint32_t tri_grid = lists.hub.empty() || !lists.tri.empty() ? ctx->tuning.hub_blocks : 0;
+        const uint32_t hub_grid = lists.hub.empty() ? 0 : ctx->tuning.hub_blocks;
+        uint32_t nums[3];
+        std::vector<work_item>& items = lists.join(nums);
+        e = ensure_capacity(p, (uint32_t)count, (uint32_t)items.size(), ctx->stream, ctx->tuning.batch_blocks, hub_grid,
+                            tri_grid, ctx->tuning.hub_tile, ctx->tuning.batch_tile);
         if (e != hipSuccess) return status_from_hip(e);
         uint32_t nitems = (uint32_t)items.size();
         e = hipMemcpyAsync(p->d_desc, descs.data(), sizeof(graph_desc) * count, hipMemcpyHostToDevice, ctx->stream);

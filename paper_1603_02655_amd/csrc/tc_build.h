@@ -11,40 +11,35 @@ namespace tc {
 constexpr int kCounters = 16;
 
 // Bucketed task records over one adjacency view: the canonical dyads of the
-// neighbour CSR, or the oriented edges of the forward lists.
+// neighbour CSR (dyad_rec, hub_task), or the edges of the forward lists
+// (edge_rec as uint4, tri_task).
+template <class Rec, class Task>
 struct rec_set {
-    dyad_rec* recs = nullptr;
-    hub_task* tasks = nullptr;
+    Rec* recs = nullptr;
+    Task* tasks = nullptr;
     uint32_t n_tasks = 0;
-    uint32_t n_groups = 0;                    // groups of consecutive tasks (hub_task::group)
-    uint32_t chunk = kHubChunk;               // records per task and per group
-    // A second set of tasks and groups of kHubChunk / 2 records over the same
-    // records (forward-list hub buckets of kHubSplitRecords records or more):
-    // the set a single-graph census runs, on the hub kernel with the smaller LDS.
-    hub_task* fine_tasks = nullptr;
-    uint32_t fine_n_tasks = 0;
-    uint32_t fine_n_groups = 0;
+    uint32_t n_groups = 0;                    // dyads: groups of consecutive tasks (hub_task::group)
+    uint32_t n_heavy = 0;                     // edges: tasks up to the last vertex with 64 records or more
+    uint32_t chunk = kHubChunk;               // records per task (dyads: and per group)
     uint64_t off[kBuckets + 1] = {0, 0, 0, 0, 0};
     uint64_t cost[kBuckets] = {0, 0, 0, 0};   // sum of the two row lengths per bucket
-    uint64_t stream = 0;                      // hub: sum of the non-anchor row lengths
+    uint64_t stream = 0;                      // hub: sum of the entries probed
     uint64_t staged = 0;                      // hub: sum over tasks of the anchor row length
-    uint64_t fine_staged = 0;                 // ... over the tasks of the second set
 };
 
-// Degree order: x precedes y when (|N(x)|, x) < (|N(y)|, y).  The forward list
-// N+(x) holds the neighbours that follow x, sorted by id with the direction
-// bits relative to x; every joined pair appears in exactly one forward list.
-// A triangle {x, y, z} in degree order is found exactly once, as the shared
-// vertex z of the forward lists of x and y.  The edge records (recs of `edges`)
-// use the dyad_rec layout with forward-list bounds: bu..ev bound N+(u), N+(v)
-// for u < v by id, vf = (v << 2) | f_uv; edges whose two forward lists cannot
-// share a vertex (one is empty) are left out.
+// Degree order: x precedes y when (|N(x)|, x) < (|N(y)|, y); the rank of a
+// vertex is its place from the end (rank 0 comes last).  The forward list N+(x)
+// holds the neighbours that follow x, sorted by rank; every joined pair appears
+// in exactly one forward list.  Rows are in rank order; the entry layout and
+// what the records hold stand in tc_tri.h.  A triangle in degree order
+// x, y, z is found exactly once, at the edge (x, y), as a vertex z of N+(y) that
+// stands before y in N+(x).  Edges where no vertex can (N+(y) is empty, or y is
+// the first of N+(x)) have no record.
 struct forward_lists {
     uint32_t* fwd = nullptr;
-    uint32_t* fwd_owner = nullptr;
-    int64_t* fwd_ptr = nullptr;   // n + 1
+    uint32_t* fptr = nullptr;     // n + 1
     uint64_t entries = 0;         // = canonical dyads
-    rec_set edges;
+    rec_set<uint4, tri_task> edges;
 };
 
 // Device memory of a context's graphs.  Freed blocks are kept, up to `keep`
@@ -79,6 +74,7 @@ struct device_graph {
     uint64_t U = 0;            // neighbour entries (2 x canonical dyads)
     uint64_t p = 0;            // canonical dyads
     uint64_t mutual = 0;       // mutual canonical dyads
+    uint32_t max_degree = 0;
     int64_t* row_ptr = nullptr;
     uint32_t* nbr = nullptr;
     uint32_t* owner = nullptr; // row of each entry (used to rebuild the buckets)

@@ -382,16 +382,17 @@ __global__ __launch_bounds__(1024) void k_runs_spine(uint64_t* __restrict__ ents
 // ptr[x] = e for the rows x in (before, upto]: the lanes with a few rows each
 // write their own, and a longer gap (vertices without entries) is written by
 // the whole wavefront.  Called by all lanes; `on` lanes have a range.
-__device__ inline void fill_rows(bool on, int64_t before, int64_t upto, uint64_t e, int64_t* __restrict__ ptr) {
+template <class P>
+__device__ inline void fill_rows(bool on, int64_t before, int64_t upto, uint64_t e, P* __restrict__ ptr) {
     const bool wide = on && upto - before > 8;
     if (on && !wide)
-        for (int64_t x = before + 1; x <= upto; ++x) ptr[x] = (int64_t)e;
+        for (int64_t x = before + 1; x <= upto; ++x) ptr[x] = (P)e;
     uint64_t todo = __ballot(wide);
     while (todo) {
         const int l = __ffsll((unsigned long long)todo) - 1;
         todo &= todo - 1;
         const int64_t b = __shfl((long long)before, l, 64), u = __shfl((long long)upto, l, 64);
-        const int64_t v = (int64_t)__shfl((unsigned long long)e, l, 64);
+        const P v = (P)__shfl((unsigned long long)e, l, 64);
         for (int64_t x = b + 1 + __lane_id(); x <= u; x += 64) ptr[x] = v;
     }
 }
@@ -488,30 +489,25 @@ __global__ __launch_bounds__(kT) void k_row_info(const int64_t* __restrict__ row
 // larger degree, ties to the larger id), so the hub bucket is anchor-major;
 // any other pair is emitted from the row of its smaller id (u-major) into the
 // lane / wave / group bucket by k = |N(u)| + |N(v)| - 2.
-// Bucket of entry e of an adjacency view.  Dyad view (tri = 0): the dyad is
-// emitted once, from its first vertex, or from its anchor in the hub bucket.
-// Forward view (tri = 1): every entry is one oriented edge and is emitted,
-// unless one of the two forward lists is empty (no shared vertex possible).
-// Hub: the longer of the two rows reaches t_hub; the anchor is the endpoint
-// with the longer row (ties to the larger id).
+// Bucket of neighbour entry e: the dyad is emitted once, from its first
+// vertex, or from its anchor in the hub bucket.
 // `len` holds the rows' lengths (one 4-byte gather per entry).
 __device__ inline int rec_bucket(const uint32_t* nbr, const uint32_t* owner, const uint32_t* len,
-                                 uint64_t e, uint64_t U, const bucket_params& bp, int tri, uint64_t* cost,
+                                 uint64_t e, uint64_t U, const bucket_params& bp, uint64_t* cost,
                                  uint64_t* stream, uint32_t* anchor) {
     if (e >= U) return kBuckets;
     const uint32_t o = owner[e], w = nbr[e] >> 2;
     const uint64_t d_o = len[o], d_w = len[w];
-    if (tri && (d_o == 0 || d_w == 0)) return kBuckets;
     *cost = d_o + d_w;
     if ((d_o > d_w ? d_o : d_w) >= bp.t_hub) {
         const bool o_anchor = d_o > d_w || (d_o == d_w && o > w);
-        if (!tri && !o_anchor) return kBuckets;
-        *stream = o_anchor ? d_w : d_o;
-        *anchor = o_anchor ? o : w;
+        if (!o_anchor) return kBuckets;
+        *stream = d_w;
+        *anchor = o;
         return kBucketHub;
     }
-    if (!tri && !(o < w)) return kBuckets;
-    const uint64_t k = tri ? d_o + d_w : d_o + d_w - 2;
+    if (!(o < w)) return kBuckets;
+    const uint64_t k = d_o + d_w - 2;
     return k < bp.t0 ? 0 : (k < bp.t1 ? 1 : 2);
 }
 
@@ -521,32 +517,10 @@ __device__ inline int rec_bucket(const uint32_t* nbr, const uint32_t* owner, con
 // k_bucket_sums: eight atomics per tile on shared counters took 1.4 of the
 // kernel's 1.5 ms on 29.5 M entries.
 constexpr uint32_t kPartWords = kBuckets + 2;
-__global__ __launch_bounds__(kT) void k_dyad_count(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
-                                                    const uint32_t* __restrict__ len, uint64_t U, bucket_params bp,
-                                                    int tri, uint64_t* __restrict__ counts, uint32_t nblocks,
-                                                    unsigned int* __restrict__ hubcnt, uint64_t* __restrict__ part) {
-    __shared__ unsigned long long sh[kT / 64];
-    uint64_t base = (uint64_t)blockIdx.x * kTile;
-    uint32_t my[kBuckets] = {0, 0, 0, 0}, mut = 0;
-    unsigned long long mycost[kBuckets] = {0, 0, 0, 0}, mystream = 0;
-    for (int k = 0; k < kI; ++k) {
-        uint64_t e = base + (uint64_t)k * kT + threadIdx.x;
-        uint64_t cost = 0, stream = 0;
-        uint32_t anchor = 0;
-        const int b = rec_bucket(nbr, owner, len, e, U, bp, tri, &cost, &stream, &anchor);
-#pragma unroll
-        for (int q = 0; q < kBuckets; ++q) {
-            my[q] += b == q ? 1u : 0u;
-            mycost[q] += b == q ? cost : 0ull;
-        }
-        if (b < kBuckets) {
-            mut += ((nbr[e] & 3u) == 3u) ? 1u : 0u;
-            if (b == kBucketHub) {
-                mystream += stream;
-                if (hubcnt) atomicAdd(&hubcnt[anchor], 1u);
-            }
-        }
-    }
+__device__ inline void store_tile_sums(const uint32_t (&my)[kBuckets], const unsigned long long (&mycost)[kBuckets],
+                                       unsigned long long mystream, unsigned long long mut,
+                                       uint64_t* __restrict__ counts, uint64_t* __restrict__ part, uint32_t nblocks,
+                                       unsigned long long* sh) {
 #pragma unroll
     for (int q = 0; q < kBuckets; ++q) {
         const unsigned long long c = block_sum(my[q], sh), x = block_sum(mycost[q], sh);
@@ -560,6 +534,32 @@ __global__ __launch_bounds__(kT) void k_dyad_count(const uint32_t* __restrict__ 
         part[(uint64_t)kBuckets * nblocks + blockIdx.x] = st;
         part[(uint64_t)(kBuckets + 1) * nblocks + blockIdx.x] = mu;
     }
+}
+
+__global__ __launch_bounds__(kT) void k_dyad_count(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
+                                                    const uint32_t* __restrict__ len, uint64_t U, bucket_params bp,
+                                                    uint64_t* __restrict__ counts, uint32_t nblocks,
+                                                    uint64_t* __restrict__ part) {
+    __shared__ unsigned long long sh[kT / 64];
+    uint64_t base = (uint64_t)blockIdx.x * kTile;
+    uint32_t my[kBuckets] = {0, 0, 0, 0}, mut = 0;
+    unsigned long long mycost[kBuckets] = {0, 0, 0, 0}, mystream = 0;
+    for (int k = 0; k < kI; ++k) {
+        uint64_t e = base + (uint64_t)k * kT + threadIdx.x;
+        uint64_t cost = 0, stream = 0;
+        uint32_t anchor = 0;
+        const int b = rec_bucket(nbr, owner, len, e, U, bp, &cost, &stream, &anchor);
+#pragma unroll
+        for (int q = 0; q < kBuckets; ++q) {
+            my[q] += b == q ? 1u : 0u;
+            mycost[q] += b == q ? cost : 0ull;
+        }
+        if (b < kBuckets) {
+            mut += ((nbr[e] & 3u) == 3u) ? 1u : 0u;
+            if (b == kBucketHub) mystream += stream;
+        }
+    }
+    store_tile_sums(my, mycost, mystream, mut, counts, part, nblocks, sh);
 }
 
 // One workgroup per quantity of `part`: its sum over the tiles to
@@ -579,18 +579,15 @@ __global__ __launch_bounds__(kT) void k_bucket_sums(const uint64_t* __restrict__
     if (threadIdx.x == 0) host[kBuckets + 1 + q] = s;
 }
 
-// Writes the records.  Lane / wave / group records keep the entry order of the
-// view (u-major for dyads) through a stable per-bucket ranking.  Hub records
-// of the dyad view come from their anchor's row and so are anchor-major in
-// entry order; hub records of the forward view may come from either endpoint
-// and are placed in their anchor's run (rec_off) through a per-anchor cursor.
+// Writes the records in entry order through a stable per-bucket ranking:
+// lane / wave / group records are u-major, and hub records, which come from
+// their anchor's row, anchor-major.
 __global__ __launch_bounds__(kT) void k_dyad_scatter(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
                                                       const int64_t* __restrict__ row_ptr,
                                                       const uint32_t* __restrict__ len, uint64_t U, bucket_params bp,
-                                                      int tri, const uint64_t* __restrict__ offsets, uint32_t nblocks,
-                                                      const uint32_t* __restrict__ rec_off,
-                                                      unsigned int* __restrict__ cursor, uint64_t hub_begin,
-                                                      uint32_t* __restrict__ anchors, dyad_rec* __restrict__ out) {
+                                                      const uint64_t* __restrict__ offsets, uint32_t nblocks,
+                                                      uint64_t hub_begin, uint32_t* __restrict__ anchors,
+                                                      dyad_rec* __restrict__ out) {
     __shared__ uint32_t running[kBuckets];
     __shared__ uint32_t wcnt[kT / 64][kBuckets];
     __shared__ uint64_t goff[kBuckets];
@@ -605,7 +602,7 @@ __global__ __launch_bounds__(kT) void k_dyad_scatter(const uint32_t* __restrict_
         uint64_t e = base + (uint64_t)r * kT + threadIdx.x;
         uint64_t cost = 0, stream = 0;
         uint32_t anchor = 0;
-        int b = rec_bucket(nbr, owner, len, e, U, bp, tri, &cost, &stream, &anchor);
+        int b = rec_bucket(nbr, owner, len, e, U, bp, &cost, &stream, &anchor);
         uint32_t rank = 0;
         for (int q = 0; q < kBuckets; ++q) {
             uint64_t mask = __ballot(b == q);
@@ -626,13 +623,9 @@ __global__ __launch_bounds__(kT) void k_dyad_scatter(const uint32_t* __restrict_
             rec.u = u;
             const uint32_t fo = nbr[e] & 3u;
             rec.vf = (v << 2) | (o == u ? fo : ((fo & 1u) << 1) | (fo >> 1));
-            if (tri && b == kBucketHub)
-                out[hub_begin + rec_off[anchor] + atomicAdd(&cursor[anchor], 1u)] = rec;
-            else {
-                const uint64_t at = goff[b] + before + rank;
-                out[at] = rec;
-                if (b == kBucketHub) anchors[at - hub_begin] = anchor;
-            }
+            const uint64_t at = goff[b] + before + rank;
+            out[at] = rec;
+            if (b == kBucketHub) anchors[at - hub_begin] = anchor;
         }
         __syncthreads();
         if (threadIdx.x < kBuckets) {
@@ -644,32 +637,240 @@ __global__ __launch_bounds__(kT) void k_dyad_scatter(const uint32_t* __restrict_
     }
 }
 
-// Forward lists: flag the entries whose vertex follows the row's owner in
-// degree order, compact them (order kept, so rows stay sorted by id), and read
-// each row's start off the scanned flags.
-__global__ __launch_bounds__(kT) void k_fwd_flag(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
-                                                  const int64_t* __restrict__ row_ptr, uint64_t U,
-                                                  uint64_t* __restrict__ flag) {
-    const uint64_t e = (uint64_t)blockIdx.x * kT + threadIdx.x;
-    if (e >= U) return;
-    const uint32_t o = owner[e], w = nbr[e] >> 2;
-    const int64_t d_o = row_ptr[o + 1] - row_ptr[o], d_w = row_ptr[w + 1] - row_ptr[w];
-    flag[e] = (d_w > d_o || (d_w == d_o && w > o)) ? 1u : 0u;
+// ---- forward lists ----------------------------------------------------------
+// Ranks: the vertices sorted by falling degree, ties by falling id (a stable
+// sort of the degrees alone, from the ids in falling order).
+__global__ __launch_bounds__(kT) void k_vertex_keys(const uint32_t* __restrict__ deg, int32_t n, uint32_t max_degree,
+                                                    uint64_t* __restrict__ keys) {
+    const int32_t i = (int32_t)(blockIdx.x * kT + threadIdx.x);
+    if (i >= n) return;
+    const uint32_t v = (uint32_t)(n - 1 - i);
+    keys[i] = ((uint64_t)(max_degree - deg[v]) << 32) | v;
 }
 
-__global__ __launch_bounds__(kT) void k_fwd_emit(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
-                                                  uint64_t U, const uint64_t* __restrict__ pos,
-                                                  uint32_t* __restrict__ fwd, uint32_t* __restrict__ fwd_owner) {
-    const uint64_t e = (uint64_t)blockIdx.x * kT + threadIdx.x;
-    if (e >= U || pos[e + 1] == pos[e]) return;
-    fwd[pos[e]] = nbr[e];
-    fwd_owner[pos[e]] = owner[e];
+__global__ __launch_bounds__(kT) void k_ranks(const uint64_t* __restrict__ keys, int32_t n, uint32_t* __restrict__ rank) {
+    const int32_t r = (int32_t)(blockIdx.x * kT + threadIdx.x);
+    if (r < n) rank[(uint32_t)keys[r]] = (uint32_t)r;
 }
 
-__global__ __launch_bounds__(kT) void k_fwd_ptr(const int64_t* __restrict__ row_ptr, int32_t n,
-                                                 const uint64_t* __restrict__ pos, int64_t* __restrict__ fwd_ptr) {
-    const int64_t x = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (x <= n) fwd_ptr[x] = (int64_t)pos[row_ptr[x]];
+// One key per joined pair, from the neighbour entry whose owner x has the
+// larger rank: rank x << (bits + 3) | rank y << 3 | f_xy << 1 | [id y > id x].
+// Without `tile_at` counts the tiles' keys into `sums`; with it (the scanned
+// sums) writes them.
+__global__ __launch_bounds__(kT) void k_pair_keys(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
+                                                  const uint32_t* __restrict__ rank, uint64_t U, uint32_t bits,
+                                                  const uint64_t* __restrict__ tile_at, uint64_t* __restrict__ sums,
+                                                  uint64_t* __restrict__ keys) {
+    __shared__ uint32_t sw[kT / 64];
+    const uint32_t lane = __lane_id(), wid = threadIdx.x >> 6;
+    const uint64_t base = (uint64_t)blockIdx.x * kTile + wid * 64 * kI;
+    uint64_t key[kI];
+    bool on[kI];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < kI; ++r) {
+        const uint64_t e = base + r * 64 + lane;
+        const uint32_t ent = e < U ? nbr[e] : 0u, o = e < U ? owner[e] : 0u, w = ent >> 2;
+        const uint32_t ro = e < U ? rank[o] : 0u, rw = e < U ? rank[w] : 0u;
+        on[r] = rw < ro;
+        key[r] = ((uint64_t)ro << (bits + 3)) | ((uint64_t)rw << 3) | ((ent & 3u) << 1) | (w > o ? 1u : 0u);
+        mine += (uint32_t)__popcll(__ballot(on[r]));
+    }
+    if (lane == 0) sw[wid] = mine;
+    __syncthreads();
+    if (!tile_at) {
+        if (threadIdx.x == 0) {
+            uint32_t t = 0;
+            for (int w = 0; w < kT / 64; ++w) t += sw[w];
+            sums[blockIdx.x] = t;
+        }
+        return;
+    }
+    uint64_t at = tile_at[blockIdx.x];
+    for (uint32_t w = 0; w < wid; ++w) at += sw[w];
+#pragma unroll
+    for (int r = 0; r < kI; ++r) {
+        const uint64_t m = __ballot(on[r]);
+        if (on[r]) keys[at + (uint32_t)__popcll(m & lanemask_lt())] = key[r];
+        at += (uint32_t)__popcll(m);
+    }
+}
+
+// The forward lists and their row starts from the sorted keys.
+__global__ __launch_bounds__(kT) void k_fwd_emit(const uint64_t* __restrict__ keys, uint64_t count, uint32_t bits,
+                                                 int32_t n, uint32_t* __restrict__ fwd, uint32_t* __restrict__ fptr) {
+    const uint64_t i = (uint64_t)blockIdx.x * kT + threadIdx.x;
+    int64_t before = -1, x = -1;
+    const bool on = i < count;
+    if (on) {
+        const uint64_t k = keys[i];
+        x = (int64_t)(k >> (bits + 3));
+        before = i == 0 ? -1 : (int64_t)(keys[i - 1] >> (bits + 3));
+        fwd[i] = ((uint32_t)(k & 7u) << 29) | ((uint32_t)((k >> 3) & ((1ull << bits) - 1ull)) << 1);
+    }
+    fill_rows(on, before, x, i, fptr);
+    fill_rows(on && i + 1 == count, x, (int64_t)n, count, fptr);
+}
+
+// Bucket of the edge of sorted key i (x, y): hub when the longer of the two
+// forward lists reaches t_hub, else by their joint length; kBuckets for an
+// edge that closes no triangle with a smaller rank.
+struct edge_at {
+    uint32_t bx, by, ey, y, pos;
+    uint64_t cost;
+    int bucket;
+};
+__device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_t i, uint64_t count, uint32_t bits,
+                                      const uint32_t* __restrict__ fptr, const bucket_params& bp) {
+    edge_at r{};
+    r.bucket = kBuckets;
+    if (i >= count) return r;
+    const uint64_t k = keys[i];
+    const uint32_t x = (uint32_t)(k >> (bits + 3));
+    r.y = (uint32_t)((k >> 3) & ((1ull << bits) - 1ull));
+    r.bx = fptr[x];
+    r.pos = (uint32_t)i - r.bx;
+    if (r.pos == 0) return r;
+    r.by = fptr[r.y];
+    r.ey = fptr[r.y + 1];
+    const uint64_t dx = fptr[x + 1] - r.bx, dy = r.ey - r.by;
+    if (dy == 0) return r;
+    r.cost = dx + dy;
+    r.bucket = (dx > dy ? dx : dy) >= bp.t_hub ? kBucketHub : r.cost < bp.t0 ? 0 : r.cost < bp.t1 ? 1 : 2;
+    return r;
+}
+
+__global__ __launch_bounds__(kT) void k_edge_count(const uint64_t* __restrict__ keys, uint64_t count, uint32_t bits,
+                                                   const uint32_t* __restrict__ fptr, bucket_params bp,
+                                                   uint64_t* __restrict__ counts, uint32_t nblocks,
+                                                   uint64_t* __restrict__ part) {
+    __shared__ unsigned long long sh[kT / 64];
+    const uint64_t base = (uint64_t)blockIdx.x * kTile;
+    uint32_t my[kBuckets] = {0, 0, 0, 0};
+    unsigned long long mycost[kBuckets] = {0, 0, 0, 0}, mystream = 0;
+    for (int k = 0; k < kI; ++k) {
+        const edge_at r = edge_bucket(keys, base + (uint64_t)k * kT + threadIdx.x, count, bits, fptr, bp);
+#pragma unroll
+        for (int q = 0; q < kBuckets; ++q) {
+            my[q] += r.bucket == q ? 1u : 0u;
+            mycost[q] += r.bucket == q ? r.cost : 0ull;
+        }
+        if (r.bucket == kBucketHub) mystream += r.pos;
+    }
+    store_tile_sums(my, mycost, mystream, 0ull, counts, part, nblocks, sh);
+}
+
+// Lane / wave / group records in x-major order; for the hub edges a key
+// y << 32 | i, in x-major order too (sorted by y next).
+__global__ __launch_bounds__(kT) void k_edge_scatter(const uint64_t* __restrict__ keys, uint64_t count, uint32_t bits,
+                                                     const uint32_t* __restrict__ fptr, bucket_params bp,
+                                                     const uint64_t* __restrict__ offsets, uint32_t nblocks,
+                                                     uint64_t hub_begin, uint64_t* __restrict__ hubkeys,
+                                                     uint4* __restrict__ out) {
+    __shared__ uint32_t wcnt[kT / 64][kBuckets];
+    const uint32_t lane = __lane_id(), wid = threadIdx.x >> 6;
+    const uint64_t base = (uint64_t)blockIdx.x * kTile + wid * 64 * kI;   // the wavefront's keys
+    uint32_t mine[kBuckets] = {0, 0, 0, 0};
+    edge_at r[kI];
+#pragma unroll
+    for (int k = 0; k < kI; ++k) {
+        r[k] = edge_bucket(keys, base + k * 64 + lane, count, bits, fptr, bp);
+#pragma unroll
+        for (int q = 0; q < kBuckets; ++q) mine[q] += (uint32_t)__popcll(__ballot(r[k].bucket == q));
+    }
+    if (lane == 0)
+        for (int q = 0; q < kBuckets; ++q) wcnt[wid][q] = mine[q];
+    __syncthreads();
+    uint64_t at[kBuckets];
+#pragma unroll
+    for (int q = 0; q < kBuckets; ++q) {
+        at[q] = offsets[(uint64_t)q * nblocks + blockIdx.x];
+        for (uint32_t w = 0; w < wid; ++w) at[q] += wcnt[w][q];
+    }
+#pragma unroll
+    for (int k = 0; k < kI; ++k) {
+        const uint64_t i = base + k * 64 + lane;
+#pragma unroll
+        for (int q = 0; q < kBuckets; ++q) {
+            const uint64_t m = __ballot(r[k].bucket == q);
+            if (r[k].bucket == q) {
+                const uint64_t to = at[q] + (uint32_t)__popcll(m & lanemask_lt());
+                if (q == kBucketHub) hubkeys[to - hub_begin] = ((uint64_t)r[k].y << 32) | i;
+                else out[to] = make_uint4(r[k].bx, (uint32_t)i, r[k].by, r[k].ey);
+            }
+            at[q] += (uint32_t)__popcll(m);
+        }
+    }
+}
+
+// Hub records from the keys sorted by y, and the run of each y (first and one
+// past the last record, zero elsewhere).
+__global__ __launch_bounds__(kT) void k_edge_hub(const uint64_t* __restrict__ hubkeys, uint32_t hubs,
+                                                 const uint64_t* __restrict__ keys, uint32_t bits,
+                                                 const uint32_t* __restrict__ fptr, const uint32_t* __restrict__ fwd,
+                                                 uint32_t* __restrict__ first, uint32_t* __restrict__ past,
+                                                 uint4* __restrict__ out) {
+    const uint32_t j = blockIdx.x * kT + threadIdx.x;
+    if (j >= hubs) return;
+    const uint64_t hk = hubkeys[j];
+    const uint32_t y = (uint32_t)(hk >> 32), i = (uint32_t)hk;
+    const uint64_t k = keys[i];
+    const uint32_t bx = fptr[(uint32_t)(k >> (bits + 3))];
+    uint32_t core = i;   // the prefix's entries lie below y
+    if (y > kCore) {
+        uint32_t lo = bx, hi = i;
+        while (lo < hi) {
+            const uint32_t mid = lo + ((hi - lo) >> 1);
+            if ((fwd[mid] & 0x00fffffeu) < 2u * kCore) lo = mid + 1; else hi = mid;
+        }
+        core = lo;
+    }
+    out[j] = make_uint4(bx, core, i, (uint32_t)(k & 7u));
+    if (j == 0 || (uint32_t)(hubkeys[j - 1] >> 32) != y) first[y] = j;
+    if (j + 1 == hubs || (uint32_t)(hubkeys[j + 1] >> 32) != y) past[y] = j + 1;
+}
+
+__global__ __launch_bounds__(kT) void k_tri_ntasks(const uint32_t* __restrict__ first, const uint32_t* __restrict__ past,
+                                                   int32_t n, const uint32_t* __restrict__ fptr, uint32_t chunk,
+                                                   uint64_t* __restrict__ ntask, unsigned long long* __restrict__ sums) {
+    __shared__ unsigned long long sh[kT / 64];
+    __shared__ uint32_t s_heavy;
+    if (threadIdx.x == 0) s_heavy = 0;
+    __syncthreads();
+    unsigned long long staged = 0;
+    for (int64_t y = (int64_t)blockIdx.x * kT + threadIdx.x; y < n; y += (int64_t)gridDim.x * kT) {
+        const uint64_t t = (past[y] - first[y] + chunk - 1) / chunk;
+        ntask[y] = t;
+        staged += t * (unsigned long long)(fptr[y + 1] - fptr[y]);
+        if (past[y] - first[y] >= 64) atomicMax(&s_heavy, (uint32_t)y + 1u);
+    }
+    staged = block_sum(staged, sh);
+    if (threadIdx.x == 0 && staged) {
+        atomicAdd(&sums[0], staged);
+        if (s_heavy) atomicMax(&sums[1], (unsigned long long)s_heavy);
+    }
+}
+
+__global__ void k_tri_publish(const uint64_t* __restrict__ task_off, int32_t n, const unsigned long long* __restrict__ sums,
+                              uint64_t* __restrict__ host) {
+    if (threadIdx.x == 0) {
+        host[0] = task_off[n];
+        host[1] = sums[0];
+        host[2] = task_off[sums[1]];
+    }
+}
+
+// Tasks in rank order: the vertices with the most records come first.
+__global__ __launch_bounds__(kT) void k_tri_tasks(const uint32_t* __restrict__ first, const uint32_t* __restrict__ past,
+                                                  int32_t n, const uint32_t* __restrict__ fptr, uint32_t chunk,
+                                                  const uint64_t* __restrict__ task_off, uint32_t hub_begin,
+                                                  tri_task* __restrict__ tasks) {
+    const int32_t y = (int32_t)(blockIdx.x * kT + threadIdx.x);
+    if (y >= n) return;
+    const uint32_t a = first[y], b = past[y];
+    uint64_t t = task_off[y];
+    for (uint32_t j = a; j < b; j += chunk, ++t)
+        tasks[t] = tri_task{hub_begin + j, hub_begin + (b - j < chunk ? b : j + chunk), fptr[y], fptr[y + 1]};
 }
 
 __global__ __launch_bounds__(kT) void k_row_len(const int64_t* __restrict__ row_ptr, int32_t n,
@@ -687,12 +888,6 @@ __global__ __launch_bounds__(kT) void k_hub_runs(const uint32_t* __restrict__ an
     const uint32_t a = anchors[i];
     if (i == 0 || anchors[i - 1] != a) first[a] = i;
     if (i + 1 == count || anchors[i + 1] != a) past[a] = i + 1;
-}
-
-__global__ __launch_bounds__(kT) void k_hub_past(const unsigned int* __restrict__ hubcnt, int32_t n,
-                                                 const uint32_t* __restrict__ first, uint32_t* __restrict__ past) {
-    const int32_t h = (int32_t)(blockIdx.x * kT + threadIdx.x);
-    if (h < n) past[h] = first[h] + hubcnt[h];
 }
 
 // Hub tasks: the hub records of anchor row h are contiguous, [first[h],
@@ -775,6 +970,11 @@ __global__ void k_publish(const uint64_t* __restrict__ a, uint64_t* __restrict__
     if ((int)threadIdx.x < count) host[threadIdx.x] = a[threadIdx.x];
 }
 
+__global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
+    uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = v;
+}
+
 __global__ void k_fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -822,8 +1022,16 @@ inline uint64_t sort_space_bytes(uint64_t m, uint32_t bits) {
 inline uint64_t bucket_space_bytes(uint64_t U, uint64_t n) {
     const uint64_t nb = (U + kTile - 1) / kTile + 1, p = U / 2, tasks = std::min(n, p) + p / (kHubChunk / 2) + 1;
     return 8 * (kBuckets * nb + 1) + 8 * kPartWords * nb + 8 * scan_scratch_words(std::max(U + 1, n + 1)) +
-           4 * 5 * (n + 2) + 4 * p + 2 * 8 * (n + 1) + 8 * (tasks / kHubGroupTasks + 2) +
-           8 * scan_scratch_words(tasks) + 8 * (U + 1) + 32 * 256;
+           4 * 3 * (n + 2) + 4 * p + 2 * 8 * (n + 1) + 8 * (tasks / kHubGroupTasks + 2) +
+           8 * scan_scratch_words(tasks) + 32 * 256;
+}
+inline uint64_t forward_space_bytes(uint64_t U, uint64_t n) {
+    const uint64_t F = U / 2, nb = (U + kTile - 1) / kTile + 1, hist = (uint64_t)kDigits * sort_tiles(std::max(F, n) + 1);
+    return 3 * 8 * F + 4 * hist + 8 * scan_scratch_words(std::max(hist, n + 1)) + 2 * 8 * n + 4 * n + 8 * nb +
+           8 * (kBuckets * nb + 1) + 8 * kPartWords * nb + 4 * 2 * (n + 2) + 8 * (n + 1) + 32 * 256;
+}
+inline uint64_t view_space_bytes(uint64_t U, uint64_t n, bool tri) {
+    return std::max(bucket_space_bytes(U, n), tri ? forward_space_bytes(U, n) : 0);
 }
 
 }  // namespace
@@ -1064,8 +1272,8 @@ uint32_t bit_width_u32(uint32_t x) {
     return b;
 }
 
-hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, build_space* sp, arena& ar,
-                      hipStream_t s);
+hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, bool fresh, build_space* sp,
+                      arena& ar, hipStream_t s);
 
 }  // namespace
 
@@ -1084,7 +1292,7 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     g->n = n;
     g->mem = pool;
     const uint64_t small = 1024 + sizeof(uint32_t) * (uint64_t)n + 1024;
-    const uint64_t need = small + std::max(sort_space_bytes((uint64_t)m, bits), bucket_space_bytes(keys_n, (uint64_t)n));
+    const uint64_t need = small + std::max(sort_space_bytes((uint64_t)m, bits), view_space_bytes(keys_n, (uint64_t)n, bp.tri != 0));
     if ((err = space_reserve(sp, need, s)) != hipSuccess) {
         st.hip = err;
         return st;
@@ -1147,9 +1355,9 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, (const uint64_t*)counters + 3, sp->host + kSpaceHostStats, 2);
     TRY(hipGetLastError());
     ar.rewind(mark);   // (the keys are read by then, in stream order)
-    TRY(bucket_all(g, bp, deg, sp, ar, s));
+    TRY(bucket_all(g, bp, deg, true, sp, ar, s));
     st.sum_d2 = sp->host[kSpaceHostStats];
-    st.max_degree = (int64_t)sp->host[kSpaceHostStats + 1];
+    st.max_degree = (int64_t)g->max_degree;
     st.ok = true;
 done:
     (void)hipStreamSynchronize(s);
@@ -1210,77 +1418,59 @@ done:
     return err;
 }
 
-// Buckets the entries of one adjacency view (nbr / owner / row_ptr over U
-// entries and n rows of length len) into `out`: records, hub tasks and the
-// per-bucket sums.
-hipError_t bucket_records(const uint32_t* nbr, const uint32_t* owner, const int64_t* row_ptr, const uint32_t* len,
-                          uint64_t U, int32_t n, int tri, const bucket_params& bp, graph_pool* mem,
-                          build_space* sp, arena& ar, hipStream_t s, rec_set* out, uint64_t* mutual) {
+// The dyad view: records of g's canonical dyads by bucket, hub tasks and the
+// per-bucket sums.  deg: the rows' lengths.
+hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const uint32_t* deg, build_space* sp,
+                               arena& ar, hipStream_t s) {
     hipError_t err = hipSuccess;
     const size_t mark = ar.mark();
+    const uint64_t U = g->U;
+    const int32_t n = g->n;
+    graph_pool* mem = g->mem;
     uint64_t *counts = nullptr, *part = nullptr;
-    unsigned int *hubcnt = nullptr, *cursor = nullptr;
     uint32_t *first = nullptr, *past = nullptr, *anchors = nullptr;
-    uint64_t total = 0, hubs = 0;
+    uint64_t hubs = 0;
     const uint32_t nb = blocks_for(U ? U : 1);
-    mem->put(out->recs);
-    mem->put(out->tasks);
-    mem->put(out->fine_tasks);
-    *out = rec_set{};
+    mem->put(g->dyads);
+    mem->put(g->hub_tasks);
+    g->dyads = nullptr;
+    g->hub_tasks = nullptr;
+    g->n_hub_tasks = 0;
+    g->n_hub_groups = 0;
+    g->hub_staged = 0;
     TAKE(counts, uint64_t, (uint64_t)kBuckets * nb + 1);
     TAKE(part, uint64_t, (uint64_t)kPartWords * nb);
-    // (an even number of words each, so that they can be cleared 8 bytes at a time)
-    TAKE(first, uint32_t, ((uint64_t)n + 2) & ~1ull);
-    TAKE(past, uint32_t, ((uint64_t)n + 2) & ~1ull);
-    if (tri) {
-        TAKE(hubcnt, unsigned int, ((uint64_t)n + 2) & ~1ull);
-        TAKE(cursor, unsigned int, ((uint64_t)n + 2) & ~1ull);
-        TRY(fill_u64((uint64_t*)hubcnt, ((uint64_t)n + 2) / 2, 0, s));
-        TRY(fill_u64((uint64_t*)cursor, ((uint64_t)n + 2) / 2, 0, s));
-    }
-    hipLaunchKernelGGL(k_dyad_count, dim3(nb), dim3(kT), 0, s, nbr, owner, len, U, bp, tri, counts, nb, hubcnt, part);
+    hipLaunchKernelGGL(k_dyad_count, dim3(nb), dim3(kT), 0, s, g->nbr, g->owner, deg, U, bp, counts, nb, part);
     TRY(scan_exclusive<uint64_t>(counts, counts, (uint64_t)kBuckets * nb, counts + (uint64_t)kBuckets * nb, ar, s));
     hipLaunchKernelGGL(k_bucket_sums, dim3(kPartWords + 1), dim3(kT), 0, s, (const uint64_t*)part,
                        (const uint64_t*)counts, nb, sp->host);
     TRY(hipGetLastError());
     TRY(hipStreamSynchronize(s));
-    for (int b = 0; b <= kBuckets; ++b) out->off[b] = sp->host[b];
-    for (int b = 0; b < kBuckets; ++b) out->cost[b] = sp->host[kBuckets + 1 + b];
-    out->stream = sp->host[2 * kBuckets + 1];
-    if (mutual) *mutual = sp->host[2 * kBuckets + 2];
-    total = out->off[kBuckets];
-    hubs = out->off[kBucketHub + 1] - out->off[kBucketHub];
-    TRY(mem->alloc((void**)&out->recs, sizeof(dyad_rec) * (total ? total : 1)));
+    for (int b = 0; b <= kBuckets; ++b) g->bucket_off[b] = sp->host[b];
+    for (int b = 0; b < kBuckets; ++b) g->bucket_cost[b] = sp->host[kBuckets + 1 + b];
+    g->hub_stream = sp->host[2 * kBuckets + 1];
+    g->mutual = sp->host[2 * kBuckets + 2];
+    g->p = g->bucket_off[kBuckets];
+    hubs = g->bucket_off[kBucketHub + 1] - g->bucket_off[kBucketHub];
+    TRY(mem->alloc((void**)&g->dyads, sizeof(dyad_rec) * (g->p ? g->p : 1)));
     if (hubs > 0) {
-        if (tri) {
-            TRY(scan_exclusive<uint32_t>(hubcnt, first, (uint64_t)n, nullptr, ar, s));
-            hipLaunchKernelGGL(k_hub_past, dim3(grid1((uint64_t)n)), dim3(kT), 0, s, (const unsigned int*)hubcnt, n,
-                               (const uint32_t*)first, past);
-        } else {
-            TAKE(anchors, uint32_t, hubs);
-            TRY(fill_u64((uint64_t*)first, ((uint64_t)n + 2) / 2, 0, s));
-            TRY(fill_u64((uint64_t*)past, ((uint64_t)n + 2) / 2, 0, s));
-        }
+        // (an even number of words each, so that they can be cleared 8 bytes at a time)
+        TAKE(first, uint32_t, ((uint64_t)n + 2) & ~1ull);
+        TAKE(past, uint32_t, ((uint64_t)n + 2) & ~1ull);
+        TAKE(anchors, uint32_t, hubs);
+        TRY(fill_u64((uint64_t*)first, ((uint64_t)n + 2) / 2, 0, s));
+        TRY(fill_u64((uint64_t*)past, ((uint64_t)n + 2) / 2, 0, s));
     }
-    if (total > 0) {
-        hipLaunchKernelGGL(k_dyad_scatter, dim3(nb), dim3(kT), 0, s, nbr, owner, row_ptr, len, U, bp, tri,
-                           (const uint64_t*)counts, nb, (const uint32_t*)first, cursor, out->off[kBucketHub], anchors,
-                           out->recs);
+    if (g->p > 0) {
+        hipLaunchKernelGGL(k_dyad_scatter, dim3(nb), dim3(kT), 0, s, g->nbr, g->owner, g->row_ptr, deg, U, bp,
+                           (const uint64_t*)counts, nb, g->bucket_off[kBucketHub], anchors, g->dyads);
         TRY(hipGetLastError());
     }
-    // hub tasks and their groups: of kHubChunk records (the set batched
-    // launches run), and for a forward-list hub bucket of kHubSplitRecords
-    // records or more also of half as many (the set a single census runs)
     if (hubs > 0) {
-        if (!tri)
-            hipLaunchKernelGGL(k_hub_runs, dim3(grid1(hubs)), dim3(kT), 0, s, (const uint32_t*)anchors, (uint32_t)hubs,
-                               first, past);
-        const bool fine = tri && hubs >= kHubSplitRecords;
-        TRY(cut_hub_tasks(first, past, n, len, out->off[kBucketHub], out->recs, bp, kHubChunk, mem, sp, ar, s,
-                          &out->tasks, &out->n_tasks, &out->n_groups, &out->staged));
-        if (fine)
-            TRY(cut_hub_tasks(first, past, n, len, out->off[kBucketHub], out->recs, bp, kHubChunk / 2, mem, sp, ar, s,
-                              &out->fine_tasks, &out->fine_n_tasks, &out->fine_n_groups, &out->fine_staged));
+        hipLaunchKernelGGL(k_hub_runs, dim3(grid1(hubs)), dim3(kT), 0, s, (const uint32_t*)anchors, (uint32_t)hubs, first,
+                           past);
+        TRY(cut_hub_tasks(first, past, n, deg, g->bucket_off[kBucketHub], g->dyads, bp, kHubChunk, mem, sp, ar, s,
+                          &g->hub_tasks, &g->n_hub_tasks, &g->n_hub_groups, &g->hub_staged));
     }
 done:
     ar.rewind(mark);
@@ -1289,87 +1479,126 @@ done:
 
 void free_forward(graph_pool* mem, forward_lists* t) {
     mem->put(t->fwd);
-    mem->put(t->fwd_owner);
-    mem->put(t->fwd_ptr);
+    mem->put(t->fptr);
     mem->put(t->edges.recs);
     mem->put(t->edges.tasks);
-    mem->put(t->edges.fine_tasks);
     *t = forward_lists{};
 }
 
-// Forward lists of g (degree order), built once per graph.
-hipError_t build_forward(device_graph* g, arena& ar, hipStream_t s) {
+// Forward lists of g (degree order), their edge records and hub tasks.
+hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_t* deg, build_space* sp, arena& ar,
+                         hipStream_t s) {
     hipError_t err = hipSuccess;
     const size_t mark = ar.mark();
-    uint64_t* pos = nullptr;
-    const uint64_t U = g->U;
+    const uint64_t U = g->U, F = U / 2;   // every joined pair is in one forward list
     const int32_t n = g->n;
+    const uint32_t bits = std::max(1u, bit_width_u32((uint32_t)std::max(n - 1, 0)));
+    graph_pool* mem = g->mem;
     forward_lists& t = g->tri;
-    t.entries = U / 2;   // every joined pair is in one forward list
-    TRY(g->mem->alloc((void**)&t.fwd_ptr, sizeof(int64_t) * ((size_t)n + 1)));
-    TRY(g->mem->alloc((void**)&t.fwd, sizeof(uint32_t) * (t.entries + kRowPad)));
-    TRY(g->mem->alloc((void**)&t.fwd_owner, sizeof(uint32_t) * (t.entries ? t.entries : 1)));
-    TAKE(pos, uint64_t, U + 1);
-    if (U > 0)
-        hipLaunchKernelGGL(k_fwd_flag, dim3(grid1(U)), dim3(kT), 0, s, g->nbr, g->owner, g->row_ptr, U, pos);
-    TRY(scan_exclusive<uint64_t>(pos, pos, U, pos + U, ar, s));
-    if (U > 0)
-        hipLaunchKernelGGL(k_fwd_emit, dim3(grid1(U)), dim3(kT), 0, s, g->nbr, g->owner, U, (const uint64_t*)pos,
-                           t.fwd, t.fwd_owner);
-    hipLaunchKernelGGL(k_fwd_ptr, dim3(grid1((uint64_t)n + 1)), dim3(kT), 0, s, g->row_ptr, n,
-                       (const uint64_t*)pos, t.fwd_ptr);
+    auto& out = t.edges;
+    uint64_t *vk = nullptr, *vt = nullptr, *keys = nullptr, *tmp = nullptr, *hk = nullptr, *sums = nullptr,
+             *counts = nullptr, *part = nullptr, *task_off = nullptr;
+    uint32_t *rank = nullptr, *first = nullptr, *past = nullptr;
+    unsigned long long* staged = nullptr;
+    uint64_t hubs = 0, total = 0;
+    size_t inner = 0;
+    const uint32_t tiles = blocks_for(U ? U : 1), nb = blocks_for(F ? F : 1);
+    t.entries = F;
+    TRY(mem->alloc((void**)&t.fptr, sizeof(uint32_t) * ((size_t)n + 1)));
+    TRY(mem->alloc((void**)&t.fwd, sizeof(uint32_t) * (F + kRowPad)));
+    out.chunk = kHubChunk;
+    if (F == 0) {
+        TRY(mem->alloc((void**)&out.recs, sizeof(uint4)));
+        hipLaunchKernelGGL(k_fill_u32, dim3(grid1((uint64_t)n + 1)), dim3(kT), 0, s, t.fptr, (uint64_t)n + 1, 0u);
+        TRY(hipGetLastError());
+        goto done;
+    }
+    TAKE(rank, uint32_t, n);
+    TAKE(keys, uint64_t, F);
+    TAKE(tmp, uint64_t, F);
+    inner = ar.mark();
+    TAKE(vk, uint64_t, n);
+    TAKE(vt, uint64_t, n);
+    hipLaunchKernelGGL(k_vertex_keys, dim3(grid1((uint64_t)n)), dim3(kT), 0, s, deg, n, g->max_degree, vk);
+    TRY(radix_sort(&vk, &vt, (uint64_t)n, 32, bit_width_u32(g->max_degree), ar, s));
+    hipLaunchKernelGGL(k_ranks, dim3(grid1((uint64_t)n)), dim3(kT), 0, s, (const uint64_t*)vk, n, rank);
+    TRY(hipGetLastError());
+    ar.rewind(inner);
+    TAKE(sums, uint64_t, tiles);
+    hipLaunchKernelGGL(k_pair_keys, dim3(tiles), dim3(kT), 0, s, g->nbr, g->owner, (const uint32_t*)rank, U, bits,
+                       (const uint64_t*)nullptr, sums, (uint64_t*)nullptr);
+    TRY(scan_exclusive<uint64_t>(sums, sums, tiles, nullptr, ar, s));
+    hipLaunchKernelGGL(k_pair_keys, dim3(tiles), dim3(kT), 0, s, g->nbr, g->owner, (const uint32_t*)rank, U, bits,
+                       (const uint64_t*)sums, (uint64_t*)nullptr, keys);
+    TRY(radix_sort(&keys, &tmp, F, 3, 2 * bits, ar, s));
+    hipLaunchKernelGGL(k_fwd_emit, dim3(grid1(F)), dim3(kT), 0, s, (const uint64_t*)keys, F, bits, n, t.fwd, t.fptr);
+    TAKE(counts, uint64_t, (uint64_t)kBuckets * nb + 1);
+    TAKE(part, uint64_t, (uint64_t)kPartWords * nb);
+    hipLaunchKernelGGL(k_edge_count, dim3(nb), dim3(kT), 0, s, (const uint64_t*)keys, F, bits, (const uint32_t*)t.fptr,
+                       bp, counts, nb, part);
+    TRY(scan_exclusive<uint64_t>(counts, counts, (uint64_t)kBuckets * nb, counts + (uint64_t)kBuckets * nb, ar, s));
+    hipLaunchKernelGGL(k_bucket_sums, dim3(kPartWords + 1), dim3(kT), 0, s, (const uint64_t*)part,
+                       (const uint64_t*)counts, nb, sp->host);
+    TRY(hipGetLastError());
+    TRY(hipStreamSynchronize(s));
+    for (int b = 0; b <= kBuckets; ++b) out.off[b] = sp->host[b];
+    for (int b = 0; b < kBuckets; ++b) out.cost[b] = sp->host[kBuckets + 1 + b];
+    out.stream = sp->host[2 * kBuckets + 1];
+    total = out.off[kBuckets];
+    hubs = out.off[kBucketHub + 1] - out.off[kBucketHub];
+    out.chunk = hubs >= kHubSplitRecords ? kHubChunk / 2 : hubs >= kHubSmallRecords ? 64 : kHubChunk;
+    TRY(mem->alloc((void**)&out.recs, sizeof(uint4) * (total ? total : 1)));
+    if (total == 0) goto done;
+    // (the second key buffer is free: it takes the hub keys)
+    hipLaunchKernelGGL(k_edge_scatter, dim3(nb), dim3(kT), 0, s, (const uint64_t*)keys, F, bits,
+                       (const uint32_t*)t.fptr, bp, (const uint64_t*)counts, nb, out.off[kBucketHub], tmp, out.recs);
+    TRY(hipGetLastError());
+    if (hubs == 0) goto done;
+    TAKE(hk, uint64_t, hubs);
+    TAKE(first, uint32_t, ((uint64_t)n + 2) & ~1ull);
+    TAKE(past, uint32_t, ((uint64_t)n + 2) & ~1ull);
+    TAKE(task_off, uint64_t, (uint64_t)n + 1);
+    TAKE(staged, unsigned long long, 2);
+    TRY(fill_u64((uint64_t*)first, ((uint64_t)n + 2) / 2, 0, s));
+    TRY(fill_u64((uint64_t*)past, ((uint64_t)n + 2) / 2, 0, s));
+    TRY(fill_u64((uint64_t*)staged, 2, 0, s));
+    TRY(radix_sort(&tmp, &hk, hubs, 32, bits, ar, s));
+    hipLaunchKernelGGL(k_edge_hub, dim3(grid1(hubs)), dim3(kT), 0, s, (const uint64_t*)tmp, (uint32_t)hubs,
+                       (const uint64_t*)keys, bits, (const uint32_t*)t.fptr, (const uint32_t*)t.fwd, first, past,
+                       out.recs + out.off[kBucketHub]);
+    hipLaunchKernelGGL(k_tri_ntasks, dim3(std::min(grid1((uint64_t)n), kStatBlocks)), dim3(kT), 0, s,
+                       (const uint32_t*)first, (const uint32_t*)past, n, (const uint32_t*)t.fptr, out.chunk, task_off,
+                       staged);
+    TRY(scan_exclusive<uint64_t>(task_off, task_off, (uint64_t)n, task_off + n, ar, s));
+    hipLaunchKernelGGL(k_tri_publish, dim3(1), dim3(64), 0, s, (const uint64_t*)task_off, n,
+                       (const unsigned long long*)staged, sp->host);
+    TRY(hipGetLastError());
+    TRY(hipStreamSynchronize(s));
+    out.n_heavy = (uint32_t)sp->host[2];
+    out.n_tasks = (uint32_t)sp->host[0];
+    out.n_groups = out.n_tasks;
+    out.staged = sp->host[1];
+    TRY(mem->alloc((void**)&out.tasks, sizeof(tri_task) * (out.n_tasks ? out.n_tasks : 1)));
+    hipLaunchKernelGGL(k_tri_tasks, dim3(grid1((uint64_t)n)), dim3(kT), 0, s, (const uint32_t*)first,
+                       (const uint32_t*)past, n, (const uint32_t*)t.fptr, out.chunk, (const uint64_t*)task_off,
+                       (uint32_t)out.off[kBucketHub], out.tasks);
     TRY(hipGetLastError());
 done:
     ar.rewind(mark);
     return err;
 }
 
-hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, build_space* sp, arena& ar,
-                      hipStream_t s) {
-    rec_set d;
-    d.recs = g->dyads;
-    d.tasks = g->hub_tasks;
-    g->dyads = nullptr;
-    g->hub_tasks = nullptr;
-    g->n_hub_tasks = 0;
-    g->n_hub_groups = 0;
-    uint64_t mutual = 0;
-    hipError_t err =
-        bucket_records(g->nbr, g->owner, g->row_ptr, deg, g->U, g->n, 0, bp, g->mem, sp, ar, s, &d, &mutual);
-    g->dyads = d.recs;
-    g->hub_tasks = d.tasks;
+// Both views of g.  `fresh`: the largest degree is on its way to the host, and
+// there once the dyad records' synchronisation has passed.
+hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, bool fresh, build_space* sp,
+                      arena& ar, hipStream_t s) {
+    hipError_t err = bucket_dyad_records(g, bp, deg, sp, ar, s);
     if (err != hipSuccess) return err;
-    g->n_hub_tasks = d.n_tasks;
-    g->n_hub_groups = d.n_groups;
-    g->hub_chunk = d.chunk;
-    g->p = d.off[kBuckets];
-    for (int b = 0; b <= kBuckets; ++b) g->bucket_off[b] = d.off[b];
-    for (int b = 0; b < kBuckets; ++b) g->bucket_cost[b] = d.cost[b];
-    g->mutual = mutual;
-    g->hub_stream = d.stream;
-    g->hub_staged = d.staged;
+    if (fresh) g->max_degree = (uint32_t)sp->host[kSpaceHostStats + 1];
     g->bp = bp;
-    if (!bp.tri) {
-        free_forward(g->mem, &g->tri);
-        return hipSuccess;
-    }
-    if (!g->tri.fwd_ptr) {
-        err = build_forward(g, ar, s);
-        if (err != hipSuccess) {
-            free_forward(g->mem, &g->tri);
-            return err;
-        }
-    }
-    forward_lists& t = g->tri;
-    uint32_t* flen = ar.take<uint32_t>((uint64_t)g->n + 1);
-    if (!flen) err = hipErrorOutOfMemory;
-    if (err == hipSuccess && g->n > 0) {
-        hipLaunchKernelGGL(k_row_len, dim3(grid1((uint64_t)g->n)), dim3(kT), 0, s, (const int64_t*)t.fwd_ptr, g->n, flen);
-        err = hipGetLastError();
-    }
-    if (err == hipSuccess)
-        err = bucket_records(t.fwd, t.fwd_owner, t.fwd_ptr, flen, t.entries, g->n, 1, bp, g->mem, sp, ar, s, &t.edges,
-                             nullptr);
+    free_forward(g->mem, &g->tri);
+    if (!bp.tri) return hipSuccess;
+    err = build_forward(g, bp, deg, sp, ar, s);
     if (err != hipSuccess) free_forward(g->mem, &g->tri);
     return err;
 }
@@ -1380,7 +1609,8 @@ hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* 
 #undef TRY
 
 hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s, build_space* sp) {
-    hipError_t e = space_reserve(sp, 4096 + sizeof(uint32_t) * (uint64_t)g->n + bucket_space_bytes(g->U, (uint64_t)g->n), s);
+    hipError_t e = space_reserve(sp, 4096 + sizeof(uint32_t) * (uint64_t)g->n +
+                                     view_space_bytes(g->U, (uint64_t)g->n, bp.tri != 0), s);
     if (e != hipSuccess) return e;
     arena ar(*sp);
     uint32_t* deg = ar.take<uint32_t>((uint64_t)g->n + 1);
@@ -1389,7 +1619,7 @@ hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s,
         hipLaunchKernelGGL(k_row_len, dim3(grid1((uint64_t)g->n)), dim3(kT), 0, s, (const int64_t*)g->row_ptr, g->n, deg);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = bucket_all(g, bp, deg, sp, ar, s);
+    if (e == hipSuccess) e = bucket_all(g, bp, deg, false, sp, ar, s);
     (void)hipStreamSynchronize(s);
     return e;
 }
@@ -1414,10 +1644,9 @@ uint64_t device_graph_bytes(const device_graph& g) {
     uint64_t b = sizeof(int64_t) * ((uint64_t)g.n + 1) + (sizeof(uint32_t) * 2 + sizeof(uint64_t)) * g.U +
                  sizeof(uint32_t) * kRowPad + sizeof(uint4) * ((uint64_t)g.n + 1) +
                  sizeof(uint64_t) + sizeof(dyad_rec) * g.p + sizeof(hub_task) * (uint64_t)g.n_hub_tasks;
-    if (g.tri.fwd_ptr)
-        b += sizeof(int64_t) * ((uint64_t)g.n + 1) + sizeof(uint32_t) * (2 * g.tri.entries + kRowPad) +
-             sizeof(dyad_rec) * g.tri.edges.off[kBuckets] +
-             sizeof(hub_task) * ((uint64_t)g.tri.edges.n_tasks + g.tri.edges.fine_n_tasks);
+    if (g.tri.fptr)
+        b += sizeof(uint32_t) * ((uint64_t)g.n + 1 + g.tri.entries + kRowPad) +
+             sizeof(uint4) * g.tri.edges.off[kBuckets] + sizeof(tri_task) * (uint64_t)g.tri.edges.n_tasks;
     return b;
 }
 

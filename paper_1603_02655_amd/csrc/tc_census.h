@@ -45,13 +45,12 @@ struct graph_desc {
     const uint32_t* owner;
     const int64_t* row_ptr;
     uint64_t U;                  // neighbour entries
-    const dyad_rec* edges;       // forward-list edge records (null without forward lists)
+    const uint4* edges;          // forward-list edge records (null without forward lists)
     const uint32_t* fwd;
-    const hub_task* edge_tasks;
+    const tri_task* edge_tasks;
     const uint4* rinfo;          // per row: bounds and prefix counts at its end
     uint32_t hub_ntasks, hub_groups;   // tasks and task groups over the dyad records
-    uint32_t tri_tasks, tri_groups;    // tasks and task groups over the edge records
-    uint32_t hub_chunk, tri_chunk;     // records per hub task and per group, each view
+    uint32_t tri_chunk;                // records per task over the edge records
     uint64_t asym, mutual;             // joined pairs, one way and both ways
 };
 // Item kinds: the mode (lane / wave / group / hub), with kItemTri when the item
@@ -60,46 +59,57 @@ struct graph_desc {
 enum : uint32_t { kItemLane = 0, kItemWave = 1, kItemGroup = 2, kItemHub = 3, kItemTri = 4, kItemRows = 8 };
 struct work_item {
     uint32_t graph, kind, begin, end;   // records [begin, end) of graph `graph`'s record array;
-                                        // hub items: task groups [begin, end) of the graph
+                                        // hub items: task groups [begin, end) of the graph, or with
+                                        // kItemTri its hub tasks [begin, end)
 };
+constexpr uint32_t kBatchTasksPerItem = 32;   // hub tasks of the forward lists per item
 constexpr uint32_t kBatchRowsPerItem = 4096;   // rows per rows item
 constexpr uint32_t kBatchLanePerItem = 256;   // one dyad per thread of a 256-thread workgroup
 constexpr uint32_t kBatchWavePerItem = 16;    // four wavefronts, four dyads each
 
-// Zeroes accs[0..acc_words) and 16 work counters, then runs two persistent
-// kernels: the hub kernel (LDS tile of hub_tile anchor entries) over the hub
-// items items[0..nums[0]) with hub_grid workgroups, and the batch kernel
-// (wave-mode tile batch_tile, group-mode tile 4 x batch_tile) over the other
-// items items[nums[0]..nums[1]) with `grid` workgroups (nums: 2 words of
-// device memory).  hub_chunk: the largest records per hub task of the graphs
-// (a launch of graphs with half-size tasks only runs the hub kernel instance
-// with the smaller LDS).  hipErrorInvalidValue for a tile the kernels are not
-// built for.
-hipError_t batch_launch(const graph_desc* descs, const work_item* items, const uint32_t* nums,
-                        unsigned long long* accs, uint64_t acc_words, unsigned int* counters, uint32_t grid,
-                        uint32_t hub_grid, uint32_t hub_tile, uint32_t batch_tile, uint32_t hub_chunk, hipStream_t s);
+// Zeroes accs[0..acc_words) and the work counters, then runs the persistent
+// kernels: over the items items[0..nums[0]) (hub tasks of forward lists) with
+// tri_grid workgroups, over those up to nums[1] (dyad hub task groups, LDS tile
+// of hub_tile anchor entries) with hub_grid, and over those up to nums[2]
+// (wave-mode tile batch_tile, group-mode tile 4 x batch_tile) with grid.  A hub
+// kernel with a grid of 0 is left out.  hipErrorInvalidValue for a tile the
+// kernels are not built for.
+struct batch_buffers {
+    const graph_desc* descs;
+    const work_item* items;
+    const uint32_t* nums;           // 3 words of device memory
+    unsigned long long* accs;       // 16 per graph
+    unsigned int* counters;         // 3 x kCounterWords
+    uint32_t tri_grid, hub_grid, grid;
+};
+hipError_t batch_launch(const batch_buffers& b, uint64_t acc_words, uint32_t hub_tile, uint32_t batch_tile,
+                        hipStream_t s);
 
 // Copies the 16-class table into the constant table the batch kernel reads.
 hipError_t census_upload_table();
 // One census on stream s: the bucket kernels over the given slices with
 // `table` (64 bytes of device memory: the bin of every code, kNumClasses for
 // codes that are not counted), the terms that need no intersection, and a last
-// kernel that writes the 16 sums to `out` (pinned host memory) and leaves acc
-// (kAccCopies x 16 u64) and counters (kBuckets x 8 u32) zero, as they have to
-// be before.  With `tri` the slices index the forward-list edge records
-// (g.tri.edges).  `labelled`: the table is one of the labelled census's, whose
-// terms come from a pass over the neighbour entries.  When `side` is given
+// kernel that writes the sums to `out` (pinned host memory) and leaves acc
+// (kAccCopies x 16 u64, x 64 for kLabelled) and counters (kBuckets x kCounterWords)
+// zero, as they have to be before.  With `tri` the slices index the
+// forward-list edge records (g.tri.edges).  When `side` is given
 // (with two events in `fork`) and the hub bucket streams more entries than the
 // graph has, these terms run on `side`, followed there by the lane bucket,
 // beside the other bucket kernels; s waits for it at the end.  ev, when not
 // null, holds 2*kBuckets + 2 events: around each bucket's launch, then around
 // the terms.
-hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tri, const uint8_t* table, bool labelled,
-                         unsigned long long* acc, unsigned int* counters, unsigned long long* out,
+// kClasses: 16 sums by a class table.  kLabelledPass: 16 sums by one of the
+// labelled census's pass tables (dyad records).  kLabelled: all 64 code sums
+// (forward lists; the table maps every code to itself).
+enum census_kind { kClasses, kLabelledPass, kLabelled };
+constexpr int kAccWords = 64 * kAccCopies;
+hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tri, const uint8_t* table,
+                         census_kind kind, unsigned long long* acc, unsigned int* counters, unsigned long long* out,
                          const census_config& cfg, hipStream_t s, hipEvent_t* ev, hipStream_t side = nullptr,
                          hipEvent_t* fork = nullptr);
-// Zeroes acc and counters (before the first census that uses them, or after a
+// Zeroes `words` accumulators and the counters (before the first census that uses them, or after a
 // failed launch).
-hipError_t census_clear(unsigned long long* acc, unsigned int* counters, hipStream_t s);
+hipError_t census_clear(unsigned long long* acc, int words, unsigned int* counters, hipStream_t s);
 
 }  // namespace tc

@@ -24,10 +24,9 @@
 //   hub   : one workgroup per group of runs of records that share an
 //           endpoint (anchor), whose rows are staged in an LDS hash table and
 //           probed by the other rows.
-// The same kernels run over the dyad records (Tri = false) or over the
-// forward-list edge records (Tri = true), where a shared vertex closes a
-// triangle that is credited to its three dyads (on_triangle) and the per-dyad
-// terms come from a separate pass over the neighbour entries (k_census_totals).
+// These run over the dyad records.  The forward-list path has kernels of the
+// same four modes over its edge records (k_tri_*, tc_tri.h), where a shared
+// vertex closes a triangle that is credited to its three dyads (on_triangle).
 // Counts accumulate in LDS bins (per lane, per wavefront, or per signature in
 // the hub mode); each workgroup adds its 16 sums to the graph's accumulators
 // with one 64-bit global atomic per class when it finishes.
@@ -38,6 +37,7 @@
 // codes whose (u, v) part is f to bin (code >> 2) and every other code to the
 // discard bin (index kNumClasses), which is never flushed.
 #include "tc_census.h"
+#include "tc_tri.h"
 
 namespace tc {
 
@@ -88,6 +88,14 @@ struct block_bins {
         __syncthreads();
         if (threadIdx.x < kNumClasses && bins[threadIdx.x] != 0) atomicAdd(&acc[threadIdx.x], bins[threadIdx.x]);
     }
+};
+
+// The forward-list kernels' bins: 16 classes or 64 codes, one row per workgroup.
+template <bool Lab>
+struct tri_bins {
+    static constexpr uint32_t kWords = Lab ? 64 : kNumClasses;
+    unsigned long long* bins;
+    __device__ inline void add(uint32_t bin, unsigned long long x) { atomicAdd(&bins[bin], x); }
 };
 
 template <int B>
@@ -167,9 +175,10 @@ __device__ inline void on_common(uint32_t w, uint32_t fa, uint32_t fb, uint32_t 
     if (w > u) h.add(T[f | (fb << 4)], ~0ull);            // not a v-only vertex
 }
 
-// The copy of the accumulators this workgroup adds to.
-__device__ inline unsigned long long* acc_copy(unsigned long long* acc) {
-    return acc + kNumClasses * (blockIdx.x % kAccCopies);
+// The copy of the accumulators (16, or 64 for the labelled census) this
+// workgroup adds to.
+__device__ inline unsigned long long* acc_copy(unsigned long long* acc, uint32_t words = kNumClasses) {
+    return acc + words * (blockIdx.x % kAccCopies);
 }
 
 __device__ inline uint32_t swap_dir(uint32_t f) { return ((f & 1u) << 1) | (f >> 1); }
@@ -189,13 +198,40 @@ __device__ inline void on_triangle(uint32_t w, uint32_t fa, uint32_t fb, uint32_
     else on_common(u, sa, sf, w, v, sb, T, h);                // dyad (w, v)
 }
 
-// What a shared vertex of the two rows of a record means: for dyad records a
-// shared neighbour of the dyad; for forward-list edge records a triangle.
-template <bool Tri, class H>
-__device__ inline void on_shared(uint32_t w, uint32_t fa, uint32_t fb, uint32_t u, uint32_t v, uint32_t f,
-                                 const uint8_t* T, H& h) {
-    if constexpr (Tri) on_triangle(w, fa, fb, u, v, f, T, h);
-    else on_common(w, fa, fb, u, v, f, T, h);
+// Scales every update of one signature by its count.
+template <class H>
+struct scaled_bins {
+    H& h;
+    unsigned long long c;
+    __device__ inline void add(uint32_t cls, unsigned long long x) { h.add(cls, x * c); }
+};
+
+// Turns the signature counts of a workgroup of `threads` into updates of h and
+// clears them.  Labelled signatures hold the order of the three ids.
+template <bool Lab, class H>
+__device__ inline void tri_flush(tri_sig<Lab>& sig, uint32_t threads, const uint8_t* T, H& h) {
+    constexpr uint32_t kB = tri_sig<Lab>::kBits, kM = (1u << kB) - 1u;
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < tri_sig<Lab>::kSlots; k += threads) {
+        const unsigned long long c = sig.n[k];
+        if (c == 0) continue;
+        sig.n[k] = 0;
+        scaled_bins<H> sh{h, c};
+        uint32_t xy = k & kM, xz = (k >> kB) & kM, yz = k >> (2 * kB);
+        uint32_t px = 0, py = 1, pz = 2;
+        if (Lab) {
+            const uint32_t gxy = xy & 1u, gxz = xz & 1u, gyz = yz & 1u;
+            px = 2u - gxy - gxz;
+            py = gxy + 1u - gyz;
+            pz = gxz + gyz;
+            xy >>= 1;
+            xz >>= 1;
+            yz >>= 1;
+        }
+        if (px < py) on_triangle(pz, xz, yz, px, py, xy, T, sh);
+        else on_triangle(pz, yz, xz, py, px, swap_dir(xy), T, sh);
+    }
+    __syncthreads();
 }
 
 __device__ inline dyad_rec load_rec(const dyad_rec* p) {
@@ -231,7 +267,7 @@ __device__ inline void load_chunk(const uint32_t* __restrict__ nbr, uint32_t pos
     for (uint32_t k = 0; k < kLaneChunk; ++k) c[k] = pos + k < end ? nbr[pos + k] : pad;
 }
 
-template <bool Tri, class H>
+template <class H>
 __device__ inline void lane_dyad(const dyad_rec& r, const uint32_t* __restrict__ nbr, const uint8_t* T, H& h) {
     const uint32_t u = r.u, v = r.vf >> 2, f = r.vf & 3u;
     // pads: never equal to an entry or to each other (entries are below 2^25)
@@ -245,7 +281,7 @@ __device__ inline void lane_dyad(const dyad_rec& r, const uint32_t* __restrict__
         for (uint32_t p = 0; p < kLaneChunk; ++p)
 #pragma unroll
             for (uint32_t q = 0; q < kLaneChunk; ++q)
-                if ((A[p] ^ B[q]) < 4u) on_shared<Tri>(A[p] >> 2, A[p] & 3u, B[q] & 3u, u, v, f, T, h);
+                if ((A[p] ^ B[q]) < 4u) on_common(A[p] >> 2, A[p] & 3u, B[q] & 3u, u, v, f, T, h);
         const uint32_t la = min(kLaneChunk, r.eu - i), lb = min(kLaneChunk, r.ev - j);
         uint32_t lastA = A[0], lastB = B[0];
 #pragma unroll
@@ -268,7 +304,7 @@ __device__ inline void lane_dyad(const dyad_rec& r, const uint32_t* __restrict__
 // PerDyad: every record adds its per-dyad terms: per-lane bins (in dynamic
 // LDS).  Otherwise a record only adds on a shared vertex, which is rare:
 // per-wavefront bins, and far less LDS.
-template <bool Tri, bool PerDyad>
+template <bool PerDyad>
 __global__ __launch_bounds__(kLaneB) void k_census_lane(census_args L) {
     extern __shared__ unsigned long long lds[];
     __shared__ uint8_t T[64];
@@ -280,7 +316,7 @@ __global__ __launch_bounds__(kLaneB) void k_census_lane(census_args L) {
         __syncthreads();
         for (uint64_t d = (uint64_t)blockIdx.x * kLaneB + threadIdx.x; d < L.count;
              d += (uint64_t)gridDim.x * kLaneB)
-            lane_dyad<Tri>(load_rec(L.dyads + d), L.nbr, T, h);
+            lane_dyad(load_rec(L.dyads + d), L.nbr, T, h);
         h.flush(acc_copy(L.acc));
     } else {
         lane_bins<kLaneB> h{lds};
@@ -290,7 +326,7 @@ __global__ __launch_bounds__(kLaneB) void k_census_lane(census_args L) {
              d += (uint64_t)gridDim.x * kLaneB) {
             const dyad_rec r = load_rec(L.dyads + d);
             const dyad_totals t = load_totals(r, L.nbr, L.tpre);
-            lane_dyad<Tri>(r, L.nbr, T, h);
+            lane_dyad(r, L.nbr, T, h);
             add_totals(r, t, L.n, T, h);
         }
         h.flush(acc_copy(L.acc));
@@ -411,7 +447,11 @@ __device__ inline void totals_entries(uint64_t base, uint64_t end, const uint32_
 }
 
 constexpr uint32_t kTotalsPer = 4;   // entries per thread and step
-constexpr uint32_t kTotalsSlots = 8; // distinct bins the totals pass can reach (any table here has <= 8)
+// Distinct bins the totals pass can reach: at most 8 with a pass table of the
+// dyad path, and the 21 codes themselves on the forward-list path, which keeps
+// all 64 codes in one pass.
+template <bool Lab>
+constexpr uint32_t totals_slot_count() { return Lab ? 21 : 8; }
 
 // Adds straight to a graph's 16 accumulators in global memory.
 struct global_bins {
@@ -420,83 +460,70 @@ struct global_bins {
 };
 
 // Per-lane bins over a few slots: the totals pass reaches only the bins of the
-// codes f, f | t << 2 and f | t << 4 (f, t in 1..3), at most kTotalsSlots of
-// them, so a lane keeps one 64-bit slot per reachable bin (16 KB of LDS for
-// 256 lanes instead of 35 KB).  The codes are remapped to slots in a table.
+// codes f, f | t << 2 and f | t << 4 (f, t in 1..3), so a lane keeps one 64-bit
+// slot per reachable bin.  The codes are remapped to slots in a table.
 struct slot_bins {
-    unsigned long long* bins;   // kTotalsSlots x kLaneB
+    unsigned long long* bins;   // slots x kLaneB
     __device__ inline void add(uint32_t slot, unsigned long long x) {
         atomicAdd(&bins[slot * kLaneB + threadIdx.x], x);
     }
 };
 
 // Fills TS (code -> slot) and bin_of_slot for the reachable codes of table T;
-// returns the number of slots, or 0 when more than kTotalsSlots bins are
-// reachable.  One thread.
+// returns the number of slots.  One thread.
+template <uint32_t SLOTS>
 __device__ inline uint32_t totals_slots(const uint8_t* T, uint8_t* TS, uint32_t* bin_of_slot) {
     uint32_t ns = 0;
-    bool all = true;
     for (uint32_t c = 0; c < 64; ++c) TS[c] = 0xff;
     for (uint32_t f = 1; f < 4; ++f)
         for (uint32_t j = 0; j < 7; ++j) {
             const uint32_t c = j == 0 ? f : (j <= 3 ? f | (j << 2) : f | ((j - 3) << 4));
             uint32_t sl = 0;
             while (sl < ns && bin_of_slot[sl] != T[c]) ++sl;
-            if (sl == ns && ns < kTotalsSlots) bin_of_slot[ns++] = T[c];
-            TS[c] = sl < ns ? (uint8_t)sl : (uint8_t)0xff;
-            all = all && sl < ns;
+            if (sl == ns && ns < SLOTS) bin_of_slot[ns++] = T[c];
+            TS[c] = (uint8_t)sl;
         }
-    return all ? ns : 0u;
+    return ns;
 }
 
 // Sums the per-lane slots over a kLaneB workgroup into h (wavefront w takes
-// slots w, w + 4) and clears them.
+// slots w, w + 4), without those of bins from `bins` on (the discard bin).
 template <class H>
-__device__ inline void slots_flush(unsigned long long* sbins, const uint32_t* bin_of_slot, uint32_t nslots, H& h) {
+__device__ inline void slots_flush(unsigned long long* sbins, const uint32_t* bin_of_slot, uint32_t nslots,
+                                   uint32_t bins, H& h) {
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
     for (uint32_t sl = threadIdx.x >> 6; sl < nslots; sl += kLaneB / 64) {
         unsigned long long v = 0;
         for (uint32_t i = lane; i < kLaneB; i += 64) v += sbins[sl * kLaneB + i];
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0 && v != 0 && bin_of_slot[sl] < kNumClasses) h.add(bin_of_slot[sl], v);
+        if (lane == 0 && v != 0 && bin_of_slot[sl] < bins) h.add(bin_of_slot[sl], v);
     }
-    __syncthreads();
-    for (uint32_t k = threadIdx.x; k < kTotalsSlots * kLaneB; k += kLaneB) sbins[k] = 0;
 }
 
-// Over the neighbour entries [e0, e1).
+// Over all U neighbour entries.
+template <bool Lab>
 __global__ __launch_bounds__(kLaneB) void k_census_totals(const uint32_t* __restrict__ nbr,
                                                           const uint32_t* __restrict__ owner,
                                                           const uint4* __restrict__ rinfo,
-                                                          const uint64_t* __restrict__ tpre, uint64_t e0, uint64_t e1,
+                                                          const uint64_t* __restrict__ tpre, uint64_t U,
                                                           uint64_t n, const uint8_t* __restrict__ table,
                                                           unsigned long long* __restrict__ acc) {
-    __shared__ unsigned long long sbins[kTotalsSlots * kLaneB];
-    __shared__ unsigned long long wbins[wave_bins<kLaneB>::kWords];
+    constexpr uint32_t kSlots = totals_slot_count<Lab>(), kWords = tri_bins<Lab>::kWords;
+    __shared__ unsigned long long sbins[kSlots * kLaneB];
     __shared__ uint8_t T[64], TS[64];
-    __shared__ uint32_t bin_of_slot[kTotalsSlots], s_nslots;
+    __shared__ uint32_t bin_of_slot[kSlots], s_nslots;
     if (threadIdx.x < 64) T[threadIdx.x] = table[threadIdx.x];
     __syncthreads();
-    if (threadIdx.x == 0) s_nslots = totals_slots(T, TS, bin_of_slot);
-    for (uint32_t k = threadIdx.x; k < kTotalsSlots * kLaneB; k += kLaneB) sbins[k] = 0;
-    wave_bins<kLaneB> hw{wbins};
-    hw.clear();
+    if (threadIdx.x == 0) s_nslots = totals_slots<kSlots>(T, TS, bin_of_slot);
+    for (uint32_t k = threadIdx.x; k < kSlots * kLaneB; k += kLaneB) sbins[k] = 0;
     __syncthreads();
-    const uint32_t nslots = s_nslots;
-    if (nslots) {
-        slot_bins hs{sbins};
-        for (uint64_t base = e0 + (uint64_t)blockIdx.x * kLaneB * kTotalsPer; base < e1;
-             base += (uint64_t)gridDim.x * kLaneB * kTotalsPer)
-            totals_entries<kTotalsPer, kLaneB>(base, e1, nbr, owner, rinfo, tpre, n, TS, hs);
-        global_bins g{acc_copy(acc)};
-        slots_flush(sbins, bin_of_slot, nslots, g);
-    } else {
-        for (uint64_t base = e0 + (uint64_t)blockIdx.x * kLaneB * kTotalsPer; base < e1;
-             base += (uint64_t)gridDim.x * kLaneB * kTotalsPer)
-            totals_entries<kTotalsPer, kLaneB>(base, e1, nbr, owner, rinfo, tpre, n, T, hw);
-        hw.flush(acc_copy(acc));
-    }
+    slot_bins hs{sbins};
+    for (uint64_t base = (uint64_t)blockIdx.x * kLaneB * kTotalsPer; base < U;
+         base += (uint64_t)gridDim.x * kLaneB * kTotalsPer)
+        totals_entries<kTotalsPer, kLaneB>(base, U, nbr, owner, rinfo, tpre, n, TS, hs);
+    global_bins g{acc_copy(acc, kWords)};
+    slots_flush(sbins, bin_of_slot, s_nslots, kWords, g);
 }
 
 // ---------------------------------------------------------- merge path ----
@@ -508,11 +535,14 @@ __global__ __launch_bounds__(kLaneB) void k_census_totals(const uint32_t* __rest
 // shared vertex is seen when its N(u) copy is taken while the N(v) head holds
 // the same vertex.  The lane that produces the round's last output publishes
 // how many N(u) entries the round consumed.
+// P says how two entries compare (le, eq; the sentinel is above every entry)
+// and what a shared vertex means (shared).
+template <class P>
 __device__ inline uint32_t co_rank(const uint32_t* sA, uint32_t na, const uint32_t* sB, uint32_t nb, uint32_t d) {
     uint32_t lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
     while (lo < hi) {
         uint32_t mid = (lo + hi + 1) >> 1;
-        if (sA[mid - 1] <= (sB[d - mid] | 3u)) lo = mid; else hi = mid - 1;
+        if (P::le(sA[mid - 1], sB[d - mid])) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -531,14 +561,37 @@ struct wave_sync {
     }
 };
 
-template <int G, int TW, class Sync, bool Tri, class H>
-__device__ inline void merge_path(const dyad_rec& r, const uint32_t* __restrict__ nbr, uint32_t* sA, uint32_t* sB,
-                                  uint32_t* s_xt, uint32_t lane, const uint8_t* T, H& h) {
+// Dyad records: a shared neighbour of the dyad.
+template <class H>
+struct dyad_rows {
+    const dyad_rec& r;
+    const uint8_t* T;
+    H& h;
+    __device__ static inline bool le(uint32_t a, uint32_t b) { return a <= (b | 3u); }
+    __device__ static inline bool eq(uint32_t a, uint32_t b) { return (a ^ b) < 4u; }
+    __device__ inline void shared(uint32_t a, uint32_t b) {
+        on_common(a >> 2, a & 3u, b & 3u, r.u, r.vf >> 2, r.vf & 3u, T, h);
+    }
+};
+// Edge records: a triangle.
+template <bool Lab>
+struct edge_rows {
+    uint32_t xy;
+    tri_sig<Lab>& sig;
+    __device__ static inline bool le(uint32_t a, uint32_t b) { return (a & kRankMask) <= (b & kRankMask); }
+    __device__ static inline bool eq(uint32_t a, uint32_t b) { return ((a ^ b) & kRankMask) == 0u; }
+    __device__ inline void shared(uint32_t a, uint32_t b) {
+        sig.hit(xy, tri_sig<Lab>::code(a), tri_sig<Lab>::code(b));
+    }
+};
+
+template <int G, int TW, class Sync, class P>
+__device__ inline void merge_path(uint32_t bu, uint32_t eu, uint32_t bv, uint32_t ev, const uint32_t* __restrict__ nbr,
+                                  uint32_t* sA, uint32_t* sB, uint32_t* s_xt, uint32_t lane, P rows) {
     constexpr uint32_t PER = TW / G;
     static_assert(TW % G == 0, "tile is a multiple of the group");
     const Sync sync{};
-    const uint32_t u = r.u, v = r.vf >> 2, f = r.vf & 3u;
-    const uint32_t la = r.eu - r.bu, lb = r.ev - r.bv;
+    const uint32_t la = eu - bu, lb = ev - bv;
     uint32_t a_pos = 0, b_pos = 0;
     while (a_pos < la && b_pos < lb) {
         const uint32_t na = min((uint32_t)TW, la - a_pos), nb = min((uint32_t)TW, lb - b_pos);
@@ -546,8 +599,8 @@ __device__ inline void merge_path(const dyad_rec& r, const uint32_t* __restrict_
 #pragma unroll
         for (uint32_t t = 0; t < PER; ++t) {
             const uint32_t k = lane + t * G;
-            ra[t] = k < na ? nbr[r.bu + a_pos + k] : kSentinel;
-            rb[t] = k < nb ? nbr[r.bv + b_pos + k] : kSentinel;
+            ra[t] = k < na ? nbr[bu + a_pos + k] : kSentinel;
+            rb[t] = k < nb ? nbr[bv + b_pos + k] : kSentinel;
         }
 #pragma unroll
         for (uint32_t t = 0; t < PER; ++t) {
@@ -563,14 +616,14 @@ __device__ inline void merge_path(const dyad_rec& r, const uint32_t* __restrict_
         const uint32_t d0 = lane * PER;
         if (d0 < total) {
             const uint32_t steps = min(PER, total - d0);
-            uint32_t i = co_rank(sA, na, sB, nb, d0);
+            uint32_t i = co_rank<P>(sA, na, sB, nb, d0);
             uint32_t j = d0 - i;
             uint32_t a = sA[i], b = sB[j];
 #pragma unroll
             for (uint32_t t = 0; t < PER; ++t) {
                 if (t < steps) {
-                    if ((a ^ b) < 4u) on_shared<Tri>(a >> 2, a & 3u, b & 3u, u, v, f, T, h);
-                    const bool ta = a <= (b | 3u);
+                    if (P::eq(a, b) && a != kSentinel) rows.shared(a, b);
+                    const bool ta = P::le(a, b);
                     i += ta ? 1u : 0u;
                     j += ta ? 0u : 1u;
                     const uint32_t x = ta ? sA[i] : sB[j];
@@ -591,10 +644,8 @@ __device__ inline void merge_path(const dyad_rec& r, const uint32_t* __restrict_
 // Dyads are handed out in chunks of CH through eight counters, one per XCD
 // (workgroup b runs on XCD b % 8 on this part), so that the atomics stay in
 // one L2: counter x hands out the chunk indices x, x + 8, x + 16, ...
-constexpr int kXcds = 8;
-
 __device__ inline uint32_t take_chunk(unsigned int* ctr, uint32_t xcd) {
-    return xcd + kXcds * atomicAdd(&ctr[xcd], 1u);
+    return xcd + kXcds * atomicAdd(&ctr[xcd * kCounterStride], 1u);
 }
 
 // ---------------------------------------------------------------- wave ----
@@ -602,7 +653,7 @@ constexpr int kWaveB = 64;
 constexpr uint32_t kWaveChunk = 16;
 
 // TW: entries of each row staged per round (the tunable LDS tile).
-template <bool Tri, int TW>
+template <int TW>
 __global__ __launch_bounds__(kWaveB) void k_census_wave(census_args L, unsigned int* ctr) {
     __shared__ unsigned long long bins[wave_bins<kWaveB>::kWords];
     __shared__ uint8_t T[64];
@@ -623,9 +674,10 @@ __global__ __launch_bounds__(kWaveB) void k_census_wave(census_args L, unsigned 
         for (uint32_t d = c * kWaveChunk; d < end; ++d) {
             const dyad_rec r = load_rec(L.dyads + d);
             dyad_totals t{};
-            const bool own = !Tri && L.per_dyad && threadIdx.x == 0;
+            const bool own = L.per_dyad && threadIdx.x == 0;
             if (own) t = load_totals(r, L.nbr, L.tpre);
-            merge_path<kWaveB, TW, block_sync, Tri>(r, L.nbr, sA, sB, &s_xt, threadIdx.x, T, h);
+            merge_path<kWaveB, TW, block_sync>(r.bu, r.eu, r.bv, r.ev, L.nbr, sA, sB, &s_xt, threadIdx.x,
+                                               dyad_rows<wave_bins<kWaveB>>{r, T, h});
             if (own) add_totals(r, t, L.n, T, h);
         }
         c = __shfl(cn, 0, 64);
@@ -637,7 +689,7 @@ __global__ __launch_bounds__(kWaveB) void k_census_wave(census_args L, unsigned 
 constexpr uint32_t kGroupChunk = 2;
 
 // B: workgroup size; TW: entries of each row staged per round (both tunable).
-template <bool Tri, int B, int TW>
+template <int B, int TW>
 __global__ __launch_bounds__(B) void k_census_group(census_args L, unsigned int* ctr) {
     __shared__ unsigned long long bins[wave_bins<B>::kWords];
     __shared__ uint8_t T[64];
@@ -657,9 +709,10 @@ __global__ __launch_bounds__(B) void k_census_group(census_args L, unsigned int*
         for (uint32_t d = c * kGroupChunk; d < end; ++d) {
             const dyad_rec r = load_rec(L.dyads + d);
             dyad_totals t{};
-            const bool own = !Tri && L.per_dyad && threadIdx.x == 0;
+            const bool own = L.per_dyad && threadIdx.x == 0;
             if (own) t = load_totals(r, L.nbr, L.tpre);
-            merge_path<B, TW, block_sync, Tri>(r, L.nbr, sA, sB, &s_xt, threadIdx.x, T, h);
+            merge_path<B, TW, block_sync>(r.bu, r.eu, r.bv, r.ev, L.nbr, sA, sB, &s_xt, threadIdx.x,
+                                          dyad_rows<wave_bins<B>>{r, T, h});
             if (own) add_totals(r, t, L.n, T, h);
         }
         __syncthreads();
@@ -756,9 +809,8 @@ __device__ inline uint32_t hub_probe(const uint32_t* hash, uint32_t key4, uint32
 // 4 * 256); a[count .. count + kScanPad) receive the total.  wsum holds 4 words
 // of LDS.
 constexpr uint32_t kScanPad = 8;
-template <uint32_t CH>
 __device__ inline void block_scan_u32(uint32_t* a, uint32_t count, uint32_t* wsum) {
-    constexpr uint32_t kPer = CH / kHubB;
+    constexpr uint32_t kPer = kHubChunk / kHubB;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wid = tid >> 6;
     uint32_t loc[kPer], s = 0;
 #pragma unroll
@@ -798,14 +850,6 @@ __device__ inline void block_scan_u32(uint32_t* a, uint32_t count, uint32_t* wsu
 // counts into class updates when it flushes.
 constexpr uint32_t kSigs = 192;
 
-// Scales every update of one signature by its count.
-template <class H>
-struct scaled_bins {
-    H& h;
-    unsigned long long c;
-    __device__ inline void add(uint32_t cls, unsigned long long x) { h.add(cls, x * c); }
-};
-
 // Aligned blocks of kHubGather entries that hold the entries [p0, p1) of a row
 // (row arrays are padded so that the last block is readable).
 static_assert(kHubGather == 8, "a block is read as two 16-byte loads");
@@ -836,34 +880,32 @@ struct hub_lds {
 constexpr uint32_t kTkBegin = 0, kTkNrec = 8, kTkHb = 16, kTkLen = 24, kTkAnchor = 32, kTkGroups = 40,
                    kTkNGroups = 49, kTkRb = 50, kTkEb = 59, kHubTkWords = 68;
 static_assert(kHubGroupTasks == 8, "the task words hold eight tasks");
-// CH: the records of a group the LDS holds (kHubChunk, or half of it for
-// graphs whose tasks and groups are half-size).
-template <uint32_t TILE, uint32_t CH>
+template <uint32_t TILE>
 constexpr uint32_t hub_lds_words() {
-    return hub_geom<TILE>::kSlots + 2 * kHubRing * (kHubB / 64) + 3 * CH + (CH + kScanPad) + 4 + kSigs +
+    return hub_geom<TILE>::kSlots + 2 * kHubRing * (kHubB / 64) + 3 * kHubChunk + (kHubChunk + kScanPad) + 4 + kSigs +
            hub_geom<TILE>::kFilterBits / 32 + kHubTkWords;
 }
 
 // Wavefronts per SIMD the hub kernels are compiled for: seven (the best
 // measured with 1024-entry tiles), or as many workgroups as the LDS of a CU
 // (160 KiB) holds for larger tiles (the kernels' other LDS takes < 256 bytes).
-template <uint32_t TILE, uint32_t CH>
+template <uint32_t TILE>
 constexpr uint32_t hub_waves_per_simd() {
-    return (163840u / (4u * hub_lds_words<TILE, CH>() + 256u)) < 7u ? (163840u / (4u * hub_lds_words<TILE, CH>() + 256u))
+    return (163840u / (4u * hub_lds_words<TILE>() + 256u)) < 7u ? (163840u / (4u * hub_lds_words<TILE>() + 256u))
                                                                    : 7u;
 }
 
-template <uint32_t TILE, uint32_t CH>
+template <uint32_t TILE>
 __device__ inline hub_lds hub_carve(uint32_t* base) {
     uint32_t* p = base;
     hub_lds S;
     S.hash = p;  p += hub_geom<TILE>::kSlots;
     S.ring_e = p;  p += kHubRing * (kHubB / 64);
     S.ring_m = p;  p += kHubRing * (kHubB / 64);
-    S.pos = p;   p += CH;
-    S.end = p;   p += CH;
-    S.meta = p;  p += CH;
-    S.off = p;   p += CH + kScanPad;
+    S.pos = p;   p += kHubChunk;
+    S.end = p;   p += kHubChunk;
+    S.meta = p;  p += kHubChunk;
+    S.off = p;   p += kHubChunk + kScanPad;
     S.wsum = p;  p += 4;
     S.sig = p;   p += kSigs;
     S.filt = p;  p += hub_geom<TILE>::kFilterBits / 32;
@@ -876,7 +918,7 @@ __device__ inline void hub_bins_clear(const hub_lds& S) {
 }
 
 // Adds the signature counts to h (one thread per signature) and clears them.
-template <bool Tri, class H>
+template <class H>
 __device__ inline void hub_bins_flush(const hub_lds& S, const uint8_t* T, H& h) {
     __syncthreads();
     for (uint32_t k = threadIdx.x; k < kSigs; k += kHubB) {
@@ -888,7 +930,7 @@ __device__ inline void hub_bins_flush(const hub_lds& S, const uint8_t* T, H& h) 
         // ids that put w below u, between u and v, or above v
         const uint32_t u = 1u, v = 3u, w = where * 2u;
         scaled_bins<H> sh{h, (unsigned long long)c};
-        on_shared<Tri>(w, fa, fb, u, v, f, T, sh);
+        on_common(w, fa, fb, u, v, f, T, sh);
     }
     __syncthreads();
 }
@@ -903,7 +945,7 @@ __device__ inline void hub_bins_flush(const hub_lds& S, const uint8_t* T, H& h) 
 // then each wavefront walks a quarter of the flattened block list, one block
 // per lane, and probes the entries that pass the tile's filter 64 at a time.
 // A hit adds one to the workgroup's count of the hit's signature.
-template <bool Tri, uint32_t TILE, uint32_t CH, class H>
+template <uint32_t TILE, class H>
 __device__ inline void hub_group_run(uint32_t js, uint32_t M, const dyad_rec* __restrict__ dyads,
                                      const uint32_t* __restrict__ nbr, const uint64_t* __restrict__ tpre, uint64_t n,
                                      uint32_t u_lo, uint32_t u_hi, bool per_dyad, const hub_lds& S,
@@ -930,7 +972,7 @@ __device__ inline void hub_group_run(uint32_t js, uint32_t M, const dyad_rec* __
             S.end[i] = xe;
             S.off[i] = hub_blocks(p0, xe);
         }
-        if (!Tri && per_dyad && in) add_totals(r, load_totals(r, nbr, tpre), n, T, h);
+        if (per_dyad && in) add_totals(r, load_totals(r, nbr, tpre), n, T, h);
     }
     for (uint32_t tb = 0; tb < total; tb += TILE) {
         const uint32_t te = min(total, tb + TILE);
@@ -961,14 +1003,14 @@ __device__ inline void hub_group_run(uint32_t js, uint32_t M, const dyad_rec* __
             }
         }
         __syncthreads();
-        block_scan_u32<CH>(S.off, nrec, S.wsum);
+        block_scan_u32(S.off, nrec, S.wsum);
         const uint32_t P = S.off[nrec];
         // The shared 32-bit signature counts grow by at most kHubGather * P in
         // this tile: they are flushed first when the tiles since the last flush
         // could take them past 2^32 (`per` is the same on every thread).
         const uint32_t per = (uint32_t)min((uint64_t)kHubGather * P / kHubB + 1, (uint64_t)kHubFlushAfter);
         if (since + per > kHubFlushAfter) {
-            hub_bins_flush<Tri>(S, T, h);
+            hub_bins_flush(S, T, h);
             since = 0;
         }
         since += per;
@@ -1100,14 +1142,13 @@ __device__ inline void hub_group_run(uint32_t js, uint32_t M, const dyad_rec* __
 
 // Hub tasks [t0, t1) (at most kHubGroupTasks) on the whole workgroup: their
 // descriptors and anchor rows are read once, and runs of consecutive tasks
-// whose records fit one chunk (`chunk` <= CH records, the graph's) and
-// whose anchor rows fit one tile are processed together; a task whose anchor
+// whose records fit one chunk and whose anchor rows fit one tile are processed together; a task whose anchor
 // row spans several tiles runs alone.
-template <bool Tri, uint32_t TILE, uint32_t CH, class H>
+template <uint32_t TILE, class H>
 __device__ inline void hub_chunk_run(const hub_task* __restrict__ tasks, uint32_t t0, uint32_t t1,
                                      const dyad_rec* __restrict__ dyads, const uint32_t* __restrict__ nbr,
                                      const uint64_t* __restrict__ tpre, uint64_t n, uint32_t u_lo, uint32_t u_hi,
-                                     bool per_dyad, uint32_t chunk, const hub_lds& S, const uint8_t* T, H& h, uint32_t& since) {
+                                     bool per_dyad, const hub_lds& S, const uint8_t* T, H& h, uint32_t& since) {
     const uint32_t tid = threadIdx.x, nt = t1 - t0;
     if (tid < nt) {
         const hub_task tk = tasks[t0 + tid];
@@ -1126,7 +1167,7 @@ __device__ inline void hub_chunk_run(const hub_task* __restrict__ tasks, uint32_
         S.tk[kTkGroups] = 0;
         for (uint32_t j = 0; j < nt; ++j) {
             const uint32_t r = S.tk[kTkNrec + j], l = S.tk[kTkLen + j];
-            if (j > S.tk[kTkGroups + ng] && (l > TILE || sr + r > chunk || se + l > TILE)) {
+            if (j > S.tk[kTkGroups + ng] && (l > TILE || sr + r > kHubChunk || se + l > TILE)) {
                 S.tk[kTkGroups + ++ng] = j;
                 sr = 0;
                 se = 0;
@@ -1153,24 +1194,24 @@ __device__ inline void hub_chunk_run(const hub_task* __restrict__ tasks, uint32_
             S.tk[kTkEb + M] = e;
         }
         __syncthreads();
-        hub_group_run<Tri, TILE, CH>(js, M, dyads, nbr, tpre, n, u_lo, u_hi, per_dyad, S, T, h, since);
+        hub_group_run<TILE>(js, M, dyads, nbr, tpre, n, u_lo, u_hi, per_dyad, S, T, h, since);
         __syncthreads();
     }
 }
 
-template <bool Tri, uint32_t TILE, uint32_t CH>
+template <uint32_t TILE>
 __global__ __launch_bounds__(kHubB)
-__attribute__((amdgpu_waves_per_eu(hub_waves_per_simd<TILE, CH>(), hub_waves_per_simd<TILE, CH>()))) void k_census_hub(
+__attribute__((amdgpu_waves_per_eu(hub_waves_per_simd<TILE>(), hub_waves_per_simd<TILE>()))) void k_census_hub(
     census_args L, const hub_task* __restrict__ tasks, uint32_t ntasks, uint32_t ngroups, uint32_t g0, uint32_t g1,
     unsigned int* ctr) {
-    __shared__ __attribute__((aligned(16))) uint32_t hub_words[hub_lds_words<TILE, CH>()];
+    __shared__ __attribute__((aligned(16))) uint32_t hub_words[hub_lds_words<TILE>()];
     __shared__ unsigned long long bins[block_bins<kHubB>::kWords];
     __shared__ uint8_t T[64];
     __shared__ uint32_t s_next;
     if (threadIdx.x < 64) T[threadIdx.x] = L.table[threadIdx.x];
     block_bins<kHubB> h{bins};
     h.clear();
-    const hub_lds S = hub_carve<TILE, CH>(hub_words);
+    const hub_lds S = hub_carve<TILE>(hub_words);
     hub_bins_clear(S);
     __syncthreads();
     uint32_t since = 0;
@@ -1183,19 +1224,147 @@ __attribute__((amdgpu_waves_per_eu(hub_waves_per_simd<TILE, CH>(), hub_waves_per
     while (c < g1) {
         if (threadIdx.x == 0) s_next = g0 + take_chunk(ctr, xcd);
         const uint32_t t0 = tasks[c].group, t1 = c + 1 < ngroups ? tasks[c + 1].group : ntasks;
-        hub_chunk_run<Tri, TILE, CH>(tasks, t0, t1, L.dyads, L.nbr, L.tpre, L.n, L.u_lo, L.u_hi, L.per_dyad,
-                                     L.hub_chunk, S, T, h, since);
+        hub_chunk_run<TILE>(tasks, t0, t1, L.dyads, L.nbr, L.tpre, L.n, L.u_lo, L.u_hi, L.per_dyad, S, T, h, since);
         c = s_next;
         __syncthreads();
     }
-    hub_bins_flush<Tri>(S, T, h);
+    hub_bins_flush(S, T, h);
     h.flush(acc_copy(L.acc));
 }
 
+// ------------------------------------------------------- forward lists ----
+// The four modes over the edge records (tc_tri.h).  Every workgroup counts
+// triangle signatures and turns them into class updates when it ends.
+template <bool Lab>
+__device__ inline void tri_end(tri_sig<Lab>& sig, uint32_t threads, unsigned long long* bins, const uint8_t* T,
+                               unsigned long long* acc) {
+    constexpr uint32_t kWords = tri_bins<Lab>::kWords;
+    for (uint32_t k = threadIdx.x; k < kWords; k += threads) bins[k] = 0;
+    tri_bins<Lab> h{bins};
+    tri_flush<Lab>(sig, threads, T, h);
+    unsigned long long* to = acc_copy(acc, kWords);
+    for (uint32_t k = threadIdx.x; k < kWords; k += threads)
+        if (bins[k] != 0) atomicAdd(&to[k], bins[k]);
+}
+
+template <bool Lab>
+__global__ __launch_bounds__(kLaneB) void k_tri_lane(tri_args L) {
+    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[tri_bins<Lab>::kWords];
+    __shared__ uint8_t T[64];
+    if (threadIdx.x < 64) T[threadIdx.x] = L.table[threadIdx.x];
+    tri_sig<Lab> sig{n};
+    sig.clear(kLaneB);
+    __syncthreads();
+    for (uint64_t d = (uint64_t)blockIdx.x * kLaneB + threadIdx.x; d < L.count; d += (uint64_t)gridDim.x * kLaneB)
+        lane_edge<Lab>(load_edge(L.recs + d), L.fwd, sig);
+    tri_end<Lab>(sig, kLaneB, bins, T, L.acc);
+}
+
+template <bool Lab, int TW>
+__global__ __launch_bounds__(kWaveB) void k_tri_wave(tri_args L, unsigned int* ctr) {
+    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[tri_bins<Lab>::kWords];
+    __shared__ uint8_t T[64];
+    __shared__ uint32_t sA[TW + 1], sB[TW + 1];
+    __shared__ uint32_t s_xt;
+    T[threadIdx.x] = L.table[threadIdx.x];
+    tri_sig<Lab> sig{n};
+    sig.clear(kWaveB);
+    __syncthreads();
+    const uint32_t xcd = blockIdx.x % kXcds;
+    uint32_t c = 0;
+    if (threadIdx.x == 0) c = take_chunk(ctr, xcd);
+    c = __shfl(c, 0, 64);
+    while ((uint64_t)c * kWaveChunk < L.count) {
+        uint32_t cn = 0;
+        if (threadIdx.x == 0) cn = take_chunk(ctr, xcd);      // next chunk, fetched early
+        const uint32_t end = min(L.count, (c + 1) * kWaveChunk);
+        for (uint32_t d = c * kWaveChunk; d < end; ++d) {
+            const edge_rec r = load_edge(L.recs + d);
+            merge_path<kWaveB, TW, block_sync>(r.bx, r.ex, r.by, r.ey, L.fwd, sA, sB, &s_xt, threadIdx.x,
+                                               edge_rows<Lab>{tri_sig<Lab>::code(L.fwd[r.ex]), sig});
+        }
+        c = __shfl(cn, 0, 64);
+    }
+    tri_end<Lab>(sig, kWaveB, bins, T, L.acc);
+}
+
+template <bool Lab, int B, int TW>
+__global__ __launch_bounds__(B) void k_tri_group(tri_args L, unsigned int* ctr) {
+    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[tri_bins<Lab>::kWords];
+    __shared__ uint8_t T[64];
+    __shared__ uint32_t sA[TW + 1], sB[TW + 1];
+    __shared__ uint32_t s_xt, s_next;
+    if (threadIdx.x < 64) T[threadIdx.x] = L.table[threadIdx.x];
+    tri_sig<Lab> sig{n};
+    sig.clear(B);
+    const uint32_t xcd = blockIdx.x % kXcds;
+    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
+    __syncthreads();
+    uint32_t c = s_next;
+    __syncthreads();
+    while ((uint64_t)c * kGroupChunk < L.count) {
+        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);  // next chunk, fetched early
+        const uint32_t end = min(L.count, (c + 1) * kGroupChunk);
+        for (uint32_t d = c * kGroupChunk; d < end; ++d) {
+            const edge_rec r = load_edge(L.recs + d);
+            merge_path<B, TW, block_sync>(r.bx, r.ex, r.by, r.ey, L.fwd, sA, sB, &s_xt, threadIdx.x,
+                                          edge_rows<Lab>{tri_sig<Lab>::code(L.fwd[r.ex]), sig});
+        }
+        __syncthreads();
+        c = s_next;
+        __syncthreads();
+    }
+    tri_end<Lab>(sig, B, bins, T, L.acc);
+}
+
+// Hub tasks, a wavefront each.  The first `heavy` tasks are handed out one at a
+// time, those after them (of vertices with few records) in runs of
+// kTriLightTasks, so that handing out does not bound them.
+constexpr uint32_t kTriLightTasks = 8;
+constexpr int kTriB = 256;
+constexpr uint32_t kTriWaves = kTriB / 64;
+// Wavefronts per SIMD the hub kernels are compiled for: five or six (96 or 80
+// registers) measure the same, seven spill (R-MAT 2^20: 0.89, 0.89, 0.93 ms).
+constexpr int kTriWavesPerSimd = 5;
+
+template <bool Lab>
+__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 : kTriWavesPerSimd))) void k_tri_hub(tri_args L, const tri_task* __restrict__ tasks, uint32_t ntasks,
+                                                   uint32_t heavy, unsigned int* ctr) {
+    __shared__ uint4 tab[kTriWaves][tri_table<Lab>::kWords / 4];
+    __shared__ uint32_t starts[kTriWaves][kTriSegment / 32];
+    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[tri_bins<Lab>::kWords];
+    __shared__ uint8_t T[64];
+    const uint32_t wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < 64) T[threadIdx.x] = L.table[threadIdx.x];
+    tri_sig<Lab> sig{n};
+    sig.clear(kTriB);
+    __syncthreads();
+    tri_counts cnt;
+    cnt.clear();
+    const uint32_t xcd = blockIdx.x % kXcds, waves = gridDim.x * kTriWaves;
+    uint32_t u = blockIdx.x * kTriWaves + wid;                // the first unit needs no counter
+    const uint32_t units = heavy + (ntasks - heavy + kTriLightTasks - 1) / kTriLightTasks;
+    while (u < units) {
+        uint32_t next = 0;
+        if (__lane_id() == 0) next = waves + take_chunk(ctr, xcd);    // fetched early
+        uint32_t k = u < heavy ? u : heavy + (u - heavy) * kTriLightTasks;
+        const uint32_t last = u < heavy ? u + 1 : min(k + kTriLightTasks, ntasks);
+        for (; k < last; ++k) {
+            const tri_task t = tasks[k];
+            tri_run<Lab>(L.recs, L.fwd, t.begin, t.end, t.by, t.ey, reinterpret_cast<uint32_t*>(tab[wid]), starts[wid],
+                         sig, cnt);
+        }
+        u = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
+    }
+    if constexpr (!Lab) cnt.flush(sig);
+    tri_end<Lab>(sig, kTriB, bins, T, L.acc);
+}
+
 // --------------------------------------------------------------- batch ----
-// Two persistent launches over the work items of many resident graphs: the
-// hub task groups of every graph (k_census_batch_hub, seven wavefronts per SIMD
-// like the single-graph hub kernel), then the other items (k_census_batch).  A
+// Persistent launches over the work items of many resident graphs: the hub
+// tasks of every graph's forward lists (k_tri_batch), the hub task groups of
+// the graphs that run their dyad records (k_census_batch_hub), then the other
+// items (k_census_batch).  A
 // workgroup takes items one at a time (per-XCD counters); an item is a slice
 // of one graph's bucket, over its dyad records or its forward-list edge
 // records: up to 256 lane-mode records (one per thread), up to
@@ -1212,48 +1381,35 @@ constexpr int batch_tile_words() {
     return (4 * 2 * (TW + 1) > 2 * (4 * TW + 1)) ? 4 * 2 * (TW + 1) : 2 * (4 * TW + 1);
 }
 
-template <bool Tri, int TW, class H>
-__device__ inline void batch_item(uint32_t kind, const work_item& it, const graph_desc& g, uint32_t* tiles,
-                                  uint32_t* s_xt, const uint8_t* T, H& h) {
-    const uint32_t tid = threadIdx.x, wid = tid >> 6, lane = tid & 63u;
-    const dyad_rec* recs = Tri ? g.edges : g.dyads;
-    const uint32_t* nbr = Tri ? g.fwd : g.nbr;
-    if (kind == kItemLane) {
-        const uint32_t d = it.begin + tid;
-        if (d < it.end) lane_dyad<Tri>(load_rec(recs + d), nbr, T, h);
-    } else if (kind == kItemWave) {
-        uint32_t* sA = tiles + wid * 2 * (TW + 1);
-        uint32_t* sB = sA + TW + 1;
-        for (uint32_t d = it.begin + wid; d < it.end; d += kBatchB / 64) {
-            const dyad_rec r = load_rec(recs + d);
-            merge_path<64, TW, wave_sync, Tri>(r, nbr, sA, sB, &s_xt[wid], lane, T, h);
-        }
-    } else if (kind == kItemGroup) {
-        const dyad_rec r = load_rec(recs + it.begin);
-        merge_path<kBatchB, 4 * TW, block_sync, Tri>(r, nbr, tiles, tiles + 4 * TW + 1, &s_xt[0], tid, T, h);
-    }
-}
-
-template <uint32_t TILE, uint32_t CH>
-__global__ __launch_bounds__(kHubB)
-__attribute__((amdgpu_waves_per_eu(hub_waves_per_simd<TILE, CH>(), hub_waves_per_simd<TILE, CH>()))) void
-k_census_batch_hub(
-    const graph_desc* __restrict__ G, const work_item* __restrict__ items, const uint32_t* __restrict__ nums,
-    unsigned long long* __restrict__ accs, unsigned int* __restrict__ ctr) {
-    __shared__ __attribute__((aligned(16))) uint32_t hub_words[hub_lds_words<TILE, CH>()];
-    __shared__ unsigned long long bins[block_bins<kHubB>::kWords];
+// The hub tasks of the forward lists: an item is a run of tasks of one graph,
+// which its four wavefronts take in turn.
+__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(kTriWavesPerSimd))) void k_tri_batch(const graph_desc* __restrict__ G,
+                                                     const work_item* __restrict__ items,
+                                                     const uint32_t* __restrict__ nums,
+                                                     unsigned long long* __restrict__ accs,
+                                                     unsigned int* __restrict__ ctr) {
+    __shared__ uint4 tab[kTriWaves][tri_table<false>::kWords / 4];
+    __shared__ uint32_t starts[kTriWaves][kTriSegment / 32];
+    __shared__ unsigned long long n[tri_sig<false>::kSlots], bins[kNumClasses];
     __shared__ uint8_t T[64];
     __shared__ uint32_t s_next;
+    const uint32_t wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x < 64) T[threadIdx.x] = c_table[threadIdx.x];
-    block_bins<kHubB> h{bins};
-    h.clear();
-    const hub_lds S = hub_carve<TILE, CH>(hub_words);
-    hub_bins_clear(S);
-    __syncthreads();
-    const uint32_t count = nums[0];
-    const uint32_t xcd = blockIdx.x % kXcds;
-    uint32_t cur = 0xffffffffu, since = 0;
-    bool cur_tri = false;
+    tri_sig<false> sig{n};
+    sig.clear(kTriB);
+    tri_counts cnt;
+    cnt.clear();
+    const uint32_t count = nums[0], xcd = blockIdx.x % kXcds;
+    uint32_t cur = 0xffffffffu;
+    auto flush = [&] {
+        cnt.flush(sig);
+        if (threadIdx.x < kNumClasses) bins[threadIdx.x] = 0;
+        tri_bins<false> h{bins};
+        tri_flush<false>(sig, kTriB, T, h);
+        if (threadIdx.x < kNumClasses && bins[threadIdx.x] != 0)
+            atomicAdd(&accs[(uint64_t)kNumClasses * cur + threadIdx.x], bins[threadIdx.x]);
+        __syncthreads();
+    };
     if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
     __syncthreads();
     uint32_t idx = s_next;
@@ -1262,41 +1418,95 @@ k_census_batch_hub(
         if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
         const work_item it = items[idx];
         if (it.graph != cur) {
+            if (cur != 0xffffffffu) flush();
+            cur = it.graph;
+        }
+        const graph_desc& g = G[it.graph];
+        const uint4* recs = g.edges;
+        const uint32_t* fwd = g.fwd;
+        const tri_task* tasks = g.edge_tasks;
+        for (uint32_t k = it.begin + wid; k < it.end; k += kTriWaves) {
+            const tri_task t = tasks[k];
+            tri_run<false>(recs, fwd, t.begin, t.end, t.by, t.ey, reinterpret_cast<uint32_t*>(tab[wid]), starts[wid], sig,
+                           cnt);
+        }
+        __syncthreads();
+        idx = s_next;
+        __syncthreads();
+    }
+    if (cur != 0xffffffffu) flush();
+}
+
+template <uint32_t TILE>
+__global__ __launch_bounds__(kHubB)
+__attribute__((amdgpu_waves_per_eu(hub_waves_per_simd<TILE>(), hub_waves_per_simd<TILE>()))) void
+k_census_batch_hub(
+    const graph_desc* __restrict__ G, const work_item* __restrict__ items, const uint32_t* __restrict__ nums,
+    unsigned long long* __restrict__ accs, unsigned int* __restrict__ ctr) {
+    __shared__ __attribute__((aligned(16))) uint32_t hub_words[hub_lds_words<TILE>()];
+    __shared__ unsigned long long bins[block_bins<kHubB>::kWords];
+    __shared__ uint8_t T[64];
+    __shared__ uint32_t s_next;
+    if (threadIdx.x < 64) T[threadIdx.x] = c_table[threadIdx.x];
+    block_bins<kHubB> h{bins};
+    h.clear();
+    const hub_lds S = hub_carve<TILE>(hub_words);
+    hub_bins_clear(S);
+    __syncthreads();
+    const uint32_t item0 = nums[0], count = nums[1];
+    const uint32_t xcd = blockIdx.x % kXcds;
+    uint32_t cur = 0xffffffffu, since = 0;
+    if (threadIdx.x == 0) s_next = item0 + take_chunk(ctr, xcd);
+    __syncthreads();
+    uint32_t idx = s_next;
+    __syncthreads();
+    while (idx < count) {
+        if (threadIdx.x == 0) s_next = item0 + take_chunk(ctr, xcd);
+        const work_item it = items[idx];
+        if (it.graph != cur) {
             if (cur != 0xffffffffu) {
-                if (cur_tri) hub_bins_flush<true>(S, T, h);
-                else hub_bins_flush<false>(S, T, h);
+                hub_bins_flush(S, T, h);
                 h.flush(accs + (uint64_t)kNumClasses * cur);
                 __syncthreads();
                 h.clear();
             }
             cur = it.graph;
-            cur_tri = (it.kind & kItemTri) != 0;   // one path per graph
             since = 0;
             __syncthreads();
         }
         const graph_desc g = G[it.graph];
         for (uint32_t k = it.begin; k < it.end; ++k) {
-            if (cur_tri) {
-                const uint32_t t0 = g.edge_tasks[k].group;
-                const uint32_t t1 = k + 1 < g.tri_groups ? g.edge_tasks[k + 1].group : g.tri_tasks;
-                hub_chunk_run<true, TILE, CH>(g.edge_tasks, t0, t1, g.edges, g.fwd, g.tpre, g.n, 0u, 0xffffffffu,
-                                          false, g.tri_chunk, S, T, h,
-                                          since);
-            } else {
-                const uint32_t t0 = g.hub_tasks[k].group;
-                const uint32_t t1 = k + 1 < g.hub_groups ? g.hub_tasks[k + 1].group : g.hub_ntasks;
-                hub_chunk_run<false, TILE, CH>(g.hub_tasks, t0, t1, g.dyads, g.nbr, g.tpre, g.n, 0u, 0xffffffffu,
-                                           false, g.hub_chunk, S, T, h,
-                                           since);
-            }
+            const uint32_t t0 = g.hub_tasks[k].group;
+            const uint32_t t1 = k + 1 < g.hub_groups ? g.hub_tasks[k + 1].group : g.hub_ntasks;
+            hub_chunk_run<TILE>(g.hub_tasks, t0, t1, g.dyads, g.nbr, g.tpre, g.n, 0u, 0xffffffffu, false, S, T, h, since);
         }
         idx = s_next;
         __syncthreads();
     }
     if (cur != 0xffffffffu) {
-        if (cur_tri) hub_bins_flush<true>(S, T, h);
-        else hub_bins_flush<false>(S, T, h);
+        hub_bins_flush(S, T, h);
         h.flush(accs + (uint64_t)kNumClasses * cur);
+    }
+}
+
+// One item in the wave or group mode: records [it.begin, it.end) with the
+// lists of `list`, by wavefronts in turn or one record by the workgroup.
+// rows(d, bu, eu, bv, ev) gives record d's rows and what a shared vertex means.
+template <int TW, class F>
+__device__ inline void batch_merge(bool group, const work_item& it, const uint32_t* __restrict__ list, uint32_t* tiles,
+                                   uint32_t* s_xt, F rows) {
+    const uint32_t tid = threadIdx.x, wid = tid >> 6, lane = tid & 63u;
+    uint32_t bu, eu, bv, ev;
+    if (group) {
+        auto r = rows(it.begin, bu, eu, bv, ev);
+        merge_path<kBatchB, 4 * TW, block_sync>(bu, eu, bv, ev, list, tiles, tiles + 4 * TW + 1, &s_xt[0], tid, r);
+        return;
+    }
+    uint32_t* sA = tiles + wid * 2 * (TW + 1);
+    uint32_t* sB = sA + TW + 1;
+    for (uint32_t d = it.begin + wid; d < it.end; d += kBatchB / 64) {
+        auto r = rows(d, bu, eu, bv, ev);
+        merge_path<64, TW, wave_sync>(bu, eu, bv, ev, list, sA, sB, &s_xt[wid], lane, r);
     }
 }
 
@@ -1308,16 +1518,18 @@ template <int TW>
 constexpr int batch_min_waves() { return TW <= 512 ? 7 : 1; }
 template <int TW>
 __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_min_waves<TW>()))) void k_census_batch(
-    const graph_desc* __restrict__ G, const work_item* __restrict__ items, const uint32_t* __restrict__ num_items,
+    const graph_desc* __restrict__ G, const work_item* __restrict__ items, const uint32_t* __restrict__ nums,
     unsigned long long* __restrict__ accs, unsigned int* __restrict__ ctr) {
     __shared__ __attribute__((aligned(16))) uint32_t tiles[batch_tile_words<TW>()];
-    __shared__ unsigned long long bins[wave_bins<kBatchB>::kWords];
+    __shared__ unsigned long long bins[wave_bins<kBatchB>::kWords], n[tri_sig<false>::kSlots];
     __shared__ uint8_t T[64];
     __shared__ uint32_t s_xt[kBatchB / 64], s_next;
     if (threadIdx.x < 64) T[threadIdx.x] = c_table[threadIdx.x];
     wave_bins<kBatchB> h{bins};
     h.clear();
-    const uint32_t first = num_items[0], count = num_items[1];
+    tri_sig<false> sig{n};
+    sig.clear(kBatchB);
+    const uint32_t first = nums[1], count = nums[2];
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t tid = threadIdx.x;
     uint32_t cur = 0xffffffffu;
@@ -1330,6 +1542,7 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
         const work_item it = items[idx];
         if (it.graph != cur) {
             if (cur != 0xffffffffu) {
+                tri_flush<false>(sig, kBatchB, T, h);
                 h.flush(accs + (uint64_t)kNumClasses * cur);
                 __syncthreads();
                 h.clear();
@@ -1337,7 +1550,7 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
             cur = it.graph;
             __syncthreads();
         }
-        const graph_desc g = G[it.graph];
+        const graph_desc& g = G[it.graph];
         if (it.kind == kItemRows) {
             unsigned long long rs[kRowSums] = {0, 0, 0, 0, 0, 0, 0, 0};
             if (it.begin == 0 && tid == 0) {
@@ -1346,16 +1559,48 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
             }
             for (uint32_t x = it.begin + tid; x < it.end; x += kBatchB) row_add(g.rinfo, x, rs);
             row_flush(rs, T, h);
+        } else if (it.kind & kItemTri) {
+            const uint4* recs = g.edges;
+            const uint32_t* fwd = g.fwd;
+            if ((it.kind & 3u) == kItemLane) {
+                if (it.begin + tid < it.end) lane_edge<false>(load_edge(recs + it.begin + tid), fwd, sig);
+            } else {
+                batch_merge<TW>((it.kind & 3u) == kItemGroup, it, fwd, tiles, s_xt,
+                                [&](uint32_t d, uint32_t& bu, uint32_t& eu, uint32_t& bv, uint32_t& ev) {
+                                    const edge_rec r = load_edge(recs + d);
+                                    bu = r.bx;
+                                    eu = r.ex;
+                                    bv = r.by;
+                                    ev = r.ey;
+                                    return edge_rows<false>{tri_sig<false>::code(fwd[r.ex]), sig};
+                                });
+            }
+        } else {
+            const dyad_rec* recs = g.dyads;
+            const uint32_t* nbr = g.nbr;
+            if (it.kind == kItemLane) {
+                if (it.begin + tid < it.end) lane_dyad(load_rec(recs + it.begin + tid), nbr, T, h);
+            } else {
+                dyad_rec r;
+                batch_merge<TW>(it.kind == kItemGroup, it, nbr, tiles, s_xt,
+                                [&](uint32_t d, uint32_t& bu, uint32_t& eu, uint32_t& bv, uint32_t& ev) {
+                                    r = load_rec(recs + d);
+                                    bu = r.bu;
+                                    eu = r.eu;
+                                    bv = r.bv;
+                                    ev = r.ev;
+                                    return dyad_rows<wave_bins<kBatchB>>{r, T, h};
+                                });
+            }
         }
-        else if (it.kind & kItemTri)
-            batch_item<true, TW>(it.kind & 3u, it, g, tiles, s_xt, T, h);
-        else
-            batch_item<false, TW>(it.kind, it, g, tiles, s_xt, T, h);
         __syncthreads();
         idx = s_next;
         __syncthreads();
     }
-    if (cur != 0xffffffffu) h.flush(accs + (uint64_t)kNumClasses * cur);
+    if (cur != 0xffffffffu) {
+        tri_flush<false>(sig, kBatchB, T, h);
+        h.flush(accs + (uint64_t)kNumClasses * cur);
+    }
 }
 
 __global__ void k_fill_u64_grid(unsigned long long* p, uint64_t n) {
@@ -1363,34 +1608,39 @@ __global__ void k_fill_u64_grid(unsigned long long* p, uint64_t n) {
         p[i] = 0;
 }
 
-__global__ void k_zero_u32(unsigned int* p, int n) {
-    if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+__global__ void k_zero_counters(unsigned int* p, int n) {
+    if ((int)threadIdx.x < n) p[threadIdx.x * kCounterStride] = 0;
 }
 
 // End of a census: the sums of the accumulators' copies go to `out` (pinned
 // host memory), and accumulators and work counters are zero again for the next
 // census, which so needs no clearing launches and no copy.
 constexpr int kFinishT = 512;
+template <int W>
 __global__ __launch_bounds__(kFinishT) void k_census_finish(unsigned long long* __restrict__ acc,
                                                             unsigned int* __restrict__ counters,
                                                             unsigned long long* __restrict__ out) {
-    static_assert(kFinishT == kNumClasses * kAccCopies, "one thread per accumulator");
+    static_assert(kFinishT % W == 0, "a thread's accumulators belong to one bin");
     __shared__ unsigned long long sh[kFinishT];
-    sh[threadIdx.x] = acc[threadIdx.x];
-    acc[threadIdx.x] = 0;
-    if (threadIdx.x < kBuckets * kXcds) counters[threadIdx.x] = 0;
+    unsigned long long v = 0;
+    for (int k = threadIdx.x; k < W * kAccCopies; k += kFinishT) {
+        v += acc[k];
+        acc[k] = 0;
+    }
+    sh[threadIdx.x] = v;
+    if (threadIdx.x < kBuckets * kXcds) counters[threadIdx.x * kCounterStride] = 0;
     __syncthreads();
-    if (threadIdx.x < kNumClasses) {
+    if (threadIdx.x < W) {
         unsigned long long s = 0;
-        for (int c = 0; c < kAccCopies; ++c) s += sh[kNumClasses * c + threadIdx.x];
+        for (int c = threadIdx.x; c < kFinishT; c += W) s += sh[c];
         out[threadIdx.x] = s;
     }
 }
 
-__global__ __launch_bounds__(kFinishT) void k_census_clear(unsigned long long* __restrict__ acc,
+__global__ __launch_bounds__(kFinishT) void k_census_clear(unsigned long long* __restrict__ acc, int words,
                                                            unsigned int* __restrict__ counters) {
-    acc[threadIdx.x] = 0;
-    if (threadIdx.x < kBuckets * kXcds) counters[threadIdx.x] = 0;
+    for (int k = threadIdx.x; k < words; k += kFinishT) acc[k] = 0;
+    if (threadIdx.x < kBuckets * kXcds) counters[threadIdx.x * kCounterStride] = 0;
 }
 
 }  // namespace
@@ -1408,43 +1658,35 @@ bool tile_supported(uint32_t hub_tile, uint32_t wave_tile, uint32_t group_tile, 
 namespace {
 
 template <uint32_t HT, int BT>
-void launch_batch_kernels(const graph_desc* descs, const work_item* items, const uint32_t* nums,
-                          unsigned long long* accs, unsigned int* counters, uint32_t grid, uint32_t hub_grid,
-                          uint32_t hub_chunk, hipStream_t s) {
-    if (hub_chunk <= kHubChunk / 2)
-        hipLaunchKernelGGL((k_census_batch_hub<HT, kHubChunk / 2>), dim3(hub_grid), dim3(kHubB), 0, s, descs, items,
-                           nums, accs, counters);
-    else
-        hipLaunchKernelGGL((k_census_batch_hub<HT, kHubChunk>), dim3(hub_grid), dim3(kHubB), 0, s, descs, items, nums,
-                           accs, counters);
-    hipLaunchKernelGGL(k_census_batch<BT>, dim3(grid), dim3(kBatchB), 0, s, descs, items, nums, accs,
-                       counters + kXcds);
+void launch_batch_kernels(const batch_buffers& b, hipStream_t s) {
+    if (b.tri_grid)
+        hipLaunchKernelGGL(k_tri_batch, dim3(b.tri_grid), dim3(kTriB), 0, s, b.descs, b.items, b.nums, b.accs,
+                           b.counters);
+    if (b.hub_grid)
+        hipLaunchKernelGGL((k_census_batch_hub<HT>), dim3(b.hub_grid), dim3(kHubB), 0, s, b.descs, b.items, b.nums,
+                           b.accs, b.counters + kCounterWords);
+    hipLaunchKernelGGL(k_census_batch<BT>, dim3(b.grid), dim3(kBatchB), 0, s, b.descs, b.items, b.nums, b.accs,
+                       b.counters + 2 * kCounterWords);
 }
 
 template <uint32_t HT>
-void launch_batch_bt(uint32_t bt, const graph_desc* descs, const work_item* items, const uint32_t* nums,
-                     unsigned long long* accs, unsigned int* counters, uint32_t grid, uint32_t hub_grid,
-                     uint32_t hub_chunk, hipStream_t s) {
-    if (bt == 512) launch_batch_kernels<HT, 512>(descs, items, nums, accs, counters, grid, hub_grid, hub_chunk, s);
-    else if (bt == 1024)
-        launch_batch_kernels<HT, 1024>(descs, items, nums, accs, counters, grid, hub_grid, hub_chunk, s);
-    else launch_batch_kernels<HT, 2048>(descs, items, nums, accs, counters, grid, hub_grid, hub_chunk, s);
+void launch_batch_bt(uint32_t bt, const batch_buffers& b, hipStream_t s) {
+    if (bt == 512) launch_batch_kernels<HT, 512>(b, s);
+    else if (bt == 1024) launch_batch_kernels<HT, 1024>(b, s);
+    else launch_batch_kernels<HT, 2048>(b, s);
 }
 
 }  // namespace
 
-hipError_t batch_launch(const graph_desc* descs, const work_item* items, const uint32_t* nums,
-                        unsigned long long* accs, uint64_t acc_words, unsigned int* counters, uint32_t grid,
-                        uint32_t hub_grid, uint32_t hub_tile, uint32_t batch_tile, uint32_t hub_chunk, hipStream_t s) {
+hipError_t batch_launch(const batch_buffers& b, uint64_t acc_words, uint32_t hub_tile, uint32_t batch_tile,
+                        hipStream_t s) {
     if (!tile_supported(hub_tile, 1024, 4096, 256, batch_tile)) return hipErrorInvalidValue;
     uint32_t zb = (uint32_t)std::min<uint64_t>((acc_words + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_fill_u64_grid, dim3(zb ? zb : 1), dim3(256), 0, s, accs, acc_words);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, counters, 2 * kXcds);
-    if (hub_tile == 512)
-        launch_batch_bt<512>(batch_tile, descs, items, nums, accs, counters, grid, hub_grid, hub_chunk, s);
-    else if (hub_tile == 1024)
-        launch_batch_bt<1024>(batch_tile, descs, items, nums, accs, counters, grid, hub_grid, hub_chunk, s);
-    else launch_batch_bt<2048>(batch_tile, descs, items, nums, accs, counters, grid, hub_grid, hub_chunk, s);
+    hipLaunchKernelGGL(k_fill_u64_grid, dim3(zb ? zb : 1), dim3(256), 0, s, b.accs, acc_words);
+    hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, s, b.counters, 3 * kXcds);
+    if (hub_tile == 512) launch_batch_bt<512>(batch_tile, b, s);
+    else if (hub_tile == 1024) launch_batch_bt<1024>(batch_tile, b, s);
+    else launch_batch_bt<2048>(batch_tile, b, s);
     return hipGetLastError();
 }
 
@@ -1454,84 +1696,98 @@ hipError_t census_upload_table() {
 
 namespace {
 
-template <bool Tri>
 void launch_bucket(int b, const census_args& L, uint64_t cnt, const census_config& cfg, unsigned int* counters,
                    hipStream_t s) {
     if (b == 0) {
         uint32_t grid = (uint32_t)std::min<uint64_t>((cnt + kLaneB - 1) / kLaneB, cfg.lane_blocks);
-        if (!Tri && L.per_dyad)
-            hipLaunchKernelGGL((k_census_lane<false, true>), dim3(grid), dim3(kLaneB),
+        if (L.per_dyad)
+            hipLaunchKernelGGL((k_census_lane<true>), dim3(grid), dim3(kLaneB),
                                sizeof(unsigned long long) * lane_bins<kLaneB>::kWords, s, L);
         else
-            hipLaunchKernelGGL((k_census_lane<Tri, false>), dim3(grid), dim3(kLaneB), 0, s, L);
+            hipLaunchKernelGGL((k_census_lane<false>), dim3(grid), dim3(kLaneB), 0, s, L);
     } else if (b == 1) {
         const dim3 grid((uint32_t)std::min<uint64_t>(cnt, cfg.wave_blocks));
-        unsigned int* c = counters + kXcds;
-        if (cfg.wave_tile == 512) hipLaunchKernelGGL((k_census_wave<Tri, 512>), grid, dim3(kWaveB), 0, s, L, c);
-        else if (cfg.wave_tile == 1024) hipLaunchKernelGGL((k_census_wave<Tri, 1024>), grid, dim3(kWaveB), 0, s, L, c);
-        else hipLaunchKernelGGL((k_census_wave<Tri, 2048>), grid, dim3(kWaveB), 0, s, L, c);
+        unsigned int* c = counters + kCounterWords;
+        if (cfg.wave_tile == 512) hipLaunchKernelGGL((k_census_wave<512>), grid, dim3(kWaveB), 0, s, L, c);
+        else if (cfg.wave_tile == 1024) hipLaunchKernelGGL((k_census_wave<1024>), grid, dim3(kWaveB), 0, s, L, c);
+        else hipLaunchKernelGGL((k_census_wave<2048>), grid, dim3(kWaveB), 0, s, L, c);
     } else if (b == 2) {
         const dim3 grid((uint32_t)std::min<uint64_t>(cnt, cfg.group_blocks));
-        unsigned int* c = counters + 2 * kXcds;
+        unsigned int* c = counters + 2 * kCounterWords;
         if (cfg.group_size == 256) {
-            if (cfg.group_tile == 2048) hipLaunchKernelGGL((k_census_group<Tri, 256, 2048>), grid, dim3(256), 0, s, L, c);
-            else if (cfg.group_tile == 4096) hipLaunchKernelGGL((k_census_group<Tri, 256, 4096>), grid, dim3(256), 0, s, L, c);
-            else hipLaunchKernelGGL((k_census_group<Tri, 256, 8192>), grid, dim3(256), 0, s, L, c);
+            if (cfg.group_tile == 2048) hipLaunchKernelGGL((k_census_group<256, 2048>), grid, dim3(256), 0, s, L, c);
+            else if (cfg.group_tile == 4096) hipLaunchKernelGGL((k_census_group<256, 4096>), grid, dim3(256), 0, s, L, c);
+            else hipLaunchKernelGGL((k_census_group<256, 8192>), grid, dim3(256), 0, s, L, c);
         } else {
-            if (cfg.group_tile == 2048) hipLaunchKernelGGL((k_census_group<Tri, 512, 2048>), grid, dim3(512), 0, s, L, c);
-            else if (cfg.group_tile == 4096) hipLaunchKernelGGL((k_census_group<Tri, 512, 4096>), grid, dim3(512), 0, s, L, c);
-            else hipLaunchKernelGGL((k_census_group<Tri, 512, 8192>), grid, dim3(512), 0, s, L, c);
+            if (cfg.group_tile == 2048) hipLaunchKernelGGL((k_census_group<512, 2048>), grid, dim3(512), 0, s, L, c);
+            else if (cfg.group_tile == 4096) hipLaunchKernelGGL((k_census_group<512, 4096>), grid, dim3(512), 0, s, L, c);
+            else hipLaunchKernelGGL((k_census_group<512, 8192>), grid, dim3(512), 0, s, L, c);
         }
     }
 }
 
-// Task groups [g0, g1) of the ngroups, on the instance whose LDS holds the
-// graph's groups (half-size groups: the smaller LDS).
-template <bool Tri, uint32_t CH>
-void launch_hub_ch(const census_args& L, const hub_task* tasks, uint32_t ntasks, uint32_t ngroups, uint32_t g0,
-                   uint32_t g1, const census_config& cfg, unsigned int* c, hipStream_t s) {
-    const dim3 grid((uint32_t)std::min<uint64_t>(g1 - g0, cfg.hub_blocks));
-    if (cfg.hub_tile == 512)
-        hipLaunchKernelGGL((k_census_hub<Tri, 512, CH>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
-    else if (cfg.hub_tile == 1024)
-        hipLaunchKernelGGL((k_census_hub<Tri, 1024, CH>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
-    else
-        hipLaunchKernelGGL((k_census_hub<Tri, 2048, CH>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
-}
-
-template <bool Tri>
+// Dyad task groups [g0, g1) of the ngroups.
 void launch_hub(const census_args& L, const hub_task* tasks, uint32_t ntasks, uint32_t ngroups, uint32_t g0,
                 uint32_t g1, const census_config& cfg, unsigned int* counters, hipStream_t s) {
-    unsigned int* c = counters + 3 * kXcds;
-    if (L.hub_chunk <= kHubChunk / 2)
-        launch_hub_ch<Tri, kHubChunk / 2>(L, tasks, ntasks, ngroups, g0, g1, cfg, c, s);
+    unsigned int* c = counters + 3 * kCounterWords;
+    const dim3 grid((uint32_t)std::min<uint64_t>(g1 - g0, cfg.hub_blocks));
+    if (cfg.hub_tile == 512)
+        hipLaunchKernelGGL((k_census_hub<512>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
+    else if (cfg.hub_tile == 1024)
+        hipLaunchKernelGGL((k_census_hub<1024>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
     else
-        launch_hub_ch<Tri, kHubChunk>(L, tasks, ntasks, ngroups, g0, g1, cfg, c, s);
+        hipLaunchKernelGGL((k_census_hub<2048>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
+}
+
+// Edge records of bucket b; for the hub bucket, the tasks [g0, g1).
+template <bool Lab>
+void launch_tri(int b, const tri_args& L, const rec_set<uint4, tri_task>& edges, uint32_t g0, uint32_t g1,
+                const census_config& cfg, unsigned int* counters, hipStream_t s) {
+    unsigned int* c = counters + b * kCounterWords;
+    if (b == 0) {
+        const uint32_t grid = (uint32_t)std::min<uint64_t>((L.count + kLaneB - 1) / kLaneB, cfg.lane_blocks);
+        hipLaunchKernelGGL((k_tri_lane<Lab>), dim3(grid), dim3(kLaneB), 0, s, L);
+    } else if (b == 1) {
+        const dim3 grid(std::min(L.count, cfg.wave_blocks));
+        if (cfg.wave_tile == 512) hipLaunchKernelGGL((k_tri_wave<Lab, 512>), grid, dim3(kWaveB), 0, s, L, c);
+        else if (cfg.wave_tile == 1024) hipLaunchKernelGGL((k_tri_wave<Lab, 1024>), grid, dim3(kWaveB), 0, s, L, c);
+        else hipLaunchKernelGGL((k_tri_wave<Lab, 2048>), grid, dim3(kWaveB), 0, s, L, c);
+    } else if (b == 2) {
+        const dim3 grid(std::min(L.count, cfg.group_blocks));
+        if (cfg.group_size == 256) {
+            if (cfg.group_tile == 2048) hipLaunchKernelGGL((k_tri_group<Lab, 256, 2048>), grid, dim3(256), 0, s, L, c);
+            else if (cfg.group_tile == 4096) hipLaunchKernelGGL((k_tri_group<Lab, 256, 4096>), grid, dim3(256), 0, s, L, c);
+            else hipLaunchKernelGGL((k_tri_group<Lab, 256, 8192>), grid, dim3(256), 0, s, L, c);
+        } else {
+            if (cfg.group_tile == 2048) hipLaunchKernelGGL((k_tri_group<Lab, 512, 2048>), grid, dim3(512), 0, s, L, c);
+            else if (cfg.group_tile == 4096) hipLaunchKernelGGL((k_tri_group<Lab, 512, 4096>), grid, dim3(512), 0, s, L, c);
+            else hipLaunchKernelGGL((k_tri_group<Lab, 512, 8192>), grid, dim3(512), 0, s, L, c);
+        }
+    } else {
+        const uint32_t nt = g1 - g0, heavy = std::min(nt, edges.n_heavy > g0 ? edges.n_heavy - g0 : 0u);
+        const dim3 grid(std::min((nt + kTriWaves - 1) / kTriWaves, cfg.hub_blocks));
+        hipLaunchKernelGGL((k_tri_hub<Lab>), grid, dim3(kTriB), 0, s, L, (const tri_task*)edges.tasks + g0, nt, heavy, c);
+    }
 }
 
 }  // namespace
 
-hipError_t census_clear(unsigned long long* acc, unsigned int* counters, hipStream_t s) {
-    hipLaunchKernelGGL(k_census_clear, dim3(1), dim3(kFinishT), 0, s, acc, counters);
+hipError_t census_clear(unsigned long long* acc, int words, unsigned int* counters, hipStream_t s) {
+    hipLaunchKernelGGL(k_census_clear, dim3(1), dim3(kFinishT), 0, s, acc, words, counters);
     return hipGetLastError();
 }
 
-hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tri, const uint8_t* table, bool labelled,
-                         unsigned long long* acc, unsigned int* counters, unsigned long long* out,
+hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tri, const uint8_t* table,
+                         census_kind kind, unsigned long long* acc, unsigned int* counters, unsigned long long* out,
                          const census_config& cfg, hipStream_t s, hipEvent_t* ev, hipStream_t side, hipEvent_t* fork) {
     if (!tile_supported(cfg.hub_tile, cfg.wave_tile, cfg.group_tile, cfg.group_size, 1024))
         return hipErrorInvalidValue;
-    const dyad_rec* recs = tri ? g.tri.edges.recs : g.dyads;
-    const uint32_t* nbr = tri ? g.tri.fwd : g.nbr;
-    // (the forward lists' half-size hub tasks when the graph has them)
-    const bool fine = tri && g.tri.edges.fine_tasks != nullptr;
-    const hub_task* tasks = fine ? g.tri.edges.fine_tasks : tri ? g.tri.edges.tasks : g.hub_tasks;
-    const uint32_t ntasks = fine ? g.tri.edges.fine_n_tasks : tri ? g.tri.edges.n_tasks : g.n_hub_tasks;
-    const uint32_t ngroups = fine ? g.tri.edges.fine_n_groups : tri ? g.tri.edges.n_groups : g.n_hub_groups;
+    const bool lab = tri && kind == kLabelled;
+    const uint32_t ngroups = tri ? g.tri.edges.n_tasks : g.n_hub_groups;
     const uint32_t hg0 = std::min(sl.hub_g0, ngroups), hg1 = std::max(hg0, std::min(sl.hub_g1, ngroups));
-    // The terms without intersection and the lane bucket wait on memory and
-    // the hub kernel on instruction issue: beside it, they use what it leaves
-    // (only when the hub kernel has more to stream than the graph has entries).
+    // The terms without intersection and the lane bucket wait on memory:
+    // beside the hub kernel, they use what it leaves (only when the hub kernel
+    // has more to stream than the graph has entries).
     const bool beside = tri && side != nullptr && fork != nullptr && g.tri.edges.stream > g.U;
     hipStream_t ts = s;
     if (beside) {
@@ -1543,11 +1799,15 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
     auto terms = [&] {
         if (ev) (void)hipEventRecord(ev[2 * kBuckets], ts);
         if (!sl.per_dyad && g.p > 0) {
-            if (labelled) {
+            if (kind != kClasses) {
                 const uint32_t grid = (uint32_t)std::min<uint64_t>(
                     (g.U + kTotalsPer * kLaneB - 1) / (kTotalsPer * kLaneB), beside ? cfg.side_blocks : cfg.lane_blocks);
-                hipLaunchKernelGGL(k_census_totals, dim3(grid), dim3(kLaneB), 0, ts, g.nbr, g.owner, g.rinfo, g.tpre,
-                                   (uint64_t)0, g.U, (uint64_t)g.n, table, acc);
+                if (lab)
+                    hipLaunchKernelGGL(k_census_totals<true>, dim3(grid), dim3(kLaneB), 0, ts, g.nbr, g.owner, g.rinfo,
+                                       g.tpre, g.U, (uint64_t)g.n, table, acc);
+                else
+                    hipLaunchKernelGGL(k_census_totals<false>, dim3(grid), dim3(kLaneB), 0, ts, g.nbr, g.owner, g.rinfo,
+                                       g.tpre, g.U, (uint64_t)g.n, table, acc);
             } else {
                 // (few workgroups: each ends with eight atomics)
                 const uint64_t rows = sl.row_end - sl.row_begin;
@@ -1575,17 +1835,18 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
         // beside the hub kernel, the lane bucket follows the terms on the side stream
         const hipStream_t bs = beside && b == 0 ? side : s;
         if (ev) (void)hipEventRecord(ev[2 * b], bs);
-        if (cnt > 0) {
-            census_args L{recs + sl.begin[b], (uint32_t)cnt, nbr, g.tpre, (uint64_t)g.n, acc, sl.u_lo, sl.u_hi,
-                          table, fine ? kHubChunk / 2 : tri ? g.tri.edges.chunk : g.hub_chunk, sl.per_dyad};
+        if (cnt > 0 && tri) {
+            const tri_args L{g.tri.edges.recs + (b == kBucketHub ? 0 : sl.begin[b]), (uint32_t)cnt, g.tri.fwd, acc, table};
+            if (lab) launch_tri<true>(b, L, g.tri.edges, hg0, hg1, cfg, counters, bs);
+            else launch_tri<false>(b, L, g.tri.edges, hg0, hg1, cfg, counters, bs);
+        } else if (cnt > 0) {
+            census_args L{g.dyads + sl.begin[b], (uint32_t)cnt, g.nbr, g.tpre, (uint64_t)g.n, acc, sl.u_lo, sl.u_hi,
+                          table, sl.per_dyad};
             if (b == kBucketHub) {
-                L.dyads = recs;
-                if (tri) launch_hub<true>(L, tasks, ntasks, ngroups, hg0, hg1, cfg, counters, s);
-                else launch_hub<false>(L, tasks, ntasks, ngroups, hg0, hg1, cfg, counters, s);
-            } else if (tri) {
-                launch_bucket<true>(b, L, cnt, cfg, counters, bs);
+                L.dyads = g.dyads;
+                launch_hub(L, g.hub_tasks, g.n_hub_tasks, ngroups, hg0, hg1, cfg, counters, s);
             } else {
-                launch_bucket<false>(b, L, cnt, cfg, counters, bs);
+                launch_bucket(b, L, cnt, cfg, counters, bs);
             }
         }
         if (ev) (void)hipEventRecord(ev[2 * b + 1], bs);
@@ -1595,7 +1856,8 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
         if (e == hipSuccess) e = hipStreamWaitEvent(s, fork[1], 0);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_census_finish, dim3(1), dim3(kFinishT), 0, s, acc, counters, out);
+    if (lab) hipLaunchKernelGGL(k_census_finish<64>, dim3(1), dim3(kFinishT), 0, s, acc, counters, out);
+    else hipLaunchKernelGGL(k_census_finish<kNumClasses>, dim3(1), dim3(kFinishT), 0, s, acc, counters, out);
     return hipGetLastError();
 }
 

@@ -49,14 +49,24 @@ struct hub_task {
     uint32_t begin, end, anchor, group;
 };
 constexpr uint32_t kHubChunk = 512;           // records per hub task and per group of tasks (hub kernels' LDS)
-// A forward-list hub bucket of at least this many records also gets tasks and
-// groups of kHubChunk / 2 records, which a single-graph census runs on the hub
-// kernel instance with the smaller LDS (R-MAT 2^20: the hub kernel takes 7 %
-// less time); batched launches keep the kHubChunk tasks (fewer, larger items).
+// A forward-list hub bucket of at least this many records gets tasks of
+// kHubChunk / 2 records.
 constexpr uint64_t kHubSplitRecords = 1ull << 20;
+// One of at least this many (and fewer than that) has tasks of 64 records, a
+// step of a wavefront: there are few tasks for the wavefronts of the chip.
+constexpr uint64_t kHubSmallRecords = 1ull << 13;
+// Ranks the forward-list hub kernel's table tells apart (tc_tri.h).
+constexpr uint32_t kCore = 16384;
+
+// Hub task of the forward lists: hub edge records [begin, end), whose edges
+// share the vertex with the forward list [by, ey).
+struct __attribute__((aligned(16))) tri_task {
+    uint32_t begin, end;
+    uint32_t by, ey;
+};
 constexpr uint32_t kHubTileEntries = 1024;    // anchor-row entries staged per LDS tile (default)
 constexpr uint32_t kHubGroupTasks = 8;        // consecutive hub tasks a workgroup takes at a time
-constexpr uint64_t kRowPad = 8;               // entries allocated past the end of a row array (block reads)
+constexpr uint64_t kRowPad = 16;              // entries allocated past the end of a row array (block reads)
 
 // Bucket thresholds.  Dyads with max(|N(u)|, |N(v)|) >= t_hub go to the hub
 // bucket (anchored at the larger-degree endpoint, ties to the larger id); the
@@ -144,7 +154,23 @@ struct census_args {
     unsigned long long* acc;  // kAccCopies blocks of 16 accumulators
     uint32_t u_lo, u_hi;      // hub kernel: only dyads with u in [u_lo, u_hi)
     const uint8_t* table;     // 64 bin indices (device memory), one per code
-    uint32_t hub_chunk;       // hub kernel: records per task and per group of tasks
-    bool per_dyad;            // dyad records: add each dyad's own terms (a census of part of the dyads)
+    bool per_dyad;            // add each dyad's own terms (a census of part of the dyads)
+};
+
+// Work counters: one per XCD, each on a line of its own (atomics on one line
+// are served one after the other, about 12 ns each, whichever word they add
+// to: with the eight counters side by side R-MAT 2^20's 170 k hub tasks could
+// not be handed out in less than 2 ms).
+constexpr int kXcds = 8;
+constexpr int kCounterStride = 64;                             // words
+constexpr int kCounterWords = kXcds * kCounterStride;          // of one kernel's counters
+
+// The forward-list kernels.
+struct tri_args {
+    const uint4* recs;        // edge records of the bucket slice (the whole array for the hub kernel)
+    uint32_t count;
+    const uint32_t* fwd;
+    unsigned long long* acc;  // kAccCopies blocks of 16 accumulators, 64 for the labelled census
+    const uint8_t* table;     // bins of the 64 codes
 };
 }  // namespace tc

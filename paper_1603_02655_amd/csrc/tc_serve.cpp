@@ -82,12 +82,12 @@ hipError_t slot_reserve(slot_buf& s, uint32_t graphs, uint32_t items) {
     s.cap_items = std::max<uint32_t>(items + items / 2, 4096);
     hipError_t e = hipMalloc((void**)&s.d_desc, sizeof(graph_desc) * s.cap_graphs);
     if (e == hipSuccess) e = hipMalloc((void**)&s.d_items, sizeof(work_item) * s.cap_items);
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_num, 2 * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc((void**)&s.d_num, 3 * sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&s.d_accs, sizeof(unsigned long long) * kNumClasses * s.cap_graphs);
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_ctr, sizeof(unsigned int) * 64);
+    if (e == hipSuccess) e = hipMalloc((void**)&s.d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_desc, sizeof(graph_desc) * s.cap_graphs);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_items, sizeof(work_item) * s.cap_items);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_num, 2 * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_num, 3 * sizeof(uint32_t));
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_accs, sizeof(unsigned long long) * kNumClasses * s.cap_graphs);
     if (e != hipSuccess) slot_free(s);
     return e;
@@ -99,9 +99,10 @@ uint64_t job_footprint(const serve_job& j) {
     if (!j.cold) {
         // the items append_items makes for the graph (forward-list items when it has forward lists)
         const device_graph& g = j.g->g;
-        const bool tri = g.tri.fwd_ptr != nullptr;
+        const bool tri = g.tri.fptr != nullptr;
         const uint64_t* off = tri ? g.tri.edges.off : g.bucket_off;
-        uint64_t items = (tri ? g.tri.edges.n_groups : g.n_hub_groups) + (off[3] - off[2]) +
+        uint64_t items = (tri ? (g.tri.edges.n_tasks + kBatchTasksPerItem - 1) / kBatchTasksPerItem : g.n_hub_groups) +
+                         (off[3] - off[2]) +
                          (off[2] - off[1] + kBatchWavePerItem - 1) / kBatchWavePerItem +
                          (off[1] - off[0] + kBatchLanePerItem - 1) / kBatchLanePerItem;
         items += ((uint64_t)g.n + kBatchRowsPerItem - 1) / kBatchRowsPerItem;
@@ -181,9 +182,8 @@ private:
             std::vector<int32_t>().swap(j->src);
             std::vector<int32_t>().swap(j->dst);
         }
-        std::vector<work_item> items, rest;
+        item_lists lists;
         std::vector<graph_desc> descs(jobs.size());
-        uint32_t hub_chunk = 0;
         for (size_t i = 0; i < jobs.size(); ++i) {
             serve_job* j = static_cast<serve_job*>(jobs[i]);
             if (j->status != TC_OK) {
@@ -192,33 +192,30 @@ private:
             }
             const device_graph& g = j->cold ? j->built : j->g->g;
             descs[i] = describe(g);
-            const bool tri = tun.tri && g.tri.fwd_ptr;
-            append_items(g, (uint32_t)i, tri, items, rest);
-            hub_chunk = std::max(hub_chunk, tri ? g.tri.edges.chunk : g.hub_chunk);
+            append_items(g, (uint32_t)i, tun.tri && g.tri.fptr, lists);
         }
-        const uint32_t n_hub = (uint32_t)items.size();
-        items.insert(items.end(), rest.begin(), rest.end());     // hub items first
+        uint32_t nums[3];
+        const std::vector<work_item>& items = lists.join(nums);
         hipError_t e = slot_reserve(s, (uint32_t)jobs.size(), (uint32_t)items.size());
         if (e == hipSuccess) {
             std::memcpy(s.h_desc, descs.data(), sizeof(graph_desc) * descs.size());
             if (!items.empty()) std::memcpy(s.h_items, items.data(), sizeof(work_item) * items.size());
-            s.h_num[0] = n_hub;
-            s.h_num[1] = (uint32_t)items.size();
+            std::memcpy(s.h_num, nums, sizeof(nums));
             e = hipMemcpyAsync(s.d_desc, s.h_desc, sizeof(graph_desc) * descs.size(), hipMemcpyHostToDevice,
                                s.stream);
             if (e == hipSuccess && !items.empty())
                 e = hipMemcpyAsync(s.d_items, s.h_items, sizeof(work_item) * items.size(), hipMemcpyHostToDevice,
                                    s.stream);
             if (e == hipSuccess)
-                e = hipMemcpyAsync(s.d_num, s.h_num, 2 * sizeof(uint32_t), hipMemcpyHostToDevice, s.stream);
+                e = hipMemcpyAsync(s.d_num, s.h_num, 3 * sizeof(uint32_t), hipMemcpyHostToDevice, s.stream);
             // grids no larger than the round's items, so that small rounds
             // leave the rest of the GPU to the rounds beside them
-            const uint32_t n_rest = (uint32_t)items.size() - n_hub;
-            const uint32_t grid = std::max<uint32_t>(1u, std::min<uint32_t>(tun.batch_blocks, n_rest));
-            const uint32_t hub_grid = std::max<uint32_t>(1u, std::min<uint32_t>(tun.hub_blocks, n_hub));
+            batch_buffers bb{s.d_desc, s.d_items, s.d_num, s.d_accs, s.d_ctr, 0, 0, 0};
+            bb.tri_grid = std::min<uint32_t>(tun.hub_blocks, nums[0]);
+            bb.hub_grid = std::min<uint32_t>(tun.hub_blocks, nums[1] - nums[0]);
+            bb.grid = std::max<uint32_t>(1u, std::min<uint32_t>(tun.batch_blocks, nums[2] - nums[1]));
             if (e == hipSuccess)
-                e = batch_launch(s.d_desc, s.d_items, s.d_num, s.d_accs, (uint64_t)kNumClasses * jobs.size(),
-                                 s.d_ctr, grid, hub_grid, tun.hub_tile, tun.batch_tile, hub_chunk, s.stream);
+                e = batch_launch(bb, (uint64_t)kNumClasses * jobs.size(), tun.hub_tile, tun.batch_tile, s.stream);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(s.h_accs, s.d_accs, sizeof(unsigned long long) * kNumClasses * jobs.size(),
                                    hipMemcpyDeviceToHost, s.stream);
