@@ -1,7 +1,7 @@
 // Batched census over many resident graphs: one persistent kernel launch over
 // a work-item list (graph, execution mode, dyad range), captured once into a
-// HIP graph (zero accumulators -> persistent kernel -> 16 counts per graph back
-// to pinned host memory) and replayed.  Descriptors and items live in device
+// HIP graph (zero accumulators -> persistent kernels -> 16 counts per graph to
+// pinned host memory) and replayed.  Descriptors and items live in device
 // buffers read by the kernel, so another set of graphs that fits the captured
 // capacities is served by rewriting those buffers and replaying; the capture is
 // redone only when a capacity grows.
@@ -130,7 +130,7 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
     hipError_t e = hipMalloc((void**)&p->d_desc, sizeof(graph_desc) * p->cap_graphs);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_items, sizeof(work_item) * p->cap_items);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_num, 3 * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs);
+    if (e == hipSuccess) e = hipMalloc((void**)&p->d_accs, sizeof(unsigned long long) * kBatchAccWords * p->cap_graphs);
     if (e == hipSuccess) e = hipMalloc((void**)&p->d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&p->h_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs);
@@ -138,16 +138,14 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
         p->release();
         return e;
     }
-    // capture: zero accumulators and counters, persistent kernel, read-back
+    // capture: zero accumulators and counters, persistent kernels, sums to host memory
     e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
-    const batch_buffers bb{p->d_desc, p->d_items, p->d_num, p->d_accs, p->d_ctr, p->tri_grid, p->hub_grid, p->grid};
-    hipError_t el = batch_launch(bb, (uint64_t)kNumClasses * p->cap_graphs, p->hub_tile, p->batch_tile, s);
-    hipError_t ec = hipMemcpyAsync(p->h_accs, p->d_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs,
-                                   hipMemcpyDeviceToHost, s);
+    const batch_buffers bb{p->d_desc, p->d_items, p->d_num, p->d_accs, p->d_ctr, p->tri_grid, p->hub_grid, p->grid,
+                           p->cap_graphs, p->h_accs};
+    hipError_t el = batch_launch(bb, p->hub_tile, p->batch_tile, s);
     e = hipStreamEndCapture(s, &p->graph);
     if (el != hipSuccess) e = el;
-    if (ec != hipSuccess) e = ec;
     if (e == hipSuccess) e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
     if (e != hipSuccess) p->release();
     return e;

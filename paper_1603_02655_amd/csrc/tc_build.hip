@@ -716,7 +716,7 @@ __global__ __launch_bounds__(kT) void k_fwd_emit(const uint64_t* __restrict__ ke
 // forward lists reaches t_hub, else by their joint length; kBuckets for an
 // edge that closes no triangle with a smaller rank.
 struct edge_at {
-    uint32_t bx, by, ey, y, pos;
+    uint32_t bx, by, dy, y, pos, bits;
     uint64_t cost;
     int bucket;
 };
@@ -732,8 +732,9 @@ __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_
     r.pos = (uint32_t)i - r.bx;
     if (r.pos == 0) return r;
     r.by = fptr[r.y];
-    r.ey = fptr[r.y + 1];
-    const uint64_t dx = fptr[x + 1] - r.bx, dy = r.ey - r.by;
+    r.dy = fptr[r.y + 1] - r.by;
+    r.bits = (uint32_t)(k & 7u);
+    const uint64_t dx = fptr[x + 1] - r.bx, dy = r.dy;
     if (dy == 0) return r;
     r.cost = dx + dy;
     r.bucket = (dx > dy ? dx : dy) >= bp.t_hub ? kBucketHub : r.cost < bp.t0 ? 0 : r.cost < bp.t1 ? 1 : 2;
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(kT) void k_edge_scatter(const uint64_t* __restrict_
             if (r[k].bucket == q) {
                 const uint64_t to = at[q] + (uint32_t)__popcll(m & lanemask_lt());
                 if (q == kBucketHub) hubkeys[to - hub_begin] = ((uint64_t)r[k].y << 32) | i;
-                else out[to] = make_uint4(r[k].bx, (uint32_t)i, r[k].by, r[k].ey);
+                else out[to] = make_uint4(r[k].bx, (uint32_t)i, r[k].by, (r[k].bits << 29) | r[k].dy);
             }
             at[q] += (uint32_t)__popcll(m);
         }

@@ -1281,7 +1281,7 @@ __global__ __launch_bounds__(kWaveB) void k_tri_wave(tri_args L, unsigned int* c
         for (uint32_t d = c * kWaveChunk; d < end; ++d) {
             const edge_rec r = load_edge(L.recs + d);
             merge_path<kWaveB, TW, block_sync>(r.bx, r.ex, r.by, r.ey, L.fwd, sA, sB, &s_xt, threadIdx.x,
-                                               edge_rows<Lab>{tri_sig<Lab>::code(L.fwd[r.ex]), sig});
+                                               edge_rows<Lab>{r.code<Lab>(), sig});
         }
         c = __shfl(cn, 0, 64);
     }
@@ -1308,7 +1308,7 @@ __global__ __launch_bounds__(B) void k_tri_group(tri_args L, unsigned int* ctr) 
         for (uint32_t d = c * kGroupChunk; d < end; ++d) {
             const edge_rec r = load_edge(L.recs + d);
             merge_path<B, TW, block_sync>(r.bx, r.ex, r.by, r.ey, L.fwd, sA, sB, &s_xt, threadIdx.x,
-                                          edge_rows<Lab>{tri_sig<Lab>::code(L.fwd[r.ex]), sig});
+                                          edge_rows<Lab>{r.code<Lab>(), sig});
         }
         __syncthreads();
         c = s_next;
@@ -1381,6 +1381,13 @@ constexpr int batch_tile_words() {
     return (4 * 2 * (TW + 1) > 2 * (4 * TW + 1)) ? 4 * 2 * (TW + 1) : 2 * (4 * TW + 1);
 }
 
+// The copy of a graph's accumulators this workgroup adds to.  A workgroup adds
+// its sums whenever it moves on to another graph, and the workgroups at one
+// graph are many (13 atomics each on one line, about 12 ns apiece).
+__device__ inline unsigned long long* batch_acc(unsigned long long* accs, uint32_t graph) {
+    return accs + (uint64_t)kNumClasses * ((uint64_t)kBatchCopies * graph + blockIdx.x % kBatchCopies);
+}
+
 // The hub tasks of the forward lists: an item is a run of tasks of one graph,
 // which its four wavefronts take in turn.
 __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(kTriWavesPerSimd))) void k_tri_batch(const graph_desc* __restrict__ G,
@@ -1407,7 +1414,7 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(kTriWaves
         tri_bins<false> h{bins};
         tri_flush<false>(sig, kTriB, T, h);
         if (threadIdx.x < kNumClasses && bins[threadIdx.x] != 0)
-            atomicAdd(&accs[(uint64_t)kNumClasses * cur + threadIdx.x], bins[threadIdx.x]);
+            atomicAdd(&batch_acc(accs, cur)[threadIdx.x], bins[threadIdx.x]);
         __syncthreads();
     };
     if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
@@ -1466,7 +1473,7 @@ k_census_batch_hub(
         if (it.graph != cur) {
             if (cur != 0xffffffffu) {
                 hub_bins_flush(S, T, h);
-                h.flush(accs + (uint64_t)kNumClasses * cur);
+                h.flush(batch_acc(accs, cur));
                 __syncthreads();
                 h.clear();
             }
@@ -1485,7 +1492,7 @@ k_census_batch_hub(
     }
     if (cur != 0xffffffffu) {
         hub_bins_flush(S, T, h);
-        h.flush(accs + (uint64_t)kNumClasses * cur);
+        h.flush(batch_acc(accs, cur));
     }
 }
 
@@ -1543,7 +1550,7 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
         if (it.graph != cur) {
             if (cur != 0xffffffffu) {
                 tri_flush<false>(sig, kBatchB, T, h);
-                h.flush(accs + (uint64_t)kNumClasses * cur);
+                h.flush(batch_acc(accs, cur));
                 __syncthreads();
                 h.clear();
             }
@@ -1572,7 +1579,7 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
                                     eu = r.ex;
                                     bv = r.by;
                                     ev = r.ey;
-                                    return edge_rows<false>{tri_sig<false>::code(fwd[r.ex]), sig};
+                                    return edge_rows<false>{r.code<false>(), sig};
                                 });
             }
         } else {
@@ -1599,8 +1606,19 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
     }
     if (cur != 0xffffffffu) {
         tri_flush<false>(sig, kBatchB, T, h);
-        h.flush(accs + (uint64_t)kNumClasses * cur);
+        h.flush(batch_acc(accs, cur));
     }
+}
+
+// The sums of every graph's copies, to pinned host memory.
+__global__ __launch_bounds__(256) void k_batch_finish(const unsigned long long* __restrict__ accs, uint32_t graphs,
+                                                      unsigned long long* __restrict__ out) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x, graph = i / kNumClasses, cls = i % kNumClasses;
+    if (graph >= graphs) return;
+    unsigned long long s = 0;
+    for (uint32_t c = 0; c < kBatchCopies; ++c)
+        s += accs[(uint64_t)kNumClasses * ((uint64_t)kBatchCopies * graph + c) + cls];
+    out[i] = s;
 }
 
 __global__ void k_fill_u64_grid(unsigned long long* p, uint64_t n) {
@@ -1667,6 +1685,8 @@ void launch_batch_kernels(const batch_buffers& b, hipStream_t s) {
                            b.accs, b.counters + kCounterWords);
     hipLaunchKernelGGL(k_census_batch<BT>, dim3(b.grid), dim3(kBatchB), 0, s, b.descs, b.items, b.nums, b.accs,
                        b.counters + 2 * kCounterWords);
+    hipLaunchKernelGGL(k_batch_finish, dim3((b.graphs * kNumClasses + 255) / 256), dim3(256), 0, s, b.accs, b.graphs,
+                       b.out);
 }
 
 template <uint32_t HT>
@@ -1678,9 +1698,9 @@ void launch_batch_bt(uint32_t bt, const batch_buffers& b, hipStream_t s) {
 
 }  // namespace
 
-hipError_t batch_launch(const batch_buffers& b, uint64_t acc_words, uint32_t hub_tile, uint32_t batch_tile,
-                        hipStream_t s) {
-    if (!tile_supported(hub_tile, 1024, 4096, 256, batch_tile)) return hipErrorInvalidValue;
+hipError_t batch_launch(const batch_buffers& b, uint32_t hub_tile, uint32_t batch_tile, hipStream_t s) {
+    if (!tile_supported(hub_tile, 1024, 4096, 256, batch_tile) || b.graphs == 0) return hipErrorInvalidValue;
+    const uint64_t acc_words = kBatchAccWords * b.graphs;
     uint32_t zb = (uint32_t)std::min<uint64_t>((acc_words + 255) / 256, 1024);
     hipLaunchKernelGGL(k_fill_u64_grid, dim3(zb ? zb : 1), dim3(256), 0, s, b.accs, acc_words);
     hipLaunchKernelGGL(k_zero_counters, dim3(1), dim3(64), 0, s, b.counters, 3 * kXcds);

@@ -83,7 +83,7 @@ hipError_t slot_reserve(slot_buf& s, uint32_t graphs, uint32_t items) {
     hipError_t e = hipMalloc((void**)&s.d_desc, sizeof(graph_desc) * s.cap_graphs);
     if (e == hipSuccess) e = hipMalloc((void**)&s.d_items, sizeof(work_item) * s.cap_items);
     if (e == hipSuccess) e = hipMalloc((void**)&s.d_num, 3 * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_accs, sizeof(unsigned long long) * kNumClasses * s.cap_graphs);
+    if (e == hipSuccess) e = hipMalloc((void**)&s.d_accs, sizeof(unsigned long long) * kBatchAccWords * s.cap_graphs);
     if (e == hipSuccess) e = hipMalloc((void**)&s.d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_desc, sizeof(graph_desc) * s.cap_graphs);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_items, sizeof(work_item) * s.cap_items);
@@ -95,7 +95,7 @@ hipError_t slot_reserve(slot_buf& s, uint32_t graphs, uint32_t items) {
 
 // Bytes a job holds on the device while it is in flight.
 uint64_t job_footprint(const serve_job& j) {
-    uint64_t ws = sizeof(unsigned long long) * kNumClasses + sizeof(graph_desc);
+    uint64_t ws = sizeof(unsigned long long) * kBatchAccWords + sizeof(graph_desc);
     if (!j.cold) {
         // the items append_items makes for the graph (forward-list items when it has forward lists)
         const device_graph& g = j.g->g;
@@ -210,15 +210,12 @@ private:
                 e = hipMemcpyAsync(s.d_num, s.h_num, 3 * sizeof(uint32_t), hipMemcpyHostToDevice, s.stream);
             // grids no larger than the round's items, so that small rounds
             // leave the rest of the GPU to the rounds beside them
-            batch_buffers bb{s.d_desc, s.d_items, s.d_num, s.d_accs, s.d_ctr, 0, 0, 0};
+            batch_buffers bb{s.d_desc, s.d_items, s.d_num, s.d_accs, s.d_ctr, 0, 0, 0, (uint32_t)jobs.size(), s.h_accs};
             bb.tri_grid = std::min<uint32_t>(tun.hub_blocks, nums[0]);
             bb.hub_grid = std::min<uint32_t>(tun.hub_blocks, nums[1] - nums[0]);
             bb.grid = std::max<uint32_t>(1u, std::min<uint32_t>(tun.batch_blocks, nums[2] - nums[1]));
             if (e == hipSuccess)
-                e = batch_launch(bb, (uint64_t)kNumClasses * jobs.size(), tun.hub_tile, tun.batch_tile, s.stream);
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(s.h_accs, s.d_accs, sizeof(unsigned long long) * kNumClasses * jobs.size(),
-                                   hipMemcpyDeviceToHost, s.stream);
+                e = batch_launch(bb, tun.hub_tile, tun.batch_tile, s.stream);
             if (e == hipSuccess) e = hipLaunchHostFunc(s.stream, on_round_done, new cb_arg{this, si});
         }
         if (e != hipSuccess) {
