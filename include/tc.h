@@ -107,7 +107,7 @@ typedef struct {
  * identical either way.  The batched and the served modes take the same path
  * per graph (forward-list items for graphs that have forward lists while tri
  * is set, dyad-record items otherwise; requests that carry their arcs are built
- * without forward lists).  tc_census_range always uses the dyad records. */
+ * for that one path).  tc_census_range always uses the dyad records. */
 typedef struct {
     uint32_t t0, t1;
     uint32_t lane_blocks;    /* grid cap, lane kernel (256-thread blocks) */

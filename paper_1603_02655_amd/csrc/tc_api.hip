@@ -51,7 +51,7 @@ census_config config_of(const tc_tuning& t) {
     return c;
 }
 
-bucket_params params_of(const tc_tuning& t) { return bucket_params{t.t0, t.t1, t.t_hub, t.tri, t.hub_tile}; }
+bucket_params params_of(const tc_tuning& t) { return bucket_params{t.t0, t.t1, t.t_hub, t.tri, t.hub_tile, 1}; }
 
 tc_tuning tuning_snapshot(tc_context_s* ctx) {
     std::lock_guard<std::mutex> lk(ctx->tuning_mu);

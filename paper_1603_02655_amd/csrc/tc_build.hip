@@ -11,6 +11,7 @@
 #include "tc_build.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <thread>
 
@@ -180,18 +181,20 @@ __global__ __launch_bounds__(kT) void k_canon(const int32_t* __restrict__ src, c
 constexpr int kDigitBits = 9;
 constexpr int kDigits = 1 << kDigitBits;
 constexpr int kSortI = 16;                  // keys per thread
-constexpr int kSortTile = kT * kSortI;      // keys per workgroup
+constexpr int kSortISmall = 4;              // ... below kSortSmall keys: four times the workgroups, a quarter
+constexpr uint64_t kSortSmall = 1ull << 21; // of the serial rounds (20 k keys: 16 us a pass less 5)
 constexpr int kSortWaves = kT / 64;
 
-// O: 32-bit key positions, or 64-bit for 2^32 keys or more.
-template <class O>
+// O: 32-bit key positions, or 64-bit for 2^32 keys or more.  I: keys per thread.
+template <class O, int I>
 __global__ __launch_bounds__(kT) void k_radix_hist(const uint64_t* __restrict__ keys, uint64_t count, uint32_t shift,
                                                     uint32_t nbins, O* __restrict__ hist, uint32_t nblocks) {
     __shared__ uint32_t h[kDigits];
     for (uint32_t d = threadIdx.x; d < nbins; d += kT) h[d] = 0;
     __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-    for (int k = 0; k < kSortI; ++k) {
+    const uint64_t base = (uint64_t)blockIdx.x * (kT * I);
+#pragma unroll
+    for (int k = 0; k < I; ++k) {
         const uint64_t i = base + (uint64_t)k * kT + threadIdx.x;
         if (i < count) atomicAdd(&h[(keys[i] >> shift) & (nbins - 1)], 1u);
     }
@@ -203,30 +206,31 @@ __global__ __launch_bounds__(kT) void k_radix_hist(const uint64_t* __restrict__ 
 // consecutive ones per round; the rank of a key among the equal digits before
 // it in its wavefront comes from ballots, those of earlier wavefronts from the
 // wavefronts' digit counts.
-template <class O>
+template <class O, int I>
 __global__ __launch_bounds__(kT) void k_radix_scatter(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
                                                        uint64_t count, uint32_t shift, uint32_t dbits,
                                                        const O* __restrict__ offsets, uint32_t nblocks) {
-    __shared__ uint64_t stage[kSortTile];
+    constexpr int kKeys = kT * I;
+    __shared__ uint64_t stage[kKeys];
     __shared__ uint16_t wcnt[kSortWaves][kDigits];
     __shared__ O to_out[kDigits];            // global offset of the digit's run minus its start in the tile
     __shared__ uint64_t wsum[kT / 64];
     const uint32_t nbins = 1u << dbits, lane = __lane_id(), wid = threadIdx.x >> 6;
-    const uint64_t base = (uint64_t)blockIdx.x * kSortTile;
-    const uint32_t here = (uint32_t)(count - base < (uint64_t)kSortTile ? count - base : (uint64_t)kSortTile);
+    const uint64_t base = (uint64_t)blockIdx.x * kKeys;
+    const uint32_t here = (uint32_t)(count - base < (uint64_t)kKeys ? count - base : (uint64_t)kKeys);
     for (uint32_t d = threadIdx.x; d < nbins; d += kT)
         for (int w = 0; w < kSortWaves; ++w) wcnt[w][d] = 0;
     __syncthreads();
-    uint64_t key[kSortI];
-    uint32_t pos[kSortI];    // rank inside the wavefront's equal digits
+    uint64_t key[I];
+    uint32_t pos[I];    // rank inside the wavefront's equal digits
 #pragma unroll
-    for (int r = 0; r < kSortI; ++r) {
-        const uint32_t i = wid * 64 * kSortI + (uint32_t)r * 64 + lane;
+    for (int r = 0; r < I; ++r) {
+        const uint32_t i = wid * 64 * I + (uint32_t)r * 64 + lane;
         key[r] = i < here ? in[base + i] : 0;
     }
 #pragma unroll
-    for (int r = 0; r < kSortI; ++r) {
-        const uint32_t i = wid * 64 * kSortI + (uint32_t)r * 64 + lane;
+    for (int r = 0; r < I; ++r) {
+        const uint32_t i = wid * 64 * I + (uint32_t)r * 64 + lane;
         const bool valid = i < here;
         const uint32_t dg = (uint32_t)(key[r] >> shift) & (nbins - 1);
         uint64_t peers = __ballot(valid);
@@ -269,14 +273,14 @@ __global__ __launch_bounds__(kT) void k_radix_scatter(const uint64_t* __restrict
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kSortI; ++r) {
-        const uint32_t i = wid * 64 * kSortI + (uint32_t)r * 64 + lane;
+    for (int r = 0; r < I; ++r) {
+        const uint32_t i = wid * 64 * I + (uint32_t)r * 64 + lane;
         const uint32_t dg = (uint32_t)(key[r] >> shift) & (nbins - 1);
         if (i < here) stage[wcnt[wid][dg] + pos[r]] = key[r];
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < kSortI; ++k) {
+    for (int k = 0; k < I; ++k) {
         const uint32_t i = (uint32_t)k * kT + threadIdx.x;
         if (i < here) {
             const uint64_t x = stage[i];
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(kT) void k_runs_emit(const uint64_t* __restrict__ k
 // 0.05 ms for both).
 __global__ __launch_bounds__(kT) void k_row_info(const int64_t* __restrict__ row_ptr, int32_t n,
                                                  const uint64_t* __restrict__ tpre, uint4* __restrict__ rinfo,
-                                                 uint32_t* __restrict__ deg,
+                                                 uint32_t* __restrict__ deg, uint2* __restrict__ rows,
                                                  unsigned long long* __restrict__ counters) {
     __shared__ unsigned long long sh[kT / 64], shm[kT / 64];
     unsigned long long sq = 0, mx = 0;
@@ -466,6 +470,7 @@ __global__ __launch_bounds__(kT) void k_row_info(const int64_t* __restrict__ row
         rinfo[x] = make_uint4((uint32_t)rb, (uint32_t)re, (uint32_t)t, (uint32_t)(t >> 32));
         const unsigned long long d = re - rb;
         deg[x] = (uint32_t)d;
+        rows[x] = make_uint2((uint32_t)rb, (uint32_t)d);
         sq += d * d;
         mx = d > mx ? d : mx;
     }
@@ -489,21 +494,22 @@ __global__ __launch_bounds__(kT) void k_row_info(const int64_t* __restrict__ row
 // larger degree, ties to the larger id), so the hub bucket is anchor-major;
 // any other pair is emitted from the row of its smaller id (u-major) into the
 // lane / wave / group bucket by k = |N(u)| + |N(v)| - 2.
-// Bucket of neighbour entry e: the dyad is emitted once, from its first
-// vertex, or from its anchor in the hub bucket.
-// `len` holds the rows' lengths (one 4-byte gather per entry).
-__device__ inline int rec_bucket(const uint32_t* nbr, const uint32_t* owner, const uint32_t* len,
-                                 uint64_t e, uint64_t U, const bucket_params& bp, uint64_t* cost,
-                                 uint64_t* stream, uint32_t* anchor) {
-    if (e >= U) return kBuckets;
-    const uint32_t o = owner[e], w = nbr[e] >> 2;
-    const uint64_t d_o = len[o], d_w = len[w];
+// Bucket of the neighbour entry (o, w): the dyad is emitted once, from its
+// first vertex, or from its anchor in the hub bucket.  The other row's length
+// is looked up only where the entry can be the emitting one: an entry below the
+// diagonal emits only as the anchor of a hub dyad, and so not from a row
+// shorter than t_hub (citation graph: half of the look-ups).
+// len_of(w): the length of row w.
+template <class F>
+__device__ inline int rec_bucket(uint32_t o, uint32_t w, uint32_t d_o, const bucket_params& bp, F len_of,
+                                 uint64_t* cost, uint64_t* stream) {
+    if (o > w && d_o < bp.t_hub) return kBuckets;
+    const uint64_t d_w = len_of(w);
     *cost = d_o + d_w;
     if ((d_o > d_w ? d_o : d_w) >= bp.t_hub) {
         const bool o_anchor = d_o > d_w || (d_o == d_w && o > w);
         if (!o_anchor) return kBuckets;
         *stream = d_w;
-        *anchor = o;
         return kBucketHub;
     }
     if (!(o < w)) return kBuckets;
@@ -539,7 +545,7 @@ __device__ inline void store_tile_sums(const uint32_t (&my)[kBuckets], const uns
 __global__ __launch_bounds__(kT) void k_dyad_count(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
                                                     const uint32_t* __restrict__ len, uint64_t U, bucket_params bp,
                                                     uint64_t* __restrict__ counts, uint32_t nblocks,
-                                                    uint64_t* __restrict__ part) {
+                                                    uint64_t* __restrict__ part, uint8_t* __restrict__ bucket) {
     __shared__ unsigned long long sh[kT / 64];
     uint64_t base = (uint64_t)blockIdx.x * kTile;
     uint32_t my[kBuckets] = {0, 0, 0, 0}, mut = 0;
@@ -547,15 +553,21 @@ __global__ __launch_bounds__(kT) void k_dyad_count(const uint32_t* __restrict__ 
     for (int k = 0; k < kI; ++k) {
         uint64_t e = base + (uint64_t)k * kT + threadIdx.x;
         uint64_t cost = 0, stream = 0;
-        uint32_t anchor = 0;
-        const int b = rec_bucket(nbr, owner, len, e, U, bp, &cost, &stream, &anchor);
+        int b = kBuckets;
+        uint32_t ent = 0;
+        if (e < U) {
+            ent = nbr[e];
+            const uint32_t o = owner[e];
+            b = rec_bucket(o, ent >> 2, len[o], bp, [&](uint32_t w) { return len[w]; }, &cost, &stream);
+            bucket[e] = (uint8_t)b;
+        }
 #pragma unroll
         for (int q = 0; q < kBuckets; ++q) {
             my[q] += b == q ? 1u : 0u;
             mycost[q] += b == q ? cost : 0ull;
         }
         if (b < kBuckets) {
-            mut += ((nbr[e] & 3u) == 3u) ? 1u : 0u;
+            mut += ((ent & 3u) == 3u) ? 1u : 0u;
             if (b == kBucketHub) mystream += stream;
         }
     }
@@ -582,58 +594,61 @@ __global__ __launch_bounds__(kT) void k_bucket_sums(const uint64_t* __restrict__
 // Writes the records in entry order through a stable per-bucket ranking:
 // lane / wave / group records are u-major, and hub records, which come from
 // their anchor's row, anchor-major.
+// Every wavefront holds 64 * kI consecutive entries, 64 per round, so that
+// ranks are ballots and lane counts and one barrier per tile is enough.  The
+// buckets come from the counting pass, so that a row is looked up only for a
+// record.
 __global__ __launch_bounds__(kT) void k_dyad_scatter(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
-                                                      const int64_t* __restrict__ row_ptr,
-                                                      const uint32_t* __restrict__ len, uint64_t U, bucket_params bp,
+                                                      const uint2* __restrict__ rows, uint64_t U,
+                                                      const uint8_t* __restrict__ bucket,
                                                       const uint64_t* __restrict__ offsets, uint32_t nblocks,
                                                       uint64_t hub_begin, uint32_t* __restrict__ anchors,
                                                       dyad_rec* __restrict__ out) {
-    __shared__ uint32_t running[kBuckets];
     __shared__ uint32_t wcnt[kT / 64][kBuckets];
-    __shared__ uint64_t goff[kBuckets];
-    const int wid = threadIdx.x >> 6;
-    if (threadIdx.x < kBuckets) {
-        running[threadIdx.x] = 0;
-        goff[threadIdx.x] = offsets[(uint64_t)threadIdx.x * nblocks + blockIdx.x];
+    const uint32_t lane = __lane_id(), wid = threadIdx.x >> 6;
+    const uint64_t base = (uint64_t)blockIdx.x * kTile + wid * 64 * kI;
+    uint32_t mine[kBuckets] = {0, 0, 0, 0};
+    int b[kI];
+#pragma unroll
+    for (int k = 0; k < kI; ++k) {
+        const uint64_t e = base + k * 64 + lane;
+        b[k] = e < U ? (int)bucket[e] : kBuckets;
+#pragma unroll
+        for (int q = 0; q < kBuckets; ++q) mine[q] += (uint32_t)__popcll(__ballot(b[k] == q));
     }
+    if (lane == 0)
+        for (int q = 0; q < kBuckets; ++q) wcnt[wid][q] = mine[q];
     __syncthreads();
-    uint64_t base = (uint64_t)blockIdx.x * kTile;
-    for (int r = 0; r < kI; ++r) {
-        uint64_t e = base + (uint64_t)r * kT + threadIdx.x;
-        uint64_t cost = 0, stream = 0;
-        uint32_t anchor = 0;
-        int b = rec_bucket(nbr, owner, len, e, U, bp, &cost, &stream, &anchor);
-        uint32_t rank = 0;
+    uint64_t at[kBuckets];
+#pragma unroll
+    for (int q = 0; q < kBuckets; ++q) {
+        at[q] = offsets[(uint64_t)q * nblocks + blockIdx.x];
+        for (uint32_t w = 0; w < wid; ++w) at[q] += wcnt[w][q];
+    }
+#pragma unroll
+    for (int k = 0; k < kI; ++k) {
+        uint64_t to = 0;
+#pragma unroll
         for (int q = 0; q < kBuckets; ++q) {
-            uint64_t mask = __ballot(b == q);
-            if (b == q) rank = (uint32_t)__popcll(mask & lanemask_lt());
-            if (__lane_id() == 0) wcnt[wid][q] = (uint32_t)__popcll(mask);
+            const uint64_t m = __ballot(b[k] == q);
+            if (b[k] == q) to = at[q] + (uint32_t)__popcll(m & lanemask_lt());
+            at[q] += (uint32_t)__popcll(m);
         }
-        __syncthreads();
-        if (b < kBuckets) {
-            uint32_t before = running[b];
-            for (int w = 0; w < wid; ++w) before += wcnt[w][b];
-            const uint32_t o = owner[e], x = nbr[e] >> 2;
-            const uint32_t u = o < x ? o : x, v = o < x ? x : o;
+        if (b[k] < kBuckets) {
+            const uint64_t e = base + k * 64 + lane;
+            const uint32_t ent = nbr[e], o = owner[e], w = ent >> 2, f = ent & 3u;
+            const bool up = o < w;
+            const uint2 ro = rows[o], rw = rows[w], ru = up ? ro : rw, rv = up ? rw : ro;
             dyad_rec rec;
-            rec.bu = (uint32_t)row_ptr[u];
-            rec.eu = rec.bu + len[u];
-            rec.bv = (uint32_t)row_ptr[v];
-            rec.ev = rec.bv + len[v];
-            rec.u = u;
-            const uint32_t fo = nbr[e] & 3u;
-            rec.vf = (v << 2) | (o == u ? fo : ((fo & 1u) << 1) | (fo >> 1));
-            const uint64_t at = goff[b] + before + rank;
-            out[at] = rec;
-            if (b == kBucketHub) anchors[at - hub_begin] = anchor;
+            rec.bu = ru.x;
+            rec.eu = ru.x + ru.y;
+            rec.bv = rv.x;
+            rec.ev = rv.x + rv.y;
+            rec.u = up ? o : w;
+            rec.vf = up ? (w << 2) | f : (o << 2) | ((f & 1u) << 1) | (f >> 1);
+            out[to] = rec;
+            if (b[k] == kBucketHub) anchors[to - hub_begin] = o;
         }
-        __syncthreads();
-        if (threadIdx.x < kBuckets) {
-            uint32_t add = 0;
-            for (int w = 0; w < kT / 64; ++w) add += wcnt[w][threadIdx.x];
-            running[threadIdx.x] += add;
-        }
-        __syncthreads();
     }
 }
 
@@ -653,63 +668,77 @@ __global__ __launch_bounds__(kT) void k_ranks(const uint64_t* __restrict__ keys,
     if (r < n) rank[(uint32_t)keys[r]] = (uint32_t)r;
 }
 
-// One key per joined pair, from the neighbour entry whose owner x has the
-// larger rank: rank x << (bits + 3) | rank y << 3 | f_xy << 1 | [id y > id x].
-// Without `tile_at` counts the tiles' keys into `sums`; with it (the scanned
-// sums) writes them.
-__global__ __launch_bounds__(kT) void k_pair_keys(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
-                                                  const uint32_t* __restrict__ rank, uint64_t U, uint32_t bits,
-                                                  const uint64_t* __restrict__ tile_at, uint64_t* __restrict__ sums,
-                                                  uint64_t* __restrict__ keys) {
-    __shared__ uint32_t sw[kT / 64];
+// One key per joined pair {x, y}, rank y < rank x: rank x << (bits + 3) |
+// rank y << 3 | f_xy << 1 | [id y > id x], from the neighbour entry above the
+// diagonal (one look-up of a rank per pair).  The keys are sorted next, so
+// their order does not matter: a workgroup takes the place of its keys from a
+// counter, one atomic per 8192 entries.
+constexpr int kPairT = 512;
+constexpr int kPairI = 16;
+constexpr int kPairTile = kPairT * kPairI;
+__global__ __launch_bounds__(kPairT) void k_pair_keys(const uint32_t* __restrict__ nbr, const uint32_t* __restrict__ owner,
+                                                      const uint32_t* __restrict__ rank, uint64_t U, uint32_t bits,
+                                                      unsigned long long* __restrict__ counter,
+                                                      uint64_t* __restrict__ keys) {
+    __shared__ uint32_t sw[kPairT / 64];
+    __shared__ unsigned long long s_at;
     const uint32_t lane = __lane_id(), wid = threadIdx.x >> 6;
-    const uint64_t base = (uint64_t)blockIdx.x * kTile + wid * 64 * kI;
-    uint64_t key[kI];
-    bool on[kI];
-    uint32_t mine = 0;
+    const uint64_t base = (uint64_t)blockIdx.x * kPairTile + wid * 64 * kPairI;
+    uint32_t ent[kPairI], o[kPairI], mine = 0;
 #pragma unroll
-    for (int r = 0; r < kI; ++r) {
+    for (int r = 0; r < kPairI; ++r) {
         const uint64_t e = base + r * 64 + lane;
-        const uint32_t ent = e < U ? nbr[e] : 0u, o = e < U ? owner[e] : 0u, w = ent >> 2;
-        const uint32_t ro = e < U ? rank[o] : 0u, rw = e < U ? rank[w] : 0u;
-        on[r] = rw < ro;
-        key[r] = ((uint64_t)ro << (bits + 3)) | ((uint64_t)rw << 3) | ((ent & 3u) << 1) | (w > o ? 1u : 0u);
-        mine += (uint32_t)__popcll(__ballot(on[r]));
+        ent[r] = e < U ? nbr[e] : 0u;
+        o[r] = e < U ? owner[e] : 0xffffffffu;
+        mine += (uint32_t)__popcll(__ballot(e < U && (ent[r] >> 2) > o[r]));
     }
     if (lane == 0) sw[wid] = mine;
     __syncthreads();
-    if (!tile_at) {
-        if (threadIdx.x == 0) {
-            uint32_t t = 0;
-            for (int w = 0; w < kT / 64; ++w) t += sw[w];
-            sums[blockIdx.x] = t;
-        }
-        return;
+    if (threadIdx.x == 0) {
+        uint32_t t = 0;
+        for (int w = 0; w < kPairT / 64; ++w) t += sw[w];
+        s_at = atomicAdd(counter, (unsigned long long)t);
     }
-    uint64_t at = tile_at[blockIdx.x];
+    __syncthreads();
+    uint64_t at = s_at;
     for (uint32_t w = 0; w < wid; ++w) at += sw[w];
 #pragma unroll
-    for (int r = 0; r < kI; ++r) {
-        const uint64_t m = __ballot(on[r]);
-        if (on[r]) keys[at + (uint32_t)__popcll(m & lanemask_lt())] = key[r];
+    for (int r = 0; r < kPairI; ++r) {
+        const uint64_t e = base + r * 64 + lane;
+        const uint32_t w = ent[r] >> 2, f = ent[r] & 3u;
+        const bool on = e < U && w > o[r];
+        const uint64_t m = __ballot(on);
+        if (on) {
+            const uint32_t ro = rank[o[r]], rw = rank[w];
+            const bool owner_x = rw < ro;   // the owner plays x (then id y > id x)
+            const uint32_t fxy = owner_x ? f : ((f & 1u) << 1) | (f >> 1);
+            const uint64_t x = owner_x ? ro : rw, y = owner_x ? rw : ro;
+            keys[at + (uint32_t)__popcll(m & lanemask_lt())] =
+                (x << (bits + 3)) | (y << 3) | (fxy << 1) | (owner_x ? 1u : 0u);
+        }
         at += (uint32_t)__popcll(m);
     }
 }
 
 // The forward lists and their row starts from the sorted keys.
+// fptr holds `count` in every row before: the rows after the last key's, the
+// vertices without any neighbour among them (R-MAT 2^20: 0.4 M, 0.11 ms for one
+// wavefront), are right so.
 __global__ __launch_bounds__(kT) void k_fwd_emit(const uint64_t* __restrict__ keys, uint64_t count, uint32_t bits,
-                                                 int32_t n, uint32_t* __restrict__ fwd, uint32_t* __restrict__ fptr) {
-    const uint64_t i = (uint64_t)blockIdx.x * kT + threadIdx.x;
-    int64_t before = -1, x = -1;
-    const bool on = i < count;
-    if (on) {
-        const uint64_t k = keys[i];
-        x = (int64_t)(k >> (bits + 3));
-        before = i == 0 ? -1 : (int64_t)(keys[i - 1] >> (bits + 3));
-        fwd[i] = ((uint32_t)(k & 7u) << 29) | ((uint32_t)((k >> 3) & ((1ull << bits) - 1ull)) << 1);
+                                                 uint32_t* __restrict__ fwd, uint32_t* __restrict__ fptr) {
+#pragma unroll
+    for (int r = 0; r < kI; ++r) {
+        const uint64_t i = (uint64_t)blockIdx.x * kTile + (uint64_t)r * kT + threadIdx.x;
+        int64_t before = -1, x = -1;
+        const bool on = i < count;
+        if (on) {
+            const uint64_t k = keys[i];
+            x = (int64_t)(k >> (bits + 3));
+            before = i == 0 ? -1 : (int64_t)(keys[i - 1] >> (bits + 3));
+            fwd[i] = ((uint32_t)(k & 7u) << 29) | ((uint32_t)((k >> 3) & ((1ull << bits) - 1ull)) << 1);
+        }
+        fill_rows(on && x != before, before, x, i, fptr);
     }
-    fill_rows(on, before, x, i, fptr);
-    fill_rows(on && i + 1 == count, x, (int64_t)n, count, fptr);
 }
 
 // Bucket of the edge of sorted key i (x, y): hub when the longer of the two
@@ -761,13 +790,26 @@ __global__ __launch_bounds__(kT) void k_edge_count(const uint64_t* __restrict__ 
     store_tile_sums(my, mycost, mystream, 0ull, counts, part, nblocks, sh);
 }
 
-// Lane / wave / group records in x-major order; for the hub edges a key
-// y << 32 | i, in x-major order too (sorted by y next).
-__global__ __launch_bounds__(kT) void k_edge_scatter(const uint64_t* __restrict__ keys, uint64_t count, uint32_t bits,
+// A hub edge's record needs i, the start bx of x's row, the code bits, and
+// whether the prefix has entries not below kCore (`tail`).  Where they fit
+// beside y in 64 bits, the key the edges are sorted by holds them all: y, i, the
+// place of y in the row (i - bx, below sqrt(2 F): the d neighbours after x have
+// degree d or more), tail, bits.  Otherwise the key holds y and i, and the
+// record gathers the rest by i (R-MAT 2^20, 14 M hub edges: 0.37 ms for the
+// gathers, which miss the L2 at 55 G lines/s, 0.15 ms without).
+struct hub_key {
+    uint32_t ibits, pbits;   // pbits 0: y << 32 | i
+    __host__ __device__ uint32_t y_shift() const { return pbits ? 4 + pbits + ibits : 32; }
+};
+
+// Lane / wave / group records in x-major order; for the hub edges a key, in
+// x-major order too (sorted by y next).  Without room in the key, keys[i]
+// becomes bx << 4 | tail << 3 | bits.
+__global__ __launch_bounds__(kT) void k_edge_scatter(uint64_t* keys, uint64_t count, uint32_t bits,
                                                      const uint32_t* __restrict__ fptr, bucket_params bp,
                                                      const uint64_t* __restrict__ offsets, uint32_t nblocks,
-                                                     uint64_t hub_begin, uint64_t* __restrict__ hubkeys,
-                                                     uint4* __restrict__ out) {
+                                                     uint64_t hub_begin, hub_key hk, const uint32_t* __restrict__ fwd,
+                                                     uint64_t* __restrict__ hubkeys, uint4* __restrict__ out) {
     __shared__ uint32_t wcnt[kT / 64][kBuckets];
     const uint32_t lane = __lane_id(), wid = threadIdx.x >> 6;
     const uint64_t base = (uint64_t)blockIdx.x * kTile + wid * 64 * kI;   // the wavefront's keys
@@ -796,8 +838,16 @@ __global__ __launch_bounds__(kT) void k_edge_scatter(const uint64_t* __restrict_
             const uint64_t m = __ballot(r[k].bucket == q);
             if (r[k].bucket == q) {
                 const uint64_t to = at[q] + (uint32_t)__popcll(m & lanemask_lt());
-                if (q == kBucketHub) hubkeys[to - hub_begin] = ((uint64_t)r[k].y << 32) | i;
-                else out[to] = make_uint4(r[k].bx, (uint32_t)i, r[k].by, (r[k].bits << 29) | r[k].dy);
+                if (q == kBucketHub) {
+                    const uint32_t low = ((fwd[i - 1] & 0x00fffffeu) >= 2u * kCore ? 8u : 0u) | r[k].bits;
+                    if (hk.pbits) {
+                        hubkeys[to - hub_begin] = ((uint64_t)r[k].y << hk.y_shift()) | (i << (4 + hk.pbits)) |
+                                                  ((uint64_t)r[k].pos << 4) | low;
+                    } else {
+                        hubkeys[to - hub_begin] = ((uint64_t)r[k].y << 32) | i;
+                        keys[i] = ((uint64_t)r[k].bx << 4) | low;
+                    }
+                } else out[to] = make_uint4(r[k].bx, (uint32_t)i, r[k].by, (r[k].bits << 29) | r[k].dy);
             }
             at[q] += (uint32_t)__popcll(m);
         }
@@ -806,29 +856,50 @@ __global__ __launch_bounds__(kT) void k_edge_scatter(const uint64_t* __restrict_
 
 // Hub records from the keys sorted by y, and the run of each y (first and one
 // past the last record, zero elsewhere).
-__global__ __launch_bounds__(kT) void k_edge_hub(const uint64_t* __restrict__ hubkeys, uint32_t hubs,
-                                                 const uint64_t* __restrict__ keys, uint32_t bits,
-                                                 const uint32_t* __restrict__ fptr, const uint32_t* __restrict__ fwd,
+__global__ __launch_bounds__(kT) void k_edge_hub(const uint64_t* __restrict__ hubkeys, uint64_t hubs, hub_key hk,
+                                                 const uint64_t* __restrict__ edges, const uint32_t* __restrict__ fwd,
                                                  uint32_t* __restrict__ first, uint32_t* __restrict__ past,
                                                  uint4* __restrict__ out) {
-    const uint32_t j = blockIdx.x * kT + threadIdx.x;
-    if (j >= hubs) return;
-    const uint64_t hk = hubkeys[j];
-    const uint32_t y = (uint32_t)(hk >> 32), i = (uint32_t)hk;
-    const uint64_t k = keys[i];
-    const uint32_t bx = fptr[(uint32_t)(k >> (bits + 3))];
-    uint32_t core = i;   // the prefix's entries lie below y
-    if (y > kCore) {
-        uint32_t lo = bx, hi = i;
-        while (lo < hi) {
-            const uint32_t mid = lo + ((hi - lo) >> 1);
-            if ((fwd[mid] & 0x00fffffeu) < 2u * kCore) lo = mid + 1; else hi = mid;
-        }
-        core = lo;
+    const uint32_t ys = hk.y_shift();
+    uint64_t key[kI], ed[kI];
+#pragma unroll
+    for (int r = 0; r < kI; ++r) {
+        const uint64_t j = (uint64_t)blockIdx.x * kTile + (uint64_t)r * kT + threadIdx.x;
+        key[r] = j < hubs ? hubkeys[j] : 0ull;
     }
-    out[j] = make_uint4(bx, core, i, (uint32_t)(k & 7u));
-    if (j == 0 || (uint32_t)(hubkeys[j - 1] >> 32) != y) first[y] = j;
-    if (j + 1 == hubs || (uint32_t)(hubkeys[j + 1] >> 32) != y) past[y] = j + 1;
+#pragma unroll
+    for (int r = 0; r < kI; ++r) {
+        const uint64_t j = (uint64_t)blockIdx.x * kTile + (uint64_t)r * kT + threadIdx.x;
+        ed[r] = j < hubs && !hk.pbits ? edges[(uint32_t)key[r]] : 0ull;
+    }
+#pragma unroll
+    for (int r = 0; r < kI; ++r) {
+        const uint64_t j = (uint64_t)blockIdx.x * kTile + (uint64_t)r * kT + threadIdx.x;
+        if (j >= hubs) continue;
+        const uint32_t y = (uint32_t)(key[r] >> ys);
+        uint32_t i, bx, low;
+        if (hk.pbits) {
+            i = (uint32_t)((key[r] >> (4 + hk.pbits)) & ((1ull << hk.ibits) - 1ull));
+            bx = i - (uint32_t)((key[r] >> 4) & ((1ull << hk.pbits) - 1ull));
+            low = (uint32_t)key[r] & 15u;
+        } else {
+            i = (uint32_t)key[r];
+            bx = (uint32_t)(ed[r] >> 4);
+            low = (uint32_t)ed[r] & 15u;
+        }
+        uint32_t core = i;
+        if (low & 8u) {
+            uint32_t lo = bx, hi = i - 1;
+            while (lo < hi) {
+                const uint32_t mid = lo + ((hi - lo) >> 1);
+                if ((fwd[mid] & 0x00fffffeu) < 2u * kCore) lo = mid + 1; else hi = mid;
+            }
+            core = lo;
+        }
+        out[j] = make_uint4(bx, core, i, low & 7u);
+        if (j == 0 || (uint32_t)(hubkeys[j - 1] >> ys) != y) first[y] = (uint32_t)j;
+        if (j + 1 == hubs || (uint32_t)(hubkeys[j + 1] >> ys) != y) past[y] = (uint32_t)j + 1;
+    }
 }
 
 __global__ __launch_bounds__(kT) void k_tri_ntasks(const uint32_t* __restrict__ first, const uint32_t* __restrict__ past,
@@ -875,9 +946,12 @@ __global__ __launch_bounds__(kT) void k_tri_tasks(const uint32_t* __restrict__ f
 }
 
 __global__ __launch_bounds__(kT) void k_row_len(const int64_t* __restrict__ row_ptr, int32_t n,
-                                                uint32_t* __restrict__ len) {
+                                                uint32_t* __restrict__ len, uint2* __restrict__ rows) {
     const int64_t x = (int64_t)blockIdx.x * kT + threadIdx.x;
-    if (x < n) len[x] = (uint32_t)(row_ptr[x + 1] - row_ptr[x]);
+    if (x >= n) return;
+    const uint32_t b = (uint32_t)row_ptr[x], l = (uint32_t)row_ptr[x + 1] - b;
+    len[x] = l;
+    rows[x] = make_uint2(b, l);
 }
 
 // The run of hub records of each anchor: first and one past the last, from
@@ -1010,7 +1084,11 @@ inline uint32_t sort_digit_bits(uint32_t sort_bits) {
     const uint32_t passes = (sort_bits + kDigitBits - 1) / kDigitBits;
     return passes ? (sort_bits + passes - 1) / passes : 1;
 }
-inline uint64_t sort_tiles(uint64_t count) { return (count + kSortTile - 1) / kSortTile; }
+inline int sort_items(uint64_t count) { return count < kSortSmall ? kSortISmall : kSortI; }
+inline uint64_t sort_tiles(uint64_t count) {
+    const uint64_t t = (uint64_t)kT * sort_items(count);
+    return (count + t - 1) / t;
+}
 inline uint64_t scan_scratch_words(uint64_t count) { return (count + kTile - 1) / kTile + 1; }
 
 // Scratch words and bytes of the two phases of a build: sorting 2 m keys, and
@@ -1023,11 +1101,13 @@ inline uint64_t sort_space_bytes(uint64_t m, uint32_t bits) {
 inline uint64_t bucket_space_bytes(uint64_t U, uint64_t n) {
     const uint64_t nb = (U + kTile - 1) / kTile + 1, p = U / 2, tasks = std::min(n, p) + p / (kHubChunk / 2) + 1;
     return 8 * (kBuckets * nb + 1) + 8 * kPartWords * nb + 8 * scan_scratch_words(std::max(U + 1, n + 1)) +
-           4 * 3 * (n + 2) + 4 * p + 2 * 8 * (n + 1) + 8 * (tasks / kHubGroupTasks + 2) +
+           4 * 3 * (n + 2) + 4 * p + U + 2 * 8 * (n + 1) + 8 * (tasks / kHubGroupTasks + 2) +
            8 * scan_scratch_words(tasks) + 32 * 256;
 }
 inline uint64_t forward_space_bytes(uint64_t U, uint64_t n) {
-    const uint64_t F = U / 2, nb = (U + kTile - 1) / kTile + 1, hist = (uint64_t)kDigits * sort_tiles(std::max(F, n) + 1);
+    const uint64_t F = U / 2, nb = (U + kTile - 1) / kTile + 1;
+    // (hub keys and vertices may be few: tiles of the small size)
+    const uint64_t hist = (uint64_t)kDigits * (std::max(F, n) / (kT * kSortISmall) + 1);
     return 3 * 8 * F + 4 * hist + 8 * scan_scratch_words(std::max(hist, n + 1)) + 2 * 8 * n + 4 * n + 8 * nb +
            8 * (kBuckets * nb + 1) + 8 * kPartWords * nb + 4 * 2 * (n + 2) + 8 * (n + 1) + 32 * 256;
 }
@@ -1235,14 +1315,14 @@ hipError_t scan_exclusive(const T* in, T* out, uint64_t count, T* total, arena& 
     return hipGetLastError();
 }
 
-template <class O>
+template <class O, int I>
 hipError_t radix_pass(const uint64_t* in, uint64_t* out, uint64_t count, uint32_t shift, uint32_t dbits, O* hist,
                       arena& ar, hipStream_t s) {
     const uint32_t nb = (uint32_t)sort_tiles(count), nbins = 1u << dbits;
-    hipLaunchKernelGGL(k_radix_hist<O>, dim3(nb), dim3(kT), 0, s, in, count, shift, nbins, hist, nb);
+    hipLaunchKernelGGL((k_radix_hist<O, I>), dim3(nb), dim3(kT), 0, s, in, count, shift, nbins, hist, nb);
     hipError_t e = scan_exclusive<O>(hist, hist, (uint64_t)nbins * nb, nullptr, ar, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_radix_scatter<O>, dim3(nb), dim3(kT), 0, s, in, out, count, shift, dbits, (const O*)hist, nb);
+    hipLaunchKernelGGL((k_radix_scatter<O, I>), dim3(nb), dim3(kT), 0, s, in, out, count, shift, dbits, (const O*)hist, nb);
     return hipGetLastError();
 }
 
@@ -1259,8 +1339,10 @@ hipError_t radix_sort(uint64_t** keys, uint64_t** tmp, uint64_t count, uint32_t 
     hipError_t e = hipSuccess;
     for (uint32_t done = 0; done < sort_bits && e == hipSuccess; done += dbits) {
         const uint32_t b = std::min(dbits, sort_bits - done);
-        e = wide ? radix_pass<uint64_t>(*keys, *tmp, count, first + done, b, (uint64_t*)hist, ar, s)
-                 : radix_pass<uint32_t>(*keys, *tmp, count, first + done, b, (uint32_t*)hist, ar, s);
+        if (wide) e = radix_pass<uint64_t, kSortI>(*keys, *tmp, count, first + done, b, (uint64_t*)hist, ar, s);
+        else if (sort_items(count) == kSortI)
+            e = radix_pass<uint32_t, kSortI>(*keys, *tmp, count, first + done, b, (uint32_t*)hist, ar, s);
+        else e = radix_pass<uint32_t, kSortISmall>(*keys, *tmp, count, first + done, b, (uint32_t*)hist, ar, s);
         std::swap(*keys, *tmp);
     }
     ar.rewind(mark);
@@ -1273,8 +1355,8 @@ uint32_t bit_width_u32(uint32_t x) {
     return b;
 }
 
-hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, bool fresh, build_space* sp,
-                      arena& ar, hipStream_t s);
+hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, const uint2* rows, bool fresh,
+                      build_space* sp, arena& ar, hipStream_t s);
 
 }  // namespace
 
@@ -1292,7 +1374,7 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     *g = device_graph{};
     g->n = n;
     g->mem = pool;
-    const uint64_t small = 1024 + sizeof(uint32_t) * (uint64_t)n + 1024;
+    const uint64_t small = 4096 + (sizeof(uint32_t) + sizeof(uint2)) * ((uint64_t)n + 1);
     const uint64_t need = small + std::max(sort_space_bytes((uint64_t)m, bits), view_space_bytes(keys_n, (uint64_t)n, bp.tri != 0));
     if ((err = space_reserve(sp, need, s)) != hipSuccess) {
         st.hip = err;
@@ -1301,11 +1383,13 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     arena ar(*sp);
     unsigned long long* counters = nullptr;
     uint32_t* deg = nullptr;
+    uint2* rows = nullptr;
     uint64_t *keys = nullptr, *tmp = nullptr, *ents = nullptr, *types = nullptr, U = 0, total_types = 0;
     const uint64_t tiles = (keys_n + kTile - 1) / kTile;
     size_t mark = 0;
     TAKE(counters, unsigned long long, kCounters);
     TAKE(deg, uint32_t, (uint64_t)n + 1);
+    TAKE(rows, uint2, (uint64_t)n + 1);
     mark = ar.mark();
     TRY(fill_u64((uint64_t*)counters, kCounters, 0, s));
     if (keys_n > 0) {
@@ -1336,6 +1420,8 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     }
     if (U >= (1ull << 32)) { st.too_large = true; goto done; }
     g->U = U;
+    g->p = U / 2;
+    g->mutual = (total_types & 0xffffffffull) - U / 2;   // a mutual pair holds two arcs
     st.arcs_kept = (int64_t)(total_types & 0xffffffffull);
     st.duplicates = m - st.self_loops - st.arcs_kept;
     TRY(g->mem->alloc((void**)&g->row_ptr, sizeof(int64_t) * ((size_t)n + 1)));
@@ -1352,11 +1438,11 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     }
     if (n > 0)
         hipLaunchKernelGGL(k_row_info, dim3(std::min(grid1((uint64_t)n), kStatBlocks)), dim3(kT), 0, s,
-                           (const int64_t*)g->row_ptr, n, (const uint64_t*)g->tpre, g->rinfo, deg, counters);
+                           (const int64_t*)g->row_ptr, n, (const uint64_t*)g->tpre, g->rinfo, deg, rows, counters);
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, (const uint64_t*)counters + 3, sp->host + kSpaceHostStats, 2);
     TRY(hipGetLastError());
     ar.rewind(mark);   // (the keys are read by then, in stream order)
-    TRY(bucket_all(g, bp, deg, true, sp, ar, s));
+    TRY(bucket_all(g, bp, deg, rows, true, sp, ar, s));
     st.sum_d2 = sp->host[kSpaceHostStats];
     st.max_degree = (int64_t)g->max_degree;
     st.ok = true;
@@ -1421,8 +1507,8 @@ done:
 
 // The dyad view: records of g's canonical dyads by bucket, hub tasks and the
 // per-bucket sums.  deg: the rows' lengths.
-hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const uint32_t* deg, build_space* sp,
-                               arena& ar, hipStream_t s) {
+hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const uint32_t* deg, const uint2* rows,
+                               build_space* sp, arena& ar, hipStream_t s) {
     hipError_t err = hipSuccess;
     const size_t mark = ar.mark();
     const uint64_t U = g->U;
@@ -1430,6 +1516,7 @@ hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const u
     graph_pool* mem = g->mem;
     uint64_t *counts = nullptr, *part = nullptr;
     uint32_t *first = nullptr, *past = nullptr, *anchors = nullptr;
+    uint8_t* bucket = nullptr;
     uint64_t hubs = 0;
     const uint32_t nb = blocks_for(U ? U : 1);
     mem->put(g->dyads);
@@ -1441,7 +1528,8 @@ hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const u
     g->hub_staged = 0;
     TAKE(counts, uint64_t, (uint64_t)kBuckets * nb + 1);
     TAKE(part, uint64_t, (uint64_t)kPartWords * nb);
-    hipLaunchKernelGGL(k_dyad_count, dim3(nb), dim3(kT), 0, s, g->nbr, g->owner, deg, U, bp, counts, nb, part);
+    TAKE(bucket, uint8_t, U);
+    hipLaunchKernelGGL(k_dyad_count, dim3(nb), dim3(kT), 0, s, g->nbr, g->owner, deg, U, bp, counts, nb, part, bucket);
     TRY(scan_exclusive<uint64_t>(counts, counts, (uint64_t)kBuckets * nb, counts + (uint64_t)kBuckets * nb, ar, s));
     hipLaunchKernelGGL(k_bucket_sums, dim3(kPartWords + 1), dim3(kT), 0, s, (const uint64_t*)part,
                        (const uint64_t*)counts, nb, sp->host);
@@ -1463,8 +1551,8 @@ hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const u
         TRY(fill_u64((uint64_t*)past, ((uint64_t)n + 2) / 2, 0, s));
     }
     if (g->p > 0) {
-        hipLaunchKernelGGL(k_dyad_scatter, dim3(nb), dim3(kT), 0, s, g->nbr, g->owner, g->row_ptr, deg, U, bp,
-                           (const uint64_t*)counts, nb, g->bucket_off[kBucketHub], anchors, g->dyads);
+        hipLaunchKernelGGL(k_dyad_scatter, dim3(nb), dim3(kT), 0, s, g->nbr, g->owner, rows, U,
+                           (const uint8_t*)bucket, (const uint64_t*)counts, nb, g->bucket_off[kBucketHub], anchors, g->dyads);
         TRY(hipGetLastError());
     }
     if (hubs > 0) {
@@ -1486,6 +1574,8 @@ void free_forward(graph_pool* mem, forward_lists* t) {
     *t = forward_lists{};
 }
 
+constexpr uint32_t hub_key_bits = 64;
+
 // Forward lists of g (degree order), their edge records and hub tasks.
 hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_t* deg, build_space* sp, arena& ar,
                          hipStream_t s) {
@@ -1497,21 +1587,22 @@ hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_
     graph_pool* mem = g->mem;
     forward_lists& t = g->tri;
     auto& out = t.edges;
-    uint64_t *vk = nullptr, *vt = nullptr, *keys = nullptr, *tmp = nullptr, *hk = nullptr, *sums = nullptr,
-             *counts = nullptr, *part = nullptr, *task_off = nullptr;
+    uint64_t *vk = nullptr, *vt = nullptr, *keys = nullptr, *tmp = nullptr, *hk = nullptr, *counts = nullptr,
+             *part = nullptr, *task_off = nullptr;
     uint32_t *rank = nullptr, *first = nullptr, *past = nullptr;
-    unsigned long long* staged = nullptr;
+    unsigned long long *staged = nullptr, *counter = nullptr;
     uint64_t hubs = 0, total = 0;
+    hub_key hkey{0, 0};
     size_t inner = 0;
-    const uint32_t tiles = blocks_for(U ? U : 1), nb = blocks_for(F ? F : 1);
+    const uint32_t nb = blocks_for(F ? F : 1);
     t.entries = F;
     TRY(mem->alloc((void**)&t.fptr, sizeof(uint32_t) * ((size_t)n + 1)));
     TRY(mem->alloc((void**)&t.fwd, sizeof(uint32_t) * (F + kRowPad)));
     out.chunk = kHubChunk;
+    hipLaunchKernelGGL(k_fill_u32, dim3(grid1((uint64_t)n + 1)), dim3(kT), 0, s, t.fptr, (uint64_t)n + 1, (uint32_t)F);
+    TRY(hipGetLastError());
     if (F == 0) {
         TRY(mem->alloc((void**)&out.recs, sizeof(uint4)));
-        hipLaunchKernelGGL(k_fill_u32, dim3(grid1((uint64_t)n + 1)), dim3(kT), 0, s, t.fptr, (uint64_t)n + 1, 0u);
-        TRY(hipGetLastError());
         goto done;
     }
     TAKE(rank, uint32_t, n);
@@ -1525,14 +1616,13 @@ hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_
     hipLaunchKernelGGL(k_ranks, dim3(grid1((uint64_t)n)), dim3(kT), 0, s, (const uint64_t*)vk, n, rank);
     TRY(hipGetLastError());
     ar.rewind(inner);
-    TAKE(sums, uint64_t, tiles);
-    hipLaunchKernelGGL(k_pair_keys, dim3(tiles), dim3(kT), 0, s, g->nbr, g->owner, (const uint32_t*)rank, U, bits,
-                       (const uint64_t*)nullptr, sums, (uint64_t*)nullptr);
-    TRY(scan_exclusive<uint64_t>(sums, sums, tiles, nullptr, ar, s));
-    hipLaunchKernelGGL(k_pair_keys, dim3(tiles), dim3(kT), 0, s, g->nbr, g->owner, (const uint32_t*)rank, U, bits,
-                       (const uint64_t*)sums, (uint64_t*)nullptr, keys);
+    TAKE(counter, unsigned long long, 1);
+    TRY(fill_u64((uint64_t*)counter, 1, 0, s));
+    hipLaunchKernelGGL(k_pair_keys, dim3((uint32_t)((U + kPairTile - 1) / kPairTile)), dim3(kPairT), 0, s, g->nbr, g->owner,
+                       (const uint32_t*)rank, U, bits, counter, keys);
+    TRY(hipGetLastError());
     TRY(radix_sort(&keys, &tmp, F, 3, 2 * bits, ar, s));
-    hipLaunchKernelGGL(k_fwd_emit, dim3(grid1(F)), dim3(kT), 0, s, (const uint64_t*)keys, F, bits, n, t.fwd, t.fptr);
+    hipLaunchKernelGGL(k_fwd_emit, dim3(blocks_for(F)), dim3(kT), 0, s, (const uint64_t*)keys, F, bits, t.fwd, t.fptr);
     TAKE(counts, uint64_t, (uint64_t)kBuckets * nb + 1);
     TAKE(part, uint64_t, (uint64_t)kPartWords * nb);
     hipLaunchKernelGGL(k_edge_count, dim3(nb), dim3(kT), 0, s, (const uint64_t*)keys, F, bits, (const uint32_t*)t.fptr,
@@ -1550,9 +1640,13 @@ hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_
     out.chunk = hubs >= kHubSplitRecords ? kHubChunk / 2 : hubs >= kHubSmallRecords ? 64 : kHubChunk;
     TRY(mem->alloc((void**)&out.recs, sizeof(uint4) * (total ? total : 1)));
     if (total == 0) goto done;
+    hkey.ibits = bit_width_u32((uint32_t)F);
+    hkey.pbits = bit_width_u32((uint32_t)std::sqrt(2.0 * (double)F) + 1u);
+    if (bits + hkey.ibits + hkey.pbits + 4 > hub_key_bits) hkey.pbits = 0;
     // (the second key buffer is free: it takes the hub keys)
-    hipLaunchKernelGGL(k_edge_scatter, dim3(nb), dim3(kT), 0, s, (const uint64_t*)keys, F, bits,
-                       (const uint32_t*)t.fptr, bp, (const uint64_t*)counts, nb, out.off[kBucketHub], tmp, out.recs);
+    hipLaunchKernelGGL(k_edge_scatter, dim3(nb), dim3(kT), 0, s, keys, F, bits,
+                       (const uint32_t*)t.fptr, bp, (const uint64_t*)counts, nb, out.off[kBucketHub], hkey,
+                       (const uint32_t*)t.fwd, tmp, out.recs);
     TRY(hipGetLastError());
     if (hubs == 0) goto done;
     TAKE(hk, uint64_t, hubs);
@@ -1563,10 +1657,9 @@ hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_
     TRY(fill_u64((uint64_t*)first, ((uint64_t)n + 2) / 2, 0, s));
     TRY(fill_u64((uint64_t*)past, ((uint64_t)n + 2) / 2, 0, s));
     TRY(fill_u64((uint64_t*)staged, 2, 0, s));
-    TRY(radix_sort(&tmp, &hk, hubs, 32, bits, ar, s));
-    hipLaunchKernelGGL(k_edge_hub, dim3(grid1(hubs)), dim3(kT), 0, s, (const uint64_t*)tmp, (uint32_t)hubs,
-                       (const uint64_t*)keys, bits, (const uint32_t*)t.fptr, (const uint32_t*)t.fwd, first, past,
-                       out.recs + out.off[kBucketHub]);
+    TRY(radix_sort(&tmp, &hk, hubs, hkey.y_shift(), bits, ar, s));
+    hipLaunchKernelGGL(k_edge_hub, dim3(blocks_for(hubs)), dim3(kT), 0, s, (const uint64_t*)tmp, hubs, hkey,
+                       (const uint64_t*)keys, (const uint32_t*)t.fwd, first, past, out.recs + out.off[kBucketHub]);
     hipLaunchKernelGGL(k_tri_ntasks, dim3(std::min(grid1((uint64_t)n), kStatBlocks)), dim3(kT), 0, s,
                        (const uint32_t*)first, (const uint32_t*)past, n, (const uint32_t*)t.fptr, out.chunk, task_off,
                        staged);
@@ -1591,9 +1684,9 @@ done:
 
 // Both views of g.  `fresh`: the largest degree is on its way to the host, and
 // there once the dyad records' synchronisation has passed.
-hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, bool fresh, build_space* sp,
-                      arena& ar, hipStream_t s) {
-    hipError_t err = bucket_dyad_records(g, bp, deg, sp, ar, s);
+hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, const uint2* rows, bool fresh,
+                      build_space* sp, arena& ar, hipStream_t s) {
+    hipError_t err = bp.dyads ? bucket_dyad_records(g, bp, deg, rows, sp, ar, s) : hipStreamSynchronize(s);
     if (err != hipSuccess) return err;
     if (fresh) g->max_degree = (uint32_t)sp->host[kSpaceHostStats + 1];
     g->bp = bp;
@@ -1610,17 +1703,19 @@ hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* 
 #undef TRY
 
 hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s, build_space* sp) {
-    hipError_t e = space_reserve(sp, 4096 + sizeof(uint32_t) * (uint64_t)g->n +
+    hipError_t e = space_reserve(sp, 4096 + (sizeof(uint32_t) + sizeof(uint2)) * ((uint64_t)g->n + 1) +
                                      view_space_bytes(g->U, (uint64_t)g->n, bp.tri != 0), s);
     if (e != hipSuccess) return e;
     arena ar(*sp);
     uint32_t* deg = ar.take<uint32_t>((uint64_t)g->n + 1);
-    if (!deg) return hipErrorOutOfMemory;
+    uint2* rows = ar.take<uint2>((uint64_t)g->n + 1);
+    if (!deg || !rows) return hipErrorOutOfMemory;
     if (g->n > 0) {
-        hipLaunchKernelGGL(k_row_len, dim3(grid1((uint64_t)g->n)), dim3(kT), 0, s, (const int64_t*)g->row_ptr, g->n, deg);
+        hipLaunchKernelGGL(k_row_len, dim3(grid1((uint64_t)g->n)), dim3(kT), 0, s, (const int64_t*)g->row_ptr, g->n, deg,
+                           rows);
         e = hipGetLastError();
     }
-    if (e == hipSuccess) e = bucket_all(g, bp, deg, false, sp, ar, s);
+    if (e == hipSuccess) e = bucket_all(g, bp, deg, rows, false, sp, ar, s);
     (void)hipStreamSynchronize(s);
     return e;
 }
@@ -1644,7 +1739,7 @@ void free_device_graph(device_graph* g) {
 uint64_t device_graph_bytes(const device_graph& g) {
     uint64_t b = sizeof(int64_t) * ((uint64_t)g.n + 1) + (sizeof(uint32_t) * 2 + sizeof(uint64_t)) * g.U +
                  sizeof(uint32_t) * kRowPad + sizeof(uint4) * ((uint64_t)g.n + 1) +
-                 sizeof(uint64_t) + sizeof(dyad_rec) * g.p + sizeof(hub_task) * (uint64_t)g.n_hub_tasks;
+                 sizeof(uint64_t) + sizeof(dyad_rec) * (g.dyads ? g.p : 0) + sizeof(hub_task) * (uint64_t)g.n_hub_tasks;
     if (g.tri.fptr)
         b += sizeof(uint32_t) * ((uint64_t)g.n + 1 + g.tri.entries + kRowPad) +
              sizeof(uint4) * g.tri.edges.off[kBuckets] + sizeof(tri_task) * (uint64_t)g.tri.edges.n_tasks;

@@ -75,6 +75,7 @@ struct bucket_params {
     uint32_t t0, t1, t_hub;
     uint32_t tri;        // also build the degree-ordered forward lists and their edge records
     uint32_t hub_tile;   // anchor entries per LDS tile of the hub mode: hub tasks are grouped for it
+    uint32_t dyads = 1;  // build the dyad records (0 only with tri, for a graph censused whole and once)
 };
 
 // ---------------------------------------------------------------------------

@@ -176,7 +176,7 @@ private:
             serve_job* j = static_cast<serve_job*>(jb);
             if (!j->cold) continue;
             bucket_params bp = params_of(tun);
-            bp.tri = 0;   // cold graphs live for one round: no forward lists (not in their footprint)
+            bp.dyads = !tun.tri;   // cold graphs live for one census: only the view it runs
             j->status = build_into(j->n, (int64_t)j->src.size(), j->src.data(), j->dst.data(), j->flags, bp, &ctx_->pool,
                                    s.stream, &s.space, space_keep(ctx_), &j->built, nullptr);
             std::vector<int32_t>().swap(j->src);

@@ -78,3 +78,28 @@ def test_runs_of_hub_records(ctx, k):
 def test_prefix_blocks(ctx, m):
     a, b = np.triu_indices(m, 1)
     _check(ctx, m + 3, np.stack([a, b], 1), m, "clique")
+
+
+def test_hub_keys_wider_than_a_word(ctx):
+    # so many vertices and pairs that a hub edge's key cannot hold its place in
+    # the row: the records gather it; against the census over the dyad records
+    rng = np.random.default_rng(7)
+    n, m = 4_800_000, 17_500_000
+    src, dst = rng.integers(0, n, m, dtype=np.int32), rng.integers(0, n, m, dtype=np.int32)
+    dst[: m // 8] = dst[: m // 8] % 3000        # popular vertices, and triangles among them
+    src[: m // 16] = src[: m // 16] % 60000
+    default = ctx.get_tuning()
+    try:
+        ctx.set_tuning(t_hub=6)
+        g = ctx.build_graph(n, src, dst)
+        try:
+            print(f"[gpu] forward wide keys edges={g.info['tri_bucket_edges']}", flush=True)
+            assert g.info["tri_bucket_edges"][3] > 1 << 20 and g.info["fwd_entries"] > 1 << 24
+            got = ctx.census(g).tolist()
+            ctx.set_tuning(**dict(default, tri=0))
+            assert ctx.census(g).tolist() == got
+            assert got[8] + got[9] > 1000
+        finally:
+            g.release()
+    finally:
+        ctx.set_tuning(**default)
