@@ -114,7 +114,8 @@ void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it) 
 namespace {
 
 hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipStream_t s, uint32_t grid,
-                           uint32_t hub_grid, uint32_t tri_grid, uint32_t hub_tile, uint32_t batch_tile) {
+                           uint32_t hub_grid, uint32_t tri_grid, uint32_t hub_tile, uint32_t batch_tile,
+                           hipStream_t side, hipEvent_t* fork) {
     if (p->exec && graphs <= p->cap_graphs && items <= p->cap_items && grid == p->grid && hub_grid == p->hub_grid &&
         tri_grid == p->tri_grid && hub_tile == p->hub_tile && batch_tile == p->batch_tile)
         return hipSuccess;
@@ -142,7 +143,7 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
     e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
     const batch_buffers bb{p->d_desc, p->d_items, p->d_num, p->d_accs, p->d_ctr, p->tri_grid, p->hub_grid, p->grid,
-                           p->cap_graphs, p->h_accs};
+                           p->cap_graphs, p->h_accs, side, fork};
     hipError_t el = batch_launch(bb, p->hub_tile, p->batch_tile, s);
     e = hipStreamEndCapture(s, &p->graph);
     if (el != hipSuccess) e = el;
@@ -186,7 +187,7 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
         uint32_t nums[3];
         std::vector<work_item>& items = lists.join(nums);
         e = ensure_capacity(p, (uint32_t)count, (uint32_t)items.size(), ctx->stream, ctx->tuning.batch_blocks, hub_grid,
-                            tri_grid, ctx->tuning.hub_tile, ctx->tuning.batch_tile);
+                            tri_grid, ctx->tuning.hub_tile, ctx->tuning.batch_tile, ctx->side, ctx->fork);
         if (e != hipSuccess) return status_from_hip(e);
         uint32_t nitems = (uint32_t)items.size();
         e = hipMemcpyAsync(p->d_desc, descs.data(), sizeof(graph_desc) * count, hipMemcpyHostToDevice, ctx->stream);

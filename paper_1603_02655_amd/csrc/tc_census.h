@@ -87,6 +87,8 @@ struct batch_buffers {
     uint32_t tri_grid, hub_grid, grid;
     uint32_t graphs;
     unsigned long long* out;        // pinned: 16 sums per graph
+    hipStream_t side = nullptr;     // a second stream and two events: the kernel of the other items runs there
+    hipEvent_t* fork = nullptr;
 };
 hipError_t batch_launch(const batch_buffers& b, uint32_t hub_tile, uint32_t batch_tile, hipStream_t s);
 
