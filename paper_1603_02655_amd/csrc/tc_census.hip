@@ -643,9 +643,10 @@ __device__ inline void merge_path(uint32_t bu, uint32_t eu, uint32_t bv, uint32_
 // ------------------------------------------------------ work distribution ----
 // Dyads are handed out in chunks of CH through eight counters, one per XCD
 // (workgroup b runs on XCD b % 8 on this part), so that the atomics stay in
-// one L2: counter x hands out the chunk indices x, x + 8, x + 16, ...
-__device__ inline uint32_t take_chunk(unsigned int* ctr, uint32_t xcd) {
-    return xcd + kXcds * atomicAdd(&ctr[xcd * kCounterStride], 1u);
+// one L2: counter x hands out the chunk indices x, x + 8, x + 16, ... (x, x + g,
+// x + 2 g, ... in a grid of g < 8 workgroups, which uses only g counters).
+__device__ inline uint32_t take_chunk(unsigned int* ctr, uint32_t xcd, uint32_t blocks) {
+    return xcd + min(blocks, (uint32_t)kXcds) * atomicAdd(&ctr[xcd * kCounterStride], 1u);
 }
 
 // ---------------------------------------------------------------- wave ----
@@ -665,11 +666,11 @@ __global__ __launch_bounds__(kWaveB) void k_census_wave(census_args L, unsigned 
     __syncthreads();
     const uint32_t xcd = blockIdx.x % kXcds;
     uint32_t c = 0;
-    if (threadIdx.x == 0) c = take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) c = take_chunk(ctr, xcd, gridDim.x);
     c = __shfl(c, 0, 64);
     while ((uint64_t)c * kWaveChunk < L.count) {
         uint32_t cn = 0;
-        if (threadIdx.x == 0) cn = take_chunk(ctr, xcd);      // next chunk, fetched early
+        if (threadIdx.x == 0) cn = take_chunk(ctr, xcd, gridDim.x);      // next chunk, fetched early
         const uint32_t end = min((uint32_t)L.count, (c + 1) * kWaveChunk);
         for (uint32_t d = c * kWaveChunk; d < end; ++d) {
             const dyad_rec r = load_rec(L.dyads + d);
@@ -699,12 +700,12 @@ __global__ __launch_bounds__(B) void k_census_group(census_args L, unsigned int*
     wave_bins<B> h{bins};
     h.clear();
     const uint32_t xcd = blockIdx.x % kXcds;
-    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd, gridDim.x);
     __syncthreads();
     uint32_t c = s_next;
     __syncthreads();
     while ((uint64_t)c * kGroupChunk < L.count) {
-        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);  // next chunk, fetched early
+        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd, gridDim.x);  // next chunk, fetched early
         const uint32_t end = min((uint32_t)L.count, (c + 1) * kGroupChunk);
         for (uint32_t d = c * kGroupChunk; d < end; ++d) {
             const dyad_rec r = load_rec(L.dyads + d);
@@ -1217,12 +1218,12 @@ __attribute__((amdgpu_waves_per_eu(hub_waves_per_simd<TILE>(), hub_waves_per_sim
     uint32_t since = 0;
     const uint32_t xcd = blockIdx.x % kXcds;
     // task groups g0 + k, k taken from the counters, below g1 (<= ngroups)
-    if (threadIdx.x == 0) s_next = g0 + take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) s_next = g0 + take_chunk(ctr, xcd, gridDim.x);
     __syncthreads();
     uint32_t c = s_next;
     __syncthreads();
     while (c < g1) {
-        if (threadIdx.x == 0) s_next = g0 + take_chunk(ctr, xcd);
+        if (threadIdx.x == 0) s_next = g0 + take_chunk(ctr, xcd, gridDim.x);
         const uint32_t t0 = tasks[c].group, t1 = c + 1 < ngroups ? tasks[c + 1].group : ntasks;
         hub_chunk_run<TILE>(tasks, t0, t1, L.dyads, L.nbr, L.tpre, L.n, L.u_lo, L.u_hi, L.per_dyad, S, T, h, since);
         c = s_next;
@@ -1272,11 +1273,11 @@ __global__ __launch_bounds__(kWaveB) void k_tri_wave(tri_args L, unsigned int* c
     __syncthreads();
     const uint32_t xcd = blockIdx.x % kXcds;
     uint32_t c = 0;
-    if (threadIdx.x == 0) c = take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) c = take_chunk(ctr, xcd, gridDim.x);
     c = __shfl(c, 0, 64);
     while ((uint64_t)c * kWaveChunk < L.count) {
         uint32_t cn = 0;
-        if (threadIdx.x == 0) cn = take_chunk(ctr, xcd);      // next chunk, fetched early
+        if (threadIdx.x == 0) cn = take_chunk(ctr, xcd, gridDim.x);      // next chunk, fetched early
         const uint32_t end = min(L.count, (c + 1) * kWaveChunk);
         for (uint32_t d = c * kWaveChunk; d < end; ++d) {
             const edge_rec r = load_edge(L.recs + d);
@@ -1298,12 +1299,12 @@ __global__ __launch_bounds__(B) void k_tri_group(tri_args L, unsigned int* ctr) 
     tri_sig<Lab> sig{n};
     sig.clear(B);
     const uint32_t xcd = blockIdx.x % kXcds;
-    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd, gridDim.x);
     __syncthreads();
     uint32_t c = s_next;
     __syncthreads();
     while ((uint64_t)c * kGroupChunk < L.count) {
-        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);  // next chunk, fetched early
+        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd, gridDim.x);  // next chunk, fetched early
         const uint32_t end = min(L.count, (c + 1) * kGroupChunk);
         for (uint32_t d = c * kGroupChunk; d < end; ++d) {
             const edge_rec r = load_edge(L.recs + d);
@@ -1346,7 +1347,7 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 :
     const uint32_t units = heavy + (ntasks - heavy + kTriLightTasks - 1) / kTriLightTasks;
     while (u < units) {
         uint32_t next = 0;
-        if (__lane_id() == 0) next = waves + take_chunk(ctr, xcd);    // fetched early
+        if (__lane_id() == 0) next = waves + take_chunk(ctr, xcd, gridDim.x);    // fetched early
         uint32_t k = u < heavy ? u : heavy + (u - heavy) * kTriLightTasks;
         const uint32_t last = u < heavy ? u + 1 : min(k + kTriLightTasks, ntasks);
         for (; k < last; ++k) {
@@ -1417,12 +1418,12 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(kTriWaves
             atomicAdd(&batch_acc(accs, cur)[threadIdx.x], bins[threadIdx.x]);
         __syncthreads();
     };
-    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd, gridDim.x);
     __syncthreads();
     uint32_t idx = s_next;
     __syncthreads();
     while (idx < count) {
-        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd);
+        if (threadIdx.x == 0) s_next = take_chunk(ctr, xcd, gridDim.x);
         const work_item it = items[idx];
         if (it.graph != cur) {
             if (cur != 0xffffffffu) flush();
@@ -1463,12 +1464,12 @@ k_census_batch_hub(
     const uint32_t item0 = nums[0], count = nums[1];
     const uint32_t xcd = blockIdx.x % kXcds;
     uint32_t cur = 0xffffffffu, since = 0;
-    if (threadIdx.x == 0) s_next = item0 + take_chunk(ctr, xcd);
+    if (threadIdx.x == 0) s_next = item0 + take_chunk(ctr, xcd, gridDim.x);
     __syncthreads();
     uint32_t idx = s_next;
     __syncthreads();
     while (idx < count) {
-        if (threadIdx.x == 0) s_next = item0 + take_chunk(ctr, xcd);
+        if (threadIdx.x == 0) s_next = item0 + take_chunk(ctr, xcd, gridDim.x);
         const work_item it = items[idx];
         if (it.graph != cur) {
             if (cur != 0xffffffffu) {
@@ -1540,12 +1541,12 @@ __global__ __launch_bounds__(kBatchB) __attribute__((amdgpu_waves_per_eu(batch_m
     const uint32_t xcd = blockIdx.x % kXcds;
     const uint32_t tid = threadIdx.x;
     uint32_t cur = 0xffffffffu;
-    if (tid == 0) s_next = first + take_chunk(ctr, xcd);
+    if (tid == 0) s_next = first + take_chunk(ctr, xcd, gridDim.x);
     __syncthreads();
     uint32_t idx = s_next;
     __syncthreads();
     while (idx < count) {
-        if (tid == 0) s_next = first + take_chunk(ctr, xcd);
+        if (tid == 0) s_next = first + take_chunk(ctr, xcd, gridDim.x);
         const work_item it = items[idx];
         if (it.graph != cur) {
             if (cur != 0xffffffffu) {

@@ -103,3 +103,36 @@ def test_hub_keys_wider_than_a_word(ctx):
             g.release()
     finally:
         ctx.set_tuning(**default)
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 7, 8, 64, 65])
+def test_small_grids(ctx, blocks):
+    # grids of fewer workgroups than there are work counters (8), and about
+    # 4 x 258 hub tasks: on either side of 16 per wavefront of the grid
+    n = 33000
+    i = np.arange(n)
+    pairs = np.concatenate([np.stack([i, (i + d) % n], 1) for d in (1, 2, 3, 4, 5, 6, 7, 8)])
+    default = ctx.get_tuning()
+    grids = {k: blocks for k in default if k.endswith("_blocks")}
+    try:
+        ctx.set_tuning(**grids)
+        _check(ctx, n, pairs, blocks, "grid")
+        ctx.set_tuning(t0=4, t1=20, t_hub=BIG)    # wave and group records
+        _check(ctx, n, pairs, blocks, "grid, wave and group modes")
+    finally:
+        ctx.set_tuning(**default)
+
+
+@pytest.mark.parametrize("blocks", [1, 7])
+def test_small_grids_over_dyads(ctx, blocks):
+    n = 2000
+    i = np.arange(n)
+    pairs = np.concatenate([np.stack([i, (i + d) % n], 1) for d in (1, 2, 3, 4, 5, 6, 7, 8)])
+    default = ctx.get_tuning()
+    try:
+        ctx.set_tuning(tri=0, **{k: blocks for k in default if k.endswith("_blocks")})
+        _check(ctx, n, pairs, blocks, "grid over dyads")
+        ctx.set_tuning(t0=4, t1=20, t_hub=BIG)
+        _check(ctx, n, pairs, blocks, "grid over dyads, wave and group modes")
+    finally:
+        ctx.set_tuning(**default)
