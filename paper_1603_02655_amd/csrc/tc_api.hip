@@ -38,12 +38,13 @@ census_slices full_slices(const device_graph& g, bool tri) {
     return sl;
 }
 
-census_config config_of(const tc_tuning& t) {
+census_config config_of(const tc_tuning& t, int cu_count) {
     census_config c;
     c.lane_blocks = t.lane_blocks;
     c.wave_blocks = t.wave_blocks;
     c.group_blocks = t.group_blocks;
     c.hub_blocks = t.hub_blocks;
+    c.tri_blocks = tri_blocks(t.hub_blocks, cu_count);
     c.hub_tile = t.hub_tile;
     c.wave_tile = t.wave_tile;
     c.group_tile = t.group_tile;
@@ -96,7 +97,7 @@ void fill_info(const tc_graph_s* g, tc_graph_info* info) {
 int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_slices& sl,
                       unsigned long long* raw, int table, bool tri) {
     hipEvent_t* ev = ctx->timing ? ctx->ev : nullptr;
-    census_config cfg = config_of(ctx->tuning);
+    census_config cfg = config_of(ctx->tuning, ctx->cu_count);
     cfg.side_blocks = (uint32_t)ctx->cu_count;
     hipError_t e = ctx->acc_clear ? hipSuccess : census_clear(ctx->acc, kAccWords, ctx->counters, ctx->stream);
     const census_kind kind = table == 0 ? kClasses : table == kAllCodes ? kLabelled : kLabelledPass;
@@ -519,7 +520,7 @@ int tc_census_each_noalloc(tc_context ctx, const tc_graph* graphs, int32_t count
     unsigned int* ctr = reinterpret_cast<unsigned int*>(ctx->scratch);
     unsigned long long* accs =
         reinterpret_cast<unsigned long long*>(static_cast<unsigned char*>(ctx->scratch) + kNoAllocCounterBytes);
-    census_config cfg = config_of(ctx->tuning);
+    census_config cfg = config_of(ctx->tuning, ctx->cu_count);
     cfg.side_blocks = (uint32_t)ctx->cu_count;
     // every graph's launch sequence leaves the accumulators and the counters
     // zero for the next; the stream orders the graphs

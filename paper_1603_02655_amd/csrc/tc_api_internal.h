@@ -62,7 +62,7 @@ namespace tc {
 int status_from_hip(hipError_t e);
 void finalize_counts(int64_t n, const unsigned long long* raw, uint64_t out[16]);
 census_slices full_slices(const device_graph& g, bool tri = false);
-census_config config_of(const tc_tuning& t);
+census_config config_of(const tc_tuning& t, int cu_count);
 void fill_info(const tc_graph_s* g, tc_graph_info* info);
 // Runs the bucket kernels over `sl` with table `table` (0: 16 classes; 1..3:
 // labelled census pass for f_uv = table, 16 sums; kAllCodes: 64 code sums,

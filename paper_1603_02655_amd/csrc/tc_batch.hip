@@ -23,7 +23,7 @@ struct batch_plan {
     unsigned long long* h_accs = nullptr;   // pinned
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    uint32_t grid = 0, hub_grid = 0, tri_grid = 0;
+    uint32_t grid = 0, hub_grid = 0, tri_grid = 0, hub_blocks = 0;
     uint32_t hub_tile = 0, batch_tile = 0;  // LDS tiles the captured kernels use
     bool valid = false;                     // buffers describe `graphs`
     bool tri = false;                       // ... through their forward lists
@@ -172,7 +172,7 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
     hipError_t e = hipSuccess;
     const bool tri = ctx->tuning.tri != 0;
     if (!(p->valid && p->graphs == want && p->grid == ctx->tuning.batch_blocks &&
-          std::max(p->hub_grid, p->tri_grid) == ctx->tuning.hub_blocks && p->hub_tile == ctx->tuning.hub_tile &&
+          p->hub_blocks == ctx->tuning.hub_blocks && p->hub_tile == ctx->tuning.hub_tile &&
           p->batch_tile == ctx->tuning.batch_tile && p->tri == tri)) {
         item_lists lists;
         std::vector<graph_desc> descs(count);
@@ -182,7 +182,8 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
             append_items(g, (uint32_t)i, tri && g.tri.fptr, lists);
         }
         // a hub kernel runs when it has items (one of them also when neither has)
-        const uint32_t tri_grid = lists.hub.empty() || !lists.tri.empty() ? ctx->tuning.hub_blocks : 0;
+        const uint32_t tri_grid =
+            lists.hub.empty() || !lists.tri.empty() ? tri_blocks(ctx->tuning.hub_blocks, ctx->cu_count) : 0;
         const uint32_t hub_grid = lists.hub.empty() ? 0 : ctx->tuning.hub_blocks;
         uint32_t nums[3];
         std::vector<work_item>& items = lists.join(nums);
@@ -202,6 +203,7 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
             return status_from_hip(e);
         }
         p->graphs = want;
+        p->hub_blocks = ctx->tuning.hub_blocks;
         p->valid = true;
         p->tri = tri;
     }

@@ -1,5 +1,7 @@
 // Census kernel launch interface (definitions in tc_census.hip).
 #pragma once
+#include <algorithm>
+
 #include "tc_build.h"
 
 namespace tc {
@@ -9,12 +11,22 @@ struct census_config {
     uint32_t wave_blocks = 8192;    // resident one-wave workgroups of the wave kernel
     uint32_t group_blocks = 1024;   // resident workgroups of the group kernel
     uint32_t hub_blocks = 1024;     // resident workgroups of the hub kernel
+    uint32_t tri_blocks = 1024;     // the same over edge records, when every workgroup has many tasks
     uint32_t side_blocks = 256;     // workgroups of the totals pass when it runs on the side stream
     uint32_t hub_tile = 1024;       // anchor entries per LDS tile, hub mode (512, 1024, 2048)
     uint32_t wave_tile = 1024;      // row entries staged per round, wave mode (512, 1024, 2048)
     uint32_t group_tile = 4096;     // row entries staged per round, group mode (2048, 4096, 8192)
     uint32_t group_size = 256;      // threads per workgroup, group mode (256, 512)
 };
+
+// Workgroups of the hub kernels over edge records with many tasks each: four
+// per CU.  Five fit; four are faster, since they leave registers for the lane
+// bucket, the terms and a batch's other items that run beside them, and none
+// waits for another to end (R-MAT 2^20: 8 per CU 0.894 ms, 5 0.876, 4 0.875, 3
+// 0.892; a batch of 512 R-MAT graphs: 0.787, 0.787, 0.757, 0.849).
+inline uint32_t tri_blocks(uint32_t hub_blocks, int cu_count) {
+    return std::min(hub_blocks, 4u * (uint32_t)(cu_count > 0 ? cu_count : 256));
+}
 
 // Whether the kernels are built for these LDS tiles and group size.
 bool tile_supported(uint32_t hub_tile, uint32_t wave_tile, uint32_t group_tile, uint32_t group_size,
