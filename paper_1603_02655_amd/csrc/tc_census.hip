@@ -1328,37 +1328,134 @@ constexpr uint32_t kTriWaves = kTriB / 64;
 // registers) measure the same, seven spill (R-MAT 2^20: 0.89, 0.89, 0.93 ms).
 constexpr int kTriWavesPerSimd = 5;
 
+// The LDS of a hub workgroup.
 template <bool Lab>
-__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 : kTriWavesPerSimd))) void k_tri_hub(tri_args L, const tri_task* __restrict__ tasks, uint32_t ntasks,
-                                                   uint32_t heavy, unsigned int* ctr) {
-    __shared__ uint4 tab[kTriWaves][tri_table<Lab>::kWords / 4];
-    __shared__ uint32_t starts[kTriWaves][kTriSegment / 32];
-    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[tri_bins<Lab>::kWords];
-    __shared__ uint8_t T[64];
+struct tri_lds {
+    uint4 tab[kTriWaves][tri_table<Lab>::kWords / 4];
+    uint32_t starts[kTriWaves][kTriSegment / 32];
+};
+
+// The tasks that this wavefront of workgroup `block` (of `blocks`) takes.
+template <bool Lab>
+__device__ inline void tri_tasks(const uint4* __restrict__ recs, const uint32_t* __restrict__ fwd,
+                                 const tri_task* __restrict__ tasks, uint32_t ntasks, uint32_t heavy,
+                                 unsigned int* ctr, uint32_t block, uint32_t blocks, tri_lds<Lab>& S,
+                                 tri_sig<Lab>& sig) {
     const uint32_t wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (threadIdx.x < 64) T[threadIdx.x] = L.table[threadIdx.x];
-    tri_sig<Lab> sig{n};
-    sig.clear(kTriB);
-    __syncthreads();
     tri_counts cnt;
     cnt.clear();
-    const uint32_t xcd = blockIdx.x % kXcds, waves = gridDim.x * kTriWaves;
-    uint32_t u = blockIdx.x * kTriWaves + wid;                // the first unit needs no counter
+    const uint32_t xcd = block % kXcds, waves = blocks * kTriWaves;
+    uint32_t u = block * kTriWaves + wid;                     // the first unit needs no counter
     const uint32_t units = heavy + (ntasks - heavy + kTriLightTasks - 1) / kTriLightTasks;
     while (u < units) {
         uint32_t next = 0;
-        if (__lane_id() == 0) next = waves + take_chunk(ctr, xcd, gridDim.x);    // fetched early
+        if (__lane_id() == 0) next = waves + take_chunk(ctr, xcd, blocks);    // fetched early
         uint32_t k = u < heavy ? u : heavy + (u - heavy) * kTriLightTasks;
         const uint32_t last = u < heavy ? u + 1 : min(k + kTriLightTasks, ntasks);
         for (; k < last; ++k) {
             const tri_task t = tasks[k];
-            tri_run<Lab>(L.recs, L.fwd, t.begin, t.end, t.by, t.ey, reinterpret_cast<uint32_t*>(tab[wid]), starts[wid],
-                         sig, cnt);
+            tri_run<Lab>(recs, fwd, t.begin, t.end, t.by, t.ey, reinterpret_cast<uint32_t*>(S.tab[wid]),
+                         S.starts[wid], sig, cnt);
         }
         u = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
     }
     if constexpr (!Lab) cnt.flush(sig);
+}
+
+template <bool Lab>
+__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 : kTriWavesPerSimd))) void k_tri_hub(
+    tri_args L, const tri_task* __restrict__ tasks, uint32_t ntasks, uint32_t heavy, unsigned int* ctr) {
+    __shared__ tri_lds<Lab> S;
+    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[tri_bins<Lab>::kWords];
+    __shared__ uint8_t T[64];
+    if (threadIdx.x < 64) T[threadIdx.x] = L.table[threadIdx.x];
+    tri_sig<Lab> sig{n};
+    sig.clear(kTriB);
+    __syncthreads();
+    tri_tasks<Lab>(L.recs, L.fwd, tasks, ntasks, heavy, ctr, blockIdx.x, gridDim.x, S, sig);
     tri_end<Lab>(sig, kTriB, bins, T, L.acc);
+}
+
+// A whole census of the 16 classes in one launch: the first workgroups run the
+// hub tasks, the next the lane bucket, the others the rows' terms, and the last
+// one to end writes the sums.
+struct one_args {
+    tri_args lane;               // its accumulators and table serve all
+    const uint4* recs;           // hub records
+    const tri_task* tasks;
+    uint32_t ntasks, heavy, hub_blocks, lane_blocks;
+    const uint4* rinfo;
+    uint32_t x0, x1;
+    uint64_t n, asym, mutual;
+    unsigned int* counters;
+    unsigned long long* out;
+};
+
+// True in the workgroup that calls it last.  Two levels of counters, since
+// adds to one line take about 12 ns each.  Nobody waits.
+__device__ inline bool last_to_end(unsigned int* ctr, unsigned int* top) {
+    __shared__ uint32_t s_last;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t g = blockIdx.x % kXcds, members = (gridDim.x - g + kXcds - 1) / kXcds;
+        bool last = atomicAdd(&ctr[g * kCounterStride], 1u) + 1 == members;
+        if (last) last = atomicAdd(top, 1u) + 1 == min(gridDim.x, (uint32_t)kXcds);
+        s_last = last;
+    }
+    __syncthreads();
+    return s_last != 0;
+}
+
+__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(kTriWavesPerSimd))) void k_tri_one(one_args A) {
+    __shared__ tri_lds<false> S;
+    __shared__ unsigned long long n[tri_sig<false>::kSlots], bins[kNumClasses], sums[kTriB];
+    __shared__ uint8_t T[64];
+    if (threadIdx.x < 64) T[threadIdx.x] = A.lane.table[threadIdx.x];
+    if (threadIdx.x < kNumClasses) bins[threadIdx.x] = 0;
+    tri_sig<false> sig{n};
+    sig.clear(kTriB);
+    tri_bins<false> h{bins};
+    __syncthreads();
+    const uint32_t rows = A.hub_blocks + A.lane_blocks;
+    if (blockIdx.x < rows) {
+        if (blockIdx.x < A.hub_blocks) {
+            tri_tasks<false>(A.recs, A.lane.fwd, A.tasks, A.ntasks, A.heavy,
+                             A.counters + kBucketHub * kCounterWords, blockIdx.x, A.hub_blocks, S, sig);
+        } else {
+            for (uint32_t d = (blockIdx.x - A.hub_blocks) * kTriB + threadIdx.x; d < A.lane.count;
+                 d += A.lane_blocks * kTriB)
+                lane_edge<false>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
+        }
+        tri_flush<false>(sig, kTriB, T, h);
+    } else {
+        unsigned long long s[kRowSums] = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (blockIdx.x == rows && threadIdx.x == 0) {
+            s[0] = A.n * A.asym;
+            s[1] = A.n * A.mutual;
+        }
+        for (uint64_t x = (uint64_t)A.x0 + (uint64_t)(blockIdx.x - rows) * kTriB + threadIdx.x; x < A.x1;
+             x += (uint64_t)(gridDim.x - rows) * kTriB)
+            row_add(A.rinfo, (uint32_t)x, s);
+        row_flush(s, T, h);
+        __syncthreads();
+    }
+    // The old value is waited for, so that the sum is in place before the
+    // workgroup says that it has ended; the last one reads with atomics too.
+    if (threadIdx.x < kNumClasses && bins[threadIdx.x] != 0) {
+        const unsigned long long old = atomicAdd(&acc_copy(A.lane.acc)[threadIdx.x], bins[threadIdx.x]);
+        asm volatile("" ::"v"(old) : "memory");
+    }
+    if (!last_to_end(A.counters, A.counters + kCounterWords)) return;
+    unsigned long long v = 0;
+    for (int k = threadIdx.x; k < kNumClasses * kAccCopies; k += kTriB) v += atomicExch(&A.lane.acc[k], 0ull);
+    sums[threadIdx.x] = v;
+    if (threadIdx.x < kBuckets * kXcds) A.counters[threadIdx.x * kCounterStride] = 0;
+    __syncthreads();
+    if (threadIdx.x < kNumClasses) {
+        unsigned long long s = 0;
+        for (int c = threadIdx.x; c < kTriB; c += kNumClasses) s += sums[c];
+        A.out[threadIdx.x] = s;
+    }
 }
 
 // --------------------------------------------------------------- batch ----
@@ -1775,6 +1872,14 @@ void launch_hub(const census_args& L, const hub_task* tasks, uint32_t ntasks, ui
         hipLaunchKernelGGL((k_census_hub<2048>), grid, dim3(kHubB), 0, s, L, tasks, ntasks, ngroups, g0, g1, c);
 }
 
+// Workgroups for nt hub tasks of the edge records.  Below 16 tasks per wave of
+// tri_blocks, more of them even out the ends (R-MAT 50021 with 3.8 tasks per
+// wave: 0.093 ms and 0.0905 ms).
+uint32_t tri_grid(uint32_t nt, const census_config& cfg) {
+    const uint32_t wgs = (nt + kTriWaves - 1) / kTriWaves;
+    return std::min(wgs, wgs >= 16 * (uint64_t)cfg.tri_blocks ? cfg.tri_blocks : cfg.hub_blocks);
+}
+
 // Edge records of bucket b; for the hub bucket, the tasks [g0, g1).
 template <bool Lab>
 void launch_tri(int b, const tri_args& L, const rec_set<uint4, tri_task>& edges, uint32_t g0, uint32_t g1,
@@ -1801,12 +1906,51 @@ void launch_tri(int b, const tri_args& L, const rec_set<uint4, tri_task>& edges,
         }
     } else {
         const uint32_t nt = g1 - g0, heavy = std::min(nt, edges.n_heavy > g0 ? edges.n_heavy - g0 : 0u);
-        // (below 16 tasks per wave of tri_blocks, more workgroups even out the
-        // ends: R-MAT 50021 with 3.8 tasks per wave, 0.093 ms and 0.0905 ms)
-        const uint32_t wgs = (nt + kTriWaves - 1) / kTriWaves;
-        const dim3 grid(std::min(wgs, wgs >= 16 * (uint64_t)cfg.tri_blocks ? cfg.tri_blocks : cfg.hub_blocks));
+        const dim3 grid(tri_grid(nt, cfg));
         hipLaunchKernelGGL((k_tri_hub<Lab>), grid, dim3(kTriB), 0, s, L, (const tri_task*)edges.tasks + g0, nt, heavy, c);
     }
+}
+
+// Launches k_tri_one if the census is one for it: whole rows' terms, no wave or
+// group records and no events between the kernels.  Without hub work the lane
+// bucket is the census, and runs eight waves per SIMD in its own kernel, five in
+// this one: up to 4096 workgroups the launches cost more (sparse graphs of 4
+// arcs per vertex, separate and one: 2000 vertices 22.8 and 19.2 us, 60 k 23.5
+// and 20.3, 150 k with 1650 lane workgroups 26.4 and 24.1, 400 k with 4402 37.2
+// and 36.5, 3 M 192 and 198).  When the hub tasks stream more than the graph has
+// entries the lane bucket runs beside them, and one launch needs no second
+// stream and no events for that (skewed graphs of 12 arcs per vertex: 20 k
+// vertices 50.3 and 31.4 us, 150 k 115 and 86.5, 1 M 416 and 397; R-MAT 50021 88
+// and 62, 2^20 881 and 863).
+constexpr uint32_t kOneLanes = 4096;
+bool launch_one(const device_graph& g, const census_slices& sl, uint32_t g0, uint32_t g1, const uint8_t* table,
+                unsigned long long* acc, unsigned int* counters, unsigned long long* out, const census_config& cfg,
+                hipEvent_t* ev, hipStream_t s) {
+    const uint64_t lanes = sl.end[0] > sl.begin[0] ? sl.end[0] - sl.begin[0] : 0;
+    if (ev || sl.per_dyad || g.p == 0 || sl.end[1] > sl.begin[1] || sl.end[2] > sl.begin[2] ||
+        (lanes > kOneLanes * (uint64_t)kTriB && g.tri.edges.stream <= g.U))
+        return false;
+    const rec_set<uint4, tri_task>& edges = g.tri.edges;
+    one_args A;
+    A.lane = tri_args{edges.recs + sl.begin[0], (uint32_t)lanes, g.tri.fwd, acc, table};
+    A.recs = edges.recs;
+    A.tasks = (const tri_task*)edges.tasks + g0;
+    A.ntasks = g1 - g0;
+    A.heavy = std::min(A.ntasks, edges.n_heavy > g0 ? edges.n_heavy - g0 : 0u);
+    A.hub_blocks = A.ntasks ? tri_grid(A.ntasks, cfg) : 0;
+    A.lane_blocks = (uint32_t)((lanes + kTriB - 1) / kTriB);
+    A.rinfo = g.rinfo;
+    A.x0 = sl.row_begin;
+    A.x1 = sl.row_end;
+    A.n = (uint64_t)g.n;
+    A.asym = sl.asym;
+    A.mutual = sl.mutual;
+    A.counters = counters;
+    A.out = out;
+    const uint64_t rows = sl.row_end - sl.row_begin;
+    const uint32_t rw = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((rows + kTriB - 1) / kTriB, cfg.side_blocks));
+    hipLaunchKernelGGL(k_tri_one, dim3(A.hub_blocks + A.lane_blocks + rw), dim3(kTriB), 0, s, A);
+    return true;
 }
 
 }  // namespace
@@ -1827,6 +1971,8 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
     // The terms without intersection and the lane bucket wait on memory:
     // beside the hub kernel, they use what it leaves (only when the hub kernel
     // has more to stream than the graph has entries).
+    if (tri && kind == kClasses && launch_one(g, sl, hg0, hg1, table, acc, counters, out, cfg, ev, s))
+        return hipGetLastError();
     const bool beside = tri && side != nullptr && fork != nullptr && g.tri.edges.stream > g.U;
     hipStream_t ts = s;
     if (beside) {
