@@ -461,41 +461,61 @@ struct global_bins {
 
 // Per-lane bins over a few slots: the totals pass reaches only the bins of the
 // codes f, f | t << 2 and f | t << 4 (f, t in 1..3), so a lane keeps one 64-bit
-// slot per reachable bin.  The codes are remapped to slots in a table.
+// slot per reachable bin (or two lanes of a workgroup share one: COLS columns).
+// The codes are remapped to slots in a table.
+template <uint32_t COLS>
 struct slot_bins {
-    unsigned long long* bins;   // slots x kLaneB
+    unsigned long long* bins;   // slots x COLS
     __device__ inline void add(uint32_t slot, unsigned long long x) {
-        atomicAdd(&bins[slot * kLaneB + threadIdx.x], x);
+        atomicAdd(&bins[slot * COLS + (threadIdx.x & (COLS - 1))], x);
     }
 };
 
+// The k-th of the 21 reachable codes: f, f | t << 2 (t = 1..3), f | t << 4.
+__device__ inline uint32_t totals_code(uint32_t k) {
+    const uint32_t f = 1 + k / 7, j = k % 7;
+    return j == 0 ? f : (j <= 3 ? f | (j << 2) : f | ((j - 3) << 4));
+}
+
 // Fills TS (code -> slot) and bin_of_slot for the reachable codes of table T;
-// returns the number of slots.  One thread.
-template <uint32_t SLOTS>
+// returns the number of slots.  The forward-list path's table tells all codes
+// apart, so each has its slot, and a thread writes each (one thread that looks
+// for equal bins takes 12 us, as long as the entries of a small graph); a pass
+// table's codes share bins, found by one thread.
+template <bool Lab>
 __device__ inline uint32_t totals_slots(const uint8_t* T, uint8_t* TS, uint32_t* bin_of_slot) {
-    uint32_t ns = 0;
-    for (uint32_t c = 0; c < 64; ++c) TS[c] = 0xff;
-    for (uint32_t f = 1; f < 4; ++f)
-        for (uint32_t j = 0; j < 7; ++j) {
-            const uint32_t c = j == 0 ? f : (j <= 3 ? f | (j << 2) : f | ((j - 3) << 4));
-            uint32_t sl = 0;
-            while (sl < ns && bin_of_slot[sl] != T[c]) ++sl;
-            if (sl == ns && ns < SLOTS) bin_of_slot[ns++] = T[c];
-            TS[c] = (uint8_t)sl;
+    constexpr uint32_t kSlots = totals_slot_count<Lab>();
+    if constexpr (Lab) {
+        if (threadIdx.x < kSlots) {
+            const uint32_t c = totals_code(threadIdx.x);
+            TS[c] = (uint8_t)threadIdx.x;
+            bin_of_slot[threadIdx.x] = T[c];
         }
-    return ns;
+        return kSlots;
+    } else {
+        uint32_t ns = 0;
+        if (threadIdx.x == 0)
+            for (uint32_t k = 0; k < 21; ++k) {
+                const uint32_t c = totals_code(k);
+                uint32_t sl = 0;
+                while (sl < ns && bin_of_slot[sl] != T[c]) ++sl;
+                if (sl == ns && ns < kSlots) bin_of_slot[ns++] = T[c];
+                TS[c] = (uint8_t)sl;
+            }
+        return ns;
+    }
 }
 
 // Sums the per-lane slots over a kLaneB workgroup into h (wavefront w takes
 // slots w, w + 4), without those of bins from `bins` on (the discard bin).
-template <class H>
+template <uint32_t COLS, class H>
 __device__ inline void slots_flush(unsigned long long* sbins, const uint32_t* bin_of_slot, uint32_t nslots,
                                    uint32_t bins, H& h) {
     __syncthreads();
     const uint32_t lane = threadIdx.x & 63u;
     for (uint32_t sl = threadIdx.x >> 6; sl < nslots; sl += kLaneB / 64) {
         unsigned long long v = 0;
-        for (uint32_t i = lane; i < kLaneB; i += 64) v += sbins[sl * kLaneB + i];
+        for (uint32_t i = lane; i < COLS; i += 64) v += sbins[sl * COLS + i];
         for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
         if (lane == 0 && v != 0 && bin_of_slot[sl] < bins) h.add(bin_of_slot[sl], v);
     }
@@ -515,15 +535,16 @@ __global__ __launch_bounds__(kLaneB) void k_census_totals(const uint32_t* __rest
     __shared__ uint32_t bin_of_slot[kSlots], s_nslots;
     if (threadIdx.x < 64) T[threadIdx.x] = table[threadIdx.x];
     __syncthreads();
-    if (threadIdx.x == 0) s_nslots = totals_slots<kSlots>(T, TS, bin_of_slot);
+    const uint32_t ns = totals_slots<Lab>(T, TS, bin_of_slot);
+    if (threadIdx.x == 0) s_nslots = ns;
     for (uint32_t k = threadIdx.x; k < kSlots * kLaneB; k += kLaneB) sbins[k] = 0;
     __syncthreads();
-    slot_bins hs{sbins};
+    slot_bins<kLaneB> hs{sbins};
     for (uint64_t base = (uint64_t)blockIdx.x * kLaneB * kTotalsPer; base < U;
          base += (uint64_t)gridDim.x * kLaneB * kTotalsPer)
         totals_entries<kTotalsPer, kLaneB>(base, U, nbr, owner, rinfo, tpre, n, TS, hs);
     global_bins g{acc_copy(acc, kWords)};
-    slots_flush(sbins, bin_of_slot, s_nslots, kWords, g);
+    slots_flush<kLaneB>(sbins, bin_of_slot, s_nslots, kWords, g);
 }
 
 // ---------------------------------------------------------- merge path ----
@@ -1376,8 +1397,8 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 :
     tri_end<Lab>(sig, kTriB, bins, T, L.acc);
 }
 
-// A whole census of the 16 classes in one launch: the first workgroups run the
-// hub tasks, the next the lane bucket, the others the rows' terms, and the last
+// A whole census in one launch: the first workgroups run the hub tasks, the
+// next the lane bucket, the others the terms without intersection, and the last
 // one to end writes the sums.
 struct one_args {
     tri_args lane;               // its accumulators and table serve all
@@ -1385,7 +1406,11 @@ struct one_args {
     const tri_task* tasks;
     uint32_t ntasks, heavy, hub_blocks, lane_blocks;
     const uint4* rinfo;
-    uint32_t x0, x1;
+    uint32_t x0, x1;             // rows of the terms (16 classes)
+    const uint32_t* nbr;         // entries of the terms (64 codes)
+    const uint32_t* owner;
+    const uint64_t* tpre;
+    uint64_t U;
     uint64_t n, asym, mutual;
     unsigned int* counters;
     unsigned long long* out;
@@ -1406,54 +1431,76 @@ __device__ inline bool last_to_end(unsigned int* ctr, unsigned int* top) {
     return s_last != 0;
 }
 
-__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(kTriWavesPerSimd))) void k_tri_one(one_args A) {
-    __shared__ tri_lds<false> S;
-    __shared__ unsigned long long n[tri_sig<false>::kSlots], bins[kNumClasses], sums[kTriB];
+// The labelled terms' slots take the place of the hub tables (two lanes to a
+// column, 21 KB).
+constexpr uint32_t kOneCols = kTriB / 2;
+static_assert(kTriB == kLaneB, "the terms' steps are of kLaneB threads");
+
+template <bool Lab>
+__global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 : kTriWavesPerSimd))) void k_tri_one(
+    one_args A) {
+    constexpr uint32_t kWords = tri_bins<Lab>::kWords, kSlots = totals_slot_count<Lab>();
+    __shared__ tri_lds<Lab> S;
+    __shared__ unsigned long long n[tri_sig<Lab>::kSlots], bins[kWords], sums[kTriB];
     __shared__ uint8_t T[64];
     if (threadIdx.x < 64) T[threadIdx.x] = A.lane.table[threadIdx.x];
-    if (threadIdx.x < kNumClasses) bins[threadIdx.x] = 0;
-    tri_sig<false> sig{n};
+    if (threadIdx.x < kWords) bins[threadIdx.x] = 0;
+    tri_sig<Lab> sig{n};
     sig.clear(kTriB);
-    tri_bins<false> h{bins};
+    tri_bins<Lab> h{bins};
     __syncthreads();
-    const uint32_t rows = A.hub_blocks + A.lane_blocks;
-    if (blockIdx.x < rows) {
+    const uint32_t terms = A.hub_blocks + A.lane_blocks;
+    if (blockIdx.x < terms) {
         if (blockIdx.x < A.hub_blocks) {
-            tri_tasks<false>(A.recs, A.lane.fwd, A.tasks, A.ntasks, A.heavy,
-                             A.counters + kBucketHub * kCounterWords, blockIdx.x, A.hub_blocks, S, sig);
+            tri_tasks<Lab>(A.recs, A.lane.fwd, A.tasks, A.ntasks, A.heavy, A.counters + kBucketHub * kCounterWords,
+                           blockIdx.x, A.hub_blocks, S, sig);
         } else {
             for (uint32_t d = (blockIdx.x - A.hub_blocks) * kTriB + threadIdx.x; d < A.lane.count;
                  d += A.lane_blocks * kTriB)
-                lane_edge<false>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
+                lane_edge<Lab>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
         }
-        tri_flush<false>(sig, kTriB, T, h);
+        tri_flush<Lab>(sig, kTriB, T, h);
+    } else if constexpr (Lab) {
+        static_assert(sizeof(S.tab) >= sizeof(unsigned long long) * kSlots * kOneCols, "the slots fit");
+        __shared__ uint8_t TS[64];
+        __shared__ uint32_t bin_of_slot[kSlots];
+        unsigned long long* sbins = reinterpret_cast<unsigned long long*>(S.tab);
+        (void)totals_slots<true>(T, TS, bin_of_slot);
+        for (uint32_t k = threadIdx.x; k < kSlots * kOneCols; k += kTriB) sbins[k] = 0;
+        __syncthreads();
+        slot_bins<kOneCols> hs{sbins};
+        for (uint64_t base = (uint64_t)(blockIdx.x - terms) * kTriB * kTotalsPer; base < A.U;
+             base += (uint64_t)(gridDim.x - terms) * kTriB * kTotalsPer)
+            totals_entries<kTotalsPer, kTriB>(base, A.U, A.nbr, A.owner, A.rinfo, A.tpre, A.n, TS, hs);
+        slots_flush<kOneCols>(sbins, bin_of_slot, kSlots, kWords, h);
+        __syncthreads();
     } else {
         unsigned long long s[kRowSums] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (blockIdx.x == rows && threadIdx.x == 0) {
+        if (blockIdx.x == terms && threadIdx.x == 0) {
             s[0] = A.n * A.asym;
             s[1] = A.n * A.mutual;
         }
-        for (uint64_t x = (uint64_t)A.x0 + (uint64_t)(blockIdx.x - rows) * kTriB + threadIdx.x; x < A.x1;
-             x += (uint64_t)(gridDim.x - rows) * kTriB)
+        for (uint64_t x = (uint64_t)A.x0 + (uint64_t)(blockIdx.x - terms) * kTriB + threadIdx.x; x < A.x1;
+             x += (uint64_t)(gridDim.x - terms) * kTriB)
             row_add(A.rinfo, (uint32_t)x, s);
         row_flush(s, T, h);
         __syncthreads();
     }
     // The old value is waited for, so that the sum is in place before the
     // workgroup says that it has ended; the last one reads with atomics too.
-    if (threadIdx.x < kNumClasses && bins[threadIdx.x] != 0) {
-        const unsigned long long old = atomicAdd(&acc_copy(A.lane.acc)[threadIdx.x], bins[threadIdx.x]);
+    if (threadIdx.x < kWords && bins[threadIdx.x] != 0) {
+        const unsigned long long old = atomicAdd(&acc_copy(A.lane.acc, kWords)[threadIdx.x], bins[threadIdx.x]);
         asm volatile("" ::"v"(old) : "memory");
     }
     if (!last_to_end(A.counters, A.counters + kCounterWords)) return;
     unsigned long long v = 0;
-    for (int k = threadIdx.x; k < kNumClasses * kAccCopies; k += kTriB) v += atomicExch(&A.lane.acc[k], 0ull);
+    for (uint32_t k = threadIdx.x; k < kWords * kAccCopies; k += kTriB) v += atomicExch(&A.lane.acc[k], 0ull);
     sums[threadIdx.x] = v;
     if (threadIdx.x < kBuckets * kXcds) A.counters[threadIdx.x * kCounterStride] = 0;
     __syncthreads();
-    if (threadIdx.x < kNumClasses) {
+    if (threadIdx.x < kWords) {
         unsigned long long s = 0;
-        for (int c = threadIdx.x; c < kTriB; c += kNumClasses) s += sums[c];
+        for (uint32_t c = threadIdx.x; c < kTriB; c += kWords) s += sums[c];
         A.out[threadIdx.x] = s;
     }
 }
@@ -1921,9 +1968,10 @@ void launch_tri(int b, const tri_args& L, const rec_set<uint4, tri_task>& edges,
 // entries the lane bucket runs beside them, and one launch needs no second
 // stream and no events for that (skewed graphs of 12 arcs per vertex: 20 k
 // vertices 50.3 and 31.4 us, 150 k 115 and 86.5, 1 M 416 and 397; R-MAT 50021 88
-// and 62, 2^20 881 and 863).
+// and 62, 2^20 881 and 863; labelled, 131071 vertices 152 and 103, 2.5 M 1595 and
+// 1332).
 constexpr uint32_t kOneLanes = 4096;
-bool launch_one(const device_graph& g, const census_slices& sl, uint32_t g0, uint32_t g1, const uint8_t* table,
+bool launch_one(bool lab, const device_graph& g, const census_slices& sl, uint32_t g0, uint32_t g1, const uint8_t* table,
                 unsigned long long* acc, unsigned int* counters, unsigned long long* out, const census_config& cfg,
                 hipEvent_t* ev, hipStream_t s) {
     const uint64_t lanes = sl.end[0] > sl.begin[0] ? sl.end[0] - sl.begin[0] : 0;
@@ -1931,7 +1979,7 @@ bool launch_one(const device_graph& g, const census_slices& sl, uint32_t g0, uin
         (lanes > kOneLanes * (uint64_t)kTriB && g.tri.edges.stream <= g.U))
         return false;
     const rec_set<uint4, tri_task>& edges = g.tri.edges;
-    one_args A;
+    one_args A{};
     A.lane = tri_args{edges.recs + sl.begin[0], (uint32_t)lanes, g.tri.fwd, acc, table};
     A.recs = edges.recs;
     A.tasks = (const tri_task*)edges.tasks + g0;
@@ -1947,9 +1995,22 @@ bool launch_one(const device_graph& g, const census_slices& sl, uint32_t g0, uin
     A.mutual = sl.mutual;
     A.counters = counters;
     A.out = out;
-    const uint64_t rows = sl.row_end - sl.row_begin;
-    const uint32_t rw = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((rows + kTriB - 1) / kTriB, cfg.side_blocks));
-    hipLaunchKernelGGL(k_tri_one, dim3(A.hub_blocks + A.lane_blocks + rw), dim3(kTriB), 0, s, A);
+    if (lab) {
+        A.nbr = g.nbr;
+        A.owner = g.owner;
+        A.tpre = g.tpre;
+        A.U = g.U;
+        // (four per CU, what fits: one and two take 105 to 112 us where four take
+        // 103 on 131071 skewed vertices, 1642 and 1429 where four take 1332 on 2.5 M)
+        const uint32_t tw = (uint32_t)std::min<uint64_t>((g.U + kTotalsPer * kTriB - 1) / (kTotalsPer * kTriB),
+                                                         4 * (uint64_t)cfg.side_blocks);
+        hipLaunchKernelGGL(k_tri_one<true>, dim3(A.hub_blocks + A.lane_blocks + tw), dim3(kTriB), 0, s, A);
+    } else {
+        const uint64_t rows = sl.row_end - sl.row_begin;
+        const uint32_t rw =
+            (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((rows + kTriB - 1) / kTriB, cfg.side_blocks));
+        hipLaunchKernelGGL(k_tri_one<false>, dim3(A.hub_blocks + A.lane_blocks + rw), dim3(kTriB), 0, s, A);
+    }
     return true;
 }
 
@@ -1971,7 +2032,7 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
     // The terms without intersection and the lane bucket wait on memory:
     // beside the hub kernel, they use what it leaves (only when the hub kernel
     // has more to stream than the graph has entries).
-    if (tri && kind == kClasses && launch_one(g, sl, hg0, hg1, table, acc, counters, out, cfg, ev, s))
+    if (tri && kind != kLabelledPass && launch_one(lab, g, sl, hg0, hg1, table, acc, counters, out, cfg, ev, s))
         return hipGetLastError();
     const bool beside = tri && side != nullptr && fork != nullptr && g.tri.edges.stream > g.U;
     hipStream_t ts = s;
