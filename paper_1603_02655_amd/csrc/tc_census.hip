@@ -26,16 +26,20 @@
 //           probed by the other rows.
 // These run over the dyad records.  The forward-list path has kernels of the
 // same four modes over its edge records (k_tri_*, tc_tri.h), where a shared
-// vertex closes a triangle that is credited to its three dyads (on_triangle).
+// vertex closes a triangle that is credited to its three dyads (on_triangle),
+// and the terms without intersection come from a pass over the rows
+// (k_census_rows) or, labelled, over the entries (k_census_totals).  Most
+// censuses on that path are one launch of all of them (k_tri_one).
 // Counts accumulate in LDS bins (per lane, per wavefront, or per signature in
 // the hub mode); each workgroup adds its 16 sums to the graph's accumulators
 // with one 64-bit global atomic per class when it finishes.
 //
 // The class of every code comes from a 64-entry table staged in LDS.  The
-// single-graph kernels take the table as an argument: the 16-class table, or
-// for the labelled (64-class) census one of three pass tables that send the
-// codes whose (u, v) part is f to bin (code >> 2) and every other code to the
-// discard bin (index kNumClasses), which is never flushed.
+// single-graph kernels take the table as an argument: the 16-class table; for
+// the labelled (64-class) census on the forward-list path a table that keeps all
+// codes apart, over the dyad records one of three pass tables that send the codes
+// whose (u, v) part is f to bin (code >> 2) and every other code to the discard
+// bin (index kNumClasses), which is never flushed.
 #include "tc_census.h"
 #include "tc_tri.h"
 
@@ -1346,7 +1350,8 @@ constexpr uint32_t kTriLightTasks = 8;
 constexpr int kTriB = 256;
 constexpr uint32_t kTriWaves = kTriB / 64;
 // Wavefronts per SIMD the hub kernels are compiled for: five or six (96 or 80
-// registers) measure the same, seven spill (R-MAT 2^20: 0.89, 0.89, 0.93 ms).
+// registers) measured the same, seven spill (R-MAT 2^20 with eight workgroups per
+// CU: 0.89, 0.89, 0.93 ms).
 constexpr int kTriWavesPerSimd = 5;
 
 // The LDS of a hub workgroup.
@@ -1399,7 +1404,11 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 :
 
 // A whole census in one launch: the first workgroups run the hub tasks, the
 // next the lane bucket, the others the terms without intersection, and the last
-// one to end writes the sums.
+// one to end writes the sums.  A small census is bound by its launches (of three
+// or four, 24 us for 2000 vertices and 8000 arcs, 19 in one; the copy-free
+// launch and wait for one kernel is most of it); beside the hub tasks the other
+// ranges start as soon as a CU has room for them, without events.  The rule of
+// its use and more times: launch_one.
 struct one_args {
     tri_args lane;               // its accumulators and table serve all
     const uint4* recs;           // hub records
@@ -1455,9 +1464,8 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 :
             tri_tasks<Lab>(A.recs, A.lane.fwd, A.tasks, A.ntasks, A.heavy, A.counters + kBucketHub * kCounterWords,
                            blockIdx.x, A.hub_blocks, S, sig);
         } else {
-            for (uint32_t d = (blockIdx.x - A.hub_blocks) * kTriB + threadIdx.x; d < A.lane.count;
-                 d += A.lane_blocks * kTriB)
-                lane_edge<Lab>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
+            const uint32_t d = (blockIdx.x - A.hub_blocks) * kTriB + threadIdx.x;   // a thread per record
+            if (d < A.lane.count) lane_edge<Lab>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
         }
         tri_flush<Lab>(sig, kTriB, T, h);
     } else if constexpr (Lab) {
@@ -1971,8 +1979,8 @@ void launch_tri(int b, const tri_args& L, const rec_set<uint4, tri_task>& edges,
 // and 62, 2^20 881 and 863; labelled, 131071 vertices 152 and 103, 2.5 M 1595 and
 // 1332).
 constexpr uint32_t kOneLanes = 4096;
-bool launch_one(bool lab, const device_graph& g, const census_slices& sl, uint32_t g0, uint32_t g1, const uint8_t* table,
-                unsigned long long* acc, unsigned int* counters, unsigned long long* out, const census_config& cfg,
+bool launch_one(bool lab, const device_graph& g, const census_slices& sl, uint32_t g0, uint32_t g1,
+                const uint8_t* table, unsigned long long* acc, unsigned int* counters, unsigned long long* out, const census_config& cfg,
                 hipEvent_t* ev, hipStream_t s) {
     const uint64_t lanes = sl.end[0] > sl.begin[0] ? sl.end[0] - sl.begin[0] : 0;
     if (ev || sl.per_dyad || g.p == 0 || sl.end[1] > sl.begin[1] || sl.end[2] > sl.begin[2] ||
@@ -2029,11 +2037,11 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
     const bool lab = tri && kind == kLabelled;
     const uint32_t ngroups = tri ? g.tri.edges.n_tasks : g.n_hub_groups;
     const uint32_t hg0 = std::min(sl.hub_g0, ngroups), hg1 = std::max(hg0, std::min(sl.hub_g1, ngroups));
+    if (tri && kind != kLabelledPass && launch_one(lab, g, sl, hg0, hg1, table, acc, counters, out, cfg, ev, s))
+        return hipGetLastError();
     // The terms without intersection and the lane bucket wait on memory:
     // beside the hub kernel, they use what it leaves (only when the hub kernel
     // has more to stream than the graph has entries).
-    if (tri && kind != kLabelledPass && launch_one(lab, g, sl, hg0, hg1, table, acc, counters, out, cfg, ev, s))
-        return hipGetLastError();
     const bool beside = tri && side != nullptr && fork != nullptr && g.tri.edges.stream > g.U;
     hipStream_t ts = s;
     if (beside) {
@@ -2065,6 +2073,8 @@ hipError_t census_launch(const device_graph& g, const census_slices& sl, bool tr
         }
         if (ev) (void)hipEventRecord(ev[2 * kBuckets + 1], ts);
     };
+    // (dyad records, and forward lists with events between the kernels or with
+    // wave or group records)
     // Beside the hub kernel, a lane bucket of more than two workgroups per CU
     // is launched after it: workgroups that come first keep the hub kernel's
     // waiting (R-MAT 2^20, 1000 lane workgroups: 1.82 ms first, 1.73 after).  A

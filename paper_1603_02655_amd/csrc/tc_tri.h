@@ -144,12 +144,12 @@ __device__ inline void lane_edge(const edge_rec& r, const uint32_t* __restrict__
 // with the code at once, and the codes of 16 entries are packed into one word
 // and counted with AND and bit counts.  No hashing, no candidates, no barriers.
 //
-// What bounds it: no unit by itself (R-MAT 2^20, 0.89 ms for 1.09e9 entries:
-// vector units 53 % busy, texture unit 55 %, 2.9 TB/s of L2 misses), but the
-// chain of a window (marks, record, entries, table) at five wavefronts per
-// SIMD, and a task's start (table and records) on graphs with many short ones.
-// The hash table with candidate rings that it replaces took 1.70 ms there (27
-// vector instructions per entry, now 11) and streamed the whole shorter list
+// What bounds it: no unit by itself (R-MAT 2^20, 0.82 ms for 1.09e9 entries:
+// vector units 58 % busy, texture unit 59 %, 6.1 TB/s of L2 misses, most of them
+// served before HBM), but the chain of a window (marks, record, entries, table)
+// at four wavefronts per SIMD, and a task's start (table and records) on graphs with many short ones.
+// The hash table with candidate rings that it replaces took 1.70 ms there (32
+// vector instructions per entry and lane, now 17) and streamed the whole shorter list
 // of an edge, 1.75e9 entries.
 //
 // kCore = 16384 ranks are 4 KiB of table: 32 wavefronts per CU.  On skewed
