@@ -115,7 +115,8 @@ typedef struct {
     uint32_t group_blocks;   /* resident 256-thread blocks, group kernel */
     uint32_t batch_blocks;   /* resident 256-thread blocks, batched (persistent) kernel */
     uint32_t t_hub;
-    uint32_t hub_blocks;     /* resident 256-thread blocks, hub kernel */
+    uint32_t hub_blocks;     /* resident 256-thread blocks, hub kernel (over edge records with many
+                                tasks at most four per CU) */
     uint32_t tri;            /* 1: whole-graph census through triangles of the forward lists */
     /* LDS tiles and group size (each among the kernel variants the library is built with) */
     uint32_t hub_tile;       /* anchor entries staged per LDS tile, hub mode: 512, 1024, 2048; graphs built
@@ -305,7 +306,8 @@ int tc_graph_rebucket(tc_context ctx, tc_graph g);
 int tc_autotune(tc_context ctx, const tc_graph* sample, int32_t count, const char* cache_path, tc_tuning* best);
 
 /* Kernel timing: when enabled, every census records HIP events around each
- * bucket kernel on the context stream and accumulates their durations. */
+ * bucket kernel on the context stream and accumulates their durations.  Such a
+ * census launches each kernel by itself; without timing most are one launch. */
 int tc_set_timing(tc_context ctx, int enable);
 int tc_get_kernel_stats(tc_context ctx, tc_kernel_stats* out);
 int tc_reset_kernel_stats(tc_context ctx);
