@@ -201,7 +201,7 @@ void scheduler::admit_locked(slot_state& s, int si, double t, std::vector<job*>&
 
 void scheduler::worker_main() {
     std::vector<job*> retired;
-    std::vector<int> abandoned;
+    bool abandoned = false;
     bool idle_released = false;
     std::unique_lock<std::mutex> lk(mu_);
     for (;;) {
@@ -225,12 +225,13 @@ void scheduler::worker_main() {
                 continue;
             }
             if (t - s.t_launch <= lim_.watchdog_ms) continue;
+            ex_->abandon((int)si);
             for (job* j : s.jobs) complete_locked(j, kErrDevice, t, retired);
             s.jobs.clear();
             s.busy = false;
             s.dead = true;
             st_.abandoned_rounds += 1;
-            abandoned.push_back((int)si);
+            abandoned = true;
         }
         bool idle = true, any_live = false;
         for (const slot_state& s : slots_) {
@@ -239,13 +240,12 @@ void scheduler::worker_main() {
         }
         // (an idle executor releases everything it holds: once per idle spell)
         const bool idle_release = idle && !idle_released && ex_->held_bytes() > 0;
-        if (!retired.empty() || !abandoned.empty() || idle_release) {
+        if (!retired.empty() || abandoned || idle_release) {
             lk.unlock();
-            for (int si : abandoned) ex_->abandon(si);
             ex_->release(idle);
             lk.lock();
             retired.clear();
-            abandoned.clear();
+            abandoned = false;
             idle_released = idle;
             continue;   // new completions may have arrived meanwhile
         }

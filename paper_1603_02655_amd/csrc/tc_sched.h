@@ -82,8 +82,10 @@ struct round_executor {
     // Device bytes the executor still holds for completed jobs (counted in
     // admission).  Any thread.
     virtual uint64_t held_bytes() const = 0;
-    // Worker thread, lock not held: the round on `slot` outlived the watchdog;
-    // its jobs have failed and the slot is never used again.
+    // Scheduler lock held, must not block: the round on `slot` outlived the
+    // watchdog; its jobs fail next and the slot is never used again.  Comes
+    // before job_done of these jobs: from then on a caller may release what
+    // the round still reads, and has to find the slot marked to wait for it.
     virtual void abandon(int slot) = 0;
     // Lock not held, when the worker stops: wait for the rounds of every slot
     // that was not abandoned.

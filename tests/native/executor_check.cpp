@@ -1,0 +1,79 @@
+// Host-only checks of what the serving scheduler (tc_sched.cpp) promises its
+// round executor: the order of the calls that memory reuse relies on.  Built and
+// run by tests/test_native_executor.py, also under ASan/UBSan and TSan.  Exit
+// status 0 when every check passes.
+#include <atomic>
+#include <chrono>
+#include <cstdio>
+#include <map>
+#include <thread>
+#include <vector>
+
+#include "tc_sched.h"
+
+using namespace tc::sched;
+
+static int g_failures = 0;
+#define CHECK(cond)                                                                      \
+    do {                                                                                 \
+        if (!(cond)) {                                                                   \
+            std::fprintf(stderr, "%s:%d: check failed: %s\n", __FILE__, __LINE__, #cond); \
+            ++g_failures;                                                                \
+        }                                                                                \
+    } while (0)
+
+// Rounds never finish: the watchdog ends them all.
+struct stuck_exec : round_executor {
+    std::atomic<bool> dead[2] = {{false}, {false}};
+    std::map<job*, int> slot_of;       // worker thread only
+    std::atomic<int> done_before_mark{0}, done{0};
+
+    int slot_count() const override { return 2; }
+    int launch(int slot, std::vector<job*>& jobs) override {
+        for (job* j : jobs) slot_of[j] = slot;
+        return kOk;
+    }
+    void collect(int, std::vector<job*>&) override {}
+    void job_done(job* j) override {
+        // from here on a caller may release the job's graph
+        if (!dead[slot_of.at(j)].load()) ++done_before_mark;
+        ++done;
+    }
+    void release(bool) override {}
+    uint64_t held_bytes() const override { return 0; }
+    void abandon(int slot) override { dead[slot].store(true); }
+    void drain() override {}
+};
+
+static void abandoned_slot_marked_before_its_jobs_end() {
+    stuck_exec ex;
+    sched_limits lim;
+    lim.budget = 1 << 20;
+    lim.watchdog_ms = 5;
+    scheduler S(&ex, lim);
+    std::vector<uint64_t> tickets;
+    for (int k = 0; k < 2; ++k) {
+        uint64_t t = 0;
+        CHECK(S.submit(new job(), &t) == kOk);
+        tickets.push_back(t);
+    }
+    for (uint64_t t : tickets) {
+        uint64_t counts[16];
+        int over = 0, rc = kOk;
+        for (int i = 0; i < 20000 && !over; ++i) {
+            rc = S.poll(t, counts, &over);
+            if (!over) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+        }
+        CHECK(over && rc == kErrDevice);
+    }
+    S.stop();
+    CHECK(ex.done.load() == 2);
+    CHECK(ex.done_before_mark.load() == 0);
+}
+
+int main() {
+    abandoned_slot_marked_before_its_jobs_end();
+    if (g_failures) return 1;
+    std::printf("all executor checks passed\n");
+    return 0;
+}
