@@ -291,7 +291,11 @@ int tc_serve_get_stats(tc_context ctx, tc_serve_stats* out);
 int tc_serve_reset_stats(tc_context ctx);
 
 /* Tuning: thresholds apply to graphs built afterwards and to graphs passed to
- * tc_graph_rebucket; launch sizes apply to the next census call. */
+ * tc_graph_rebucket; launch sizes apply to the next census call.
+ * tc_graph_rebucket gives the old records up before it builds the new ones
+ * (there may not be room for both).  When it fails g stays resident, but a
+ * census that needs records it has lost returns TC_ERR_NOMEM until a
+ * tc_graph_rebucket of g succeeds. */
 int tc_set_tuning(tc_context ctx, const tc_tuning* t);
 int tc_get_tuning(tc_context ctx, tc_tuning* t);
 int tc_graph_rebucket(tc_context ctx, tc_graph g);

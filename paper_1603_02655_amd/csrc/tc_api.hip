@@ -96,6 +96,7 @@ void fill_info(const tc_graph_s* g, tc_graph_info* info) {
 
 int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_slices& sl,
                       unsigned long long* raw, int table, bool tri) {
+    if (!has_records(g, tri)) return TC_ERR_NOMEM;
     hipEvent_t* ev = ctx->timing ? ctx->ev : nullptr;
     census_config cfg = config_of(ctx->tuning, ctx->cu_count);
     cfg.side_blocks = (uint32_t)ctx->cu_count;
@@ -425,6 +426,7 @@ int tc_census_range(tc_context ctx, tc_graph g, int32_t u_begin, int32_t u_end, 
     if (u_begin < 0) u_begin = 0;
     if (u_end > n) u_end = n;
     unsigned long long raw[16] = {0};
+    if (!has_records(g->g, false)) return TC_ERR_NOMEM;
     if (u_begin < u_end && g->g.p > 0) {
         uint64_t *off_dev = nullptr, *bnd_dev = nullptr;
         uint64_t bnd[2 * kBuckets];
@@ -516,6 +518,8 @@ int tc_census_each_noalloc(tc_context ctx, const tc_graph* graphs, int32_t count
     std::lock_guard<std::mutex> lk(ctx->mu);
     for (int32_t i = 0; i < count; ++i)
         if (!graphs[i] || !ctx->graphs.count(graphs[i])) return TC_ERR_ARG;
+    for (int32_t i = 0; i < count; ++i)
+        if (!has_records(graphs[i]->g, ctx->tuning.tri && graphs[i]->g.tri.fptr)) return TC_ERR_NOMEM;
     if (count == 0) return TC_OK;
     unsigned int* ctr = reinterpret_cast<unsigned int*>(ctx->scratch);
     unsigned long long* accs =
@@ -562,7 +566,7 @@ int tc_graph_rebucket(tc_context ctx, tc_graph g) {
     if (!ctx->graphs.count(g)) return TC_ERR_ARG;
     if (g->pending.load() > 0) return TC_ERR_BUSY;
     const bucket_params bp = params_of(ctx->tuning);
-    if (g->g.bp.t0 == bp.t0 && g->g.bp.t1 == bp.t1 && g->g.bp.t_hub == bp.t_hub && g->g.bp.tri == bp.tri &&
+    if (g->g.bucketed && g->g.bp.t0 == bp.t0 && g->g.bp.t1 == bp.t1 && g->g.bp.t_hub == bp.t_hub && g->g.bp.tri == bp.tri &&
         g->g.bp.hub_tile == bp.hub_tile)
         return TC_OK;
     batch_forget_graph_locked(ctx, g);

@@ -181,6 +181,7 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
         std::vector<graph_desc> descs(count);
         for (int32_t i = 0; i < count; ++i) {
             const device_graph& g = graphs[i]->g;
+            if (!has_records(g, tri && g.tri.fptr)) return TC_ERR_NOMEM;
             descs[i] = describe(g);
             append_items(g, (uint32_t)i, tri && g.tri.fptr, lists);
         }

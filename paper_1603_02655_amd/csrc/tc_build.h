@@ -90,6 +90,7 @@ struct device_graph {
     uint64_t hub_stream = 0;   // sum over hub dyads of the non-anchor degree (entries probed)
     uint64_t hub_staged = 0;   // sum over hub tasks of the anchor degree (entries staged)
     bucket_params bp{0, 0, 0, 0, kHubTileEntries, 1};
+    bool bucketed = false;     // the records are those of bp (not after a rebucket that failed)
     forward_lists tri;         // built when bp.tri
 };
 
@@ -128,6 +129,9 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
                                 const bucket_params& bp, graph_pool* pool, hipStream_t s, build_space* sp,
                                 device_graph* g);
 hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s, build_space* sp);
+// Whether g has the records its census reads: the forward lists', or the
+// dyads', which a rebucket that failed has given up.
+inline bool has_records(const device_graph& g, bool tri) { return g.p == 0 || (tri ? g.tri.fptr != nullptr : g.dyads != nullptr); }
 void free_device_graph(device_graph* g);
 uint64_t device_graph_bytes(const device_graph& g);
 

@@ -1500,9 +1500,24 @@ hipError_t cut_hub_tasks(const uint32_t* first, const uint32_t* past, int32_t n,
     *ntasks_out = (uint32_t)ntasks;
     *ngroups_out = (uint32_t)sp->host[0];
 done:
+    if (tasks) (void)hipStreamSynchronize(s);   // (an error: what was launched may still write them)
     mem->put(tasks);
     ar.rewind(mark);
     return err;
+}
+
+// Gives up g's dyad records (nothing on the device uses them).
+void drop_dyads(device_graph* g) {
+    g->mem->put(g->dyads);
+    g->mem->put(g->hub_tasks);
+    g->dyads = nullptr;
+    g->hub_tasks = nullptr;
+    g->n_hub_tasks = 0;
+    g->n_hub_groups = 0;
+    g->hub_stream = 0;
+    g->hub_staged = 0;
+    for (uint64_t& o : g->bucket_off) o = 0;
+    for (uint64_t& c : g->bucket_cost) c = 0;
 }
 
 // The dyad view: records of g's canonical dyads by bucket, hub tasks and the
@@ -1519,13 +1534,7 @@ hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const u
     uint8_t* bucket = nullptr;
     uint64_t hubs = 0;
     const uint32_t nb = blocks_for(U ? U : 1);
-    mem->put(g->dyads);
-    mem->put(g->hub_tasks);
-    g->dyads = nullptr;
-    g->hub_tasks = nullptr;
-    g->n_hub_tasks = 0;
-    g->n_hub_groups = 0;
-    g->hub_staged = 0;
+    drop_dyads(g);
     TAKE(counts, uint64_t, (uint64_t)kBuckets * nb + 1);
     TAKE(part, uint64_t, (uint64_t)kPartWords * nb);
     TAKE(bucket, uint8_t, U);
@@ -1538,8 +1547,6 @@ hipError_t bucket_dyad_records(device_graph* g, const bucket_params& bp, const u
     for (int b = 0; b <= kBuckets; ++b) g->bucket_off[b] = sp->host[b];
     for (int b = 0; b < kBuckets; ++b) g->bucket_cost[b] = sp->host[kBuckets + 1 + b];
     g->hub_stream = sp->host[2 * kBuckets + 1];
-    g->mutual = sp->host[2 * kBuckets + 2];
-    g->p = g->bucket_off[kBuckets];
     hubs = g->bucket_off[kBucketHub + 1] - g->bucket_off[kBucketHub];
     TRY(mem->alloc((void**)&g->dyads, sizeof(dyad_rec) * (g->p ? g->p : 1)));
     if (hubs > 0) {
@@ -1683,18 +1690,30 @@ done:
 }
 
 // Both views of g.  `fresh`: the largest degree is on its way to the host, and
-// there once the dyad records' synchronisation has passed.
+// there once the dyad records' synchronisation has passed.  The old records
+// are given up before the new ones are built (there may not be room for both),
+// so an error leaves g without the view that failed: no null pointer with a
+// count beside it, and `bucketed` false, so that the next rebucket builds.
 hipError_t bucket_all(device_graph* g, const bucket_params& bp, const uint32_t* deg, const uint2* rows, bool fresh,
                       build_space* sp, arena& ar, hipStream_t s) {
+    g->bucketed = false;
     hipError_t err = bp.dyads ? bucket_dyad_records(g, bp, deg, rows, sp, ar, s) : hipStreamSynchronize(s);
-    if (err != hipSuccess) return err;
+    if (err != hipSuccess) {
+        (void)hipStreamSynchronize(s);
+        drop_dyads(g);
+        return err;
+    }
     if (fresh) g->max_degree = (uint32_t)sp->host[kSpaceHostStats + 1];
     g->bp = bp;
     free_forward(g->mem, &g->tri);
-    if (!bp.tri) return hipSuccess;
-    err = build_forward(g, bp, deg, sp, ar, s);
-    if (err != hipSuccess) free_forward(g->mem, &g->tri);
-    return err;
+    if (bp.tri) err = build_forward(g, bp, deg, sp, ar, s);
+    if (err != hipSuccess) {
+        (void)hipStreamSynchronize(s);
+        free_forward(g->mem, &g->tri);
+        return err;
+    }
+    g->bucketed = true;
+    return hipSuccess;
 }
 
 }  // namespace

@@ -191,8 +191,14 @@ private:
                 continue;
             }
             const device_graph& g = j->cold ? j->built : j->g->g;
+            const bool tri = tun.tri && g.tri.fptr;
+            if (!has_records(g, tri)) {
+                j->status = TC_ERR_NOMEM;
+                descs[i] = graph_desc{};
+                continue;
+            }
             descs[i] = describe(g);
-            append_items(g, (uint32_t)i, tun.tri && g.tri.fptr, lists);
+            append_items(g, (uint32_t)i, tri, lists);
         }
         uint32_t nums[3];
         const std::vector<work_item>& items = lists.join(nums);

@@ -1,0 +1,69 @@
+/* hipMalloc and hipFree with failures on demand and a limit on the live bytes,
+ * for tests/test_gpu_memory.py: loaded with RTLD_GLOBAL before libtc.so, so that
+ * the library's calls come here first.  Every call that is not refused goes to
+ * the HIP runtime. */
+#define _GNU_SOURCE
+#include <dlfcn.h>
+#include <pthread.h>
+#include <stddef.h>
+#include <stdint.h>
+
+enum { kOutOfMemory = 2 }; /* hipErrorOutOfMemory */
+enum { kMax = 1 << 16 };
+
+static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
+static struct { void* p; size_t bytes; } live_blocks[kMax];
+static int blocks;
+static uint64_t live, limit = UINT64_MAX;
+static long fail_from = -1, calls, refused;
+
+static void* real(const char* name) {
+    void* h = dlopen("libamdhip64.so.7", RTLD_NOW);
+    return h ? dlsym(h, name) : NULL;
+}
+
+int hipMalloc(void** out, size_t bytes) {
+    int (*f)(void**, size_t) = (int (*)(void**, size_t))real("hipMalloc");
+    pthread_mutex_lock(&mu);
+    int rc = kOutOfMemory;
+    const long k = calls++;
+    if (f && !(fail_from >= 0 && k >= fail_from) && live + bytes <= limit && blocks < kMax) rc = f(out, bytes);
+    else ++refused;
+    if (rc == 0) {
+        live_blocks[blocks].p = *out;
+        live_blocks[blocks++].bytes = bytes;
+        live += bytes;
+    }
+    pthread_mutex_unlock(&mu);
+    return rc;
+}
+
+int hipFree(void* p) {
+    int (*f)(void*) = (int (*)(void*))real("hipFree");
+    pthread_mutex_lock(&mu);
+    for (int k = 0; k < blocks; ++k)
+        if (live_blocks[k].p == p) {
+            live -= live_blocks[k].bytes;
+            live_blocks[k] = live_blocks[--blocks];
+            break;
+        }
+    pthread_mutex_unlock(&mu);
+    return f ? f(p) : 1;
+}
+
+/* The k-th call from now (0: the next) and all after it fail; k < 0: none. */
+void shim_fail_from(long k) {
+    pthread_mutex_lock(&mu);
+    calls = 0;
+    refused = 0;
+    fail_from = k;
+    pthread_mutex_unlock(&mu);
+}
+void shim_set_limit(uint64_t bytes) {
+    pthread_mutex_lock(&mu);
+    limit = bytes;
+    refused = 0;
+    pthread_mutex_unlock(&mu);
+}
+uint64_t shim_live(void) { return live; }
+long shim_refused(void) { return refused; }

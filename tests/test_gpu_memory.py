@@ -1,0 +1,146 @@
+"""Device memory that runs out, and memory that is kept for reuse.
+
+Each test runs its scenario in a process of its own, in which hipMalloc and
+hipFree go through tests/native/alloc_shim.c: it refuses calls on demand, or
+once the live bytes would pass a limit, as a smaller GPU would.  Whatever is
+refused, a call returns the right counts or TC_ERR_NOMEM."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+from paper_1603_02655_amd import synth, tc  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(tmp_path, scenario):
+    shim = str(tmp_path / "alloc_shim.so")
+    subprocess.run(["gcc", "-O1", "-Wall", "-shared", "-fPIC", os.path.join(ROOT, "tests", "native", "alloc_shim.c"),
+                    "-o", shim, "-ldl", "-lpthread"], check=True)
+    r = subprocess.run([sys.executable, "-u", os.path.abspath(__file__), scenario, shim], capture_output=True, text=True,
+                       cwd=ROOT, timeout=100)
+    print(r.stdout[-4000:], r.stderr[-4000:], flush=True)
+    assert r.returncode == 0 and "scenario passed" in r.stdout
+
+
+def _graph():
+    g = synth.rmat_digraph(1 << 12, 1 << 16, synth.rng_for(71, 0), reciprocity=0.2)
+    return g.n, g.src, g.dst
+
+
+def _poll(c, t):
+    while True:
+        r = c.poll(t)
+        if r is not None:
+            return r
+
+
+def _results(c, g):
+    """Every census of g on the current path, as the 16 counts."""
+    n, k = g.n, 5
+    cuts = [n * i // k for i in range(k + 1)]
+
+    def parts(fs):
+        s = np.zeros(16, np.uint64)
+        for f in fs:
+            s += f()
+        s[0] = 0
+        return s
+
+    table = tc.tc_class_table()
+    return {
+        "census": lambda: c.census(g),
+        "census64": lambda: np.array([c.census64(g)[table == q].sum() for q in range(16)], np.uint64),
+        "range": lambda: parts([lambda i=i: c.census_range(g, cuts[i], cuts[i + 1]) for i in range(k)]),
+        "shard": lambda: parts([lambda i=i: c.census_shard(g, i, k) for i in range(k)]),
+        "each": lambda: c.census_each([g])[0],
+        "noalloc": lambda: c.census_each_noalloc([g])[0],
+        "batch": lambda: c.census_batch([g])[0],
+        "submit": lambda: _poll(c, c.submit(g)),
+    }
+
+
+def _check_all(c, g, want, may_fail):
+    """Every call returns the right counts, or (may_fail) TC_ERR_NOMEM; the calls that failed."""
+    failed = []
+    for tri in (1, 0):
+        c.set_tuning(tri=tri)
+        for name, f in _results(c, g).items():
+            try:
+                got = f()
+            except tc.TcError as e:
+                assert may_fail and e.code == tc.TC_ERR_NOMEM, (name, tri, e)
+                failed.append((name, tri))
+                continue
+            w = want.copy()
+            if name in ("range", "shard"):
+                w[0] = 0
+            assert got.tolist() == w.tolist(), (name, tri)
+    return failed
+
+
+# ---------------------------------------------------------------- scenarios --
+
+NEW = dict(t0=16, t1=256, t_hub=64, hub_tile=512)
+
+
+def scenario_rebucket(shim):
+    """A rebucket that fails at its k-th allocation, for every k; the next one mends the graph."""
+    n, src, dst = _graph()
+    lost, k = set(), 0
+    while True:
+        # (a budget of one byte: nothing is kept, so that every allocation is a hipMalloc)
+        with tc.Context(0, hbm_budget_bytes=1) as c:
+            g = c.build_graph(n, src, dst)
+            want = c.census(g)
+            old = c.get_tuning()
+            c.set_tuning(**NEW)
+            shim.shim_fail_from(k)
+            try:
+                c.rebucket(g)
+                ok = True
+            except tc.TcError as e:
+                assert e.code == tc.TC_ERR_NOMEM
+                ok = False
+            refused = shim.shim_refused()
+            shim.shim_fail_from(-1)
+            assert ok == (refused == 0)
+            print("allocation", k, "ok" if ok else "failed", flush=True)
+            # (with a budget of one byte a served request never fits)
+            failed = [f for f in _check_all(c, g, want, True) if f[0] != "submit"]
+            lost.update(failed)
+            if ok:
+                assert not failed
+                break
+            c.set_tuning(**dict(old, **NEW, tri=1))
+            c.rebucket(g)
+            assert not [f for f in _check_all(c, g, want, True) if f[0] != "submit"]
+            c.set_tuning(**dict(old, **NEW, tri=1))
+            fresh = c.build_graph(n, src, dst)
+            same = [q for q in g.info if not q.startswith(("arcs", "self", "dup"))]
+            assert {q: g.info[q] for q in same} == {q: fresh.info[q] for q in same}
+        k += 1
+    assert k >= 6                    # scratch, records, tasks, lists, edge records, edge tasks
+    assert ("census", 0) in lost     # (the dyad records were refused)
+
+
+def test_failed_rebucket_leaves_no_dangling_records(tmp_path):
+    _run(tmp_path, "rebucket")
+
+
+if __name__ == "__main__":
+    so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
+    so.shim_fail_from.argtypes = [ctypes.c_long]
+    so.shim_set_limit.argtypes = [ctypes.c_uint64]
+    so.shim_live.restype = ctypes.c_uint64
+    so.shim_refused.restype = ctypes.c_long
+    globals()["scenario_" + sys.argv[1]](so)
+    print("scenario passed", flush=True)
