@@ -203,6 +203,7 @@ void scheduler::worker_main() {
     std::vector<job*> retired;
     bool abandoned = false;
     bool idle_released = false;
+    ex_->thread_start();
     std::unique_lock<std::mutex> lk(mu_);
     for (;;) {
         const double t = now_ms();

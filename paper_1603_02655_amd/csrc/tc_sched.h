@@ -59,6 +59,9 @@ private:
 // The device side of the rounds.
 struct round_executor {
     virtual ~round_executor() = default;
+    // Worker thread, once, before every other call from it (the device is a
+    // property of the thread).
+    virtual void thread_start() {}
     // Number of rounds that may be in flight at once.
     virtual int slot_count() const = 0;
     // Worker thread, scheduler lock not held: starts the round of `jobs` on

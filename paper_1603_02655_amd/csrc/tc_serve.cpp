@@ -135,6 +135,9 @@ public:
 
     int slot_count() const override { return kSlots; }
 
+    // A new thread's device is 0, whichever the context is on.
+    void thread_start() override { (void)hipSetDevice(ctx_->device); }
+
     int launch(int si, std::vector<sched::job*>& jobs) override {
         bool cold = false;
         for (sched::job* jb : jobs) cold = cold || static_cast<serve_job*>(jb)->cold;
@@ -238,6 +241,7 @@ private:
     };
 
     void builder_main(int si) {
+        thread_start();
         std::unique_lock<std::mutex> lk(bmu_);
         for (;;) {
             bcv_.wait(lk, [&] { return bstop_ || has_[si]; });
@@ -451,7 +455,8 @@ int submit_job(tc_context ctx, serve_job* j, tc_ticket* out) {
     serve_state* st;
     {
         std::lock_guard<std::mutex> lk(ctx->mu);
-        st = ensure_serving(ctx, &rc);
+        rc = TC_ERR_DEVICE;
+        st = hipSetDevice(ctx->device) == hipSuccess ? ensure_serving(ctx, &rc) : nullptr;
     }
     if (!st) {
         if (!j->cold) j->g->pending.fetch_sub(1);

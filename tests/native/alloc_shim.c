@@ -1,5 +1,5 @@
 /* hipMalloc and hipFree with failures on demand and a limit on the live bytes,
- * for tests/test_gpu_memory.py: loaded with RTLD_GLOBAL before libtc.so, so that
+ * and a count of calls from threads that chose no device, for tests/test_gpu_memory.py: loaded with RTLD_GLOBAL before libtc.so, so that
  * the library's calls come here first.  Every call that is not refused goes to
  * the HIP runtime. */
 #define _GNU_SOURCE
@@ -17,6 +17,8 @@ static int blocks;
 static uint64_t live, limit = UINT64_MAX;
 static long fail_from = -1, calls, refused;
 
+static void count_unchosen(void);
+
 static void* real(const char* name) {
     void* h = dlopen("libamdhip64.so.7", RTLD_NOW);
     return h ? dlsym(h, name) : NULL;
@@ -24,6 +26,7 @@ static void* real(const char* name) {
 
 int hipMalloc(void** out, size_t bytes) {
     int (*f)(void**, size_t) = (int (*)(void**, size_t))real("hipMalloc");
+    count_unchosen();
     pthread_mutex_lock(&mu);
     int rc = kOutOfMemory;
     const long k = calls++;
@@ -50,6 +53,28 @@ int hipFree(void* p) {
     pthread_mutex_unlock(&mu);
     return f ? f(p) : 1;
 }
+
+/* Calls that the device of the calling thread decides, from threads that never chose one. */
+static __thread int chosen;
+static long unchosen;
+
+static void count_unchosen(void) {
+    if (!chosen) __atomic_add_fetch(&unchosen, 1, __ATOMIC_SEQ_CST);
+}
+
+int hipSetDevice(int device) {
+    int (*f)(int) = (int (*)(int))real("hipSetDevice");
+    chosen = 1;
+    return f ? f(device) : 1;
+}
+
+int hipStreamCreateWithFlags(void** out, unsigned flags) {
+    int (*f)(void**, unsigned) = (int (*)(void**, unsigned))real("hipStreamCreateWithFlags");
+    count_unchosen();
+    return f ? f(out, flags) : 1;
+}
+
+long shim_unchosen(void) { return __atomic_load_n(&unchosen, __ATOMIC_SEQ_CST); }
 
 /* The k-th call from now (0: the next) and all after it fail; k < 0: none. */
 void shim_fail_from(long k) {

@@ -71,7 +71,53 @@ static void abandoned_slot_marked_before_its_jobs_end() {
     CHECK(ex.done_before_mark.load() == 0);
 }
 
+// thread_start comes first on the thread that makes the other calls.
+struct thread_exec : round_executor {
+    scheduler* S = nullptr;
+    std::atomic<int> starts{0}, out_of_order{0};
+    std::thread::id id;
+    void here() {
+        if (starts.load() != 1 || std::this_thread::get_id() != id) ++out_of_order;
+    }
+    void thread_start() override {
+        id = std::this_thread::get_id();
+        ++starts;
+    }
+    int slot_count() const override { return 1; }
+    int launch(int slot, std::vector<job*>&) override {
+        here();
+        S->round_done(slot);
+        return kOk;
+    }
+    void collect(int, std::vector<job*>&) override { here(); }
+    void job_done(job*) override { here(); }
+    void release(bool) override { here(); }
+    uint64_t held_bytes() const override { return 0; }
+    void abandon(int) override {}
+    void drain() override { here(); }
+};
+
+static void worker_thread_starts_first() {
+    thread_exec ex;
+    sched_limits lim;
+    lim.budget = 1 << 20;
+    scheduler S(&ex, lim);
+    ex.S = &S;
+    uint64_t t = 0, counts[16];
+    CHECK(S.submit(new job(), &t) == kOk);
+    int over = 0;
+    for (int i = 0; i < 20000 && !over; ++i) {
+        CHECK(S.poll(t, counts, &over) == kOk);
+        if (!over) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    }
+    CHECK(over);
+    S.stop();
+    CHECK(ex.starts.load() == 1);
+    CHECK(ex.out_of_order.load() == 0);
+}
+
 int main() {
+    worker_thread_starts_first();
     abandoned_slot_marked_before_its_jobs_end();
     if (g_failures) return 1;
     std::printf("all executor checks passed\n");

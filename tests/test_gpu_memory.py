@@ -8,6 +8,7 @@ import ctypes
 import os
 import subprocess
 import sys
+import threading
 
 import numpy as np
 import pytest
@@ -136,11 +137,34 @@ def test_failed_rebucket_leaves_no_dangling_records(tmp_path):
     _run(tmp_path, "rebucket")
 
 
+def scenario_threads(shim):
+    """Every thread that makes streams or allocates has chosen the context's device."""
+    n, src, dst = _graph()
+    with tc.Context(0) as c:
+        g = c.build_graph(n, src, dst)
+        want, got = c.census(g), []
+
+        def requests():     # (a thread of the caller's that has made no HIP call)
+            tickets = [c.submit(g)] + [c.submit_arcs(n, src, dst) for _ in range(4)]
+            got.extend(_poll(c, t) for t in tickets)
+
+        th = threading.Thread(target=requests)
+        th.start()
+        th.join()
+        assert len(got) == 5 and all(r.tolist() == want.tolist() for r in got)
+    assert shim.shim_unchosen() == 0
+
+
+def test_serving_threads_choose_the_device(tmp_path):
+    _run(tmp_path, "threads")
+
+
 if __name__ == "__main__":
     so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
     so.shim_fail_from.argtypes = [ctypes.c_long]
     so.shim_set_limit.argtypes = [ctypes.c_uint64]
     so.shim_live.restype = ctypes.c_uint64
     so.shim_refused.restype = ctypes.c_long
+    so.shim_unchosen.restype = ctypes.c_long
     globals()["scenario_" + sys.argv[1]](so)
     print("scenario passed", flush=True)
