@@ -178,8 +178,18 @@ int tc_build_graph(tc_context ctx, int32_t n, int64_t m, const int32_t* src, con
 /* Copies the build information of g into *info. */
 int tc_graph_get_info(tc_context ctx, tc_graph g, tc_graph_info* info);
 
-/* Frees g.  TC_ERR_BUSY while tickets that use g are pending. */
+/* Frees g.  TC_ERR_BUSY while tickets that use g are pending.  The context
+ * keeps freed graphs' memory for the graphs it builds next, at most 4 GiB and an
+ * eighth of the budget, and the scratch of its builds, at most 1 GiB and an
+ * eighth of the budget in each of five areas (tc_build_graph's and the serving
+ * loop's four).  When the device is full, every allocation of the library takes
+ * back what the process's contexts on it keep; tc_context_trim and
+ * tc_context_destroy return it at once. */
 int tc_graph_release(tc_context ctx, tc_graph g);
+
+/* Returns to the device the memory ctx keeps for reuse (see tc_graph_release),
+ * except scratch that a build is using.  May wait for the device. */
+int tc_context_trim(tc_context ctx);
 
 /* Synchronous census: counts[16] (host) receives the 16 class counts of g,
  * the census array of section "Triad Census Algorithm" (figure "Subquadratic

@@ -137,6 +137,7 @@ int run_full_locked(tc_context_s* ctx, const device_graph& g, unsigned long long
 int build_into(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, uint32_t flags, const bucket_params& bp,
                graph_pool* pool, hipStream_t stream, build_space* sp, uint64_t keep, device_graph* out,
                tc_graph_info* info) {
+    std::lock_guard<std::mutex> lk(sp->busy);
     const build_status st =
         build_graph_device(n, m, src, dst, !(flags & TC_BUILD_DEVICE_PTRS), bp, pool, stream, sp, out);
     space_trim(sp, keep, stream);
@@ -253,14 +254,14 @@ int tc_context_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, t
         ctx->own_stream = true;
     }
     if (e == hipSuccess) e = census_upload_table();
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->acc, sizeof(unsigned long long) * kAccWords);
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->counters, sizeof(unsigned int) * kBuckets * kCounterWords);
+    if (e == hipSuccess) e = device_alloc((void**)&ctx->acc, sizeof(unsigned long long) * kAccWords);
+    if (e == hipSuccess) e = device_alloc((void**)&ctx->counters, sizeof(unsigned int) * kBuckets * kCounterWords);
     if (e == hipSuccess) e = hipHostMalloc((void**)&ctx->host_raw, sizeof(unsigned long long) * 64);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&ctx->host_many,
                           sizeof(unsigned long long) * kNumClasses * (size_t)TC_NOALLOC_MAX_GRAPHS);
     if (e == hipSuccess) e = scratch_for_device(device, &ctx->scratch);
-    if (e == hipSuccess) e = hipMalloc((void**)&ctx->tables, 5 * 64);
+    if (e == hipSuccess) e = device_alloc((void**)&ctx->tables, 5 * 64);
     if (e == hipSuccess) {
         // table 0: the 64 -> 16 class map; table f (1..3): code -> code >> 2 for
         // the codes whose (u, v) part is f, every other code to the discard bin;
@@ -280,7 +281,8 @@ int tc_context_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, t
         size_t free_b = 0, total_b = 0;
         e = hipMemGetInfo(&free_b, &total_b);
         ctx->budget = hbm_budget_bytes ? hbm_budget_bytes : (uint64_t)(0.9 * (double)free_b);
-        ctx->pool.keep = pool_keep(ctx);
+        ctx->pool.open(device, pool_keep(ctx));
+        ctx->pool.add(&ctx->space);
         hipDeviceProp_t prop;
         if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
         if (e == hipSuccess) {
@@ -430,7 +432,7 @@ int tc_census_range(tc_context ctx, tc_graph g, int32_t u_begin, int32_t u_end, 
     if (u_begin < u_end && g->g.p > 0) {
         uint64_t *off_dev = nullptr, *bnd_dev = nullptr;
         uint64_t bnd[2 * kBuckets];
-        hipError_t e = hipMalloc((void**)&off_dev, sizeof(uint64_t) * (kBuckets + 1 + 2 * kBuckets));
+        hipError_t e = device_alloc((void**)&off_dev, sizeof(uint64_t) * (kBuckets + 1 + 2 * kBuckets));
         if (e != hipSuccess) return status_from_hip(e);
         bnd_dev = off_dev + kBuckets + 1;
         e = hipMemcpyAsync(off_dev, g->g.bucket_off, sizeof(uint64_t) * (kBuckets + 1), hipMemcpyHostToDevice,
@@ -543,6 +545,13 @@ int tc_census_each_noalloc(tc_context ctx, const tc_graph* graphs, int32_t count
     return TC_OK;
 }
 
+int tc_context_trim(tc_context ctx) {
+    if (!ctx) return TC_ERR_ARG;
+    if (hipSetDevice(ctx->device) != hipSuccess) return TC_ERR_DEVICE;
+    ctx->pool.give_back(0);
+    return TC_OK;
+}
+
 int tc_set_tuning(tc_context ctx, const tc_tuning* t) {
     if (!ctx || !t) return TC_ERR_ARG;
     if (check_tuning(*t) != TC_OK) return TC_ERR_ARG;
@@ -572,6 +581,7 @@ int tc_graph_rebucket(tc_context ctx, tc_graph g) {
     batch_forget_graph_locked(ctx, g);
     (void)hipStreamSynchronize(ctx->stream);
     serve_wait_abandoned(ctx);
+    std::lock_guard<std::mutex> ls(ctx->space.busy);
     const hipError_t e = bucket_dyads(&g->g, bp, ctx->stream, &ctx->space);
     space_trim(&ctx->space, space_keep(ctx), ctx->stream);
     return status_from_hip(e);

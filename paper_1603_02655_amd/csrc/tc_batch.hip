@@ -131,11 +131,11 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
     p->batch_tile = batch_tile;
     p->tri_grid = tri_grid;
     p->forked = side != nullptr;
-    hipError_t e = hipMalloc((void**)&p->d_desc, sizeof(graph_desc) * p->cap_graphs);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_items, sizeof(work_item) * p->cap_items);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_num, 3 * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_accs, sizeof(unsigned long long) * kBatchAccWords * p->cap_graphs);
-    if (e == hipSuccess) e = hipMalloc((void**)&p->d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
+    hipError_t e = device_alloc((void**)&p->d_desc, sizeof(graph_desc) * p->cap_graphs);
+    if (e == hipSuccess) e = device_alloc((void**)&p->d_items, sizeof(work_item) * p->cap_items);
+    if (e == hipSuccess) e = device_alloc((void**)&p->d_num, 3 * sizeof(uint32_t));
+    if (e == hipSuccess) e = device_alloc((void**)&p->d_accs, sizeof(unsigned long long) * kBatchAccWords * p->cap_graphs);
+    if (e == hipSuccess) e = device_alloc((void**)&p->d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&p->h_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs);
     if (e != hipSuccess) {

@@ -3,6 +3,7 @@
 #include <deque>
 #include <mutex>
 #include <unordered_map>
+#include <vector>
 
 #include "tc_internal.h"
 
@@ -42,19 +43,34 @@ struct forward_lists {
     rec_set<uint4, tri_task> edges;
 };
 
+// hipMalloc on the calling thread's device.  When the device is full, what the
+// contexts on it keep for reuse (their pools' blocks and the scratch of builds
+// that are not running) goes back to it first.
+hipError_t device_alloc(void** out, uint64_t bytes);
+
+struct build_space;
+
 // Device memory of a context's graphs.  Freed blocks are kept, up to `keep`
 // bytes in all, and given to later allocations of about their size; beyond
 // that the oldest are returned to the driver, which takes 2-40 ms per graph of
 // R-MAT 2^20's size and waits for the whole device.  A block is put back only
 // once nothing on the device uses it any more (a graph is freed after the
 // streams that ran on it were waited for), so it can serve any stream next.
-// Safe from several threads.
+// The pool also knows the scratch its context keeps (add), so that all of it
+// can be given back.  Safe from several threads.
 class graph_pool {
 public:
     ~graph_pool();
+    // Before the first use: the device, and the bytes of freed blocks kept.
+    void open(int device, uint64_t keep);
     hipError_t alloc(void** out, uint64_t bytes);
     void put(void* p);
-    uint64_t keep = 0;
+    void add(build_space* sp);
+    void remove(build_space* sp);
+    // Frees kept memory until at most `to` bytes are left (scratch in use by a
+    // running build does not count and stays).
+    void give_back(uint64_t to);
+    int device() const { return device_; }
 
 private:
     struct block {
@@ -62,9 +78,12 @@ private:
         uint64_t bytes;
     };
     void shrink(uint64_t to);      // mu_ held
+    int device_ = -1;
+    uint64_t keep_ = 0;
     std::mutex mu_;
     std::deque<block> free_;       // oldest first
     std::unordered_map<void*, uint64_t> live_;
+    std::vector<build_space*> spaces_;
     uint64_t held_ = 0;            // bytes in free_
 };
 
@@ -104,7 +123,8 @@ struct build_status {
 
 // Device scratch and a page of pinned host memory that builds reuse: grown to
 // the largest build, kept between builds up to kSpaceKeep bytes (space_trim)
-// and freed with its owner.  One build at a time uses a build_space.
+// and freed with its owner.  One build at a time uses a build_space, and holds
+// `busy` meanwhile; the pool it is added to frees the scratch of one that is not.
 constexpr uint32_t kSpaceHostWords = 64;
 constexpr uint32_t kSpaceHostStats = 32;          // words the build's statistics are published to
 constexpr uint64_t kSpaceKeep = 1ull << 30;
@@ -114,6 +134,8 @@ constexpr uint64_t kSpaceKeep = 1ull << 30;
 constexpr int kStageThreads = 4;
 constexpr uint64_t kStageChunk = 1ull << 20;
 struct build_space {
+    std::mutex busy;
+    graph_pool* pool = nullptr;
     void* base = nullptr;
     uint64_t cap = 0;
     uint64_t* host = nullptr;

@@ -1123,7 +1123,73 @@ hipError_t fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
     return hipGetLastError();
 }
 
+namespace {
+
+// The pools of every context, for give-backs to a device that is full.  Lock
+// order: the registry, a pool, a build_space (tried only); hipMalloc runs under none.
+std::mutex g_pools_mu;
+std::vector<graph_pool*> g_pools;
+
+}  // namespace
+
+hipError_t device_alloc(void** out, uint64_t bytes) {
+    hipError_t e = hipMalloc(out, bytes);
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return e;
+    {
+        std::lock_guard<std::mutex> lk(g_pools_mu);
+        for (graph_pool* p : g_pools)
+            if (p->device() == device) p->give_back(0);
+    }
+    e = hipMalloc(out, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+void graph_pool::open(int device, uint64_t keep) {
+    device_ = device;
+    keep_ = keep;
+    std::lock_guard<std::mutex> lk(g_pools_mu);
+    g_pools.push_back(this);
+}
+
+void graph_pool::add(build_space* sp) {
+    std::lock_guard<std::mutex> lk(mu_);
+    spaces_.push_back(sp);
+    sp->pool = this;
+}
+
+void graph_pool::remove(build_space* sp) {
+    std::lock_guard<std::mutex> lk(mu_);
+    spaces_.erase(std::remove(spaces_.begin(), spaces_.end(), sp), spaces_.end());
+}
+
+void graph_pool::give_back(uint64_t to) {
+    std::lock_guard<std::mutex> lk(mu_);
+    uint64_t scratch = 0;
+    for (build_space* sp : spaces_) {
+        std::unique_lock<std::mutex> idle(sp->busy, std::try_to_lock);
+        if (idle) scratch += sp->cap;
+    }
+    shrink(to > scratch ? to - scratch : 0);
+    for (build_space* sp : spaces_) {
+        if (scratch + held_ <= to) break;
+        std::unique_lock<std::mutex> idle(sp->busy, std::try_to_lock);
+        if (!idle || !sp->cap) continue;
+        scratch -= std::min(scratch, sp->cap);
+        (void)hipFree(sp->base);   // (its last build ended with a wait)
+        sp->base = nullptr;
+        sp->cap = 0;
+    }
+}
+
 graph_pool::~graph_pool() {
+    {
+        std::lock_guard<std::mutex> lk(g_pools_mu);
+        g_pools.erase(std::remove(g_pools.begin(), g_pools.end(), this), g_pools.end());
+    }
     shrink(0);
     for (auto& b : live_) (void)hipFree(b.first);
 }
@@ -1143,38 +1209,32 @@ hipError_t graph_pool::alloc(void** out, uint64_t bytes) {
     uint64_t step = 4096;
     while (16 * step < bytes) step *= 2;
     bytes = (std::max<uint64_t>(bytes, 1) + step - 1) / step * step;
-    std::lock_guard<std::mutex> lk(mu_);
+    void* p = nullptr;
     try {
-        size_t best = free_.size();
-        for (size_t i = 0; i < free_.size(); ++i)
-            if (free_[i].bytes >= bytes && free_[i].bytes <= bytes + bytes / 4 &&
-                (best == free_.size() || free_[i].bytes < free_[best].bytes))
-                best = i;
-        if (best < free_.size()) {
-            const block b = free_[best];
-            live_.emplace(b.p, b.bytes);
-            free_.erase(free_.begin() + (std::ptrdiff_t)best);
-            held_ -= b.bytes;
-            *out = b.p;
-            return hipSuccess;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            size_t best = free_.size();
+            for (size_t i = 0; i < free_.size(); ++i)
+                if (free_[i].bytes >= bytes && free_[i].bytes <= bytes + bytes / 4 &&
+                    (best == free_.size() || free_[i].bytes < free_[best].bytes))
+                    best = i;
+            if (best < free_.size()) {
+                const block b = free_[best];
+                live_.emplace(b.p, b.bytes);
+                free_.erase(free_.begin() + (std::ptrdiff_t)best);
+                held_ -= b.bytes;
+                *out = b.p;
+                return hipSuccess;
+            }
         }
-        void* p = nullptr;
-        hipError_t e = hipMalloc(&p, bytes);
-        if (e != hipSuccess && held_ > 0) {   // full: what is kept goes back first
-            (void)hipGetLastError();
-            shrink(0);
-            e = hipMalloc(&p, bytes);
-        }
+        const hipError_t e = device_alloc(&p, bytes);
         if (e != hipSuccess) return e;
-        try {
-            live_.emplace(p, bytes);
-        } catch (...) {
-            (void)hipFree(p);
-            return hipErrorOutOfMemory;
-        }
+        std::lock_guard<std::mutex> lk(mu_);
+        live_.emplace(p, bytes);
         *out = p;
         return hipSuccess;
     } catch (...) {
+        if (p) (void)hipFree(p);
         return hipErrorOutOfMemory;
     }
 }
@@ -1186,11 +1246,11 @@ void graph_pool::put(void* p) {
     if (it == live_.end()) return;
     const uint64_t bytes = it->second;
     live_.erase(it);
-    if (bytes <= keep) {
+    if (bytes <= keep_) {
         try {
             free_.push_back(block{p, bytes});
             held_ += bytes;
-            shrink(keep);
+            shrink(keep_);
             return;
         } catch (...) {
         }
@@ -1206,7 +1266,7 @@ hipError_t space_reserve(build_space* sp, uint64_t bytes, hipStream_t s) {
         if (sp->base) (void)hipFree(sp->base);
         sp->base = nullptr;
         sp->cap = 0;
-        e = hipMalloc(&sp->base, bytes);
+        e = device_alloc(&sp->base, bytes);
         if (e == hipSuccess) sp->cap = bytes;
     }
     return e;
@@ -1281,12 +1341,19 @@ hipError_t stage_copy(build_space* sp, const void* from, void* to, uint64_t byte
 }  // namespace
 
 void space_free(build_space* sp) {
+    if (sp->pool) sp->pool->remove(sp);
+    sp->pool = nullptr;
     if (sp->stage) (void)hipHostFree(sp->stage);
-    for (hipEvent_t ev : sp->stage_ev)
+    for (hipEvent_t& ev : sp->stage_ev) {
         if (ev) (void)hipEventDestroy(ev);
+        ev = nullptr;
+    }
     if (sp->base) (void)hipFree(sp->base);
     if (sp->host) (void)hipHostFree(sp->host);
-    *sp = build_space{};
+    sp->stage = nullptr;
+    sp->base = nullptr;
+    sp->host = nullptr;
+    sp->cap = 0;
 }
 
 namespace {

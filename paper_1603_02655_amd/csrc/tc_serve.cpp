@@ -80,11 +80,11 @@ hipError_t slot_reserve(slot_buf& s, uint32_t graphs, uint32_t items) {
     slot_free(s);
     s.cap_graphs = std::max<uint32_t>(graphs * 2, 64);
     s.cap_items = std::max<uint32_t>(items + items / 2, 4096);
-    hipError_t e = hipMalloc((void**)&s.d_desc, sizeof(graph_desc) * s.cap_graphs);
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_items, sizeof(work_item) * s.cap_items);
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_num, 3 * sizeof(uint32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_accs, sizeof(unsigned long long) * kBatchAccWords * s.cap_graphs);
-    if (e == hipSuccess) e = hipMalloc((void**)&s.d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
+    hipError_t e = device_alloc((void**)&s.d_desc, sizeof(graph_desc) * s.cap_graphs);
+    if (e == hipSuccess) e = device_alloc((void**)&s.d_items, sizeof(work_item) * s.cap_items);
+    if (e == hipSuccess) e = device_alloc((void**)&s.d_num, 3 * sizeof(uint32_t));
+    if (e == hipSuccess) e = device_alloc((void**)&s.d_accs, sizeof(unsigned long long) * kBatchAccWords * s.cap_graphs);
+    if (e == hipSuccess) e = device_alloc((void**)&s.d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_desc, sizeof(graph_desc) * s.cap_graphs);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_items, sizeof(work_item) * s.cap_items);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s.h_num, 3 * sizeof(uint32_t));
@@ -391,6 +391,7 @@ serve_state* ensure_serving(tc_context_s* ctx, int* rc) {
             return nullptr;
         }
     }
+    for (slot_buf& s : st->ex.slots) ctx->pool.add(&s.space);
     sched::sched_limits lim;
     lim.budget = ctx->budget;
     lim.max_jobs_per_round = kMaxJobsPerRound;
@@ -401,7 +402,10 @@ serve_state* ensure_serving(tc_context_s* ctx, int* rc) {
     try {
         st->S.reset(new sched::scheduler(&st->ex, lim));
     } catch (...) {
-        for (slot_buf& t : st->ex.slots) (void)hipStreamDestroy(t.stream);
+        for (slot_buf& t : st->ex.slots) {
+            space_free(&t.space);
+            (void)hipStreamDestroy(t.stream);
+        }
         delete st;
         *rc = TC_ERR_NOMEM;
         return nullptr;

@@ -106,6 +106,7 @@ _P = ctypes.POINTER
 SIGNATURES = {
     "tc_context_create": (ctypes.c_int, [ctypes.c_int, _u64, _vp, _P(_vp)]),
     "tc_context_destroy": (ctypes.c_int, [_vp]),
+    "tc_context_trim": (ctypes.c_int, [_vp]),
     "tc_build_graph": (ctypes.c_int, [_vp, _i32, _i64, _vp, _vp, _u32, _P(_vp), _P(tc_graph_info)]),
     "tc_graph_get_info": (ctypes.c_int, [_vp, _vp, _P(tc_graph_info)]),
     "tc_graph_release": (ctypes.c_int, [_vp, _vp]),
@@ -248,6 +249,9 @@ class Context:
         if getattr(self, "handle", None):
             load().tc_context_destroy(self.handle)
             self.handle = None
+
+    def trim(self):
+        _check(load().tc_context_trim(self.handle), "tc_context_trim")
 
     def __enter__(self):
         return self

@@ -159,6 +159,88 @@ def test_serving_threads_choose_the_device(tmp_path):
     _run(tmp_path, "threads")
 
 
+def _er(n, m, seed):
+    rng = synth.rng_for(72, seed)
+    return n, rng.integers(0, n, m, dtype=np.int32), rng.integers(0, n, m, dtype=np.int32)
+
+
+def _released(c, count=5):
+    """Builds `count` graphs of 2^18 arcs and releases them all: their memory is kept."""
+    gs = [c.build_graph(*_er(1 << 14, 1 << 18, i)) for i in range(count)]
+    for g in gs:
+        g.release()
+
+
+def scenario_kept(shim):
+    """Kept memory goes back when an allocation of any kind needs it, and on trim."""
+    big = _er(1 << 15, 1 << 19, 9)
+    n, src, dst = _graph()
+
+    def full(slack=0):
+        shim.shim_set_limit(shim.shim_live() + slack)
+
+    def free():
+        assert shim.shim_refused() > 0, "the limit was not reached"
+        shim.shim_set_limit(2**63)
+
+    with tc.Context(0) as c:
+        empty = shim.shim_live()
+        g = c.build_graph(n, src, dst)
+        want = c.census(g)
+        wb = tc.Context(0)
+        want_big = wb.census(wb.build_graph(*big))
+        wb.close()
+
+        _released(c)
+        full(64 << 10)                  # scratch and graph of a larger build
+        b = c.build_graph(*big)
+        free()
+        assert c.census(b).tolist() == want_big.tolist()
+        b.release()
+
+        other = tc.Context(0)           # another context's allocations
+        o = None
+        try:
+            full(64 << 10)
+            o = other.build_graph(*big)
+            free()
+            assert other.census(o).tolist() == want_big.tolist()
+        finally:
+            other.close()
+
+        tiny = dict(census_range=lambda: c.census_range(g, 0, n)[1:].tolist() == want[1:].tolist(),
+                    batch=lambda: c.census_batch([g])[0].tolist() == want.tolist(),
+                    submit=lambda: _poll(c, c.submit(g)).tolist() == want.tolist(),
+                    context=lambda: tc.Context(0).close() is None)
+        for name, f in tiny.items():    # buffers of the calls
+            print(name, flush=True)
+            _released(c)
+            full()
+            assert f(), name
+            free()
+
+        t = [c.submit_arcs(*big) for _ in range(3)]     # the serving slots' scratch
+        for x in t:
+            assert _poll(c, x).tolist() == want_big.tolist()
+        _released(c)
+        full(64 << 10)
+        b = c.build_graph(*_er(1 << 16, 1 << 20, 10))
+        free()
+        b.release()
+        g.release()
+        before = shim.shim_live()
+        c.trim()
+        # left: the batch plan's and the slots' small buffers
+        assert before - empty > (32 << 20) and shim.shim_live() - empty < (4 << 20)
+        h = c.build_graph(n, src, dst)
+        assert c.census(h).tolist() == want.tolist()
+        h.release()
+
+
+def test_kept_memory_goes_back(tmp_path):
+    _run(tmp_path, "kept")
+
+
 if __name__ == "__main__":
     so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
     so.shim_fail_from.argtypes = [ctypes.c_long]
