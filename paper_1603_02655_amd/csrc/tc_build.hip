@@ -1205,10 +1205,13 @@ void graph_pool::shrink(uint64_t to) {
 hipError_t graph_pool::alloc(void** out, uint64_t bytes) {
     *out = nullptr;
     // sizes in steps of an eighth of their power of two, so that graphs of
-    // about one size reuse each other's blocks
+    // about one size reuse each other's blocks; a block too large to be kept
+    // has its own size, and so has one that only fits without the rest
+    const uint64_t exact = std::max<uint64_t>(bytes, 1);
     uint64_t step = 4096;
     while (16 * step < bytes) step *= 2;
-    bytes = (std::max<uint64_t>(bytes, 1) + step - 1) / step * step;
+    bytes = (exact + step - 1) / step * step;
+    if (bytes > keep_) bytes = exact;
     void* p = nullptr;
     try {
         {
@@ -1227,7 +1230,8 @@ hipError_t graph_pool::alloc(void** out, uint64_t bytes) {
                 return hipSuccess;
             }
         }
-        const hipError_t e = device_alloc(&p, bytes);
+        hipError_t e = device_alloc(&p, bytes);
+        if (e != hipSuccess && exact < bytes) e = device_alloc(&p, bytes = exact);
         if (e != hipSuccess) return e;
         std::lock_guard<std::mutex> lk(mu_);
         live_.emplace(p, bytes);

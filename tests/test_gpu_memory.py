@@ -241,6 +241,37 @@ def test_kept_memory_goes_back(tmp_path):
     _run(tmp_path, "kept")
 
 
+def scenario_rounding(shim):
+    """A block that fits only in its exact size is allocated so."""
+    big = _er(1 << 15, 1 << 19, 9)
+    with tc.Context(0, hbm_budget_bytes=1) as c:     # nothing kept: exact sizes
+        at = shim.shim_live()
+        g = c.build_graph(*big)
+        want, exact = c.census(g), shim.shim_live() - at
+        g.release()
+        assert shim.shim_live() == at
+    with tc.Context(0) as c:
+        g = c.build_graph(*_er(1 << 15, 1 << 19, 11))   # (the scratch)
+        g.release()
+        c.trim()
+        at = shim.shim_live()
+        g = c.build_graph(*big)
+        rounded = shim.shim_live() - at
+        g.release()
+        c.trim()
+        scratch = rounded - exact
+        assert scratch > 0
+        shim.shim_set_limit(shim.shim_live() + rounded - (64 << 10))
+        g = c.build_graph(*big)
+        assert shim.shim_refused() > 0
+        shim.shim_set_limit(2**63)
+        assert c.census(g).tolist() == want.tolist()
+
+
+def test_blocks_that_fit_only_exactly(tmp_path):
+    _run(tmp_path, "rounding")
+
+
 if __name__ == "__main__":
     so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
     so.shim_fail_from.argtypes = [ctypes.c_long]
