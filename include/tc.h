@@ -152,7 +152,8 @@ typedef struct {
 } tc_serve_stats;
 
 /* Creates a context on HIP device `device`.  hbm_budget_bytes bounds the device
- * memory of jobs admitted by tc_submit (0 = 90% of free memory).  hip_stream,
+ * memory of jobs admitted by tc_submit (0 = 90% of free memory), with what
+ * the context keeps for reuse beside them when a round starts.  hip_stream,
  * when not null, is a hipStream_t the context uses instead of its own (the
  * caller keeps it alive until tc_context_destroy).  *out receives the handle. */
 int tc_context_create(int device, uint64_t hbm_budget_bytes, void* hip_stream, tc_context* out);

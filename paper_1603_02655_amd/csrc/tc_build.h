@@ -150,6 +150,9 @@ void space_free(build_space* sp);
 build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const int32_t* dst, bool host_arcs,
                                 const bucket_params& bp, graph_pool* pool, hipStream_t s, build_space* sp,
                                 device_graph* g);
+// Device bytes that a build of m arcs over n vertices for one census holds at
+// its peak, at most: scratch and graph, through either view.
+uint64_t build_footprint(uint64_t n, uint64_t m);
 hipError_t bucket_dyads(device_graph* g, const bucket_params& bp, hipStream_t s, build_space* sp);
 // Whether g has the records its census reads: the forward lists', or the
 // dyads', which a rebucket that failed has given up.

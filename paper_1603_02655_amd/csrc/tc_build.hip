@@ -1114,8 +1114,31 @@ inline uint64_t forward_space_bytes(uint64_t U, uint64_t n) {
 inline uint64_t view_space_bytes(uint64_t U, uint64_t n, bool tri) {
     return std::max(bucket_space_bytes(U, n), tri ? forward_space_bytes(U, n) : 0);
 }
+// Scratch of a whole build: the counters and per-row words, then the larger phase.
+inline uint64_t build_space_bytes(uint64_t n, uint64_t m, uint32_t bits, bool tri) {
+    return 4096 + (sizeof(uint32_t) + sizeof(uint2)) * (n + 1) +
+           std::max(sort_space_bytes(m, bits), view_space_bytes(2 * m, n, tri));
+}
+// Ids below 2^bits.
+inline uint32_t id_bits(uint64_t n) {
+    uint32_t b = 1;
+    while ((1ull << b) < n) ++b;
+    return b;
+}
 
 }  // namespace
+
+uint64_t build_footprint(uint64_t n, uint64_t m) {
+    const uint64_t base = sizeof(int64_t) * (n + 1) + 2 * m * (2 * sizeof(uint32_t) + sizeof(uint64_t)) +
+                          sizeof(uint4) * (n + 1) + sizeof(uint32_t) * kRowPad + sizeof(uint64_t);
+    const uint64_t runs = std::min(n, m);   // (a vertex's last hub task is short)
+    const uint64_t dyads = sizeof(dyad_rec) * m + sizeof(hub_task) * (runs + m / kHubChunk);
+    const uint64_t tri = sizeof(uint32_t) * (n + 1 + m + kRowPad) + sizeof(uint4) * m +
+                         sizeof(tri_task) * (runs + m / 64);
+    const uint64_t graph = base + std::max(dyads, tri);
+    // (a reused block may be a quarter larger than asked for)
+    return build_space_bytes(n, m, id_bits(n), true) + graph + graph / 4;
+}
 
 hipError_t fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s) {
     if (n == 0) return hipSuccess;
@@ -1440,13 +1463,12 @@ build_status build_graph_device(int32_t n, int64_t m, const int32_t* src, const 
     build_status st{};
     hipError_t err = hipSuccess;
     // ids below 2^bits; the sentinel key is a loop of id 2^bits - 1
-    const uint32_t bits = std::max(1u, bit_width_u32((uint32_t)std::max(n - 1, 0)));
+    const uint32_t bits = id_bits((uint64_t)n);
     const uint64_t keys_n = 2ull * (uint64_t)m;
     *g = device_graph{};
     g->n = n;
     g->mem = pool;
-    const uint64_t small = 4096 + (sizeof(uint32_t) + sizeof(uint2)) * ((uint64_t)n + 1);
-    const uint64_t need = small + std::max(sort_space_bytes((uint64_t)m, bits), view_space_bytes(keys_n, (uint64_t)n, bp.tri != 0));
+    const uint64_t need = build_space_bytes((uint64_t)n, (uint64_t)m, bits, bp.tri != 0);
     if ((err = space_reserve(sp, need, s)) != hipSuccess) {
         st.hip = err;
         return st;
@@ -1661,7 +1683,7 @@ hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_
     const size_t mark = ar.mark();
     const uint64_t U = g->U, F = U / 2;   // every joined pair is in one forward list
     const int32_t n = g->n;
-    const uint32_t bits = std::max(1u, bit_width_u32((uint32_t)std::max(n - 1, 0)));
+    const uint32_t bits = id_bits((uint64_t)n);
     graph_pool* mem = g->mem;
     forward_lists& t = g->tri;
     auto& out = t.edges;

@@ -279,7 +279,9 @@ void scheduler::worker_main() {
                 idle_released = false;
                 st_.rounds += 1;
                 rotate_ = (free_slot + 1) % (int)slots_.size();
+                const uint64_t used = bytes_in_flight_ + ex_->held_bytes();
                 lk.unlock();
+                ex_->make_room(lim_.budget > used ? lim_.budget - used : 0);
                 const int rc = ex_->launch(free_slot, s.jobs);   // only this thread touches s.jobs
                 lk.lock();
                 if (rc != kOk) {

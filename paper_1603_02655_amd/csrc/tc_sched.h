@@ -64,6 +64,10 @@ struct round_executor {
     virtual void thread_start() {}
     // Number of rounds that may be in flight at once.
     virtual int slot_count() const = 0;
+    // Worker thread, lock not held, before each launch: what the admitted jobs
+    // and held_bytes() leave of the budget, the most that device memory kept
+    // for reuse may hold.
+    virtual void make_room(uint64_t bytes) { (void)bytes; }
     // Worker thread, scheduler lock not held: starts the round of `jobs` on
     // `slot` and returns kOk, after which the executor calls
     // scheduler::round_done(slot) exactly once, from any thread, when the

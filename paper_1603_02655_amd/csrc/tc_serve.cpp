@@ -108,11 +108,8 @@ uint64_t job_footprint(const serve_job& j) {
         items += ((uint64_t)g.n + kBatchRowsPerItem - 1) / kBatchRowsPerItem;
         return ws + sizeof(work_item) * items;
     }
-    uint64_t m = j.src.size();
-    // arcs on the device, two sort buffers, run heads and unique index, the
-    // graph (entries, owners, prefix counts, dyad records) and its work items
-    return ws + 8 * m + 2 * m * 8 * 2 + 2 * m * 16 + 2 * m * 16 + m * sizeof(dyad_rec) + 16 * ((uint64_t)j.n + 1) +
-           sizeof(work_item) * (m + 1);
+    // the build's scratch and graph, and its work items
+    return ws + build_footprint((uint64_t)j.n, j.src.size()) + sizeof(work_item) * (j.src.size() + 1);
 }
 
 // The device side of the rounds: one stream and one set of staging buffers
@@ -137,6 +134,10 @@ public:
 
     // A new thread's device is 0, whichever the context is on.
     void thread_start() override { (void)hipSetDevice(ctx_->device); }
+
+    void make_room(uint64_t bytes) override {
+        if (bytes < pool_keep(ctx_) + (kSlots + 1) * space_keep(ctx_)) ctx_->pool.give_back(bytes);
+    }
 
     int launch(int si, std::vector<sched::job*>& jobs) override {
         bool cold = false;

@@ -14,7 +14,7 @@ enum { kMax = 1 << 16 };
 static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static struct { void* p; size_t bytes; } live_blocks[kMax];
 static int blocks;
-static uint64_t live, limit = UINT64_MAX;
+static uint64_t live, peak, limit = UINT64_MAX;
 static long fail_from = -1, calls, refused;
 
 static void count_unchosen(void);
@@ -36,6 +36,7 @@ int hipMalloc(void** out, size_t bytes) {
         live_blocks[blocks].p = *out;
         live_blocks[blocks++].bytes = bytes;
         live += bytes;
+        if (live > peak) peak = live;
     }
     pthread_mutex_unlock(&mu);
     return rc;
@@ -91,4 +92,12 @@ void shim_set_limit(uint64_t bytes) {
     pthread_mutex_unlock(&mu);
 }
 uint64_t shim_live(void) { return live; }
+/* The most live bytes since the last call. */
+uint64_t shim_peak(void) {
+    pthread_mutex_lock(&mu);
+    const uint64_t p = peak;
+    peak = live;
+    pthread_mutex_unlock(&mu);
+    return p;
+}
 long shim_refused(void) { return refused; }

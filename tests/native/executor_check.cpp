@@ -116,7 +116,59 @@ static void worker_thread_starts_first() {
     CHECK(ex.out_of_order.load() == 0);
 }
 
+// Before a round starts, memory kept for reuse shrinks to what the admitted
+// jobs and the held bytes leave of the budget.
+struct room_exec : round_executor {
+    scheduler* S = nullptr;
+    std::atomic<uint64_t> held{0};
+    uint64_t room = ~0ull;                 // worker thread only
+    std::atomic<int> launches{0}, wrong{0};
+    int slot_count() const override { return 1; }
+    void make_room(uint64_t bytes) override { room = bytes; }
+    int launch(int slot, std::vector<job*>& jobs) override {
+        uint64_t fp = 0;
+        for (job* j : jobs) fp += j->footprint;
+        if (room != 1000 - fp - held.load()) ++wrong;
+        room = ~0ull;
+        ++launches;
+        S->round_done(slot);
+        return kOk;
+    }
+    void collect(int, std::vector<job*>&) override {}
+    void job_done(job*) override {}
+    void release(bool) override {}
+    uint64_t held_bytes() const override { return held.load(); }
+    void abandon(int) override {}
+    void drain() override {}
+};
+
+static void kept_memory_makes_room() {
+    room_exec ex;
+    sched_limits lim;
+    lim.budget = 1000;
+    scheduler S(&ex, lim);
+    ex.S = &S;
+    const uint64_t footprints[] = {100, 600, 1}, held[] = {0, 300, 999};
+    for (int k = 0; k < 3; ++k) {
+        ex.held.store(held[k]);
+        job* j = new job();
+        j->footprint = footprints[k];
+        uint64_t t = 0, counts[16];
+        CHECK(S.submit(j, &t) == kOk);
+        int over = 0;
+        for (int i = 0; i < 20000 && !over; ++i) {
+            CHECK(S.poll(t, counts, &over) == kOk);
+            if (!over) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+        }
+        CHECK(over);
+    }
+    S.stop();
+    CHECK(ex.launches.load() == 3);
+    CHECK(ex.wrong.load() == 0);
+}
+
 int main() {
+    kept_memory_makes_room();
     worker_thread_starts_first();
     abandoned_slot_marked_before_its_jobs_end();
     if (g_failures) return 1;

@@ -272,11 +272,38 @@ def test_blocks_that_fit_only_exactly(tmp_path):
     _run(tmp_path, "rounding")
 
 
+def scenario_budget(shim):
+    """Served requests that bring their arcs, few of them beside many vertices or
+    the other way round, hold no more than the budget, kept memory included."""
+    budget = 200 << 20
+    few = [(1_000_000, np.array([k, 3], np.int32), np.array([999_999, k + 5], np.int32)) for k in range(6)]
+    many = [_er(1 << 15, 1 << 19, 20 + k) for k in range(6)]
+    with tc.Context(0) as c:
+        want = [c.census(c.build_graph(*x)) for x in few + many]
+    with tc.Context(0, hbm_budget_bytes=budget) as c:
+        c.submit_arcs(3, [0], [1])
+        base = shim.shim_live()
+        shim.shim_peak()
+        for order in (range(12), range(11, -1, -1), (0, 6, 1, 7, 2, 8, 3, 9, 4, 10, 5, 11)):
+            x = few + many
+            tickets = {k: c.submit_arcs(*x[k]) for k in order}
+            for k, t in tickets.items():
+                assert _poll(c, t).tolist() == want[k].tolist()
+            peak = shim.shim_peak() - base
+            print("peak", peak >> 20, "MB", flush=True)
+            assert peak <= budget + (4 << 20)    # (the slots' own small buffers)
+
+
+def test_served_builds_hold_the_budget(tmp_path):
+    _run(tmp_path, "budget")
+
+
 if __name__ == "__main__":
     so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
     so.shim_fail_from.argtypes = [ctypes.c_long]
     so.shim_set_limit.argtypes = [ctypes.c_uint64]
     so.shim_live.restype = ctypes.c_uint64
+    so.shim_peak.restype = ctypes.c_uint64
     so.shim_refused.restype = ctypes.c_long
     so.shim_unchosen.restype = ctypes.c_long
     globals()["scenario_" + sys.argv[1]](so)
