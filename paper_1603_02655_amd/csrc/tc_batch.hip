@@ -4,13 +4,18 @@
 // pinned host memory) and replayed.  Descriptors and items live in device
 // buffers read by the kernel, so another set of graphs that fits the captured
 // capacities is served by rewriting those buffers and replaying; the capture is
-// redone only when a capacity grows.
+// redone only when a capacity grows or the tuning changes.  Which hub kernels a
+// launch has depends on the set; each of the four kinds has a capture of its own,
+// made when it is first needed, so that sets of different kinds can alternate.
 #include <algorithm>
 #include <cstring>
 
 #include "tc_api_internal.h"
 
 namespace tc {
+
+// What a launch holds: hub tasks over forward lists, over dyad records.
+enum : uint32_t { kHasTri = 1, kHasHub = 2, kKinds = 4 };
 
 struct batch_plan {
     std::vector<tc_graph> graphs;       // graphs the device buffers currently describe
@@ -21,17 +26,19 @@ struct batch_plan {
     unsigned long long* d_accs = nullptr;
     unsigned int* d_ctr = nullptr;
     unsigned long long* h_accs = nullptr;   // pinned
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    uint32_t grid = 0, hub_grid = 0, tri_grid = 0, hub_blocks = 0;
-    bool forked = false;   // the captured launch has a branch for the items that are no hub tasks
+    hipGraph_t graph[kKinds] = {};
+    hipGraphExec_t exec[kKinds] = {};
+    uint32_t grid = 0, hub_blocks = 0;
     uint32_t hub_tile = 0, batch_tile = 0;  // LDS tiles the captured kernels use
     bool valid = false;                     // buffers describe `graphs`
     bool tri = false;                       // ... through their forward lists
+    uint32_t kind = 0;                      // ... whose launch is this one
 
     void release() {
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
+        for (uint32_t k = 0; k < kKinds; ++k) {
+            if (exec[k]) (void)hipGraphExecDestroy(exec[k]);
+            if (graph[k]) (void)hipGraphDestroy(graph[k]);
+        }
         if (d_desc) (void)hipFree(d_desc);
         if (d_items) (void)hipFree(d_items);
         if (d_num) (void)hipFree(d_num);
@@ -114,23 +121,22 @@ void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it) 
 
 namespace {
 
-hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipStream_t s, uint32_t grid,
-                           uint32_t hub_grid, uint32_t tri_grid, uint32_t hub_tile, uint32_t batch_tile,
-                           hipStream_t side, hipEvent_t* fork) {
-    if (p->exec && graphs <= p->cap_graphs && items <= p->cap_items && grid == p->grid && hub_grid == p->hub_grid &&
-        tri_grid == p->tri_grid && hub_tile == p->hub_tile && batch_tile == p->batch_tile &&
-        (side != nullptr) == p->forked)
-        return hipSuccess;
+// Whether the buffers' capacities are those of a captured launch.
+bool holds(const batch_plan& p, uint32_t graphs, uint32_t items, const tc_tuning& t) {
+    return p.d_desc && graphs <= p.cap_graphs && items <= p.cap_items && p.grid == t.batch_blocks &&
+           p.hub_blocks == t.hub_blocks && p.hub_tile == t.hub_tile && p.batch_tile == t.batch_tile;
+}
+
+hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, const tc_tuning& t, hipStream_t s) {
+    if (holds(*p, graphs, items, t)) return hipSuccess;
     (void)hipStreamSynchronize(s);
     p->release();
     p->cap_graphs = std::max<uint32_t>(graphs + graphs / 4, 16);
     p->cap_items = std::max<uint32_t>(items + items / 4, 1024);
-    p->grid = grid;
-    p->hub_grid = hub_grid;
-    p->hub_tile = hub_tile;
-    p->batch_tile = batch_tile;
-    p->tri_grid = tri_grid;
-    p->forked = side != nullptr;
+    p->grid = t.batch_blocks;
+    p->hub_blocks = t.hub_blocks;
+    p->hub_tile = t.hub_tile;
+    p->batch_tile = t.batch_tile;
     hipError_t e = device_alloc((void**)&p->d_desc, sizeof(graph_desc) * p->cap_graphs);
     if (e == hipSuccess) e = device_alloc((void**)&p->d_items, sizeof(work_item) * p->cap_items);
     if (e == hipSuccess) e = device_alloc((void**)&p->d_num, 3 * sizeof(uint32_t));
@@ -138,19 +144,28 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, hipSt
     if (e == hipSuccess) e = device_alloc((void**)&p->d_ctr, sizeof(unsigned int) * 3 * kCounterWords);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&p->h_accs, sizeof(unsigned long long) * kNumClasses * p->cap_graphs);
-    if (e != hipSuccess) {
-        p->release();
-        return e;
-    }
-    // capture: zero accumulators and counters, persistent kernels, sums to host memory
-    e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) p->release();
+    return e;
+}
+
+// Captures the launch of `kind`: zero accumulators and counters, persistent
+// kernels, sums to host memory.
+hipError_t ensure_captured(batch_plan* p, uint32_t kind, tc_context_s* ctx) {
+    if (p->exec[kind]) return hipSuccess;
+    // a hub kernel runs when it has items (one of them also when neither has)
+    const uint32_t tri_grid = kind != kHasHub ? tri_blocks(p->hub_blocks, ctx->cu_count) : 0;
+    const uint32_t hub_grid = kind & kHasHub ? p->hub_blocks : 0;
+    // The branch costs 7 us and gains where there are hub tasks (1 graph
+    // without: 46 us with it, 39 without; 4 graphs with 1600 tasks: 60 and 78).
+    const hipStream_t s = ctx->stream, side = kind != 0 ? ctx->side : nullptr;
+    hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return e;
-    const batch_buffers bb{p->d_desc, p->d_items, p->d_num, p->d_accs, p->d_ctr, p->tri_grid, p->hub_grid, p->grid,
-                           p->cap_graphs, p->h_accs, side, fork};
+    const batch_buffers bb{p->d_desc, p->d_items, p->d_num, p->d_accs, p->d_ctr, tri_grid, hub_grid, p->grid,
+                           p->cap_graphs, p->h_accs, side, ctx->fork};
     hipError_t el = batch_launch(bb, p->hub_tile, p->batch_tile, s);
-    e = hipStreamEndCapture(s, &p->graph);
+    e = hipStreamEndCapture(s, &p->graph[kind]);
     if (el != hipSuccess) e = el;
-    if (e == hipSuccess) e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
+    if (e == hipSuccess) e = hipGraphInstantiate(&p->exec[kind], p->graph[kind], nullptr, nullptr, 0);
     if (e != hipSuccess) p->release();
     return e;
 }
@@ -174,9 +189,7 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
     std::vector<tc_graph> want(graphs, graphs + count);
     hipError_t e = hipSuccess;
     const bool tri = ctx->tuning.tri != 0;
-    if (!(p->valid && p->graphs == want && p->grid == ctx->tuning.batch_blocks &&
-          p->hub_blocks == ctx->tuning.hub_blocks && p->hub_tile == ctx->tuning.hub_tile &&
-          p->batch_tile == ctx->tuning.batch_tile && p->tri == tri)) {
+    if (!(p->valid && p->graphs == want && holds(*p, 0, 0, ctx->tuning) && p->tri == tri)) {
         item_lists lists;
         std::vector<graph_desc> descs(count);
         for (int32_t i = 0; i < count; ++i) {
@@ -185,17 +198,12 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
             descs[i] = describe(g);
             append_items(g, (uint32_t)i, tri && g.tri.fptr, lists);
         }
-        // a hub kernel runs when it has items (one of them also when neither has)
-        const uint32_t tri_grid =
-            lists.hub.empty() || !lists.tri.empty() ? tri_blocks(ctx->tuning.hub_blocks, ctx->cu_count) : 0;
-        const uint32_t hub_grid = lists.hub.empty() ? 0 : ctx->tuning.hub_blocks;
-        // The branch costs 7 us and gains where there are hub tasks (1 graph
-        // without: 46 us with it, 39 without; 4 graphs with 1600 tasks: 60 and 78).
-        const bool two = !lists.tri.empty() || !lists.hub.empty();
+        const uint32_t kind = (lists.tri.empty() ? 0u : kHasTri) | (lists.hub.empty() ? 0u : kHasHub);
         uint32_t nums[3];
         std::vector<work_item>& items = lists.join(nums);
-        e = ensure_capacity(p, (uint32_t)count, (uint32_t)items.size(), ctx->stream, ctx->tuning.batch_blocks, hub_grid,
-                            tri_grid, ctx->tuning.hub_tile, ctx->tuning.batch_tile, two ? ctx->side : nullptr, ctx->fork);
+        p->valid = false;   // (until the buffers are written)
+        e = ensure_capacity(p, (uint32_t)count, (uint32_t)items.size(), ctx->tuning, ctx->stream);
+        if (e == hipSuccess) e = ensure_captured(p, kind, ctx);
         if (e != hipSuccess) return status_from_hip(e);
         uint32_t nitems = (uint32_t)items.size();
         e = hipMemcpyAsync(p->d_desc, descs.data(), sizeof(graph_desc) * count, hipMemcpyHostToDevice, ctx->stream);
@@ -205,17 +213,14 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
         if (e == hipSuccess)
             e = hipMemcpyAsync(p->d_num, nums, sizeof(nums), hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);   // host vectors go out of scope
-        if (e != hipSuccess) {
-            p->valid = false;
-            return status_from_hip(e);
-        }
+        if (e != hipSuccess) return status_from_hip(e);
         p->graphs = want;
-        p->hub_blocks = ctx->tuning.hub_blocks;
         p->valid = true;
         p->tri = tri;
+        p->kind = kind;
     }
     if (ctx->timing) (void)hipEventRecord(ctx->ev[0], ctx->stream);
-    e = hipGraphLaunch(p->exec, ctx->stream);
+    e = hipGraphLaunch(p->exec[p->kind], ctx->stream);
     if (ctx->timing) (void)hipEventRecord(ctx->ev[1], ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return status_from_hip(e);

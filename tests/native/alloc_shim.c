@@ -101,3 +101,5 @@ uint64_t shim_peak(void) {
     return p;
 }
 long shim_refused(void) { return refused; }
+/* hipMalloc calls since the last shim_fail_from. */
+long shim_calls(void) { return calls; }

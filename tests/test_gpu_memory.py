@@ -298,12 +298,40 @@ def test_served_builds_hold_the_budget(tmp_path):
     _run(tmp_path, "budget")
 
 
+def scenario_batches(shim):
+    """Sets of every kind (with hub tasks over forward lists, over dyad records,
+    both or neither) alternate on one batch plan without a new allocation, and
+    each replay is right."""
+    with tc.Context(0) as c:
+        ring = np.arange(500, dtype=np.int32)
+        flat = [c.build_graph(500, ring, (ring + k) % 500) for k in (1, 2, 3)]
+        hubs = [c.build_graph(*_graph()), c.build_graph(*_er(300, 9000, 30))]
+        c.set_tuning(tri=0)
+        dyads = [c.build_graph(*_er(300, 9000, 31))]       # (no forward lists)
+        c.set_tuning(tri=1)
+        sets = [flat, hubs, dyads, hubs + dyads + flat]
+        want = [c.census_each(s) for s in sets]
+        for s in reversed(sets):
+            c.census_batch(s)
+        shim.shim_fail_from(-1)
+        for r in range(3):
+            for s, w in zip(sets, want):
+                for _ in range(1 + r):
+                    assert c.census_batch(s).tolist() == w.tolist()
+        assert shim.shim_calls() == 0
+
+
+def test_alternating_batches_keep_their_buffers(tmp_path):
+    _run(tmp_path, "batches")
+
+
 if __name__ == "__main__":
     so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
     so.shim_fail_from.argtypes = [ctypes.c_long]
     so.shim_set_limit.argtypes = [ctypes.c_uint64]
     so.shim_live.restype = ctypes.c_uint64
     so.shim_peak.restype = ctypes.c_uint64
+    so.shim_calls.restype = ctypes.c_long
     so.shim_refused.restype = ctypes.c_long
     so.shim_unchosen.restype = ctypes.c_long
     globals()["scenario_" + sys.argv[1]](so)
