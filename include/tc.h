@@ -76,7 +76,8 @@ typedef struct {
                                                   with a vertex after both omitted) */
     uint64_t tri_bucket_cost[TC_NUM_BUCKETS];  /* sum of |N+(x)|+|N+(y)| per bucket */
     uint64_t tri_tasks;           /* hub tasks over the forward lists */
-    uint64_t tri_stream;          /* sum over hub edges (x, y) of the entries of N+(x) before y */
+    uint64_t tri_stream;          /* sum over hub edges (x, y) of the entries streamed: those of N+(x) before y,
+                                     or N+(y) where that is much shorter */
     uint64_t tri_staged;          /* sum over those tasks of the shared vertex's forward-list length */
     /* groups of consecutive hub tasks that one workgroup stages into a single LDS tile */
     uint64_t hub_groups;          /* over the hub dyads */

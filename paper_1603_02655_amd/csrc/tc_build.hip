@@ -760,11 +760,27 @@ __global__ __launch_bounds__(kT) void k_fwd_emit(const uint64_t* __restrict__ ke
 // Bucket of the edge of sorted key i (x, y): hub when the longer of the two
 // forward lists reaches t_hub, else by their joint length; kBuckets for an
 // edge that closes no triangle with a smaller rank.
+//
+// A hub edge is found at y (its prefix of N+(x) streams against a table of
+// N+(y)) or, `at_x`, at x (N+(y) streams against a table of N+(x); x and y
+// change their roles in the record, so the kernels see no difference).  The
+// prefix is seldom much longer than N+(y), which is all ranks below y that y is
+// joined to, and the choice is y; but where y has few neighbours of smaller
+// rank and x many (items of a user, both sides of a bipartite graph with a
+// vertex joined to all), the prefixes add up to the square of the row lengths.
+// x takes the edge when that more than halves the blocks of 16 to stream: never
+// on R-MAT, random, complete or citation graphs (there finding an edge at x for
+// one block less gains 0.5 % of the blocks or, random graph of 200 neighbours
+// per vertex, 2.4 %, for a third of the edges moved).  4000 vertices joined to each
+// of 2000 and one vertex to all: 2.20 ms, now 0.20; 20000 users with 1000 of 6000
+// items each, a few links among the items: 2.98 ms, now 0.21.
 struct edge_at {
-    uint32_t bx, by, dy, y, pos, bits;
+    uint32_t bx, by, dy, x, y, pos, bits;
     uint64_t cost;
     int bucket;
+    bool at_x;
 };
+__device__ inline uint32_t blocks16(uint32_t entries) { return (entries + 15u) >> 4; }
 __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_t i, uint64_t count, uint32_t bits,
                                       const uint32_t* __restrict__ fptr, const bucket_params& bp) {
     edge_at r{};
@@ -772,6 +788,7 @@ __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_
     if (i >= count) return r;
     const uint64_t k = keys[i];
     const uint32_t x = (uint32_t)(k >> (bits + 3));
+    r.x = x;
     r.y = (uint32_t)((k >> 3) & ((1ull << bits) - 1ull));
     r.bx = fptr[x];
     r.pos = (uint32_t)i - r.bx;
@@ -783,6 +800,7 @@ __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_
     if (dy == 0) return r;
     r.cost = dx + dy;
     r.bucket = (dx > dy ? dx : dy) >= bp.t_hub ? kBucketHub : r.cost < bp.t0 ? 0 : r.cost < bp.t1 ? 1 : 2;
+    r.at_x = r.bucket == kBucketHub && blocks16(r.pos) > 2u * blocks16(r.dy);
     return r;
 }
 
@@ -801,7 +819,7 @@ __global__ __launch_bounds__(kT) void k_edge_count(const uint64_t* __restrict__ 
             my[q] += r.bucket == q ? 1u : 0u;
             mycost[q] += r.bucket == q ? r.cost : 0ull;
         }
-        if (r.bucket == kBucketHub) mystream += r.pos;
+        if (r.bucket == kBucketHub) mystream += r.at_x ? r.dy : r.pos;
     }
     store_tile_sums(my, mycost, mystream, 0ull, counts, part, nblocks, sh);
 }
@@ -812,15 +830,18 @@ __global__ __launch_bounds__(kT) void k_edge_count(const uint64_t* __restrict__ 
 // place of y in the row (i - bx, below sqrt(2 F): the d neighbours after x have
 // degree d or more), tail, bits.  Otherwise the key holds y and i, and the
 // record gathers the rest by i (R-MAT 2^20, 14 M hub edges: 0.37 ms for the
-// gathers, which miss the L2 at 55 G lines/s, 0.15 ms without).
+// gathers, which miss the L2 at 55 G lines/s, 0.15 ms without).  An edge found
+// at x has x in the place of y, and a place of 0 (which no hub edge has), or
+// the top bit, to tell it by; its record gathers y by i either way.
 struct hub_key {
     uint32_t ibits, pbits;   // pbits 0: y << 32 | i
     __host__ __device__ uint32_t y_shift() const { return pbits ? 4 + pbits + ibits : 32; }
 };
+constexpr uint64_t kFoundAtX = 1ull << 63;
 
 // Lane / wave / group records in x-major order; for the hub edges a key, in
-// x-major order too (sorted by y next).  Without room in the key, keys[i]
-// becomes bx << 4 | tail << 3 | bits.
+// x-major order too (sorted by y next, or x).  Without room in the key, keys[i]
+// becomes bx << 4 | tail << 3 | bits, except for an edge found at x.
 __global__ __launch_bounds__(kT) void k_edge_scatter(uint64_t* keys, uint64_t count, uint32_t bits,
                                                      const uint32_t* __restrict__ fptr, bucket_params bp,
                                                      const uint64_t* __restrict__ offsets, uint32_t nblocks,
@@ -856,7 +877,11 @@ __global__ __launch_bounds__(kT) void k_edge_scatter(uint64_t* keys, uint64_t co
                 const uint64_t to = at[q] + (uint32_t)__popcll(m & lanemask_lt());
                 if (q == kBucketHub) {
                     const uint32_t low = ((fwd[i - 1] & 0x00fffffeu) >= 2u * kCore ? 8u : 0u) | r[k].bits;
-                    if (hk.pbits) {
+                    if (r[k].at_x) {
+                        hubkeys[to - hub_begin] =
+                            hk.pbits ? ((uint64_t)r[k].x << hk.y_shift()) | (i << (4 + hk.pbits))
+                                     : kFoundAtX | ((uint64_t)r[k].x << 32) | i;
+                    } else if (hk.pbits) {
                         hubkeys[to - hub_begin] = ((uint64_t)r[k].y << hk.y_shift()) | (i << (4 + hk.pbits)) |
                                                   ((uint64_t)r[k].pos << 4) | low;
                     } else {
@@ -871,12 +896,15 @@ __global__ __launch_bounds__(kT) void k_edge_scatter(uint64_t* keys, uint64_t co
 }
 
 // Hub records from the keys sorted by y, and the run of each y (first and one
-// past the last record, zero elsewhere).
+// past the last record, zero elsewhere); x in the place of y where the edge is
+// found at x.  fptr, bits: for the records of these.
 __global__ __launch_bounds__(kT) void k_edge_hub(const uint64_t* __restrict__ hubkeys, uint64_t hubs, hub_key hk,
                                                  const uint64_t* __restrict__ edges, const uint32_t* __restrict__ fwd,
+                                                 const uint32_t* __restrict__ fptr, uint32_t bits,
                                                  uint32_t* __restrict__ first, uint32_t* __restrict__ past,
                                                  uint4* __restrict__ out) {
     const uint32_t ys = hk.y_shift();
+    const uint64_t idmask = (1ull << bits) - 1ull;
     uint64_t key[kI], ed[kI];
 #pragma unroll
     for (int r = 0; r < kI; ++r) {
@@ -888,20 +916,32 @@ __global__ __launch_bounds__(kT) void k_edge_hub(const uint64_t* __restrict__ hu
         const uint64_t j = (uint64_t)blockIdx.x * kTile + (uint64_t)r * kT + threadIdx.x;
         ed[r] = j < hubs && !hk.pbits ? edges[(uint32_t)key[r]] : 0ull;
     }
+    auto run = [&](uint64_t k) { return (uint32_t)((k >> ys) & idmask); };
 #pragma unroll
     for (int r = 0; r < kI; ++r) {
         const uint64_t j = (uint64_t)blockIdx.x * kTile + (uint64_t)r * kT + threadIdx.x;
         if (j >= hubs) continue;
-        const uint32_t y = (uint32_t)(key[r] >> ys);
+        const uint32_t y = run(key[r]);
         uint32_t i, bx, low;
+        bool at_x;
         if (hk.pbits) {
             i = (uint32_t)((key[r] >> (4 + hk.pbits)) & ((1ull << hk.ibits) - 1ull));
             bx = i - (uint32_t)((key[r] >> 4) & ((1ull << hk.pbits) - 1ull));
             low = (uint32_t)key[r] & 15u;
+            at_x = bx == i;
         } else {
             i = (uint32_t)key[r];
             bx = (uint32_t)(ed[r] >> 4);
             low = (uint32_t)ed[r] & 15u;
+            at_x = (key[r] & kFoundAtX) != 0;
+        }
+        if (at_x) {   // the pair as (y, x): its arcs the other way, the order of the ids turned
+            const uint64_t e = hk.pbits ? edges[i] : ed[r];
+            const uint32_t other = (uint32_t)((e >> 3) & idmask), b = (uint32_t)e & 7u;
+            bx = fptr[other];
+            i = fptr[other + 1];
+            low = ((fwd[i - 1] & 0x00fffffeu) >= 2u * kCore ? 8u : 0u) | ((b & 2u) << 1) | ((b & 4u) >> 1) |
+                  ((b & 1u) ^ 1u);
         }
         uint32_t core = i;
         if (low & 8u) {
@@ -913,8 +953,8 @@ __global__ __launch_bounds__(kT) void k_edge_hub(const uint64_t* __restrict__ hu
             core = lo;
         }
         out[j] = make_uint4(bx, core, i, low & 7u);
-        if (j == 0 || (uint32_t)(hubkeys[j - 1] >> ys) != y) first[y] = (uint32_t)j;
-        if (j + 1 == hubs || (uint32_t)(hubkeys[j + 1] >> ys) != y) past[y] = (uint32_t)j + 1;
+        if (j == 0 || run(hubkeys[j - 1]) != y) first[y] = (uint32_t)j;
+        if (j + 1 == hubs || run(hubkeys[j + 1]) != y) past[y] = (uint32_t)j + 1;
     }
 }
 
@@ -1775,7 +1815,8 @@ hipError_t build_forward(device_graph* g, const bucket_params& bp, const uint32_
     TRY(fill_u64((uint64_t*)staged, 2, 0, s));
     TRY(radix_sort(&tmp, &hk, hubs, hkey.y_shift(), bits, ar, s));
     hipLaunchKernelGGL(k_edge_hub, dim3(blocks_for(hubs)), dim3(kT), 0, s, (const uint64_t*)tmp, hubs, hkey,
-                       (const uint64_t*)keys, (const uint32_t*)t.fwd, first, past, out.recs + out.off[kBucketHub]);
+                       (const uint64_t*)keys, (const uint32_t*)t.fwd, (const uint32_t*)t.fptr, bits, first, past,
+                       out.recs + out.off[kBucketHub]);
     hipLaunchKernelGGL(k_tri_ntasks, dim3(std::min(grid1((uint64_t)n), kStatBlocks)), dim3(kT), 0, s,
                        (const uint32_t*)first, (const uint32_t*)past, n, (const uint32_t*)t.fptr, out.chunk, task_off,
                        staged);

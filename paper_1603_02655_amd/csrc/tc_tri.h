@@ -6,7 +6,9 @@
 // 2 IsEdge(y, x) and g = [id(y) > id(x)].  A triangle {x, y, z}, z < y < x by
 // rank, is found at the edge (x, y), as an entry z of N+(y) that is also in
 // N+(x), where it stands before y: the part of N+(x) before y (its prefix) is
-// all of N+(x) an edge has to look at.
+// all of N+(x) an edge has to look at.  A hub record may have x and y the other
+// way round (all of N+(y) against N+(x), where y's list is much the shorter):
+// what follows holds for it with the two names exchanged.
 //
 // What a triangle adds to the census depends on the direction codes of its
 // three pairs only (with g, the order of the three ids): a kernel counts
