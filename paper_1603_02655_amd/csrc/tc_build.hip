@@ -312,19 +312,21 @@ struct run_of {
     uint32_t f;
 };
 __device__ inline run_of run_at(const uint64_t* __restrict__ keys, uint64_t i, uint64_t count, uint64_t sentinel) {
-    const uint64_t k = keys[i];
-    if (i != 0 && (keys[i - 1] >> 2) == (k >> 2)) return run_of{false, 0u};
-    if ((k >> 2) == (sentinel >> 2)) return run_of{false, 0u};
-    if ((k & 3u) == 2u) return run_of{true, 2u};
-    uint64_t last = i, step = 1;   // keys[last] is in the run
-    while (last + step < count && (keys[last + step] >> 2) == (k >> 2)) {
-        last += step;
-        if ((keys[last] & 3u) == 2u) return run_of{true, 3u};
-        step *= 2;
+    const uint64_t k = keys[i], before = keys[i ? i - 1 : 0], after = keys[i + 1 < count ? i + 1 : i];
+    if ((i != 0 && (before >> 2) == (k >> 2)) || (k >> 2) == (sentinel >> 2)) return run_of{false, 0u};
+    const bool more = i + 1 < count && (after >> 2) == (k >> 2);
+    uint32_t f = (uint32_t)(k & 3u) | (more ? (uint32_t)(after & 3u) : 0u);
+    if (more && f == 1u) {
+        uint64_t last = i + 1, step = 1;   // keys[last] is in the run
+        while (last + step < count && (keys[last + step] >> 2) == (k >> 2)) {
+            last += step;
+            step *= 2;
+        }
+        for (step /= 2; step != 0; step /= 2)
+            if (last + step < count && (keys[last + step] >> 2) == (k >> 2)) last += step;
+        f |= (uint32_t)(keys[last] & 3u);
     }
-    for (step /= 2; step != 0; step /= 2)
-        if (last + step < count && (keys[last + step] >> 2) == (k >> 2)) last += step;
-    return run_of{true, (keys[last] & 3u) == 2u ? 3u : 1u};
+    return run_of{true, f};
 }
 
 // Per tile: entries, and the two direction-bit counts (as in tpre).
@@ -775,12 +777,11 @@ __global__ __launch_bounds__(kT) void k_fwd_emit(const uint64_t* __restrict__ ke
 // of 2000 and one vertex to all: 2.20 ms, now 0.20; 20000 users with 1000 of 6000
 // items each, a few links among the items: 2.98 ms, now 0.21.
 struct edge_at {
-    uint32_t bx, by, dy, x, y, pos, bits;
+    uint32_t bx, by, dy, y, pos, bits;
     uint64_t cost;
     int bucket;
-    bool at_x;
+    __device__ inline bool at_x() const { return (pos + 15u) >> 4 > 2u * ((dy + 15u) >> 4); }
 };
-__device__ inline uint32_t blocks16(uint32_t entries) { return (entries + 15u) >> 4; }
 __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_t i, uint64_t count, uint32_t bits,
                                       const uint32_t* __restrict__ fptr, const bucket_params& bp) {
     edge_at r{};
@@ -788,7 +789,6 @@ __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_
     if (i >= count) return r;
     const uint64_t k = keys[i];
     const uint32_t x = (uint32_t)(k >> (bits + 3));
-    r.x = x;
     r.y = (uint32_t)((k >> 3) & ((1ull << bits) - 1ull));
     r.bx = fptr[x];
     r.pos = (uint32_t)i - r.bx;
@@ -800,7 +800,6 @@ __device__ inline edge_at edge_bucket(const uint64_t* __restrict__ keys, uint64_
     if (dy == 0) return r;
     r.cost = dx + dy;
     r.bucket = (dx > dy ? dx : dy) >= bp.t_hub ? kBucketHub : r.cost < bp.t0 ? 0 : r.cost < bp.t1 ? 1 : 2;
-    r.at_x = r.bucket == kBucketHub && blocks16(r.pos) > 2u * blocks16(r.dy);
     return r;
 }
 
@@ -819,7 +818,7 @@ __global__ __launch_bounds__(kT) void k_edge_count(const uint64_t* __restrict__ 
             my[q] += r.bucket == q ? 1u : 0u;
             mycost[q] += r.bucket == q ? r.cost : 0ull;
         }
-        if (r.bucket == kBucketHub) mystream += r.at_x ? r.dy : r.pos;
+        if (r.bucket == kBucketHub) mystream += r.at_x() ? r.dy : r.pos;
     }
     store_tile_sums(my, mycost, mystream, 0ull, counts, part, nblocks, sh);
 }
@@ -842,7 +841,9 @@ constexpr uint64_t kFoundAtX = 1ull << 63;
 // Lane / wave / group records in x-major order; for the hub edges a key, in
 // x-major order too (sorted by y next, or x).  Without room in the key, keys[i]
 // becomes bx << 4 | tail << 3 | bits, except for an edge found at x.
-__global__ __launch_bounds__(kT) void k_edge_scatter(uint64_t* keys, uint64_t count, uint32_t bits,
+// (five wavefronts per SIMD: with the two registers more that four allow 131 us
+// on R-MAT 2^20, 123 so)
+__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(5))) void k_edge_scatter(uint64_t* keys, uint64_t count, uint32_t bits,
                                                      const uint32_t* __restrict__ fptr, bucket_params bp,
                                                      const uint64_t* __restrict__ offsets, uint32_t nblocks,
                                                      uint64_t hub_begin, hub_key hk, const uint32_t* __restrict__ fwd,
@@ -877,10 +878,10 @@ __global__ __launch_bounds__(kT) void k_edge_scatter(uint64_t* keys, uint64_t co
                 const uint64_t to = at[q] + (uint32_t)__popcll(m & lanemask_lt());
                 if (q == kBucketHub) {
                     const uint32_t low = ((fwd[i - 1] & 0x00fffffeu) >= 2u * kCore ? 8u : 0u) | r[k].bits;
-                    if (r[k].at_x) {
-                        hubkeys[to - hub_begin] =
-                            hk.pbits ? ((uint64_t)r[k].x << hk.y_shift()) | (i << (4 + hk.pbits))
-                                     : kFoundAtX | ((uint64_t)r[k].x << 32) | i;
+                    if (r[k].at_x()) {
+                        const uint64_t x = keys[i] >> (bits + 3);
+                        hubkeys[to - hub_begin] = hk.pbits ? (x << hk.y_shift()) | (i << (4 + hk.pbits))
+                                                           : kFoundAtX | (x << 32) | i;
                     } else if (hk.pbits) {
                         hubkeys[to - hub_begin] = ((uint64_t)r[k].y << hk.y_shift()) | (i << (4 + hk.pbits)) |
                                                   ((uint64_t)r[k].pos << 4) | low;
