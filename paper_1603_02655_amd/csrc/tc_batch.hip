@@ -104,8 +104,9 @@ void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it) 
         off = g.tri.edges.off;
         flag = kItemTri;
         const uint32_t nt = g.tri.edges.n_tasks;
-        for (uint32_t t = 0; t < nt; t += kBatchTasksPerItem)
-            it.tri.push_back(work_item{gi, kItemHub | kItemTri, t, std::min(t + kBatchTasksPerItem, nt)});
+        const uint32_t per = batch_tasks_per_item(g.tri.edges.chunk);
+        for (uint32_t t = 0; t < nt; t += per)
+            it.tri.push_back(work_item{gi, kItemHub | kItemTri, t, std::min(t + per, nt)});
     } else {
         for (uint32_t t = 0; t < g.n_hub_groups; ++t) it.hub.push_back(work_item{gi, kItemHub, t, t + 1});
     }

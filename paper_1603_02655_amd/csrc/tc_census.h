@@ -74,7 +74,14 @@ struct work_item {
                                         // hub items: task groups [begin, end) of the graph, or with
                                         // kItemTri its hub tasks [begin, end)
 };
-constexpr uint32_t kBatchTasksPerItem = 32;   // hub tasks of the forward lists per item
+// Hub tasks of the forward lists per item, of a graph whose tasks have up to
+// `chunk` records.  Tasks of 256 are those of a graph with 2^20 hub edges or
+// more, which has to fill the chip by itself: a task per wavefront (one random
+// graph of 5000 vertices and 500 neighbours each: 32 tasks 414 us, 8 156, 4 130;
+// a complete one of 1500: 1736, 512, 355; R-MAT 2^20 1066, 881, 885; four of
+// 100000 vertices with 200 neighbours 2842, 2855, 2874).  Of shorter tasks and of
+// fewer, 32 (256 R-MAT graphs of up to 20000 rows: 355 us, 8 tasks of 64 389).
+inline uint32_t batch_tasks_per_item(uint32_t chunk) { return chunk == kHubChunk / 2 ? 4 : 32; }
 constexpr uint32_t kBatchRowsPerItem = 4096;   // rows per rows item
 // (1024, four per thread: 0.96 ms instead of 0.92 for 512 graphs of up to 20 k
 // vertices, and 3.9 instead of 3.5 ms for 48 served ones of up to 10^6)

@@ -101,7 +101,8 @@ uint64_t job_footprint(const serve_job& j) {
         const device_graph& g = j.g->g;
         const bool tri = g.tri.fptr != nullptr;
         const uint64_t* off = tri ? g.tri.edges.off : g.bucket_off;
-        uint64_t items = (tri ? (g.tri.edges.n_tasks + kBatchTasksPerItem - 1) / kBatchTasksPerItem : g.n_hub_groups) +
+        const uint32_t per = batch_tasks_per_item(g.tri.edges.chunk);
+        uint64_t items = (tri ? (g.tri.edges.n_tasks + per - 1) / per : g.n_hub_groups) +
                          (off[3] - off[2]) +
                          (off[2] - off[1] + kBatchWavePerItem - 1) / kBatchWavePerItem +
                          (off[1] - off[0] + kBatchLanePerItem - 1) / kBatchLanePerItem;
