@@ -120,7 +120,7 @@ int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_sli
             }
         }
         float ms = 0.f;
-        if (!sl.per_dyad && g.p > 0 && hipEventElapsedTime(&ms, ev[2 * kBuckets], ev[2 * kBuckets + 1]) == hipSuccess) {
+        if (!sl.range && g.p > 0 && hipEventElapsedTime(&ms, ev[2 * kBuckets], ev[2 * kBuckets + 1]) == hipSuccess) {
             ctx->kstats.totals_ms += ms;
             ctx->kstats.totals_launches += 1;
         }
@@ -195,13 +195,21 @@ hipError_t scratch_for_device(int device, void** out) {
     return hipSuccess;
 }
 
-// u-range bounds inside the u-major merge buckets (the hub bucket is filtered
-// by the kernel instead).
-__global__ void k_bounds(const dyad_rec* dyads, const uint64_t* off, uint32_t u0, uint32_t u1, uint64_t* out) {
+// u-range bounds inside the u-major merge buckets, and of the rows' entries in
+// the place of the hub bucket's (which the kernel filters instead).
+struct bucket_offsets {
+    uint64_t at[kBuckets + 1];
+};
+__global__ void k_bounds(const dyad_rec* dyads, bucket_offsets off, const int64_t* row_ptr, uint32_t u0, uint32_t u1,
+                         unsigned long long* out) {
     int b = threadIdx.x >> 1;
-    if (b >= kBucketHub) return;
+    if (b > kBucketHub) return;
+    if (b == kBucketHub) {
+        out[threadIdx.x] = (uint64_t)row_ptr[(threadIdx.x & 1) ? u1 : u0];
+        return;
+    }
     uint32_t key = (threadIdx.x & 1) ? u1 : u0;
-    uint64_t lo = off[b], hi = off[b + 1];
+    uint64_t lo = off.at[b], hi = off.at[b + 1];
     while (lo < hi) {
         uint64_t mid = lo + ((hi - lo) >> 1);
         if (dyads[mid].u < key) lo = mid + 1; else hi = mid;
@@ -430,22 +438,13 @@ int tc_census_range(tc_context ctx, tc_graph g, int32_t u_begin, int32_t u_end, 
     unsigned long long raw[16] = {0};
     if (!has_records(g->g, false)) return TC_ERR_NOMEM;
     if (u_begin < u_end && g->g.p > 0) {
-        uint64_t *off_dev = nullptr, *bnd_dev = nullptr;
-        uint64_t bnd[2 * kBuckets];
-        hipError_t e = device_alloc((void**)&off_dev, sizeof(uint64_t) * (kBuckets + 1 + 2 * kBuckets));
-        if (e != hipSuccess) return status_from_hip(e);
-        bnd_dev = off_dev + kBuckets + 1;
-        e = hipMemcpyAsync(off_dev, g->g.bucket_off, sizeof(uint64_t) * (kBuckets + 1), hipMemcpyHostToDevice,
-                           ctx->stream);
-        if (e == hipSuccess) {
-            hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, ctx->stream, g->g.dyads, off_dev, (uint32_t)u_begin,
-                               (uint32_t)u_end, bnd_dev);
-            e = hipGetLastError();
-        }
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(bnd, bnd_dev, sizeof(bnd), hipMemcpyDeviceToHost, ctx->stream);
+        bucket_offsets off;
+        std::memcpy(off.at, g->g.bucket_off, sizeof(off.at));
+        const unsigned long long* bnd = ctx->host_raw;   // (pinned: no copy)
+        hipLaunchKernelGGL(k_bounds, dim3(1), dim3(64), 0, ctx->stream, g->g.dyads, off, g->g.row_ptr, (uint32_t)u_begin,
+                           (uint32_t)u_end, ctx->host_raw);
+        hipError_t e = hipGetLastError();
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-        (void)hipFree(off_dev);
         if (e != hipSuccess) return status_from_hip(e);
         census_slices sl;
         for (int b = 0; b < kBucketHub; ++b) {
@@ -454,7 +453,9 @@ int tc_census_range(tc_context ctx, tc_graph g, int32_t u_begin, int32_t u_end, 
         }
         sl.begin[kBucketHub] = g->g.bucket_off[kBucketHub];
         sl.end[kBucketHub] = g->g.bucket_off[kBucketHub + 1];
-        sl.per_dyad = true;
+        sl.range = true;
+        sl.ent_begin = bnd[2 * kBucketHub];
+        sl.ent_end = bnd[2 * kBucketHub + 1];
         sl.u_lo = (uint32_t)u_begin;
         sl.u_hi = (uint32_t)u_end;
         int rc = run_census_locked(ctx, g->g, sl, raw);

@@ -35,14 +35,16 @@ bool tile_supported(uint32_t hub_tile, uint32_t wave_tile, uint32_t group_tile, 
 // Per-bucket record slices [begin, end) into g.dyads or the edge records
 // (merge buckets); the hub bucket runs its task groups [hub_g0, hub_g1),
 // restricted to dyads with u in [u_lo, u_hi).  The terms that need no
-// intersection are added dyad by dyad (per_dyad, dyad records only), or cover
-// the rows [row_begin, row_end) and the bases of `asym` and `mutual` pairs.
+// intersection are those of the dyads with u in [u_lo, u_hi), whose rows hold
+// the entries [ent_begin, ent_end) (range, dyad records only), or cover the rows
+// [row_begin, row_end) and the bases of `asym` and `mutual` pairs.
 struct census_slices {
     uint64_t begin[kBuckets];
     uint64_t end[kBuckets];
     uint32_t u_lo = 0, u_hi = 0xffffffffu;
     uint32_t hub_g0 = 0, hub_g1 = 0xffffffffu;
-    bool per_dyad = false;
+    bool range = false;
+    uint64_t ent_begin = 0, ent_end = 0;
     uint32_t row_begin = 0, row_end = 0;
     uint64_t asym = 0, mutual = 0;
 };

@@ -150,12 +150,9 @@ struct census_args {
     const dyad_rec* dyads;    // bucket slice (the whole record array for the hub kernel)
     uint32_t count;           // dyads in the slice
     const uint32_t* nbr;
-    const uint64_t* tpre;
-    uint64_t n;               // vertices of the graph
     unsigned long long* acc;  // kAccCopies blocks of 16 accumulators
     uint32_t u_lo, u_hi;      // hub kernel: only dyads with u in [u_lo, u_hi)
     const uint8_t* table;     // 64 bin indices (device memory), one per code
-    bool per_dyad;            // add each dyad's own terms (a census of part of the dyads)
 };
 
 // Work counters: one per XCD, each on a line of its own (atomics on one line
