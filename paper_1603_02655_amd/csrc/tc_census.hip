@@ -1432,8 +1432,9 @@ __global__ __launch_bounds__(kTriB) __attribute__((amdgpu_waves_per_eu(Lab ? 4 :
             tri_tasks<Lab>(A.recs, A.lane.fwd, A.tasks, A.ntasks, A.heavy, A.counters + kBucketHub * kCounterWords,
                            blockIdx.x, A.hub_blocks, S, sig);
         } else {
-            const uint32_t d = (blockIdx.x - A.hub_blocks) * kTriB + threadIdx.x;   // a thread per record
-            if (d < A.lane.count) lane_edge<Lab>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
+            for (uint64_t d = (uint64_t)(blockIdx.x - A.hub_blocks) * kTriB + threadIdx.x; d < A.lane.count;
+                 d += (uint64_t)A.lane_blocks * kTriB)
+                lane_edge<Lab>(load_edge(A.lane.recs + d), A.lane.fwd, sig);
         }
         tri_flush<Lab>(sig, kTriB, T, h);
     } else if constexpr (Lab) {
@@ -1958,7 +1959,7 @@ bool launch_one(bool lab, const device_graph& g, const census_slices& sl, uint32
     A.ntasks = g1 - g0;
     A.heavy = std::min(A.ntasks, edges.n_heavy > g0 ? edges.n_heavy - g0 : 0u);
     A.hub_blocks = A.ntasks ? tri_grid(A.ntasks, cfg) : 0;
-    A.lane_blocks = (uint32_t)((lanes + kTriB - 1) / kTriB);
+    A.lane_blocks = (uint32_t)std::min<uint64_t>((lanes + kTriB - 1) / kTriB, cfg.lane_blocks);
     A.rinfo = g.rinfo;
     A.x0 = sl.row_begin;
     A.x1 = sl.row_end;
