@@ -94,6 +94,19 @@ void fill_info(const tc_graph_s* g, tc_graph_info* info) {
     info->tri_chunk = t.fptr ? t.edges.chunk : 0;
 }
 
+namespace {
+
+// The status of a launch sequence that failed.  What it had launched by then may
+// still run, on the side stream without a join: it ends before the caller can
+// release a graph or start a census.
+int failed_launch(tc_context_s* ctx, hipError_t e) {
+    (void)hipStreamSynchronize(ctx->stream);
+    (void)hipStreamSynchronize(ctx->side);
+    return status_from_hip(e);
+}
+
+}  // namespace
+
 int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_slices& sl,
                       unsigned long long* raw, int table, bool tri) {
     if (!has_records(g, tri)) return TC_ERR_NOMEM;
@@ -107,7 +120,7 @@ int run_census_locked(tc_context_s* ctx, const device_graph& g, const census_sli
         e = census_launch(g, sl, tri, ctx->tables + 64 * table, kind, ctx->acc, ctx->counters, ctx->host_raw, cfg,
                           ctx->stream, ev, ctx->side, ctx->fork);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return status_from_hip(e);
+    if (e != hipSuccess) return failed_launch(ctx, e);
     ctx->acc_clear = true;
     std::memcpy(raw, ctx->host_raw, sizeof(unsigned long long) * (kind == kLabelled ? 64 : kNumClasses));
     if (ev) {
@@ -539,7 +552,7 @@ int tc_census_each_noalloc(tc_context ctx, const tc_graph* graphs, int32_t count
                           ctx->host_many + (size_t)kNumClasses * i, cfg, ctx->stream, nullptr, ctx->side, ctx->fork);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) return status_from_hip(e);
+    if (e != hipSuccess) return failed_launch(ctx, e);
     for (int32_t i = 0; i < count; ++i)
         finalize_counts(graphs[i]->g.n, ctx->host_many + (size_t)kNumClasses * i, counts + 16 * (size_t)i);
     ctx->kstats.census_calls += (uint64_t)count;

@@ -1,5 +1,5 @@
 /* hipMalloc and hipFree with failures on demand and a limit on the live bytes,
- * and a count of calls from threads that chose no device, for tests/test_gpu_memory.py: loaded with RTLD_GLOBAL before libtc.so, so that
+ * a count of calls from threads that chose no device, and failures of events, for tests/test_gpu_memory.py: loaded with RTLD_GLOBAL before libtc.so, so that
  * the library's calls come here first.  Every call that is not refused goes to
  * the HIP runtime. */
 #define _GNU_SOURCE
@@ -76,6 +76,41 @@ int hipStreamCreateWithFlags(void** out, unsigned flags) {
 }
 
 long shim_unchosen(void) { return __atomic_load_n(&unchosen, __ATOMIC_SEQ_CST); }
+
+/* Event records and waits: those from the k-th on fail (k < 0: none), and the
+ * stream synchronisations since the first that failed are counted. */
+static long fail_event = -1, event_calls, event_failed, syncs;
+
+static int event_fails(void) {
+    pthread_mutex_lock(&mu);
+    const int f = fail_event >= 0 && event_calls++ >= fail_event;
+    event_failed += f;
+    pthread_mutex_unlock(&mu);
+    return f;
+}
+int hipEventRecord(void* ev, void* stream) {
+    int (*f)(void*, void*) = (int (*)(void*, void*))real("hipEventRecord");
+    return !f || event_fails() ? 1 : f(ev, stream);
+}
+int hipStreamWaitEvent(void* stream, void* ev, unsigned flags) {
+    int (*f)(void*, void*, unsigned) = (int (*)(void*, void*, unsigned))real("hipStreamWaitEvent");
+    return !f || event_fails() ? 1 : f(stream, ev, flags);
+}
+int hipStreamSynchronize(void* stream) {
+    int (*f)(void*) = (int (*)(void*))real("hipStreamSynchronize");
+    pthread_mutex_lock(&mu);
+    syncs += event_failed != 0;
+    pthread_mutex_unlock(&mu);
+    return f ? f(stream) : 1;
+}
+void shim_fail_events(long k) {
+    pthread_mutex_lock(&mu);
+    fail_event = k;
+    event_calls = event_failed = syncs = 0;
+    pthread_mutex_unlock(&mu);
+}
+long shim_events_failed(void) { return event_failed; }
+long shim_syncs(void) { return syncs; }
 
 /* The k-th call from now (0: the next) and all after it fail; k < 0: none. */
 void shim_fail_from(long k) {

@@ -324,12 +324,52 @@ def test_alternating_batches_keep_their_buffers(tmp_path):
     _run(tmp_path, "batches")
 
 
+def scenario_events(shim):
+    """A fork or join of the side stream that fails: the call returns once both
+    streams have ended what was launched, and the next one is right."""
+    a, b = np.triu_indices(500, 1)
+    n, src, dst = 500, a.astype(np.int32), b.astype(np.int32)
+    with tc.Context(0) as c:
+        c.set_tuning(t0=40, t1=300, t_hub=350)        # edges of every mode: several launches
+        g = c.build_graph(n, src, dst)
+        assert min(g.info["tri_bucket_edges"]) > 0
+        want, want64 = c.census(g), c.census64(g)
+        calls = dict(census=(lambda: c.census(g), want), census64=(lambda: c.census64(g), want64),
+                     noalloc=(lambda: c.census_each_noalloc([g])[0], want))
+        for name, (f, w) in calls.items():
+            k = 0
+            while True:
+                shim.shim_fail_events(k)
+                try:
+                    got = f()
+                except tc.TcError as e:
+                    assert e.code == tc.TC_ERR_DEVICE
+                    got = None
+                failed, syncs = shim.shim_events_failed(), shim.shim_syncs()
+                shim.shim_fail_events(-1)
+                print(name, "event", k, "failed" if failed else "ok", syncs, flush=True)
+                assert (got is None) == (failed > 0)
+                assert f().tolist() == w.tolist()
+                if not failed:
+                    assert got.tolist() == w.tolist()
+                    break
+                assert syncs >= 2
+                k += 1
+            assert k == 4                             # fork and join, a record and a wait each
+
+
+def test_failed_forks_and_joins(tmp_path):
+    _run(tmp_path, "events")
+
+
 if __name__ == "__main__":
     so = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)   # before libtc.so
     so.shim_fail_from.argtypes = [ctypes.c_long]
     so.shim_set_limit.argtypes = [ctypes.c_uint64]
     so.shim_live.restype = ctypes.c_uint64
     so.shim_peak.restype = ctypes.c_uint64
+    so.shim_fail_events.argtypes = [ctypes.c_long]
+    so.shim_events_failed.restype = so.shim_syncs.restype = ctypes.c_long
     so.shim_calls.restype = ctypes.c_long
     so.shim_refused.restype = ctypes.c_long
     so.shim_unchosen.restype = ctypes.c_long
