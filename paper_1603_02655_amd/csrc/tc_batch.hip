@@ -70,19 +70,14 @@ graph_desc describe(const device_graph& g) {
     graph_desc d{};
     d.dyads = g.dyads;
     d.nbr = g.nbr;
-    d.tpre = g.tpre;
     d.rinfo = g.rinfo;
     d.n = (uint64_t)g.n;
     d.hub_tasks = g.hub_tasks;
-    d.owner = g.owner;
-    d.row_ptr = g.row_ptr;
-    d.U = g.U;
     d.edges = g.tri.edges.recs;
     d.fwd = g.tri.fwd;
     d.edge_tasks = g.tri.edges.tasks;
     d.hub_ntasks = g.n_hub_tasks;
     d.hub_groups = g.n_hub_groups;
-    d.tri_chunk = g.tri.edges.chunk;
     d.asym = g.p - g.mutual;
     d.mutual = g.mutual;
     return d;

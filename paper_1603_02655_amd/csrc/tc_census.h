@@ -53,18 +53,13 @@ struct census_slices {
 struct graph_desc {
     const dyad_rec* dyads;       // dyad records
     const uint32_t* nbr;
-    const uint64_t* tpre;
     uint64_t n;
     const hub_task* hub_tasks;
-    const uint32_t* owner;
-    const int64_t* row_ptr;
-    uint64_t U;                  // neighbour entries
     const uint4* edges;          // forward-list edge records (null without forward lists)
     const uint32_t* fwd;
     const tri_task* edge_tasks;
     const uint4* rinfo;          // per row: bounds and prefix counts at its end
     uint32_t hub_ntasks, hub_groups;   // tasks and task groups over the dyad records
-    uint32_t tri_chunk;                // records per task over the edge records
     uint64_t asym, mutual;             // joined pairs, one way and both ways
 };
 // Item kinds: the mode (lane / wave / group / hub), with kItemTri when the item
