@@ -129,12 +129,32 @@ def generate_pool(fn, count):
         return list(ex.map(fn, range(count), chunksize=max(1, count // (4 * workers))))
 
 
-def kernel_key(name: str, tri: bool, tuning: dict, chunk: int = 512) -> str:
+# What limits a kernel, by the counters under profiles/: the hub kernel over edge
+# records waits for the chain of a step (vector units 58 % busy, LDS and texture
+# units about as much), the one over dyad records issues vector instructions 84 %
+# of its time, the others move bytes.
+BOUND = {"k_tri_hub": "latency", "k_census_hub": "valu"}
+
+
+def instance_name(name: str, tri: bool, tuning: dict) -> str:
     """The name rocprofv3 gives the template instance of a census kernel that
     runs with this tuning (namespace and arguments dropped), as used in the
-    tables under profiles/; `chunk`: the graph's records per hub task
-    (`tri_chunk` or `hub_chunk` of its info), which picks the hub kernel's
-    LDS instance."""
+    tables under profiles/."""
+    if name == "k_census_rows" or name == "k_census_lane":
+        return name
+    label = "false, " if tri else ""     # (16 classes)
+    if name.endswith("_hub"):
+        return f"{name}<false>" if tri else f"{name}<{tuning['hub_tile']}u>"
+    if name.endswith("_wave"):
+        return f"{name}<{label}{tuning['wave_tile']}>"
+    if name.endswith("_group"):
+        return f"{name}<{label}{tuning['group_size']}, {tuning['group_tile']}>"
+    return f"{name}<false>"
+
+
+def kernel_key(name: str, tri: bool, tuning: dict, chunk: int = 512) -> str:
+    """The instance names of the kernels that ran over both kinds of records,
+    as older tables have them; instance_name gives those of the current ones."""
     t = "true" if tri else "false"
     if name == "k_census_hub":
         return f"k_census_hub<{t}, {tuning['hub_tile']}u, {256 if chunk <= 256 else 512}u>"
@@ -286,7 +306,7 @@ def run_batch(args, autotune_sample: int) -> dict:
         "arcs_per_s": arcs / step_s, "graphs_per_s": len(hs) / step_s,
         "per_graph_launches": {"graphs_per_s": len(hs) / each_s, "arcs_per_s": arcs / each_s, "ms": 1000 * each_s},
         "speedup_vs_per_graph": each_s / step_s,
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "roofline": {"bound": "valu", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "kernel": "k_tri_batch + k_census_batch" if tri else "k_census_batch_hub + k_census_batch",
                      "kernel_ms": launch_ms, "bytes_per_launch": bytes_alg},
         "tuning": tuning, "autotune_s": tune_s,
@@ -669,7 +689,7 @@ def main():
     achieved = bytes_dom / (dom_ms / 1000.0) / 1e9 if dom_ms > 0 else 0.0
     b_alg = 4.0 * info["sum_d2"] + 8.0 * (info["asym_dyads"] + info["mutual_dyads"]) + 4.0 * (g0.n + 1)
     # (template instance as the profiler names it)
-    dom_key = f"{dom_name}<false>" if tri else kernel_key(dom_name, tri, ctx.get_tuning(), info["hub_chunk"])
+    dom_key = instance_name(dom_name, tri, ctx.get_tuning())
     line = {
         "metric": "census arcs/sec",
         "value": value,
@@ -687,7 +707,8 @@ def main():
                    "reciprocity": 2.0 * info["mutual_dyads"] / max(1, m_kept),
                    "sum_d2": info["sum_d2"], "max_degree": info["max_degree"],
                    "tuning": ctx.get_tuning()},
-        "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        # modelled bytes against the HBM rate; `bound`: what limits the kernel
+        "roofline": {"bound": BOUND.get(dom_name, "hbm"), "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic(args.workload, dom_key),
                      "kernel": dom_name, "bytes_per_launch": bytes_dom, "kernel_ms": dom_ms,

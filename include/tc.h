@@ -117,7 +117,7 @@ typedef struct {
     uint32_t batch_blocks;   /* resident 256-thread blocks, batched (persistent) kernel */
     uint32_t t_hub;
     uint32_t hub_blocks;     /* resident 256-thread blocks, hub kernel (over edge records with many
-                                tasks at most four per CU) */
+                                tasks at most four per CU, except in the serving loop's rounds) */
     uint32_t tri;            /* 1: whole-graph census through triangles of the forward lists */
     /* LDS tiles and group size (each among the kernel variants the library is built with) */
     uint32_t hub_tile;       /* anchor entries staged per LDS tile, hub mode: 512, 1024, 2048; graphs built
@@ -136,7 +136,7 @@ typedef struct {
     uint64_t census_calls;
     double batch_ms;             /* replays of the captured batched launch */
     uint64_t batch_launches;
-    double totals_ms;            /* per-dyad totals pass (tri = 1 only) */
+    double totals_ms;            /* terms without intersection, over rows or entries */
     uint64_t totals_launches;
 } tc_kernel_stats;
 
@@ -220,10 +220,11 @@ int tc_census64(tc_context ctx, tc_graph g, uint64_t counts[64]);
 int tc_census_range(tc_context ctx, tc_graph g, int32_t u_begin, int32_t u_end, uint64_t partial[16]);
 
 /* Shard `shard` of `nshards` of the census of g, on the path tc_census takes:
- * each bucket's records (dyads, or forward-list edge records), the hub task
- * groups and the neighbour entries of the per-dyad totals pass are cut into
- * nshards contiguous ranges of equal length and this call runs range `shard`
- * of each; every record, task group and entry falls in exactly one shard.
+ * each bucket's records (dyads, or forward-list edge records), the hub tasks
+ * (or dyad task groups) and the rows of the terms without intersection are cut
+ * into nshards contiguous ranges of equal length, the joined pairs' bases into
+ * as many shares, and this call runs range `shard` of each; every record, task,
+ * row and pair falls in exactly one shard.
  * This is the unit of work a multi-GPU census would give one GPU (section
  * "Future work": distribute the canonical dyads).  partial[0] is 0; the other
  * counts are exact modulo 2^64 (a shard may hold only one side of a dyad's
