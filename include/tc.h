@@ -117,7 +117,8 @@ typedef struct {
     uint32_t batch_blocks;   /* resident 256-thread blocks, batched (persistent) kernel */
     uint32_t t_hub;
     uint32_t hub_blocks;     /* resident 256-thread blocks, hub kernel (over edge records with many
-                                tasks at most four per CU, except in the serving loop's rounds) */
+                                tasks at most four per CU, in a batch with a graph of 2^20 hub
+                                edges five; not in the serving loop's rounds) */
     uint32_t tri;            /* 1: whole-graph census through triangles of the forward lists */
     /* LDS tiles and group size (each among the kernel variants the library is built with) */
     uint32_t hub_tile;       /* anchor entries staged per LDS tile, hub mode: 512, 1024, 2048; graphs built

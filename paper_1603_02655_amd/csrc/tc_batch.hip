@@ -5,8 +5,8 @@
 // buffers read by the kernel, so another set of graphs that fits the captured
 // capacities is served by rewriting those buffers and replaying; the capture is
 // redone only when a capacity grows or the tuning changes.  Which hub kernels a
-// launch has depends on the set; each of the four kinds has a capture of its own,
-// made when it is first needed, so that sets of different kinds can alternate.
+// launch has depends on the set; each of the kinds has a capture of its own, made
+// when it is first needed, so that sets of different kinds can alternate.
 #include <algorithm>
 #include <cstring>
 
@@ -14,8 +14,9 @@
 
 namespace tc {
 
-// What a launch holds: hub tasks over forward lists, over dyad records.
-enum : uint32_t { kHasTri = 1, kHasHub = 2, kKinds = 4 };
+// What a launch holds: hub tasks over forward lists, over dyad records, and of a
+// graph with 2^20 hub edges or more.
+enum : uint32_t { kHasTri = 1, kHasHub = 2, kHasLarge = 4, kKinds = 8 };
 
 struct batch_plan {
     std::vector<tc_graph> graphs;       // graphs the device buffers currently describe
@@ -149,7 +150,7 @@ hipError_t ensure_capacity(batch_plan* p, uint32_t graphs, uint32_t items, const
 hipError_t ensure_captured(batch_plan* p, uint32_t kind, tc_context_s* ctx) {
     if (p->exec[kind]) return hipSuccess;
     // a hub kernel runs when it has items (one of them also when neither has)
-    const uint32_t tri_grid = kind != kHasHub ? tri_blocks(p->hub_blocks, ctx->cu_count) : 0;
+    const uint32_t tri_grid = kind != kHasHub ? tri_blocks(p->hub_blocks, ctx->cu_count, (kind & kHasLarge) != 0) : 0;
     const uint32_t hub_grid = kind & kHasHub ? p->hub_blocks : 0;
     // The branch costs 7 us and gains where there are hub tasks (1 graph
     // without: 46 us with it, 39 without; 4 graphs with 1600 tasks: 60 and 78).
@@ -188,13 +189,16 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
     if (!(p->valid && p->graphs == want && holds(*p, 0, 0, ctx->tuning) && p->tri == tri)) {
         item_lists lists;
         std::vector<graph_desc> descs(count);
+        bool large = false;
         for (int32_t i = 0; i < count; ++i) {
             const device_graph& g = graphs[i]->g;
             if (!has_records(g, tri && g.tri.fptr)) return TC_ERR_NOMEM;
             descs[i] = describe(g);
             append_items(g, (uint32_t)i, tri && g.tri.fptr, lists);
+            large = large || (tri && g.tri.edges.n_tasks > 0 && g.tri.edges.chunk == kHubChunk / 2);
         }
-        const uint32_t kind = (lists.tri.empty() ? 0u : kHasTri) | (lists.hub.empty() ? 0u : kHasHub);
+        const uint32_t kind = (lists.tri.empty() ? 0u : kHasTri) | (lists.hub.empty() ? 0u : kHasHub) |
+                              (large ? kHasLarge : 0u);
         uint32_t nums[3];
         std::vector<work_item>& items = lists.join(nums);
         p->valid = false;   // (until the buffers are written)

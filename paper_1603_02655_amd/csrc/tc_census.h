@@ -24,8 +24,12 @@ struct census_config {
 // bucket, the terms and a batch's other items that run beside them, and none
 // waits for another to end (R-MAT 2^20: 8 per CU 0.894 ms, 5 0.876, 4 0.875, 3
 // 0.892; a batch of 512 R-MAT graphs: 0.787, 0.787, 0.757, 0.849).
-inline uint32_t tri_blocks(uint32_t hub_blocks, int cu_count) {
-    return std::min(hub_blocks, 4u * (uint32_t)(cu_count > 0 ? cu_count : 256));
+// A batch with a graph whose tasks have 256 records (2^20 hub edges or more) has
+// five: its other items are few beside them (four random graphs of 100000
+// vertices with 200 neighbours each 2.72 ms, 2.89 with four; two of R-MAT 2^20
+// 1.61, 1.74; 512 graphs of 50 to 20000 rows, none so large, 0.71, 0.68).
+inline uint32_t tri_blocks(uint32_t hub_blocks, int cu_count, bool large_batch = false) {
+    return std::min(hub_blocks, (large_batch ? 5u : 4u) * (uint32_t)(cu_count > 0 ? cu_count : 256));
 }
 
 // Whether the kernels are built for these LDS tiles and group size.
