@@ -127,7 +127,7 @@ struct item_lists {
         return tri;
     }
 };
-void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it);
+void append_items(const device_graph& g, uint32_t gi, bool tri, bool served, item_lists& it);
 void batch_release_all(tc_context_s* ctx);
 void batch_forget_graph_locked(tc_context_s* ctx, tc_graph g);
 

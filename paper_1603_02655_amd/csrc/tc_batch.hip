@@ -88,7 +88,7 @@ graph_desc describe(const device_graph& g) {
 // or into it.hub the hub task groups of the dyad records; into it.rest the
 // chunks of rows, then group-mode records (largest), wave-mode chunks and
 // lane-mode chunks, over the forward-list edge records when `tri`.
-void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it) {
+void append_items(const device_graph& g, uint32_t gi, bool tri, bool served, item_lists& it) {
     std::vector<work_item>& out = it.rest;
     const uint64_t* off = g.bucket_off;
     uint32_t flag = 0;
@@ -100,7 +100,7 @@ void append_items(const device_graph& g, uint32_t gi, bool tri, item_lists& it) 
         off = g.tri.edges.off;
         flag = kItemTri;
         const uint32_t nt = g.tri.edges.n_tasks;
-        const uint32_t per = batch_tasks_per_item(g.tri.edges.chunk);
+        const uint32_t per = batch_tasks_per_item(g.tri.edges.chunk, nt, served);
         for (uint32_t t = 0; t < nt; t += per)
             it.tri.push_back(work_item{gi, kItemHub | kItemTri, t, std::min(t + per, nt)});
     } else {
@@ -194,7 +194,7 @@ extern "C" int tc_census_batch(tc_context ctx, const tc_graph* graphs, int32_t c
             const device_graph& g = graphs[i]->g;
             if (!has_records(g, tri && g.tri.fptr)) return TC_ERR_NOMEM;
             descs[i] = describe(g);
-            append_items(g, (uint32_t)i, tri && g.tri.fptr, lists);
+            append_items(g, (uint32_t)i, tri && g.tri.fptr, false, lists);
             large = large || (tri && g.tri.edges.n_tasks > 0 && g.tri.edges.chunk == kHubChunk / 2);
         }
         const uint32_t kind = (lists.tri.empty() ? 0u : kHasTri) | (lists.hub.empty() ? 0u : kHasHub) |

@@ -82,7 +82,12 @@ struct work_item {
 // a complete one of 1500: 1736, 512, 355; R-MAT 2^20 1066, 881, 885; four of
 // 100000 vertices with 200 neighbours 2842, 2855, 2874).  Of shorter tasks and of
 // fewer, 32 (256 R-MAT graphs of up to 20000 rows: 355 us, 8 tasks of 64 389).
-inline uint32_t batch_tasks_per_item(uint32_t chunk) { return chunk == kHubChunk / 2 ? 4 : 32; }
+// In the serving loop also of many tasks: its one thread makes and copies the
+// items of every round, other rounds fill the chip, and 8000 requests/s waited 14
+// to 21 ms (median) with 4 tasks of every large graph in an item, 4.7 so.
+inline uint32_t batch_tasks_per_item(uint32_t chunk, uint32_t tasks, bool served) {
+    return chunk == kHubChunk / 2 && !(served && tasks > 16384) ? 4 : 32;
+}
 constexpr uint32_t kBatchRowsPerItem = 4096;   // rows per rows item
 // (1024, four per thread: 0.96 ms instead of 0.92 for 512 graphs of up to 20 k
 // vertices, and 3.9 instead of 3.5 ms for 48 served ones of up to 10^6)

@@ -101,7 +101,7 @@ uint64_t job_footprint(const serve_job& j) {
         const device_graph& g = j.g->g;
         const bool tri = g.tri.fptr != nullptr;
         const uint64_t* off = tri ? g.tri.edges.off : g.bucket_off;
-        const uint32_t per = batch_tasks_per_item(g.tri.edges.chunk);
+        const uint32_t per = batch_tasks_per_item(g.tri.edges.chunk, g.tri.edges.n_tasks, true);
         uint64_t items = (tri ? (g.tri.edges.n_tasks + per - 1) / per : g.n_hub_groups) +
                          (off[3] - off[2]) +
                          (off[2] - off[1] + kBatchWavePerItem - 1) / kBatchWavePerItem +
@@ -203,7 +203,7 @@ private:
                 continue;
             }
             descs[i] = describe(g);
-            append_items(g, (uint32_t)i, tri, lists);
+            append_items(g, (uint32_t)i, tri, true, lists);
         }
         uint32_t nums[3];
         const std::vector<work_item>& items = lists.join(nums);
