@@ -25,9 +25,8 @@ struct census_config {
 // waits for another to end (R-MAT 2^20: 8 per CU 0.894 ms, 5 0.876, 4 0.875, 3
 // 0.892; a batch of 512 R-MAT graphs: 0.787, 0.787, 0.757, 0.849).
 // A batch with a graph whose tasks have 256 records (2^20 hub edges or more) has
-// five: its other items are few beside them (four random graphs of 100000
-// vertices with 200 neighbours each 2.72 ms, 2.89 with four; two of R-MAT 2^20
-// 1.61, 1.74; 512 graphs of 50 to 20000 rows, none so large, 0.71, 0.68).
+// five: its other items are few beside them (two graphs of R-MAT 2^20 1.61 ms, with
+// four 1.74; 512 graphs of 50 to 20000 rows, none so large, 0.71, 0.68).
 inline uint32_t tri_blocks(uint32_t hub_blocks, int cu_count, bool large_batch = false) {
     return std::min(hub_blocks, (large_batch ? 5u : 4u) * (uint32_t)(cu_count > 0 ? cu_count : 256));
 }
@@ -79,9 +78,8 @@ struct work_item {
 // `chunk` records.  Tasks of 256 are those of a graph with 2^20 hub edges or
 // more, which has to fill the chip by itself: a task per wavefront (one random
 // graph of 5000 vertices and 500 neighbours each: 32 tasks 414 us, 8 156, 4 130;
-// a complete one of 1500: 1736, 512, 355; R-MAT 2^20 1066, 881, 885; four of
-// 100000 vertices with 200 neighbours 2842, 2855, 2874).  Of shorter tasks and of
-// fewer, 32 (256 R-MAT graphs of up to 20000 rows: 355 us, 8 tasks of 64 389).
+// a complete one of 1500: 1736, 512, 355; R-MAT 2^20 1066, 881, 885).  Of shorter
+// tasks and of fewer, 32 (256 R-MAT graphs of up to 20000 rows: 355 us, 8 tasks of 64 389).
 // In the serving loop also of many tasks: its one thread makes and copies the
 // items of every round, other rounds fill the chip, and 8000 requests/s waited 14
 // to 21 ms (median) with 4 tasks of every large graph in an item, 4.7 so.

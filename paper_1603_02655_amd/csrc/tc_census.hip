@@ -155,8 +155,10 @@ struct scaled_bins {
 template <bool Lab, class H>
 __device__ inline void tri_flush(tri_sig<Lab>& sig, uint32_t threads, const uint8_t* T, H& h) {
     constexpr uint32_t kB = tri_sig<Lab>::kBits, kM = (1u << kB) - 1u;
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));   // (what follows from it stays out of a caller's loop, whose registers it would take)
     __syncthreads();
-    for (uint32_t k = threadIdx.x; k < tri_sig<Lab>::kSlots; k += threads) {
+    for (uint32_t k = tid; k < tri_sig<Lab>::kSlots; k += threads) {
         const unsigned long long c = sig.n[k];
         if (c == 0) continue;
         sig.n[k] = 0;

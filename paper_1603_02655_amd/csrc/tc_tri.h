@@ -51,14 +51,13 @@ __device__ inline void load_entries4(const uint32_t* __restrict__ p, uint32_t* e
     e[3] = q.d;
 }
 
-// The entry of a rank (its bits in place) in a row, or 0.
-__device__ inline uint32_t find_rank(const uint32_t* __restrict__ fwd, uint32_t lo, uint32_t hi, uint32_t key) {
+// First position in [lo, hi) of a row whose rank (its bits in place) is >= key.
+__device__ inline uint32_t rank_bound(const uint32_t* __restrict__ fwd, uint32_t lo, uint32_t hi, uint32_t key) {
     while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo) >> 1), e = fwd[mid];
-        if ((e & kRankMask) == key) return e;
-        if ((e & kRankMask) < key) lo = mid + 1; else hi = mid;
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if ((fwd[mid] & kRankMask) < key) lo = mid + 1; else hi = mid;
     }
-    return 0u;
+    return lo;
 }
 
 // Edge record: the prefix of N+(x), [bx, ex) (ex is also the position of y's
@@ -155,9 +154,14 @@ __device__ inline void lane_edge(const edge_rec& r, const uint32_t* __restrict__
 // of an edge, 1.75e9 entries.
 //
 // kCore = 16384 ranks are 4 KiB of table: 32 wavefronts per CU.  On skewed
-// graphs nearly all of the stream lies below it (R-MAT 2^20: 99.0 %).  Ranks
-// above share the table modulo kCore in a second pass over the rest of the
-// prefixes (only for y >= kCore), where a hit is looked up in N+(y).
+// graphs nearly all of the stream lies below it (R-MAT 2^20: 99.0 %).  In further
+// passes, over the rest of the prefixes, the same LDS holds kTail entries of N+(y)
+// from kCore on, as codes modulo kCore / 2 and in a hash table of buckets of four:
+// where few entries hit a code, a lane looks its hits up one after the other,
+// where many do, all its entries.  (Hits looked up in N+(y) itself, by halving:
+// 200 complete graphs of 300 took 6.2 ms, now 1.03; 60000 vertices with 300 random
+// neighbours 0.92, now 0.75; 100000 on a ring with the 80 nearest 0.71, now 0.24.)
+constexpr int kFewHits = 4;               // hits among a lane's 16 entries up to which it looks them up one by one
 constexpr uint32_t kTriSegment = 1024;    // blocks whose row starts are marked in LDS at a time
 
 template <bool Lab>
@@ -171,6 +175,37 @@ struct tri_table {
     __device__ static inline uint32_t word(uint32_t e) { return (e >> (Lab ? 4 : 5)) & (kWords - 1); }
     __device__ static inline uint32_t shift(uint32_t e) { return Lab ? (e << 1) & 28u : e & 31u; }
     __device__ static inline uint32_t field(uint32_t e) { return (e >> (32 - kTop)) << (32 - kTop); }
+
+    // The tables of ranks from kCore on: codes modulo kCore / 2 in the first half
+    // of the words, where an answer may be another rank's, and a hash table of the
+    // entries in the second.  Slots of a bucket fill in order, and a full bucket
+    // goes on in the next; half the slots at most are taken, so a search ends.
+    static constexpr uint32_t kHalf = kWords / 2;
+    static constexpr uint32_t kBuckets = kHalf / 4;
+    static constexpr uint32_t kTail = kHalf / 2;
+    static_assert(kBuckets == (Lab ? 256 : 128), "the bits of a bucket");
+    __device__ static inline uint32_t tail_word(uint32_t e) { return word(e) & (kHalf - 1); }
+    __device__ static inline uint32_t bucket(uint32_t key) {   // the top bits of a 24 x 24-bit product
+        return (uint32_t)__umul24(key, 0x9E3779u) >> (32 - (Lab ? 8 : 7));
+    }
+    __device__ static inline void insert(uint32_t* tab, uint32_t e) {
+        atomicOr(&tab[tail_word(e)], field(e) >> shift(e));
+        for (uint32_t b = bucket(e & kRankMask);; b = (b + 1) & (kBuckets - 1))
+            for (uint32_t s = 0; s < 4; ++s)
+                if (atomicCAS(&tab[kHalf + 4 * b + s], 0u, e) == 0u) return;
+    }
+    // The entry of e's rank, or 0.
+    __device__ static inline uint32_t find(const uint32_t* tab, uint32_t e) {
+        const uint32_t key = e & kRankMask;
+        for (uint32_t b = bucket(key);; b = (b + 1) & (kBuckets - 1)) {
+            const uint4 q = reinterpret_cast<const uint4*>(tab + kHalf)[b];
+            uint32_t f = (q.x & kRankMask) == key ? q.x : 0u;
+            f = (q.y & kRankMask) == key ? q.y : f;
+            f = (q.z & kRankMask) == key ? q.z : f;
+            f = (q.w & kRankMask) == key ? q.w : f;
+            if (f != 0u || q.w == 0u) return f;
+        }
+    }
 };
 
 // Sums over the wavefront's lanes, inclusive (lane 63 holds the whole sum).
@@ -199,7 +234,8 @@ struct tri_counts {
     }
     // The wavefront's sums go to the signature counts in LDS.
     __device__ inline void flush(tri_sig<false>& sig) {
-        const uint32_t lane = __lane_id();
+        uint32_t lane = __lane_id();
+        asm volatile("" : "+v"(lane));   // (addresses are made here, not kept in registers through the stream)
 #pragma unroll
         for (uint32_t i = 0; i < 3; ++i)
 #pragma unroll
@@ -243,12 +279,20 @@ __device__ inline uint32_t quad_transpose(uint32_t x) {
     return hi | lo;
 }
 
-// Runs the records [begin, end) of a task on one wavefront.  tab: kWords of
-// LDS, starts: kTriSegment / 32 words, both the wavefront's own.
-template <bool Lab>
-__device__ inline void tri_run(const uint4* __restrict__ recs, const uint32_t* __restrict__ fwd, uint32_t begin,
-                               uint32_t end, uint32_t by, uint32_t ey, uint32_t* tab, uint32_t* starts,
-                               tri_sig<Lab>& sig, tri_counts& cnt) {
+// The part of the records' lists that a table answers for: entries below kCore
+// (Tail false), or from kCore on, of those with ranks from `key0` (if cut_lo) and
+// below `key1` (if cut_hi; ranks with their bits in place).
+struct tri_part {
+    bool none, cut_lo, cut_hi;   // none: the table is empty
+    uint32_t key0, key1;
+};
+
+// Streams that part of the records [begin, end) against the table in tab; `first`
+// is the lane's first record.  True if some record has entries from kCore on.
+template <bool Lab, bool Tail>
+__device__ inline bool tri_stream(const uint4* __restrict__ recs, const uint32_t* __restrict__ fwd, uint32_t begin,
+                                  uint32_t end, const uint4& first, const tri_part& part, const uint32_t* tab,
+                                  uint32_t* starts, tri_sig<Lab>& sig, tri_counts& cnt) {
     using TB = tri_table<Lab>;
     using S = tri_sig<Lab>;
     const uint32_t lane = __lane_id();
@@ -257,136 +301,177 @@ __device__ inline void tri_run(const uint4* __restrict__ recs, const uint32_t* _
     const uint32_t block = ((lane & 3u) << 4) | (lane >> 2);
     const uint64_t upto = (2ull << block) - 1ull;
     const uint4 none = make_uint4(0, 0, 0, 0);
-    const uint4 first = begin + lane < end ? recs[begin + lane] : none;   // (read beside the table's entries)
-    bool tails = false;   // a prefix has entries from kCore on
-    for (uint32_t pass = 0; pass < 2; ++pass) {
-        // the table of N+(y): ranks below kCore first, then the others
-        sync();
-        for (uint32_t k = lane; k < TB::kWords / 4; k += 64) reinterpret_cast<uint4*>(tab)[k] = make_uint4(0, 0, 0, 0);
-        sync();
-        bool others = false;
-        for (uint32_t k = by; k < ey; k += 64) {
-            const uint32_t p = k + lane;
-            const bool in = p < ey;
-            const uint32_t e = in ? fwd[p] : 0u;
-            const bool core = rank_of(e) < kCore;
-            others = others || __ballot(in && !core) != 0;
-            if (in && core == (pass == 0)) atomicOr(&tab[TB::word(e)], TB::field(e) >> TB::shift(e));
+    bool tails = false;
+    for (uint32_t b = begin; b < end; b += 64) {
+        // 64 records, one per lane: their parts in blocks of 16 entries
+        const uint4 r = b == begin ? first : b + lane < end ? recs[b + lane] : none;
+        if (!Tail) tails = tails || __ballot(r.y != r.z) != 0;
+        uint32_t p0 = Tail ? r.y : r.x, p1 = Tail ? r.z : r.y;
+        if (!Tail && part.none) continue;
+        if (Tail && part.cut_lo) p0 = rank_bound(fwd, p0, p1, part.key0);
+        if (Tail && part.cut_hi) p1 = rank_bound(fwd, p0, p1, part.key1);
+        const uint32_t nb = (p1 - p0 + 15u) >> 4;
+        const uint32_t incl = wave_scan(nb), start = incl - nb;
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        if (total == 0) continue;
+        uint32_t q_base = p0 - 16u * start, q_end = p1, q_code = r.w;
+        const uint64_t some = __ballot(nb != 0);
+        if ((some & (some + 1ull)) != 0) {
+            // the records with blocks move to the first lanes: lane j holds
+            // the j-th of them (first entry minus 16 x its first block, end,
+            // code); the others go to the places above
+            const uint32_t to = (uint32_t)__popcll(some & ((1ull << lane) - 1ull));
+            const int dst = (int)(4u * (nb != 0 ? to : (uint32_t)__popcll(some) + (lane - to)));
+            q_base = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)q_base);
+            q_end = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)q_end);
+            q_code = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)q_code);
         }
-        sync();
-        for (uint32_t b = begin; b < end; b += 64) {
-            // 64 records, one per lane: the part of the prefix this pass
-            // covers, in blocks of 16 entries
-            const uint4 r = b == begin ? first : b + lane < end ? recs[b + lane] : none;
-            tails = tails || __ballot(r.y != r.z) != 0;
-            const uint32_t p0 = pass == 0 ? r.x : r.y, p1 = pass == 0 ? r.y : r.z;
-            const uint32_t nb = (p1 - p0 + 15u) >> 4;
-            const uint32_t incl = wave_scan(nb), start = incl - nb;
-            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-            if (total == 0) continue;
-            uint32_t q_base = p0 - 16u * start, q_end = p1, q_code = r.w;
-            const uint64_t some = __ballot(nb != 0);
-            if ((some & (some + 1ull)) != 0) {
-                // the records with blocks move to the first lanes: lane j holds
-                // the j-th of them (first entry minus 16 x its first block, end,
-                // code); the others go to the places above
-                const uint32_t to = (uint32_t)__popcll(some & ((1ull << lane) - 1ull));
-                const int dst = (int)(4u * (nb != 0 ? to : (uint32_t)__popcll(some) + (lane - to)));
-                q_base = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)q_base);
-                q_end = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)q_end);
-                q_code = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)q_code);
-            }
-            uint32_t before = 0;   // records that start before the window
-            for (uint32_t seg = 0; seg < total; seg += kTriSegment) {
-                // one bit per block: a record starts there
-                sync();
-                if (lane < kTriSegment / 32) starts[lane] = 0;
-                sync();
-                if (nb != 0 && start >= seg && start < seg + kTriSegment)
-                    atomicOr(&starts[(start - seg) >> 5], 1u << ((start - seg) & 31u));
-                sync();
-                const uint32_t stop = min(total, seg + kTriSegment);
-                for (uint32_t win = seg; win < stop; win += 64) {
-                    const uint32_t wi = (win - seg) >> 5;
-                    const uint32_t m0 = __builtin_amdgcn_readfirstlane((int)starts[wi]),
-                                   m1 = __builtin_amdgcn_readfirstlane((int)starts[wi + 1]);
-                    const uint64_t m = (uint64_t)m0 | ((uint64_t)m1 << 32);
-                    // the record of the lane's block: the last that starts at or before it
-                    const uint32_t at = before + (uint32_t)__popcll(m & upto) - 1u;
-                    before += (uint32_t)__popcll(m);
-                    const int src = (int)(4u * at);
-                    const uint32_t base = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)q_base);
-                    const uint32_t pe = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)q_end);
-                    const uint32_t xy3 = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)q_code);
-                    const uint32_t t = win + block;
-                    const bool on = t < total;
-                    const uint32_t e0 = on ? base + 16u * t : 0u;       // (entries 0..15 are readable)
-                    const uint32_t ne = on ? min(pe - e0, 16u) : 0u;    // entries of the row in the block
-                    // Load k reads blocks 16 k .. 16 k + 15 of the window, four lanes the
-                    // quarters of one block, so that it touches no line that another
-                    // of the four loads does: lane l gets entries 4 (l % 4) .. + 3
-                    // of the four blocks of its quad.
-                    uint32_t e[16];
+        uint32_t before = 0;   // records that start before the window
+        for (uint32_t seg = 0; seg < total; seg += kTriSegment) {
+            // one bit per block: a record starts there
+            sync();
+            if (lane < kTriSegment / 32) starts[lane] = 0;
+            sync();
+            if (nb != 0 && start >= seg && start < seg + kTriSegment)
+                atomicOr(&starts[(start - seg) >> 5], 1u << ((start - seg) & 31u));
+            sync();
+            const uint32_t stop = min(total, seg + kTriSegment);
+            for (uint32_t win = seg; win < stop; win += 64) {
+                const uint32_t wi = (win - seg) >> 5;
+                const uint32_t m0 = __builtin_amdgcn_readfirstlane((int)starts[wi]),
+                               m1 = __builtin_amdgcn_readfirstlane((int)starts[wi + 1]);
+                const uint64_t m = (uint64_t)m0 | ((uint64_t)m1 << 32);
+                // the record of the lane's block: the last that starts at or before it
+                const uint32_t at = before + (uint32_t)__popcll(m & upto) - 1u;
+                before += (uint32_t)__popcll(m);
+                const int src = (int)(4u * at);
+                const uint32_t base = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)q_base);
+                const uint32_t pe = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)q_end);
+                const uint32_t xy3 = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)q_code);
+                const uint32_t t = win + block;
+                const bool on = t < total;
+                const uint32_t e0 = on ? base + 16u * t : 0u;       // (entries 0..15 are readable)
+                const uint32_t ne = on ? min(pe - e0, 16u) : 0u;    // entries of the row in the block
+                // Load k reads blocks 16 k .. 16 k + 15 of the window, four lanes the
+                // quarters of one block, so that it touches no line that another
+                // of the four loads does: lane l gets entries 4 (l % 4) .. + 3
+                // of the four blocks of its quad.
+                uint32_t e[16];
 #pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k)
-                        load_entries4(fwd + quad_lane(e0, k) + 4u * (lane & 3u), e + 4 * k);
-                    if (!Lab) {
-                        // codes of (y, z) and (x, z), first entry in the top bits
-                        // (all table reads are issued before the first is used)
-                        uint32_t A = 0, B = 0, w[16];
+                for (uint32_t k = 0; k < 4; ++k)
+                    load_entries4(fwd + quad_lane(e0, k) + 4u * (lane & 3u), e + 4 * k);
+                if (!Lab) {
+                    // codes of (y, z) and (x, z), first entry in the top bits
+                    // (all table reads are issued before the first is used)
+                    uint32_t A = 0, B = 0, w[16];
 #pragma unroll
-                        for (uint32_t k = 0; k < 16; ++k) w[k] = tab[TB::word(e[k])];
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (uint32_t k = 0; k < 16; ++k) w[k] = tab[Tail ? TB::tail_word(e[k]) : TB::word(e[k])];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (uint32_t k = 0; k < 16; ++k) {
+                        A = __builtin_amdgcn_alignbit(A, w[k] << TB::shift(e[k]), 30);
+                        B = __builtin_amdgcn_alignbit(B, e[k], 30);
+                    }
+                    const bool many = Tail && __any(__popc((A | (A >> 1)) & 0x55555555u) > kFewHits);
+                    if (many) {
 #pragma unroll
                         for (uint32_t k = 0; k < 16; ++k) {
-                            A = __builtin_amdgcn_alignbit(A, w[k] << TB::shift(e[k]), 30);
-                            B = __builtin_amdgcn_alignbit(B, e[k], 30);
+                            A = __builtin_amdgcn_alignbit(A, TB::find(tab, e[k]), 30);
+                            __builtin_amdgcn_sched_barrier(0);   // (their buckets would take 64 registers)
                         }
-                        // byte 3 - k is this lane's quarter of the quad's block k:
-                        // the lanes of the quad exchange them, each for its own block
-                        A = quad_transpose(A);
-                        B = quad_transpose(B);
-                        A &= (uint32_t)(0xffffffff00000000ull >> (2u * ne));
-                        if (pass == 0) {
-                            constexpr uint32_t kOdd = 0x55555555u;
-                            const uint32_t a1 = A & kOdd, a2 = (A >> 1) & kOdd, a3 = a1 & a2;
-                            const uint32_t b1 = B & kOdd, b2 = (B >> 1) & kOdd, b3 = b1 & b2;
-                            const uint32_t av[3] = {a1 ^ a3, a2 ^ a3, a3}, bv[3] = {b1 ^ b3, b2 ^ b3, b3};
-                            const uint32_t mul = 1u << (10u * ((xy3 >> 1) - 1u));
-#pragma unroll
-                            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                                for (int j = 0; j < 3; ++j)
-                                    cnt.c[i][j] += (uint32_t)__umul24(__popc(av[i] & bv[j]), mul);
-                            if (++cnt.steps == 63) {
-                                if constexpr (!Lab) cnt.flush(sig);
-                            }
-                        } else {
-                            uint32_t h = (A | (A >> 1)) & 0x55555555u;
-                            while (h) {
-                                const uint32_t k = (uint32_t)__clz((int)h) >> 1;
-                                h &= ~(1u << (30u - 2u * k));
-                                const uint32_t z = fwd[e0 + k];
-                                const uint32_t yz = find_rank(fwd, by, ey, z & kRankMask);
-                                if (yz) sig.hit(xy3 >> 1, S::code(z), S::code(yz));
-                            }
+                    }
+                    // byte 3 - k is this lane's quarter of the quad's block k:
+                    // the lanes of the quad exchange them, each for its own block
+                    A = quad_transpose(A);
+                    B = quad_transpose(B);
+                    A &= (uint32_t)(0xffffffff00000000ull >> (2u * ne));
+                    if (Tail && !many) {
+                        uint32_t h = (A | (A >> 1)) & 0x55555555u;
+                        while (h) {
+                            const uint32_t k = (uint32_t)__clz((int)h) >> 1, at_k = 30u - 2u * k;
+                            h &= ~(1u << at_k);
+                            const uint32_t yz = TB::find(tab, fwd[e0 + k]);
+                            A = (A & ~(3u << at_k)) | (S::code(yz) << at_k);
                         }
-                    } else {
+                    }
+                    constexpr uint32_t kOdd = 0x55555555u;
+                    const uint32_t a1 = A & kOdd, a2 = (A >> 1) & kOdd, a3 = a1 & a2;
+                    const uint32_t b1 = B & kOdd, b2 = (B >> 1) & kOdd, b3 = b1 & b2;
+                    const uint32_t av[3] = {a1 ^ a3, a2 ^ a3, a3}, bv[3] = {b1 ^ b3, b2 ^ b3, b3};
+                    const uint32_t mul = 1u << (10u * ((xy3 >> 1) - 1u));
 #pragma unroll
-                        for (uint32_t k = 0; k < 16; ++k) {
-                            const uint32_t n_k = quad_lane(ne, k / 4), xy_k = quad_lane(xy3, k / 4);
-                            const uint32_t w = tab[TB::word(e[k])] << TB::shift(e[k]);
-                            if (4u * (lane & 3u) + k % 4 < n_k && w >= 0x20000000u) {
-                                uint32_t yz = w;
-                                if (pass != 0) yz = find_rank(fwd, by, ey, e[k] & kRankMask);
-                                if (yz) sig.hit(xy_k, S::code(e[k]), S::code(yz));
-                            }
+                    for (int i = 0; i < 3; ++i)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j)
+                            cnt.c[i][j] += (uint32_t)__umul24(__popc(av[i] & bv[j]), mul);
+                    if (++cnt.steps == 63) {
+                        if constexpr (!Lab) cnt.flush(sig);
+                    }
+                } else {
+#pragma unroll
+                    for (uint32_t k = 0; k < 16; ++k) {
+                        const uint32_t n_k = quad_lane(ne, k / 4), xy_k = quad_lane(xy3, k / 4);
+                        const bool in = 4u * (lane & 3u) + k % 4 < n_k;
+                        uint32_t yz = tab[Tail ? TB::tail_word(e[k]) : TB::word(e[k])] << TB::shift(e[k]);   // (code in the top bits)
+                        if (in && yz >= 0x20000000u) {
+                            if (Tail) yz = TB::find(tab, e[k]);
+                            if (yz != 0u) sig.hit(xy_k, S::code(e[k]), S::code(yz));
                         }
                     }
                 }
             }
         }
-        if (!others || !tails) break;
+    }
+    return tails;
+}
+
+// Runs the records [begin, end) of a task on one wavefront.  tab: kWords of
+// LDS, starts: kTriSegment / 32 words, both the wavefront's own.  The pass over
+// the ranks below kCore and those over the others are two instances of the stream:
+// as one, the tests for the others cost the former 1 to 5 %.
+template <bool Lab>
+__device__ inline void tri_run(const uint4* __restrict__ recs, const uint32_t* __restrict__ fwd, uint32_t begin,
+                               uint32_t end, uint32_t by, uint32_t ey, uint32_t* tab, uint32_t* starts,
+                               tri_sig<Lab>& sig, tri_counts& cnt) {
+    using TB = tri_table<Lab>;
+    const uint32_t lane = __lane_id();
+    const tri_wave_sync sync{};
+    const uint4 none = make_uint4(0, 0, 0, 0);
+    const uint4 first = begin + lane < end ? recs[begin + lane] : none;   // (read beside the table's entries)
+    auto clear = [&] {
+        sync();
+        uint32_t zero = 0;
+        asm volatile("" : "+v"(zero));   // (not kept in registers through the stream)
+        for (uint32_t k = lane; k < TB::kWords / 4; k += 64) reinterpret_cast<uint4*>(tab)[k] = make_uint4(zero, zero, zero, zero);
+        sync();
+    };
+    clear();
+    uint32_t ty = by;   // end of the entries of N+(y) below kCore
+    for (uint32_t k = by; k < ey; k += 64) {
+        const uint32_t p = k + lane;
+        const uint32_t e = p < ey ? fwd[p] : 0u;
+        const bool core = p < ey && rank_of(e) < kCore;
+        if (core) atomicOr(&tab[TB::word(e)], TB::field(e) >> TB::shift(e));
+        const uint32_t n = (uint32_t)__popcll(__ballot(core));
+        ty += n;
+        if (n != 64) break;   // (ranks rise)
+    }
+    sync();
+    const bool tails = tri_stream<Lab, false>(recs, fwd, begin, end, first, tri_part{ty == by, false, false, 0u, 0u}, tab,
+                                              starts, sig, cnt);
+    if (!tails) return;
+    // The others, kTail to a table: met by the part of a prefix from the table's
+    // first rank to the first of the next.
+    for (uint32_t from = ty; from < ey; from += TB::kTail) {
+        const uint32_t past = min(from + TB::kTail, ey);
+        clear();
+        for (uint32_t p = from + lane; p < past; p += 64) TB::insert(tab, fwd[p]);
+        sync();
+        const bool cut_lo = from > ty, cut_hi = past < ey;
+        (void)tri_stream<Lab, true>(recs, fwd, begin, end, first,
+                                    tri_part{false, cut_lo, cut_hi, cut_lo ? fwd[from] & kRankMask : 0u,
+                                             cut_hi ? fwd[past] & kRankMask : 0u},
+                                    tab, starts, sig, cnt);
     }
 }
 
