@@ -130,8 +130,8 @@ def generate_pool(fn, count):
 
 
 # What limits a kernel, by the counters under profiles/: the hub kernel over edge
-# records waits for the chain of a step (vector units 58 % busy, LDS and texture
-# units about as much), the one over dyad records issues vector instructions 84 %
+# records waits for the chain of a step (vector and texture units 60 % busy, LDS
+# 31 %), the one over dyad records issues vector instructions 84 %
 # of its time, the others move bytes.
 BOUND = {"k_tri_hub": "latency", "k_census_hub": "valu"}
 

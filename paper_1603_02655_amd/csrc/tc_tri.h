@@ -146,7 +146,7 @@ __device__ inline void lane_edge(const edge_rec& r, const uint32_t* __restrict__
 // and counted with AND and bit counts.  No hashing, no candidates, no barriers.
 //
 // What bounds it: no unit by itself (R-MAT 2^20, 0.82 ms for 1.09e9 entries:
-// vector units 58 % busy, texture unit 59 %, 6.1 TB/s of L2 misses, most of them
+// vector units 59 % busy, texture units 61 %, LDS 31 %, 6.1 TB/s of L2 misses, most
 // served before HBM), but the chain of a window (marks, record, entries, table)
 // at four wavefronts per SIMD, and a task's start (table and records) on graphs with many short ones.
 // The hash table with candidate rings that it replaces took 1.70 ms there (32
